@@ -7,15 +7,13 @@
 //     beyond what bf16 matrices and a bf16 cache leave).
 //
 // One workgroup of 4 waves owns a (64 WT) x (64 WT) output tile, each wave a quadrant of WT x WT
-// MFMA 32x32x16 tiles (WT = 4: 256x256 tile, 128x128 per wave, 256 fp32 accumulators per lane; WT = 2 and 1 for
-// problems with too few big tiles to fill the chip).  K is walked in 64-wide slabs of x and W held in 2 LDS
+// MFMA 32x32x16 tiles (WT = 2 and 1: problems with too few 256-wide tiles to fill the chip).  K is walked in 64-wide slabs of x and W held in 2 LDS
 // buffers (4 at the smaller tiles); the coming slabs are moved global -> LDS directly (no staging registers) while the current slab's MFMAs run, and operand fragments are
 // double-buffered in registers.  LDS rows are 128 (64) bytes with the 16-byte column index XOR-ed with row bits,
 // which keeps the 128-bit operand reads of 16 consecutive rows on distinct banks.  Workgroup ids are remapped so
 // that the tiles resident on one XCD at a time share x row-blocks and W column-blocks in that XCD's L2.
-// What bounds the kernel is the rate at which a compute unit takes its slabs in (about 40 bytes per ns), not the
-// matrix cores: the tile is as large as the accumulator registers allow, and the gate/up projection forms SwiGLU
-// in the accumulators instead of writing both halves.
+// Large problems take the counter-phase kernel further down.  The gate/up projection forms SwiGLU in the accumulators
+// instead of writing both halves.
 #include <type_traits>
 
 #include "photon_device.h"
@@ -264,6 +262,209 @@ __global__ __launch_bounds__(G_THREADS) void gemm_bf16_kernel(
   if (m0 + BM <= M) epilogue(std::true_type{}); else epilogue(std::false_type{});
 }
 
+// ---- shared by the tile kernels built on 16x16x32 MFMAs ----------------------------------------------------------------
+
+// One contraction as the kernels take it.  `slabs`: K slabs of 64 per split; `group_m`: row tiles that are walked
+// together (see tile_position).
+struct GemmArgs {
+  const bf16_t* x; const bf16_t* W; const float* bias; const float* res; void* out;
+  int64_t ldres, ldo;
+  int M, N, K, tiles_m, tiles_n, group_m;
+};
+
+// Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes a contiguous run of tiles (also when the count is
+// not a multiple of 8), walked as bands of group_m row tiles, row tiles fastest: the 32 tiles resident on an XCD form a
+// patch of about group_m x 32 / group_m whose x rows and W rows that XCD's L2 holds once.
+struct TilePos { int tm, tn; };
+__device__ __forceinline__ TilePos tile_position(const GemmArgs& p) {
+  const int total = gridDim.x, id = blockIdx.x, xcd = id & 7, base = total >> 3, rem = total & 7;
+  const int logical = xcd * base + (xcd < rem ? xcd : rem) + (id >> 3);
+  const int band = p.group_m * p.tiles_n;
+  const int b = logical / band, in_band = logical - b * band;
+  const int gm = min(p.group_m, p.tiles_m - b * p.group_m);
+  return TilePos{b * p.group_m + in_band % gm, in_band / gm};
+}
+
+// 16-byte column c of staged row r (128 bytes per row) lies at column c ^ ((r >> 1) & 7): the 16 rows that a
+// quarter-wave reads together fall on distinct 16-byte slots of the 256-byte bank line.
+__device__ __forceinline__ int swizzled_column(int r, int c) { return c ^ ((r >> 1) & 7); }
+__device__ __forceinline__ bf16x8_t fragment(const char* slab, int r, int c16) {
+  return as_bf16x8(*reinterpret_cast<const uint4_t*>(slab + r * 128 + (swizzled_column(r, c16) << 4)));
+}
+
+// Row of W behind staged W row r of a tile whose output columns start at n0 (clamped into the matrix).  SwiGLU: 16 gate
+// rows, then the 16 up rows of the same columns, so that both products of a column meet in one lane.
+template <bool GU> __device__ __forceinline__ int weight_row(int r, int n0, int N) {
+  if (!GU) return n0 + r < N ? n0 + r : N - 1;
+  const int c = n0 + (r >> 5) * 16 + (r & 15);
+  return (c < N ? c : N - 1) + ((r >> 4) & 1) * N;
+}
+
+template <int VM> __device__ __forceinline__ void wait_loads_and_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
+}
+
+// One row of a wave's accumulators: the MFMAs take W as their row operand, so a lane holds 4 consecutive columns of
+// output row m: acc[j] is columns wave_col + j * 16 + 4 fk .. +3 of the tile's staged W rows.
+template <int OUT, int TJ>
+__device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int n0, int wave_col, int fk) {
+  if (m >= p.M) return;
+  if constexpr (OUT == GEMM_OUT_SWIGLU) {
+#pragma unroll
+    for (int j = 0; j < TJ; j += 2) {
+      const int n = n0 + (wave_col + j * 16) / 2 + fk * 4;
+      if (n >= p.N) continue;
+      const float4_t g = acc[j], u = acc[j + 1];
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)m * p.ldo + n) =
+          uint2{pack_bf16x2(silu(g.x) * u.x, silu(g.y) * u.y), pack_bf16x2(silu(g.z) * u.z, silu(g.w) * u.w)};
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int n = n0 + wave_col + j * 16 + fk * 4;
+      if (n >= p.N) continue;                                    // N is a multiple of 16
+      float4_t y = acc[j];
+      if (p.bias != nullptr) y += float4_t{p.bias[n], p.bias[n + 1], p.bias[n + 2], p.bias[n + 3]};
+      if constexpr (OUT == GEMM_OUT_F32) {
+        if (p.res != nullptr) y += *reinterpret_cast<const float4_t*>(p.res + (int64_t)m * p.ldres + n);
+        *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(p.out) + (int64_t)m * p.ldo + n) = y;
+      } else {
+        *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)m * p.ldo + n) = uint2{pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w)};
+      }
+    }
+  }
+}
+
+// ---- large contractions: 256 x 256 tile, two groups of waves in counter-phase ----------------------------------------
+//
+// What bounds a large contraction here is how much of the time the matrix cores have an instruction to run: with one
+// group of waves that reads operands, meets at a barrier and multiplies, the cores idle through every read phase (58 %
+// busy at 32768 x 2048 x 16384 on all-zero operands, where the clock does not drop).  So 8 waves work as two groups of
+// four, one wave of each group on every SIMD, half a phase apart: while one group issues a half-slab of MFMAs the
+// other fetches its next operands from LDS, and every phase ends at a barrier.  Per 64-wide K slab and wave:
+//   read 0: W fragments (64 columns) and x fragments of the wave's upper 64 rows    | barrier
+//   mma  0: 32 MFMAs 16x16x32                                                       | barrier
+//   read 1: x fragments of the lower 64 rows (the W fragments stay in registers)    | barrier
+//   mma  1: 32 MFMAs                                                                | barrier
+// The rows a slab buffer holds are ordered by when they are last read: [W rows | upper x rows of both groups] (part X,
+// 48 KB) is free after read 0, [lower x rows] (part Y) after read 1, so the direct global -> LDS loads of slab kt + 2
+// go out part by part, X in read 1 and Y in the next read 0, with four phases (about 1 us) to land before the wait for
+// them; two 64 KB buffers suffice.  Every wait names the number of younger loads (XI + YI, a constant).
+// MFMA 16x16x32 rather than 32x32x16: at the same schedule 10-15 % faster on real data, where power limits the clock.
+// Measured (MI355X, data spread like N(0,1)): 32768 x 2048 x 16384 1972 -> 1496 us (1.47 PFLOP/s); 8192 x 2048 x 5120
+// 122 us (1.41 PFLOP/s) where a 16-wave kernel without the counter-phase takes 134 us.
+constexpr int PP_BM = 256, PP_BN = 256, PP_THREADS = 512;
+constexpr int PP_STAGE = (PP_BM + PP_BN) * 128;                  // one slab: 512 rows of 64 bf16
+constexpr int PP_XI = (PP_BN + PP_BM / 2) / 64;                  // load instructions per wave and slab, part X
+constexpr int PP_YI = PP_BM / 2 / 64;                            // part Y
+
+template <int OUT>
+__global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArgs p) {
+  constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
+  constexpr int TI = 4, TJ = 4;                                  // MFMA tiles of a wave's half: 64 rows x 64 columns
+  extern __shared__ __align__(16) char lds[];                    // [2 buffers][256 W rows | 128 upper x rows | 128 lower x rows]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave >> 2, wcol = wave & 3;                  // group 0: rows 0..127 of the tile, group 1: rows 128..255
+  const TilePos at = tile_position(p);
+  const int m0 = at.tm * PP_BM, n0 = at.tn * (GU ? PP_BN / 2 : PP_BN);
+  const int KT = p.K / G_BK;
+
+  // one load instruction moves 64 lanes x 16 B = 8 staged rows; instruction i of wave w covers rows (i * 8 + w) * 8 .. +8
+  const char* src[PP_XI + PP_YI];
+#pragma unroll
+  for (int i = 0; i < PP_XI + PP_YI; ++i) {
+    const int r = (i * 8 + wave) * 8 + (lane >> 3);
+    const bf16_t* row;
+    if ((i * 8 + wave) * 8 < PP_BN) {
+      row = p.W + (int64_t)weight_row<GU>(r, n0, p.N) * p.K;
+    } else {
+      const int a = r - PP_BN, half = a >> 7, w = a & 127;       // staged x row -> row of the tile
+      const int m = m0 + (w >> 6) * 128 + half * 64 + (w & 63);
+      row = p.x + (int64_t)(m < p.M ? m : p.M - 1) * p.K;        // rows past the end repeat the last one: never stored
+    }
+    src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
+  // past the end: the last slab again, into rows nobody reads any more (the number of loads in flight stays constant)
+  auto load = [&](int kt, auto first, auto last) {
+    const uint32_t to = lds0 + (kt & 1) * PP_STAGE;
+    const int64_t ko = (int64_t)(kt < KT ? kt : KT - 1) * (G_BK * 2);
+#pragma unroll
+    for (int i = decltype(first)::value; i < decltype(last)::value; ++i) load16_to_lds(src[i] + ko, to + (i * 8 + wave) * 1024);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using IX = std::integral_constant<int, PP_XI>;
+  using IE = std::integral_constant<int, PP_XI + PP_YI>;
+
+  float4_t acc[2][TI][TJ];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) acc[h][i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15, fk = lane >> 4;                      // operand fragment: row, 8-wide k group
+  bf16x8_t xf[2][TI], wf[2][TJ];
+  auto read_w = [&](int kt) {
+    const char* s = lds + (kt & 1) * PP_STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) wf[ks][j] = fragment(s, wcol * 64 + j * 16 + fr, ks * 4 + fk);
+  };
+  auto read_x = [&](int kt, int half) {
+    const char* s = lds + (kt & 1) * PP_STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) xf[ks][i] = fragment(s, PP_BN + half * 128 + group * 64 + i * 16 + fr, ks * 4 + fk);
+  };
+  auto mma = [&](int half) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          acc[half][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][j], xf[ks][i], acc[half][i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // End of a read phase: own fragments in registers (part of the buffer may be overwritten from here on), own share of
+  // what the next read phase needs landed; after the barrier both hold for every wave.
+  auto read_done = [&] {
+    __builtin_amdgcn_sched_barrier(0);
+    wait_loads_and_barrier<PP_XI + PP_YI>();
+  };
+
+  load(0, I0{}, IX{});
+  load(0, IX{}, IE{});
+  load(1, I0{}, IX{});
+  wait_loads_and_barrier<PP_XI + PP_YI>();                       // part X of slab 0
+  if (group == 1) asm volatile("s_barrier" ::: "memory");        // half a phase behind group 0 from here on
+  for (int kt = 0; kt < KT; ++kt) {
+    read_w(kt);
+    read_x(kt, 0);
+    load(kt + 1, IX{}, IE{});                                    // part Y of the other buffer: last read in slab kt - 1
+    read_done();
+    mma(0);
+    read_x(kt, 1);
+    load(kt + 2, I0{}, IX{});                                    // part X of this buffer: both groups are past read 0
+    read_done();
+    mma(1);
+  }
+  if (group == 0) asm volatile("s_barrier" ::: "memory");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // the surplus loads of the tail land before the workgroup ends
+
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < TI; ++i) store_row<OUT, TJ>(p, acc[h][i], m0 + group * 128 + h * 64 + i * 16 + fr, n0, wcol * 64, fk);
+}
+
 // Row kernel in front of the contraction of fp32 activations: optional RMS norm with gain, then rounding to bf16
 // (nearest even).  One workgroup per row.
 __global__ __launch_bounds__(256) void norm_round_rows_kernel(const float* __restrict__ x, int64_t ldx, const float* __restrict__ gain,
@@ -310,6 +511,23 @@ __global__ __launch_bounds__(256) void copy_bytes16_kernel(const uint4_t* __rest
   if (idx < n16) dst[idx] = src[idx];
 }
 
+template <int OUT>
+static int32_t launch_pingpong(int cls, const bf16_t* A, const bf16_t* B, const float* bias, const float* res, int64_t ldres, void* out,
+                               int64_t ldc, int64_t M, int N, int K, hipStream_t st) {
+  constexpr int BN = (OUT == GEMM_OUT_SWIGLU) ? PP_BN / 2 : PP_BN;
+  GemmArgs p{A, B, bias, res, out, ldres, ldc, (int)M, N, K, (int)((M + PP_BM - 1) / PP_BM), (N + BN - 1) / BN, 8};
+  constexpr size_t lds_bytes = 2 * PP_STAGE;
+  static bool attr_set = false;                                  // more than 64 KiB of dynamic LDS has to be allowed once
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_pingpong_kernel<OUT>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (e != hipSuccess) return fail(PHOTON_ERR_HIP, "gemm: cannot reserve %zu bytes of LDS: %s", lds_bytes, hipGetErrorString(e));
+    attr_set = true;
+  }
+  PHOTON_LAUNCH(cls, st, gemm_pingpong_kernel<OUT>, dim3((unsigned)((int64_t)p.tiles_m * p.tiles_n)), dim3(PP_THREADS), lds_bytes, st, p);
+  return check_launch("gemm_pingpong_kernel");
+}
+
 template <int WT, int OUT, int BK, int NB>
 static int32_t launch_gemm_v(int cls, const bf16_t* A, const bf16_t* B, const float* bias, const float* res,
                              int64_t ldres, void* out, int64_t ldc, int64_t M, int N, int K, hipStream_t st) {
@@ -330,8 +548,6 @@ static int32_t launch_gemm_v(int cls, const bf16_t* A, const bf16_t* B, const fl
   return check_launch("gemm_bf16_kernel");
 }
 
-// The 256-wide tile, measured: 64-wide slabs in two buffers.  32-wide slabs in three to five buffers (up to 128 KB in
-// flight per compute unit instead of 64 KB) are no faster at the large shapes.
 template <int WT, int OUT>
 static int32_t launch_gemm_t(int cls, const bf16_t* A, const bf16_t* B, const float* bias, const float* res, int64_t ldres, void* out,
                              int64_t ldc, int64_t M, int N, int K, hipStream_t st) {
@@ -346,7 +562,7 @@ static int32_t launch_gemm_t(int cls, const bf16_t* A, const bf16_t* B, const fl
     if (((M + 127) / 128) * ((N + BN - 1) / BN) > 256) return launch_gemm_v<WT, OUT, 64, 2>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
   }
   if constexpr (WT <= 2) return launch_gemm_v<WT, OUT, 64, 4>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
-  return launch_gemm_v<WT, OUT, 64, 2>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
+  return launch_pingpong<OUT>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
 }
 
 // Largest tile that still gives the chip enough workgroups.
