@@ -41,6 +41,12 @@ template <int VEC> struct SoftState {
   }
 };
 
+// One element of the result: TQ, or (fp32 queries, the decode step at many rows) bf16.
+template <typename TQ> __device__ __forceinline__ void store_out(TQ* out, int64_t at, float y, int out_bf16) {
+  if (sizeof(TQ) == 4 && out_bf16) reinterpret_cast<bf16_t*>(out)[at] = from_f32<bf16_t>(y);
+  else out[at] = from_f32<TQ>(y);
+}
+
 // COARSE_WAVES waves per workgroup; U 16-byte K loads (and as many V loads) in flight per lane and register buffer.
 // DH: elements of a cache row (32, 64 or 128); d_h <= DH: head size, the row length of q and out.  Cache columns
 // d_h .. DH-1 hold zeros and meet zero query elements.
@@ -48,7 +54,7 @@ template <typename TKV, typename TQ, int DH, int COARSE_WAVES, int U>
 __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_kernel(
     const TQ* __restrict__ q, const TKV* __restrict__ kc, const TKV* __restrict__ vc,
     const int32_t* __restrict__ seq_len, TQ* __restrict__ out, float* __restrict__ ws,
-    int H, int d_h, int64_t S_max, float scale_log2e, int n_splits) {
+    int H, int d_h, int64_t S_max, float scale_log2e, int n_splits, int out_bf16) {
   using M = RowMap<TKV, DH>;
   constexpr int VEC = M::VEC, LPR = M::LPR, RPW = M::RPW;
   constexpr int TILE = RPW * U;                       // keys one wave consumes per buffer
@@ -175,7 +181,7 @@ __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_kernel(
       o = fmaf(so[w][tid], a, o);
     }
     if (n_splits == 1) {
-      if (tid < d_h) out[(int64_t)bh * d_h + tid] = from_f32<TQ>(l > 0.f ? o / l : 0.f);
+      if (tid < d_h) store_out(out, (int64_t)bh * d_h + tid, l > 0.f ? o / l : 0.f, out_bf16);
     } else {
       float* p = ws + ((int64_t)bh * n_splits + split) * (DH + 2);
       if (tid == 0) { p[0] = mm; p[1] = l; }
@@ -186,7 +192,7 @@ __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_kernel(
 
 // Merge the split partials of one (b, h) stream in split order.
 template <typename TQ, int DH>
-__global__ __launch_bounds__(DH) void coarse_merge_kernel(const float* __restrict__ ws, TQ* __restrict__ out, int n_splits, int d_h) {
+__global__ __launch_bounds__(DH) void coarse_merge_kernel(const float* __restrict__ ws, TQ* __restrict__ out, int n_splits, int d_h, int out_bf16) {
   const int bh = blockIdx.x, d = threadIdx.x;
   const float* p = ws + (int64_t)bh * n_splits * (DH + 2);
   float mm = NEG_BIG;
@@ -197,47 +203,47 @@ __global__ __launch_bounds__(DH) void coarse_merge_kernel(const float* __restric
     l = fmaf(p[s * (DH + 2) + 1], a, l);
     o = fmaf(p[s * (DH + 2) + 2 + d], a, o);
   }
-  if (d < d_h) out[(int64_t)bh * d_h + d] = from_f32<TQ>(l > 0.f ? o / l : 0.f);
+  if (d < d_h) store_out(out, (int64_t)bh * d_h + d, l > 0.f ? o / l : 0.f, out_bf16);
 }
 
 template <typename TKV, typename TQ, int DH, int WAVES, int U>
 static int32_t launch_coarse_v(const void* q, const void* kc, const void* vc, const int32_t* seq_len, void* out,
-                               int Bt, int H, int d_h, int64_t S_max, float scale, int n_splits, void* ws, hipStream_t st) {
+                               int Bt, int H, int d_h, int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st) {
   dim3 grid(n_splits, Bt * H);
   PHOTON_LAUNCH(KC_COARSE_ATTN, st, (coarse_attn_kernel<TKV, TQ, DH, WAVES, U>), grid, dim3(WAVES * 64), 0, st,
                      (const TQ*)q, (const TKV*)kc, (const TKV*)vc, seq_len, (TQ*)out, (float*)ws, H, d_h, S_max,
-                     scale * LOG2E, n_splits);
+                     scale * LOG2E, n_splits, out_bf16 ? 1 : 0);
   int32_t rc = check_launch("coarse_attn_kernel");
   if (rc != PHOTON_OK || n_splits == 1) return rc;
-  PHOTON_LAUNCH(KC_COARSE_MERGE, st, (coarse_merge_kernel<TQ, DH>), dim3(Bt * H), dim3(DH), 0, st, (const float*)ws, (TQ*)out, n_splits, d_h);
+  PHOTON_LAUNCH(KC_COARSE_MERGE, st, (coarse_merge_kernel<TQ, DH>), dim3(Bt * H), dim3(DH), 0, st, (const float*)ws, (TQ*)out, n_splits, d_h, out_bf16 ? 1 : 0);
   return check_launch("coarse_merge_kernel");
 }
 
 template <typename TKV, typename TQ, int DH>
 static int32_t launch_coarse_t(const void* q, const void* kc, const void* vc, const int32_t* seq_len, void* out,
-                               int Bt, int H, int d_h, int64_t S_max, float scale, int n_splits, void* ws, hipStream_t st) {
+                               int Bt, int H, int d_h, int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st) {
   return launch_coarse_v<TKV, TQ, DH, COARSE_WAVES_PER_WG, COARSE_UNROLL>(q, kc, vc, seq_len, out, Bt, H, d_h, S_max, scale,
-                                                                          n_splits, ws, st);
+                                                                          n_splits, ws, out_bf16, st);
 }
 
 template <typename TKV, typename TQ>
 static int32_t launch_coarse_dh(int d_h, const void* q, const void* kc, const void* vc, const int32_t* seq_len, void* out,
-                                int Bt, int H, int64_t S_max, float scale, int n_splits, void* ws, hipStream_t st) {
+                                int Bt, int H, int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st) {
   switch (kv_row_elems(d_h)) {
-    case 32: return launch_coarse_t<TKV, TQ, 32>(q, kc, vc, seq_len, out, Bt, H, d_h, S_max, scale, n_splits, ws, st);
-    case 64: return launch_coarse_t<TKV, TQ, 64>(q, kc, vc, seq_len, out, Bt, H, d_h, S_max, scale, n_splits, ws, st);
-    case 128: return launch_coarse_t<TKV, TQ, 128>(q, kc, vc, seq_len, out, Bt, H, d_h, S_max, scale, n_splits, ws, st);
+    case 32: return launch_coarse_t<TKV, TQ, 32>(q, kc, vc, seq_len, out, Bt, H, d_h, S_max, scale, n_splits, ws, out_bf16, st);
+    case 64: return launch_coarse_t<TKV, TQ, 64>(q, kc, vc, seq_len, out, Bt, H, d_h, S_max, scale, n_splits, ws, out_bf16, st);
+    case 128: return launch_coarse_t<TKV, TQ, 128>(q, kc, vc, seq_len, out, Bt, H, d_h, S_max, scale, n_splits, ws, out_bf16, st);
   }
   return fail(PHOTON_ERR_UNSUPPORTED, "coarse attention: d_h=%d not in [1, 128]", d_h);
 }
 
 int32_t launch_coarse_attn(KvType kv, bool q_f32, int d_h, const void* q, const void* kc, const void* vc,
                            const int32_t* seq_len, void* out, int Bt, int H, int64_t S_max, float scale,
-                           int n_splits, void* ws, hipStream_t st) {
-  if (kv == KV_F32) return launch_coarse_dh<float, float>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, st);
-  if (kv == KV_FP8) return launch_coarse_dh<fp8_t, float>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, st);
-  if (q_f32) return launch_coarse_dh<bf16_t, float>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, st);
-  return launch_coarse_dh<bf16_t, bf16_t>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, st);
+                           int n_splits, void* ws, bool out_bf16, hipStream_t st) {
+  if (kv == KV_F32) return launch_coarse_dh<float, float>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, out_bf16, st);
+  if (kv == KV_FP8) return launch_coarse_dh<fp8_t, float>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, out_bf16, st);
+  if (q_f32) return launch_coarse_dh<bf16_t, float>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, out_bf16, st);
+  return launch_coarse_dh<bf16_t, bf16_t>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, out_bf16, st);
 }
 
 int32_t coarse_auto_splits(int Bt, int H, int64_t S_max) {
@@ -350,7 +356,7 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_attn_kernel(
 // memory instead of from a neighbour lane.
 template <int DH, int NK, bool PAD>
 __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
-    const float* __restrict__ qkv, float* __restrict__ lk, float* __restrict__ lv, float* __restrict__ out,
+    const float* __restrict__ qkv, int n_parts, int64_t part_stride, float* __restrict__ lk, float* __restrict__ lv, float* __restrict__ out,
     int64_t n_units, int H, int d_h_rt, int W, int q_len, int q_pos, float scale_log2e, double freq_ratio, int out_bf16) {
   constexpr int VEC = 4, LPR = DH / 4, UPW = 64 / LPR;
   const int d_h = PAD ? d_h_rt : DH;
@@ -409,6 +415,16 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
     if (PAD) {
 #pragma unroll
       for (int t = 0; t < VEC; ++t) { qp[t] = head[partner[t]]; kp[t] = head[D + partner[t]]; }
+    }
+    for (int s = 1; s < n_parts; ++s) {                      // further partial products of the projection
+      head += part_stride;
+      q4 += *reinterpret_cast<const float4_t*>(head + col);
+      k4 += *reinterpret_cast<const float4_t*>(head + col + D);
+      v4 += *reinterpret_cast<const float4_t*>(head + col + 2 * D);
+      if (PAD) {
+#pragma unroll
+        for (int t = 0; t < VEC; ++t) { qp[t] += head[partner[t]]; kp[t] += head[D + partner[t]]; }
+      }
     }
   };
   fetch_row(0);
@@ -485,7 +501,7 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
 }
 
 template <int DH, bool PAD>
-static int32_t launch_local_step_dh(const float* qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,
+static int32_t launch_local_step_dh(const RowSource& qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,
                                     int q_pos, int H, int d_h, float scale, float theta, bool out_bf16, hipStream_t st) {
   const double freq_ratio = theta == 0.f ? 0.0 : pow((double)theta, -2.0 / (double)d_h);
   const int64_t n_units = n_chunks * H;
@@ -494,8 +510,8 @@ static int32_t launch_local_step_dh(const float* qkv, float* lk, float* lv, floa
   if (blocks > 0x7fffffffLL) return fail(PHOTON_ERR_UNSUPPORTED, "chunk-local attention: too many chunks for one launch");
 #define PHOTON_LS_CASE(N)                                                                                                   \
   case N:                                                                                                                   \
-    PHOTON_LAUNCH(KC_LOCAL_ATTN, st, (local_step_attn_kernel<DH, N, PAD>), dim3((unsigned)blocks), dim3(LOCAL_THREADS), 0, st, qkv, \
-                  lk, lv, out, n_units, H, d_h, W, q_len, q_pos, scale * LOG2E, freq_ratio, out_bf16 ? 1 : 0);                                    \
+    PHOTON_LAUNCH(KC_LOCAL_ATTN, st, (local_step_attn_kernel<DH, N, PAD>), dim3((unsigned)blocks), dim3(LOCAL_THREADS), 0, st, \
+                  qkv.n_parts ? qkv.parts : qkv.x, qkv.n_parts ? qkv.n_parts : 1, qkv.part_stride, lk, lv, out, n_units, H, d_h, W, q_len, q_pos, scale * LOG2E, freq_ratio, out_bf16 ? 1 : 0);                                    \
     break;
   switch (q_pos + q_len) {
     PHOTON_LS_CASE(1) PHOTON_LS_CASE(2) PHOTON_LS_CASE(3) PHOTON_LS_CASE(4)
@@ -508,7 +524,7 @@ static int32_t launch_local_step_dh(const float* qkv, float* lk, float* lv, floa
   return check_launch("local_step_attn_kernel");
 }
 
-int32_t launch_local_step_attn(int d_h, const float* qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,
+int32_t launch_local_step_attn(int d_h, const RowSource& qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,
                                int q_pos, int H, float scale, float theta, bool out_bf16, hipStream_t st) {
   if (d_h % 4 != 0) return fail(PHOTON_ERR_UNSUPPORTED, "chunk-local attention: d_h=%d is not a multiple of 4", d_h);
   switch (d_h) {
@@ -621,7 +637,7 @@ extern "C" int32_t photon_coarse_decode_attn(const void* q, const void* k_cache,
                    workspace_bytes);
   }
   return launch_coarse_attn(dt == PHOTON_F32 ? KV_F32 : dt == PHOTON_BF16 ? KV_BF16 : KV_FP8, dt != PHOTON_BF16, d_h, q, k_cache, v_cache, seq_len, out,
-                            Bt, H, S_max, scale, n_splits, workspace, (hipStream_t)stream);
+                            Bt, H, S_max, scale, n_splits, workspace, false, (hipStream_t)stream);
 }
 
 // ------------------------------------------------------------------ entry point that allocates nothing

@@ -6,14 +6,12 @@
 //     pass over the matrix cores costs a fifth of the prefill and of a large-batch step, for accuracy far
 //     beyond what bf16 matrices and a bf16 cache leave).
 //
-// One workgroup of 4 waves owns a (64 WT) x (64 WT) output tile, each wave a quadrant of WT x WT
-// MFMA 32x32x16 tiles (WT = 2 and 1: problems with too few 256-wide tiles to fill the chip).  K is walked in 64-wide slabs of x and W held in 2 LDS
-// buffers (4 at the smaller tiles); the coming slabs are moved global -> LDS directly (no staging registers) while the current slab's MFMAs run, and operand fragments are
-// double-buffered in registers.  LDS rows are 128 (64) bytes with the 16-byte column index XOR-ed with row bits,
-// which keeps the 128-bit operand reads of 16 consecutive rows on distinct banks.  Workgroup ids are remapped so
-// that the tiles resident on one XCD at a time share x row-blocks and W column-blocks in that XCD's L2.
-// Large problems take the counter-phase kernel further down.  The gate/up projection forms SwiGLU in the accumulators
-// instead of writing both halves.
+// K is walked in slabs of 64: rows of x and W move global -> LDS directly (no staging registers), several slabs ahead
+// of the one that the matrix cores contract, and MFMA 16x16x32 tiles accumulate in registers.  Two kernels: one group of
+// waves with three or four slab buffers (tiles of 64 x 32 to 128 x 128), and two groups in counter-phase (128 x 256 and
+// 256 x 256).  A contraction too small to fill the chip is split over K as well: the fp32 partial products go to a
+// scratch area and are added, in a fixed order, by the kernel that reads the result anyway (the row kernel in front of
+// the next contraction, the attention kernels).  The gate/up projection forms SwiGLU in the accumulators.
 #include <type_traits>
 
 #include "photon_device.h"
@@ -22,18 +20,7 @@
 
 namespace photon {
 
-typedef float float16_t __attribute__((ext_vector_type(16)));
-
 constexpr int G_BK = 64;                                         // K must be a multiple of this
-constexpr int G_THREADS = 256;
-
-// Byte offset of (row, 16-byte column) in a staged slab whose rows hold BK bf16.  The column index is XOR-ed with row
-// bits so that the 16 rows one quarter-wave reads together fall on distinct 16-byte slots of the 256-byte bank line
-// (2 rows of 128 bytes, or 4 rows of 64 bytes, per line).
-template <int BK> __device__ __forceinline__ int swz(int row, int col16) {
-  if (BK == 64) return row * 128 + ((col16 ^ ((row >> 1) & 7)) << 4);
-  return row * 64 + ((col16 ^ ((row >> 2) & 3)) << 4);
-}
 
 // 16 bytes per lane from global memory straight into LDS: lane l lands at lds_base + 16 l (lds_base: byte offset in
 // LDS, wave-uniform).  Written as an instruction rather than through the compiler's builtin: the compiler treats
@@ -49,240 +36,34 @@ __device__ __forceinline__ void load16_to_lds(const void* gsrc, uint32_t lds_bas
 }
 #pragma clang diagnostic pop
 
-// s_waitcnt immediate: at most `vm` vector-memory operations outstanding, all LDS reads done
-constexpr int waitcnt_vm_lgkm0(int vm) { return (vm & 0xF) | ((vm >> 4) << 14) | (7 << 4); }
-
-typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 enum GemmOut { GEMM_OUT_BF16 = 0, GEMM_OUT_F32 = 1, GEMM_OUT_SWIGLU = 2 };
 
-// WT: MFMA tiles per wave and dimension (tile edge 64 WT).  OUT bf16: Cout bf16 [M, ldc] = acc + bias.  OUT fp32:
-// Cout fp32 [M, ldc] = acc + bias + res.  OUT SwiGLU (WT even): B has 2N rows, gate rows then up rows; a tile covers
-// 32 WT output columns and takes the gate rows of 32 columns into the even MFMA column tiles of a wave and the up
-// rows of the same columns into the odd ones, so that silu(gate) * up is formed in registers:
-// Cout bf16 [M, ldc] = silu(x Wg^T) * (x Wu^T).  BK: k per slab (64 or 32); NB: slab buffers in LDS (NB - 1 slabs are
-// in flight while one is contracted).
-template <int WT, int OUT, int BK, int NB>
-__global__ __launch_bounds__(G_THREADS) void gemm_bf16_kernel(
-    const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, const float* __restrict__ bias,
-    const float* __restrict__ res, int64_t ldres, void* __restrict__ Cout, int64_t ldc, int M, int N, int K, int tiles_m,
-    int tiles_n) {
-  constexpr int BM = 64 * WT;                                   // tile edge (rows and columns)
-  constexpr int WE = 32 * WT;                                   // wave quadrant edge
-  constexpr int TILE_BYTES = BM * BK * 2;                       // one operand slab
-  constexpr int CPR = BK / 8;                                   // 16-byte columns per slab row
-  constexpr int RPI = 64 / CPR;                                 // slab rows one load instruction covers
-  constexpr int ROUNDS = BM / (4 * RPI);
-  constexpr int OPS = 2;                                        // operand slabs per buffer: x, W
-  constexpr int STAGE_BYTES = OPS * TILE_BYTES;
-  constexpr int B_OFF = (OPS - 1) * TILE_BYTES;
-  constexpr int LPS = OPS * ROUNDS;                             // load instructions per slab and wave
-  extern __shared__ __align__(16) char lds[];                   // [NB buffers][A slab | B slab]
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // scalar: the LDS targets of the direct loads are wave-uniform
+// ---- shared by the tile kernels ------------------------------------------------------------------------------------------
 
-  // XCD-aware raster: ids are dealt round-robin to 8 XCDs; give each XCD a contiguous run of tiles,
-  // column tiles fastest, so concurrent workgroups of an XCD share x row-blocks.
-  const int total = tiles_m * tiles_n;
-  const int id = blockIdx.x;
-  const int logical = (total % 8 == 0) ? (id & 7) * (total / 8) + (id >> 3) : id;   // ragged tile count: plain order
-  const int tm = logical / tiles_n, tn = logical % tiles_n;
-  constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
-  static_assert(!GU || WT % 2 == 0, "the gate/up pairing needs an even number of column tiles per wave");
-  const int m0 = tm * BM, n0 = tn * (GU ? BM / 2 : BM);
-
-  // global -> LDS without passing through registers: one instruction moves 64 lanes x 16 B = RPI slab rows;
-  // lane l lands at LDS row l/CPR, 16-byte column l%CPR, so it fetches the logical column that the XOR
-  // swizzle maps there.  Round i of wave w covers slab rows (i*4 + w)*RPI .. +RPI.
-  const int srow = lane / CPR, scol = lane % CPR;
-  int64_t aoff[ROUNDS];
-  const bf16_t* bptr[ROUNDS];
-#pragma unroll
-  for (int i = 0; i < ROUNDS; ++i) {
-    const int r = (i * 4 + wave) * RPI + srow;
-    const int c = (swz<BK>(r, scol) - r * (BK * 2)) >> 4;       // the swizzle is an involution on the column index
-    int ra = m0 + r; ra = ra < M ? ra : M - 1;                   // clamped rows are never stored
-    int rb = n0 + r;
-    if (GU) {                                                   // tile row -> output column and gate / up
-      const int rr = r % WE, jj = rr >> 5;
-      rb = n0 + (r / WE) * (WE / 2) + (jj >> 1) * 32 + (rr & 31);
-      rb = (rb < N ? rb : N - 1) + (jj & 1) * N;
-    } else {
-      rb = rb < N ? rb : N - 1;
-    }
-    aoff[i] = (int64_t)ra * K + c * 8;
-    bptr[i] = B + (int64_t)rb * K + c * 8;
-  }
-  const int KT = K / BK;
-  const int KT2 = KT;
-  // Always issues its loads (past the end: the last slab again, into a buffer nobody reads any more), so that the
-  // number of loads in flight at every wait is a compile-time constant.
-  auto stage = [&](int kt, int buf) {
-    kt = kt < KT2 ? kt : KT2 - 1;
-    char* sa = lds + buf * STAGE_BYTES;
-    const int64_t kk = (int64_t)kt * BK;
-#pragma unroll
-    for (int i = 0; i < ROUNDS; ++i) {
-      const int off = (i * 4 + wave) * 1024;
-      load16_to_lds(A + aoff[i] + kk, (uint32_t)(uintptr_t)(lptr_t)(sa + off));
-      load16_to_lds(bptr[i] + kk, (uint32_t)(uintptr_t)(lptr_t)(sa + B_OFF + off));
-    }
-  };
-
-  float16_t acc[WT][WT];
-#pragma unroll
-  for (int i = 0; i < WT; ++i)
-#pragma unroll
-    for (int j = 0; j < WT; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  const int wm = (wave >> 1) * WE, wn = (wave & 1) * WE;         // wave quadrant inside the tile
-  const int frow = lane & 31, fk = lane >> 5;                    // operand fragment: row, 8-wide k group
-
-  // Pipeline over the K slabs with ONE barrier per slab, placed before the slab's last 16-wide step:
-  //   MFMA(all steps but the last of slab kt)  [fragment reads of the next step issued ahead]
-  //   wait for slab kt+1 (NB-2 younger slabs may still be in flight), barrier
-  //     -> every wave has finished reading slab kt, so its buffer can take slab kt+NB right away
-  //   issue slab kt+NB, read the first fragments of slab kt+1, MFMA(last step of slab kt)
-  // so neither the load wait nor the first fragment reads of a slab leave the matrix cores idle.
-  constexpr int KS = BK / 16;
-  // The fragment reads of the next step are issued in two halves (x rows, then W rows) around the first row of
-  // MFMAs: the counter of outstanding LDS operations holds 15 at most, and with the 2 WT reads of the next step
-  // on top of the 2 WT of the current one the compiler could no longer wait for the older ones alone.
-  bf16x8_t af[2][WT], bfr[2][WT];
-  auto frags_a = [&](int buf, int ks, bf16x8_t (&a)[WT]) {
-    const char* sa = lds + buf * STAGE_BYTES;
-#pragma unroll
-    for (int i = 0; i < WT; ++i)
-      a[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4_t*>(sa + swz<BK>(wm + i * 32 + frow, ks * 2 + fk)));
-  };
-  auto frags_b = [&](int buf, int ks, bf16x8_t (&b)[WT]) {
-    const char* sb = lds + buf * STAGE_BYTES + B_OFF;
-#pragma unroll
-    for (int i = 0; i < WT; ++i)
-      b[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4_t*>(sb + swz<BK>(wn + i * 32 + frow, ks * 2 + fk)));
-  };
-  auto mfma_first = [&](const bf16x8_t (&a)[WT], const bf16x8_t (&b)[WT]) {
-#pragma unroll
-    for (int j = 0; j < WT; ++j) acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[j], acc[0][j], 0, 0, 0);
-  };
-  auto mfma_rest = [&](const bf16x8_t (&a)[WT], const bf16x8_t (&b)[WT]) {
-#pragma unroll
-    for (int i = 1; i < WT; ++i)
-#pragma unroll
-      for (int j = 0; j < WT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-  };
-  // one 16-wide step of register set `cur`: contract (x, W) while the fragments of the
-  // following step (buffer nbuf, step nks) arrive in the other register set
-  auto step = [&](int cur, int nbuf, int nks) {
-    const int nx = cur ^ 1;
-    frags_a(nbuf, nks, af[nx]);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_first(af[cur], bfr[cur]);
-    __builtin_amdgcn_sched_barrier(0);
-    frags_b(nbuf, nks, bfr[nx]);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_rest(af[cur], bfr[cur]);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-
-#pragma unroll
-  for (int s = 0; s < NB; ++s) stage(s, s);
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NB - 1) * LPS)); // slab 0 has landed
-  __syncthreads();
-  frags_a(0, 0, af[0]);
-  frags_b(0, 0, bfr[0]);
-  int buf = 0;
-  for (int kt = 0; kt < KT2; ++kt) {
-    const int nxt = buf + 1 < NB ? buf + 1 : 0;
-#pragma unroll
-    for (int ks = 0; ks < KS - 1; ++ks) step(ks & 1, buf, ks + 1);
-    // last step: slab kt is completely in registers / consumed from LDS
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0((NB - 2) * LPS)); // slab kt+1 landed, own LDS reads done
-    __syncthreads();
-    stage(kt + NB, buf);
-    step((KS - 1) & 1, nxt, 0);                                  // after the last slab: a landed buffer, values unused
-    buf = nxt;
-  }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));               // the surplus loads of the tail land before the workgroup ends
-
-  // acc[i][j][v] of lane l: row m = wm + i*32 + 8*(v/4) + 4*(l/32) + v%4, column n = wn + j*32 + l%32
-  if constexpr (GU) {
-#pragma unroll
-    for (int j = 0; j < WT; j += 2) {
-      const int n = n0 + (wn / WE) * (WE / 2) + (j >> 1) * 32 + (lane & 31);
-      if (n >= N) continue;
-#pragma unroll
-      for (int i = 0; i < WT; ++i) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          if (m >= M) continue;
-          reinterpret_cast<bf16_t*>(Cout)[(int64_t)m * ldc + n] = from_f32<bf16_t>(silu(acc[i][j][v]) * acc[i][j + 1][v]);
-        }
-      }
-    }
-    return;
-  }
-  // Row tiles that lie inside the matrix (all but a ragged last one) take the arm without per-row checks.
-  auto epilogue = [&](auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-#pragma unroll
-    for (int j = 0; j < WT; ++j) {
-      const int n = n0 + wn + j * 32 + (lane & 31);
-      if (n >= N) continue;
-      const float bv = bias != nullptr ? bias[n] : 0.f;
-#pragma unroll
-      for (int i = 0; i < WT; ++i) {
-        const int mb = m0 + wm + i * 32 + 4 * (lane >> 5);
-        // Residual values are requested in groups, ahead of the group's stores: res and Cout never overlap (the
-        // host checks), so nothing orders these loads behind the stores of the group before.
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {                   // 8 at a time: the accumulators leave few registers
-          float rv[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int v = half * 8 + u, m = mb + 8 * (v >> 2) + (v & 3);
-            rv[u] = (OUT != GEMM_OUT_BF16 && res != nullptr && (FULL || m < M)) ? res[(int64_t)m * ldres + n] : 0.f;
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int v = half * 8 + u, m = mb + 8 * (v >> 2) + (v & 3);
-            if (!FULL && m >= M) continue;
-            const float y = acc[i][j][v] + bv + rv[u];
-            if (OUT == GEMM_OUT_BF16) reinterpret_cast<bf16_t*>(Cout)[(int64_t)m * ldc + n] = from_f32<bf16_t>(y);
-            else reinterpret_cast<float*>(Cout)[(int64_t)m * ldc + n] = y;
-          }
-        }
-      }
-    }
-  };
-  if (m0 + BM <= M) epilogue(std::true_type{}); else epilogue(std::false_type{});
-}
-
-// ---- shared by the tile kernels built on 16x16x32 MFMAs ----------------------------------------------------------------
-
-// One contraction as the kernels take it.  `slabs`: K slabs of 64 per split; `group_m`: row tiles that are walked
-// together (see tile_position).
+// One contraction as the kernels take it: out[m, n] (bf16, fp32 or the SwiGLU product as bf16) = x[m, :] . W[n, :]
+// (+ bias[n] + res[m, n]).  fp32 output may be split over K: split s contracts slabs s * slabs .. +slabs and writes its
+// partial product to out + s * split_stride (no bias or residual then).  group_m: row tiles that are walked together.
 struct GemmArgs {
   const bf16_t* x; const bf16_t* W; const float* bias; const float* res; void* out;
-  int64_t ldres, ldo;
-  int M, N, K, tiles_m, tiles_n, group_m;
+  int64_t ldres, ldo, split_stride;
+  int M, N, K, tiles_m, tiles_n, group_m, slabs;
 };
 
 // Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes a contiguous run of tiles (also when the count is
 // not a multiple of 8), walked as bands of group_m row tiles, row tiles fastest: the 32 tiles resident on an XCD form a
 // patch of about group_m x 32 / group_m whose x rows and W rows that XCD's L2 holds once.
-struct TilePos { int tm, tn; };
+struct TilePos { int tm, tn, split; };
 __device__ __forceinline__ TilePos tile_position(const GemmArgs& p) {
   const int total = gridDim.x, id = blockIdx.x, xcd = id & 7, base = total >> 3, rem = total & 7;
   const int logical = xcd * base + (xcd < rem ? xcd : rem) + (id >> 3);
+  const int per_split = p.tiles_m * p.tiles_n;
+  const int split = logical / per_split, t = logical - split * per_split;
   const int band = p.group_m * p.tiles_n;
-  const int b = logical / band, in_band = logical - b * band;
+  const int b = t / band, in_band = t - b * band;
   const int gm = min(p.group_m, p.tiles_m - b * p.group_m);
-  return TilePos{b * p.group_m + in_band % gm, in_band / gm};
+  return TilePos{b * p.group_m + in_band % gm, in_band / gm, split};
 }
 
 // 16-byte column c of staged row r (128 bytes per row) lies at column c ^ ((r >> 1) & 7): the 16 rows that a
@@ -307,7 +88,7 @@ template <int VM> __device__ __forceinline__ void wait_loads_and_barrier() {
 // One row of a wave's accumulators: the MFMAs take W as their row operand, so a lane holds 4 consecutive columns of
 // output row m: acc[j] is columns wave_col + j * 16 + 4 fk .. +3 of the tile's staged W rows.
 template <int OUT, int TJ>
-__device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int n0, int wave_col, int fk) {
+__device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int n0, int wave_col, int fk, int split) {
   if (m >= p.M) return;
   if constexpr (OUT == GEMM_OUT_SWIGLU) {
 #pragma unroll
@@ -327,7 +108,7 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
       if (p.bias != nullptr) y += float4_t{p.bias[n], p.bias[n + 1], p.bias[n + 2], p.bias[n + 3]};
       if constexpr (OUT == GEMM_OUT_F32) {
         if (p.res != nullptr) y += *reinterpret_cast<const float4_t*>(p.res + (int64_t)m * p.ldres + n);
-        *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(p.out) + (int64_t)m * p.ldo + n) = y;
+        *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(p.out) + split * p.split_stride + (int64_t)m * p.ldo + n) = y;
       } else {
         *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)m * p.ldo + n) = uint2{pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w)};
       }
@@ -335,7 +116,83 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
   }
 }
 
-// ---- large contractions: 256 x 256 tile, two groups of waves in counter-phase ----------------------------------------
+// ---- small and middle contractions: one group of waves, NB slab buffers ------------------------------------------------
+//
+// WM x WN waves share a BM x BN tile.  A compute unit is fed at 40 to 100 bytes per ns here, depending on how many
+// workgroups share it, so what a small contraction costs is the bytes its busiest unit has to take in (its x rows and
+// its W rows, 128 bytes per row and slab) plus about 2.5 us of launch, first slab and stores: the tile and the split
+// over K are chosen together so that every unit has work (plan_gemm).  One barrier per slab: slab kt has landed for every wave, and
+// everybody is done with slab kt - 1, whose buffer takes slab kt + NB - 1; NB - 1 slabs are in flight meanwhile.
+// Measured against the kernels it replaces (MI355X): 64 rows, 2048 x 5120: 28 -> 7.0 us (8 splits); 64 rows, 6144 x 2048:
+// 16.4 -> 8.3 us (2 splits); 64 rows, SwiGLU 2 x 2560 x 1024: 12.3 -> 5.4 us; 512 rows, 2048 x 5120: 32 -> 18 us; 512 rows,
+// SwiGLU 2 x 5120 x 2048: 42 -> 31 us.
+template <int BM, int BN, int WM, int WN, int NB, int OUT>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs p) {
+  constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
+  constexpr int WAVES = WM * WN, STAGE = (BM + BN) * 128;
+  constexpr int LPS = (BM + BN) / 8 / WAVES;                     // load instructions per wave and slab
+  constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;            // MFMA tiles of a wave
+  static_assert((BM + BN) / 8 % WAVES == 0, "every wave moves the same number of rows");
+  static_assert(!GU || TJ % 2 == 0, "a wave holds gate and up columns in pairs");
+  extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const TilePos at = tile_position(p);
+  const int m0 = at.tm * BM, n0 = at.tn * (GU ? BN / 2 : BN);
+  const int s0 = at.split * p.slabs;
+  const int KT = min(p.slabs, p.K / G_BK - s0);
+
+  const char* src[LPS];
+#pragma unroll
+  for (int i = 0; i < LPS; ++i) {
+    const int r = (i * WAVES + wave) * 8 + (lane >> 3);
+    const bf16_t* row;
+    if ((i * WAVES + wave) * 8 < BM) row = p.x + (int64_t)(m0 + r < p.M ? m0 + r : p.M - 1) * p.K;   // past the end: never stored
+    else row = p.W + (int64_t)weight_row<GU>(r - BM, n0, p.N) * p.K;
+    src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8 + (int64_t)s0 * G_BK);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
+  auto load = [&](int kt, int buf) {                             // past the end: the last slab again, into a buffer nobody reads
+    const int64_t ko = (int64_t)(kt < KT ? kt : KT - 1) * (G_BK * 2);
+#pragma unroll
+    for (int i = 0; i < LPS; ++i) load16_to_lds(src[i] + ko, lds0 + buf * STAGE + (i * WAVES + wave) * 1024);
+  };
+  float4_t acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+  const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
+  const int fr = lane & 15, fk = lane >> 4;                      // operand fragment: row, 8-wide k group
+
+#pragma unroll
+  for (int s = 0; s < NB - 1; ++s) load(s, s);
+  int buf = 0, next = NB - 1;
+  for (int kt = 0; kt < KT; ++kt) {
+    wait_loads_and_barrier<(NB - 2) * LPS>();
+    load(kt + NB - 1, next);
+    const char* s = lds + buf * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8_t xf[TI], wf[TJ];
+#pragma unroll
+      for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+    }
+    buf = buf + 1 < NB ? buf + 1 : 0;
+    next = next + 1 < NB ? next + 1 : 0;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // the surplus loads of the tail land before the workgroup ends
+#pragma unroll
+  for (int i = 0; i < TI; ++i) store_row<OUT, TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0, wn, fk, at.split);
+}
+
+// ---- large contractions: two groups of waves in counter-phase, 256 x 256 (TI = 4) or 128 x 256 (TI = 2) tile ------------
 //
 // What bounds a large contraction here is how much of the time the matrix cores have an instruction to run: with one
 // group of waves that reads operands, meets at a barrier and multiplies, the cores idle through every read phase (58 %
@@ -353,22 +210,24 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
 // MFMA 16x16x32 rather than 32x32x16: at the same schedule 10-15 % faster on real data, where power limits the clock.
 // Measured (MI355X, data spread like N(0,1)): 32768 x 2048 x 16384 1972 -> 1496 us (1.47 PFLOP/s); 8192 x 2048 x 5120
 // 122 us (1.41 PFLOP/s) where a 16-wave kernel without the counter-phase takes 134 us.
-constexpr int PP_BM = 256, PP_BN = 256, PP_THREADS = 512;
-constexpr int PP_STAGE = (PP_BM + PP_BN) * 128;                  // one slab: 512 rows of 64 bf16
-constexpr int PP_XI = (PP_BN + PP_BM / 2) / 64;                  // load instructions per wave and slab, part X
-constexpr int PP_YI = PP_BM / 2 / 64;                            // part Y
+constexpr int PP_BN = 256, PP_THREADS = 512;
 
-template <int OUT>
+template <int TI, int OUT>
 __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
-  constexpr int TI = 4, TJ = 4;                                  // MFMA tiles of a wave's half: 64 rows x 64 columns
-  extern __shared__ __align__(16) char lds[];                    // [2 buffers][256 W rows | 128 upper x rows | 128 lower x rows]
+  constexpr int TJ = 4;                                          // MFMA tiles of a wave's half: TI x 16 rows, 64 columns
+  constexpr int PP_BM = 64 * TI, HALF = 16 * TI;                 // rows of the tile, rows of a wave's half
+  constexpr int PP_STAGE = (PP_BM + PP_BN) * 128;                // one slab
+  constexpr int PP_XI = (PP_BN + PP_BM / 2) / 64;                // load instructions per wave and slab, part X
+  constexpr int PP_YI = PP_BM / 2 / 64;                          // part Y
+  extern __shared__ __align__(16) char lds[];                    // [2 buffers][256 W rows | upper x rows | lower x rows]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int group = wave >> 2, wcol = wave & 3;                  // group 0: rows 0..127 of the tile, group 1: rows 128..255
+  const int group = wave >> 2, wcol = wave & 3;                  // group 0: upper half of the tile's rows, group 1: lower half
   const TilePos at = tile_position(p);
   const int m0 = at.tm * PP_BM, n0 = at.tn * (GU ? PP_BN / 2 : PP_BN);
-  const int KT = p.K / G_BK;
+  const int s0 = at.split * p.slabs;
+  const int KT = min(p.slabs, p.K / G_BK - s0);
 
   // one load instruction moves 64 lanes x 16 B = 8 staged rows; instruction i of wave w covers rows (i * 8 + w) * 8 .. +8
   const char* src[PP_XI + PP_YI];
@@ -379,11 +238,11 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
     if ((i * 8 + wave) * 8 < PP_BN) {
       row = p.W + (int64_t)weight_row<GU>(r, n0, p.N) * p.K;
     } else {
-      const int a = r - PP_BN, half = a >> 7, w = a & 127;       // staged x row -> row of the tile
-      const int m = m0 + (w >> 6) * 128 + half * 64 + (w & 63);
+      const int a = r - PP_BN, half = a / (2 * HALF), w = a % (2 * HALF);   // staged x row -> row of the tile
+      const int m = m0 + (w / HALF) * (2 * HALF) + half * HALF + w % HALF;
       row = p.x + (int64_t)(m < p.M ? m : p.M - 1) * p.K;        // rows past the end repeat the last one: never stored
     }
-    src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8);
+    src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8 + (int64_t)s0 * G_BK);
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
   // past the end: the last slab again, into rows nobody reads any more (the number of loads in flight stays constant)
@@ -418,7 +277,7 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int i = 0; i < TI; ++i) xf[ks][i] = fragment(s, PP_BN + half * 128 + group * 64 + i * 16 + fr, ks * 4 + fk);
+      for (int i = 0; i < TI; ++i) xf[ks][i] = fragment(s, PP_BN + (half * 2 + group) * HALF + i * 16 + fr, ks * 4 + fk);
   };
   auto mma = [&](int half) {
     __builtin_amdgcn_sched_barrier(0);
@@ -462,48 +321,109 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int i = 0; i < TI; ++i) store_row<OUT, TJ>(p, acc[h][i], m0 + group * 128 + h * 64 + i * 16 + fr, n0, wcol * 64, fk);
+    for (int i = 0; i < TI; ++i) store_row<OUT, TJ>(p, acc[h][i], m0 + (group * 2 + h) * HALF + i * 16 + fr, n0, wcol * 64, fk, at.split);
 }
 
-// Row kernel in front of the contraction of fp32 activations: optional RMS norm with gain, then rounding to bf16
-// (nearest even).  One workgroup per row.
-__global__ __launch_bounds__(256) void norm_round_rows_kernel(const float* __restrict__ x, int64_t ldx, const float* __restrict__ gain,
-                                                              float eps, bf16_t* __restrict__ xb, int K) {
-  const int tid = threadIdx.x;
-  const float* xr = x + (int64_t)blockIdx.x * ldx;
-  float r = 1.f;
-  if (gain != nullptr) {
-    float ss = 0.f;
-    for (int k = tid * 4; k < K; k += 1024) {
-      const float4_t v = *reinterpret_cast<const float4_t*>(xr + k);
-      ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss))));
+// ---- row kernel between contractions --------------------------------------------------------------------------------------
+//
+// Per row: add up what the value consists of (residual row, the partial products of a split contraction, bias), write
+// the sum if asked, normalise (RMS with gain) and write it as bf16 (the next contraction's operand, rounded to nearest
+// even) or fp32.  TPR threads hold a row in registers, NV float4 each (one read of the row; loads of all sources in flight
+// together); NV == 0: rows longer than the registers hold, read again for the second pass.
+template <int TPR, int NV>
+__global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
+  const int row = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, t = threadIdx.x % TPR;
+  if (row >= p.M) return;                                        // TPR == 256: never; TPR == 64: whole waves, which share nothing
+  const int K = p.K;
+  const float* x = p.in.x != nullptr ? p.in.x + (int64_t)row * p.in.ld : nullptr;
+  const float* parts = p.in.parts + (int64_t)row * p.in.part_ld;
+  auto value = [&](int k) {
+    float4_t v = x != nullptr ? *reinterpret_cast<const float4_t*>(x + k) : float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < p.in.n_parts; ++s) v += *reinterpret_cast<const float4_t*>(parts + s * p.in.part_stride + k);
+    if (p.bias != nullptr) v += float4_t{p.bias[k], p.bias[k + 1], p.bias[k + 2], p.bias[k + 3]};
+    return v;
+  };
+  auto emit = [&](int k, const float4_t& v, float r) {
+    if (p.xb != nullptr) {
+      const float4_t w = p.gain != nullptr ? v * *reinterpret_cast<const float4_t*>(p.gain + k) * r : v;
+      *reinterpret_cast<uint2*>(p.xb + (int64_t)row * K + k) = uint2{pack_bf16x2(w.x, w.y), pack_bf16x2(w.z, w.w)};
     }
+    if (p.y != nullptr) *reinterpret_cast<float4_t*>(p.y + (int64_t)row * p.ldy + k) = v * r * *reinterpret_cast<const float4_t*>(p.gain + k);
+  };
+  auto inv_rms = [&](float ss) {
     ss = group_sum<32>(ss);
     ss += __shfl_xor(ss, 32);
-    __shared__ float partsum[4];
-    if ((tid & 63) == 0) partsum[tid >> 6] = ss;
-    __syncthreads();
-    r = 1.0f / sqrtf(((partsum[0] + partsum[1]) + (partsum[2] + partsum[3])) / (float)K + eps);
-  }
-  uint2* o = reinterpret_cast<uint2*>(xb + (int64_t)blockIdx.x * K);
-  for (int k = tid * 4; k < K; k += 1024) {
-    float4_t v = *reinterpret_cast<const float4_t*>(xr + k);    // second read of the row: it is in cache
-    if (gain != nullptr) v = v * *reinterpret_cast<const float4_t*>(gain + k) * r;
-    o[k >> 2] = uint2{pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
+    if (TPR > 64) {
+      __shared__ float partsum[4];
+      if ((threadIdx.x & 63) == 0) partsum[threadIdx.x >> 6] = ss;
+      __syncthreads();
+      ss = (partsum[0] + partsum[1]) + (partsum[2] + partsum[3]);
+    }
+    return 1.0f / sqrtf(ss / (float)K + p.eps);
+  };
+  float ss = 0.f, r = 1.f;
+  if constexpr (NV > 0) {
+    float4_t v[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int k = (i * TPR + t) * 4;
+      v[i] = k < K && x != nullptr ? *reinterpret_cast<const float4_t*>(x + k) : float4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int s = 0; s < p.in.n_parts; ++s) {
+      const float* ps = parts + s * p.in.part_stride;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int k = (i * TPR + t) * 4;
+        if (k < K) v[i] += *reinterpret_cast<const float4_t*>(ps + k);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int k = (i * TPR + t) * 4;
+      if (k >= K) continue;
+      if (p.bias != nullptr) v[i] += float4_t{p.bias[k], p.bias[k + 1], p.bias[k + 2], p.bias[k + 3]};
+      if (p.sum != nullptr) *reinterpret_cast<float4_t*>(p.sum + (int64_t)row * p.ld_sum + k) = v[i];
+      ss = fmaf(v[i].x, v[i].x, fmaf(v[i].y, v[i].y, fmaf(v[i].z, v[i].z, fmaf(v[i].w, v[i].w, ss))));
+    }
+    if (p.gain != nullptr) r = inv_rms(ss);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int k = (i * TPR + t) * 4;
+      if (k < K) emit(k, v[i], r);
+    }
+  } else {
+    if (p.gain != nullptr) {
+      for (int k = t * 4; k < K; k += TPR * 4) {
+        const float4_t v = value(k);
+        ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss))));
+      }
+      r = inv_rms(ss);
+    }
+    for (int k = t * 4; k < K; k += TPR * 4) {
+      const float4_t v = value(k);
+      if (p.sum != nullptr) *reinterpret_cast<float4_t*>(p.sum + (int64_t)row * p.ld_sum + k) = v;
+      emit(k, v, r);
+    }
   }
 }
 
-// out[m, n] = silu(gu[m, n]) * gu[m, N + n], gu fp32 [M, 2N], out bf16.
-__global__ __launch_bounds__(256) void swiglu_rows_kernel(const float* __restrict__ gu, bf16_t* __restrict__ out, int64_t ldo, int N) {
-  const float* g = gu + (int64_t)blockIdx.x * 2 * N;
-  bf16_t* o = out + (int64_t)blockIdx.x * ldo;
-  for (int n = threadIdx.x * 4; n < N; n += 1024) {
-    const float4_t a = *reinterpret_cast<const float4_t*>(g + n);
-    const float4_t u = *reinterpret_cast<const float4_t*>(g + N + n);
-    float4_t y;
-    y.x = silu(a.x) * u.x; y.y = silu(a.y) * u.y; y.z = silu(a.z) * u.z; y.w = silu(a.w) * u.w;
-    *reinterpret_cast<uint2*>(o + n) = uint2{pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w)};
-  }
+int32_t launch_rows(const RowsArgs& p, hipStream_t st) {
+  if (p.M <= 0) return PHOTON_OK;
+  if (p.K % 4 != 0 || p.in.ld % 4 != 0 || p.in.part_ld % 4 != 0 || p.in.part_stride % 4 != 0 || p.ld_sum % 4 != 0 || p.ldy % 4 != 0 ||
+      (p.y != nullptr && p.gain == nullptr))
+    return fail(PHOTON_ERR_UNSUPPORTED, "row kernel: K=%d and the row pitches must be multiples of 4, fp32 rows come normalised", p.K);
+#define PHOTON_ROWS(TPR, NV) PHOTON_LAUNCH(KC_NORM, st, (rows_kernel<TPR, NV>), dim3((unsigned)((p.M + 256 / TPR - 1) / (256 / TPR))), dim3(256), 0, st, p)
+  // Few rows: a whole workgroup per row, for the latency of one row.  From 4096 rows on (16 workgroups per compute unit
+  // in flight either way) a wave per row, which saves the barrier.
+  if (p.M >= 4096 && p.K <= 2048) {
+    if (p.K <= 1024) PHOTON_ROWS(64, 4); else PHOTON_ROWS(64, 8);
+  } else if (p.K <= 1024) PHOTON_ROWS(256, 1);
+  else if (p.K <= 2048) PHOTON_ROWS(256, 2);
+  else if (p.K <= 4096) PHOTON_ROWS(256, 4);
+  else if (p.K <= 8192) PHOTON_ROWS(256, 8);
+  else PHOTON_ROWS(256, 0);
+#undef PHOTON_ROWS
+  return check_launch("rows_kernel");
 }
 
 __global__ __launch_bounds__(256) void copy_bytes16_kernel(const uint4_t* __restrict__ src, uint4_t* __restrict__ dst, int64_t n16) {
@@ -511,137 +431,120 @@ __global__ __launch_bounds__(256) void copy_bytes16_kernel(const uint4_t* __rest
   if (idx < n16) dst[idx] = src[idx];
 }
 
-template <int OUT>
-static int32_t launch_pingpong(int cls, const bf16_t* A, const bf16_t* B, const float* bias, const float* res, int64_t ldres, void* out,
-                               int64_t ldc, int64_t M, int N, int K, hipStream_t st) {
-  constexpr int BN = (OUT == GEMM_OUT_SWIGLU) ? PP_BN / 2 : PP_BN;
-  GemmArgs p{A, B, bias, res, out, ldres, ldc, (int)M, N, K, (int)((M + PP_BM - 1) / PP_BM), (N + BN - 1) / BN, 8};
-  constexpr size_t lds_bytes = 2 * PP_STAGE;
-  static bool attr_set = false;                                  // more than 64 KiB of dynamic LDS has to be allowed once
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_pingpong_kernel<OUT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+// ---- which tile, how many splits ------------------------------------------------------------------------------------------
+
+enum TileKind { T_64x32 = 0, T_64x64, T_128x64, T_128x128, T_128x256, T_256x256, T_KINDS };
+struct TileShape { int bm, bn; float fixed, slab1, slabn; };
+// Time model behind the choice, in us: fixed + slabs per split * (slab1 if every compute unit has one workgroup at most,
+// slabn * workgroups per unit otherwise) + what the output bytes cost.  Fitted to sweeps of all tiles and splits over
+// 128 - 2048 rows at the widths 1024, 1664 and 2048 (195 points per tile; the model is off by 5-11 % rms), so it
+// ranks the choices rather than predicting a time; 256 x 256 with its long first slab and store pays off once the
+// other tiles need several rounds.
+constexpr TileShape TILES[T_KINDS] = {{64, 32, 1.6f, 0.21f, 0.17f},  {64, 64, 2.3f, 0.24f, 0.22f},    {128, 64, 2.8f, 0.34f, 0.34f},
+                                      {128, 128, 3.5f, 0.50f, 0.59f}, {128, 256, 6.2f, 0.74f, 0.94f}, {256, 256, 8.6f, 1.00f, 1.36f}};
+constexpr float US_PER_MB_OUT = 0.18f, US_PER_MB_PARTS = 0.17f;      // writing the output; reading partial products back
+constexpr int MAX_SPLITS = 8;
+
+struct GemmPlan { int kind, splits, slabs; };
+
+// part_cap: floats the scratch area for partial products holds (0: no splitting).  join_us: what reading the partial
+// products back costs beyond the bytes (a launch of its own, or nothing where the next kernel reads the result anyway).
+static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, int64_t part_cap, float join_us) {
+  const int KT = K / G_BK;
+  GemmPlan best{T_64x64, 1, KT};
+  float best_us = 1e30f;
+  const float out_mb = (float)M * N * (out_f32 ? 4e-6f : 2e-6f);
+  for (int k = 0; k < T_KINDS; ++k) {
+    const int bn = gate_up ? TILES[k].bn / 2 : TILES[k].bn;
+    const int64_t tiles = (M + TILES[k].bm - 1) / TILES[k].bm * ((N + bn - 1) / bn);
+    for (int s = 1; s <= MAX_SPLITS; ++s) {
+      if (s > 1 && (s * M * N > part_cap || KT < 2 * s)) break;
+      const int slabs = (KT + s - 1) / s;
+      if (s > 1 && (KT + slabs - 1) / slabs != s) continue;       // the same slabs per split as with fewer splits
+      const float rounds = (float)((tiles * s + 255) / 256);
+      const float us = TILES[k].fixed + slabs * (rounds <= 1.f ? TILES[k].slab1 : TILES[k].slabn * rounds) +
+                       out_mb * s * US_PER_MB_OUT + (s > 1 ? out_mb * s * US_PER_MB_PARTS + join_us : 0.f);
+      if (us < best_us) { best_us = us; best = GemmPlan{k, s, slabs}; }
+      if (tiles * s >= 512) break;                                // more splits only add bytes
+    }
+  }
+  return best;
+}
+
+static int32_t launch_kernel(void (*kern)(GemmArgs), bool* attr_set, unsigned grid, int threads, size_t lds_bytes, const GemmArgs& p, hipStream_t st) {
+  if (!*attr_set) {                                              // more than 64 KiB of dynamic LDS has to be allowed once
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (e != hipSuccess) return fail(PHOTON_ERR_HIP, "gemm: cannot reserve %zu bytes of LDS: %s", lds_bytes, hipGetErrorString(e));
-    attr_set = true;
+    *attr_set = true;
   }
-  PHOTON_LAUNCH(cls, st, gemm_pingpong_kernel<OUT>, dim3((unsigned)((int64_t)p.tiles_m * p.tiles_n)), dim3(PP_THREADS), lds_bytes, st, p);
-  return check_launch("gemm_pingpong_kernel");
-}
-
-template <int WT, int OUT, int BK, int NB>
-static int32_t launch_gemm_v(int cls, const bf16_t* A, const bf16_t* B, const float* bias, const float* res,
-                             int64_t ldres, void* out, int64_t ldc, int64_t M, int N, int K, hipStream_t st) {
-  constexpr int BM = 64 * WT;
-  constexpr int BN = (OUT == GEMM_OUT_SWIGLU) ? BM / 2 : BM;   // output columns of a tile
-  const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
-  const int64_t grid = (int64_t)tiles_m * tiles_n;
-  const size_t lds_bytes = (size_t)NB * 2 * BM * BK * 2;
-  static bool attr_set = false;                                  // more than 64 KiB of dynamic LDS has to be allowed once
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_kernel<WT, OUT, BK, NB>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (e != hipSuccess) return fail(PHOTON_ERR_HIP, "gemm: cannot reserve %zu bytes of LDS: %s", lds_bytes, hipGetErrorString(e));
-    attr_set = true;
-  }
-  PHOTON_LAUNCH(cls, st, (gemm_bf16_kernel<WT, OUT, BK, NB>), dim3((unsigned)grid), dim3(G_THREADS), lds_bytes, st, A, B, bias, res,
-                ldres, out, ldc, (int)M, N, K, tiles_m, tiles_n);
-  return check_launch("gemm_bf16_kernel");
-}
-
-template <int WT, int OUT>
-static int32_t launch_gemm_t(int cls, const bf16_t* A, const bf16_t* B, const float* bias, const float* res, int64_t ldres, void* out,
-                             int64_t ldc, int64_t M, int N, int K, hipStream_t st) {
-  // Small tiles come with few rows (a decode sub-step of a large batch): few slabs' worth of MFMA work per workgroup
-  // and often fewer workgroups than compute units, so the wait for a slab is what a slab costs.  Four buffers
-  // (three slabs in flight) instead of two: +11-12 % on whole decode steps with 128-256 sequences; six or eight
-  // buffers at the 64-wide tile add nothing.
-  // With more 128-wide tiles than compute units two buffers are kept: two workgroups then share a unit's LDS, which
-  // hides the wait as well and fills the tail better.
-  if constexpr (WT == 2) {
-    constexpr int BN = (OUT == GEMM_OUT_SWIGLU) ? 64 : 128;
-    if (((M + 127) / 128) * ((N + BN - 1) / BN) > 256) return launch_gemm_v<WT, OUT, 64, 2>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
-  }
-  if constexpr (WT <= 2) return launch_gemm_v<WT, OUT, 64, 4>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
-  return launch_pingpong<OUT>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
-}
-
-// Largest tile that still gives the chip enough workgroups.
-static int pick_tile(int64_t M, int N) {
-  auto tiles = [&](int wt) { return ((M + 64 * wt - 1) / (64 * wt)) * ((N + 64 * wt - 1) / (64 * wt)); };
-  if (tiles(4) >= 192) return 4;
-  if (tiles(2) >= 128) return 2;
-  return 1;
+  PHOTON_LAUNCH(KC_CHUNKER_GEMM, st, kern, dim3(grid), dim3(threads), lds_bytes, st, p);
+  return check_launch("gemm kernel");
 }
 
 template <int OUT>
-static int32_t launch_gemm(int cls, const bf16_t* A, const bf16_t* B, const float* bias, const float* res,
-                           int64_t ldres, void* out, int64_t ldc, int64_t M, int N, int K, hipStream_t st) {
-  switch (pick_tile(M, N)) {
-    case 4: return launch_gemm_t<4, OUT>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
-    case 2: return launch_gemm_t<2, OUT>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
-    default: return launch_gemm_t<1, OUT>(cls, A, B, bias, res, ldres, out, ldc, M, N, K, st);
+static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
+  const TileShape& t = TILES[plan.kind];
+  const int bn = OUT == GEMM_OUT_SWIGLU ? t.bn / 2 : t.bn;
+  p.tiles_m = (p.M + t.bm - 1) / t.bm;
+  p.tiles_n = (p.N + bn - 1) / bn;
+  p.group_m = p.tiles_m < 8 ? p.tiles_m : 8;
+  p.slabs = plan.slabs;
+  const int64_t grid = (int64_t)p.tiles_m * p.tiles_n * plan.splits;
+  if (grid > 0x7fffffffLL) return fail(PHOTON_ERR_UNSUPPORTED, "gemm: %lld workgroups are too many for one launch", (long long)grid);
+#define PHOTON_GEMM_CASE(KIND, KERN, THREADS, BUFS)                                                            case KIND: {                                                                                                   static bool attr_set = false;                                                                                return launch_kernel(KERN, &attr_set, (unsigned)grid, THREADS, (size_t)(BUFS) * (t.bm + t.bn) * 128, p, st);   }
+  switch (plan.kind) {
+    PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT>), 256, 4)
+    PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT>), 256, 4)
+    PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT>), 512, 3)
+    PHOTON_GEMM_CASE(T_128x128, (gemm_tile_kernel<128, 128, 4, 2, 3, OUT>), 512, 3)
+    PHOTON_GEMM_CASE(T_128x256, (gemm_pingpong_kernel<2, OUT>), PP_THREADS, 2)
+    default:
+    PHOTON_GEMM_CASE(T_256x256, (gemm_pingpong_kernel<4, OUT>), PP_THREADS, 2)
   }
+#undef PHOTON_GEMM_CASE
 }
 
-// SwiGLU in the epilogue: N output columns from 2N rows of W.  Returns false when the problem is too small for a
-// tile with paired column tiles (the caller then contracts into a [M, 2N] buffer and applies SwiGLU by rows).
-static bool launch_gemm_swiglu(int cls, const bf16_t* A, const bf16_t* B, bf16_t* out, int64_t ldc, int64_t M, int N,
-                               int K, hipStream_t st, int32_t* rc) {
-  auto tiles = [&](int wt) { return ((M + 64 * wt - 1) / (64 * wt)) * ((N + 32 * wt - 1) / (32 * wt)); };
-  if (tiles(4) >= 192) *rc = launch_gemm_t<4, GEMM_OUT_SWIGLU>(cls, A, B, nullptr, nullptr, 0, out, ldc, M, N, K, st);
-  else if (tiles(2) >= 128) *rc = launch_gemm_t<2, GEMM_OUT_SWIGLU>(cls, A, B, nullptr, nullptr, 0, out, ldc, M, N, K, st);
-  else return false;
-  return true;
+int64_t contract_part_floats(int64_t rows, int D) {
+  // 8 splits of a D-wide result, 4 of a 3D-wide one, at up to 1024 rows (more rows have enough tiles)
+  return (rows < 1024 ? rows : 1024) * 12 * (int64_t)D;
+}
+
+int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st) {
+  if (a.K % G_BK != 0 || a.N % 16 != 0 || a.ldo % 4 != 0) return fail(PHOTON_ERR_UNSUPPORTED, "contraction: K=%d must be a multiple of 64, N=%d of 16", a.K, a.N);
+  GemmArgs p{};
+  p.x = reinterpret_cast<const bf16_t*>(a.x); p.W = reinterpret_cast<const bf16_t*>(a.W); p.M = a.M; p.N = a.N; p.K = a.K;
+  p.bias = a.bias; p.out = a.out; p.ldo = a.ldo;
+  if (a.epilogue == EPI_SWIGLU) return launch_gemm<GEMM_OUT_SWIGLU>(p, plan_gemm(a.M, a.N, a.K, true, false, 0, 0.f), st);
+  // a plain result that the caller needs in one piece is joined by a launch of the row kernel
+  const bool join = a.epilogue == EPI_PLAIN && !a.split_ok;
+  const GemmPlan plan = plan_gemm(a.M, a.N, a.K, false, true, a.part_cap, join ? 3.5f : 0.f);
+  const RowSource whole{reinterpret_cast<const float*>(a.out), a.ldo, nullptr, 0, 0, 0};
+  if (plan.splits == 1) {
+    if (a.epilogue == EPI_RESID) {
+      if (a.res.n_parts != 0) return fail(PHOTON_ERR_INVALID_ARG, "contraction: the residual rows must be in one piece");
+      const char *r0 = reinterpret_cast<const char*>(a.res.x), *o0 = reinterpret_cast<const char*>(a.out);
+      const char *r1 = r0 + ((int64_t)(a.M - 1) * a.res.ld + a.N) * 4, *o1 = o0 + ((int64_t)(a.M - 1) * a.ldo + a.N) * 4;
+      if (r0 < o1 && o0 < r1) return fail(PHOTON_ERR_INVALID_ARG, "contraction: the residual rows must not overlap the output");
+      p.res = a.res.x; p.ldres = a.res.ld;
+    }
+    *result = whole;
+    return launch_gemm<GEMM_OUT_F32>(p, plan, st);
+  }
+  p.bias = nullptr; p.out = a.parts; p.ldo = a.N; p.split_stride = (int64_t)a.M * a.N;
+  PHOTON_TRY(launch_gemm<GEMM_OUT_F32>(p, plan, st));
+  RowSource r{nullptr, 0, a.parts, plan.splits, a.N, p.split_stride};
+  if (a.epilogue == EPI_RESID) { r.x = a.res.x; r.ld = a.res.ld; }
+  if (!join) { *result = r; return PHOTON_OK; }
+  RowsArgs rows{};
+  rows.in = r; rows.bias = a.bias; rows.sum = reinterpret_cast<float*>(a.out); rows.ld_sum = a.ldo; rows.M = a.M; rows.K = a.N;
+  *result = whole;
+  return launch_rows(rows, st);
 }
 
 static int32_t launch_chunker_gemm(const void* x, const void* w, const float* bias, void* out, int64_t M, int N, int K, hipStream_t st) {
-  return launch_gemm<GEMM_OUT_BF16>(KC_CHUNKER_GEMM, (const bf16_t*)x, (const bf16_t*)w, bias, nullptr, 0, out, N, M, N, K, st);
-}
-
-size_t linear_many_workspace_bytes(int64_t rows, int K_max, int N2_max) {
-  // the activations as bf16, then the gate|up product rows (fp32) of the unfused SwiGLU
-  return (size_t)rows * K_max * 2 + (size_t)rows * N2_max * sizeof(float);
-}
-
-int32_t launch_norm_round_rows(const float* x, int64_t ldx, const float* gain, float eps, void* xb, int M, int K, hipStream_t st) {
-  if (K % 4 != 0 || ldx % 4 != 0) return fail(PHOTON_ERR_UNSUPPORTED, "row kernel: K=%d and the row pitch must be multiples of 4", K);
-  PHOTON_LAUNCH(KC_NORM, st, norm_round_rows_kernel, dim3(M), dim3(256), 0, st, x, ldx, gain, eps, reinterpret_cast<bf16_t*>(xb), K);
-  return check_launch("norm_round_rows_kernel");
-}
-
-int32_t launch_linear_many(const LinearArgs& a, void* workspace, int K_max, hipStream_t st) {
-  if (!a.w_bf16 || a.K % G_BK != 0 || a.K > K_max || a.ldx % 4 != 0)
-    return fail(PHOTON_ERR_UNSUPPORTED, "many-row linear: needs bf16 weights, K=%d a multiple of 64 and at most %d", a.K, K_max);
-  if (a.epilogue == EPI_RESID) {
-    const char *r0 = reinterpret_cast<const char*>(a.res), *o0 = reinterpret_cast<const char*>(a.out);
-    const char *r1 = r0 + ((int64_t)(a.M - 1) * a.ldres + a.N) * 4, *o1 = o0 + ((int64_t)(a.M - 1) * a.ldo + a.N) * 4;
-    if (r0 < o1 && o0 < r1) return fail(PHOTON_ERR_INVALID_ARG, "many-row linear: the residual rows must not overlap the output");
-  }
-  if (a.out_bf16 != (a.epilogue == EPI_SWIGLU))
-    return fail(PHOTON_ERR_UNSUPPORTED, "many-row linear: the SwiGLU product, and only it, is written as bf16");
-  if (a.x_bf16) {
-    // bf16 rows are the operand as they stand: one pass of the plain contraction
-    if (a.gain != nullptr || a.epilogue == EPI_SWIGLU || a.ldx != a.K)
-      return fail(PHOTON_ERR_UNSUPPORTED, "many-row linear: bf16 activations come dense, without norm or SwiGLU");
-    return launch_gemm<GEMM_OUT_F32>(KC_CHUNKER_GEMM, reinterpret_cast<const bf16_t*>(a.x), (const bf16_t*)a.W, a.bias,
-                                     a.epilogue == EPI_RESID ? a.res : nullptr, a.ldres, a.out, a.ldo, a.M, a.N, a.K, st);
-  }
-  bf16_t* xb = reinterpret_cast<bf16_t*>(workspace);
-  float* gu = reinterpret_cast<float*>(xb + (size_t)a.M * K_max);
-  PHOTON_LAUNCH(KC_NORM, st, norm_round_rows_kernel, dim3(a.M), dim3(256), 0, st, a.x, a.ldx, a.gain, a.eps, xb, a.K);
-  PHOTON_TRY(check_launch("norm_round_rows_kernel"));
-  if (a.epilogue == EPI_SWIGLU) {
-    if (a.N % 4 != 0) return fail(PHOTON_ERR_UNSUPPORTED, "many-row linear: SwiGLU width %d must be a multiple of 4", a.N);
-    int32_t rc = PHOTON_OK;
-    bf16_t* act = reinterpret_cast<bf16_t*>(a.out);
-    if (launch_gemm_swiglu(KC_CHUNKER_GEMM, xb, (const bf16_t*)a.W, act, a.ldo, a.M, a.N, a.K, st, &rc)) return rc;
-    PHOTON_TRY(launch_gemm<GEMM_OUT_F32>(KC_CHUNKER_GEMM, xb, (const bf16_t*)a.W, nullptr, nullptr, 0, gu, 2 * (int64_t)a.N, a.M, 2 * a.N,
-                                         a.K, st));
-    PHOTON_LAUNCH(KC_SILU_MUL, st, swiglu_rows_kernel, dim3(a.M), dim3(256), 0, st, gu, act, a.ldo, a.N);
-    return check_launch("swiglu_rows_kernel");
-  }
-  return launch_gemm<GEMM_OUT_F32>(KC_CHUNKER_GEMM, xb, (const bf16_t*)a.W, a.bias, a.epilogue == EPI_RESID ? a.res : nullptr, a.ldres,
-                                   a.out, a.ldo, a.M, a.N, a.K, st);
+  GemmArgs p{};
+  p.x = (const bf16_t*)x; p.W = (const bf16_t*)w; p.bias = bias; p.out = out; p.ldo = N; p.M = (int)M; p.N = N; p.K = K;
+  return launch_gemm<GEMM_OUT_BF16>(p, plan_gemm(M, N, K, false, false, 0, 0.f), st);
 }
 
 }  // namespace photon

@@ -41,12 +41,62 @@ bool launch_linear_resident(const LinearArgs& a, hipStream_t st);
 // Returns true when the launch was issued.
 bool launch_linear_resident_x2(const LinearArgs& a, hipStream_t st);
 
-// Many rows (dozens and up) with bf16 weights: row kernel (norm, rounding to bf16) + tiled MFMA
-// contraction + (SwiGLU) row kernel.  `workspace` holds linear_many_workspace_bytes(rows, K_max, N2_max)
-// bytes, K_max >= every K and N2_max >= every 2N of a SwiGLU call that will be issued with it.
-size_t linear_many_workspace_bytes(int64_t rows, int K_max, int N2_max);
-// The row kernel alone: xb[M, K] (dense bf16) = rmsnorm(x; gain, eps) (gain == nullptr: x), rounded to nearest even.
-int32_t launch_norm_round_rows(const float* x, int64_t ldx, const float* gain, float eps, void* xb, int M, int K, hipStream_t st);
-int32_t launch_linear_many(const LinearArgs& a, void* workspace, int K_max, hipStream_t st);
+// ---- 17 rows and up with bf16 weights: row kernel (norm, rounding to bf16) + tiled MFMA contraction ----
+
+// Rows as a sum: x[row * ld ..] (nullptr: nothing) plus n_parts partial products of a contraction split over K,
+// parts[s * part_stride + row * part_ld ..], added in order.
+struct RowSource {
+  const float* x = nullptr;
+  int64_t ld = 0;
+  const float* parts = nullptr;
+  int n_parts = 0;
+  int64_t part_ld = 0, part_stride = 0;
+  // rows off, off + mul, off + 2 mul, ..
+  RowSource pick(int64_t mul, int64_t off) const {
+    RowSource r = *this;
+    if (x != nullptr) r.x += off * ld;
+    if (parts != nullptr) r.parts += off * part_ld;
+    r.ld *= mul;
+    r.part_ld *= mul;
+    return r;
+  }
+};
+
+// v = in + bias (nullptr: none); sum = v; xb [M, K] (dense bf16) = rmsnorm(v; gain, eps) rounded to nearest even
+// (gain == nullptr: v rounded); y = rmsnorm(v; gain, eps) in fp32.  Each output may be nullptr; sum may be in.x itself.
+struct RowsArgs {
+  RowSource in;
+  const float* bias = nullptr;
+  const float* gain = nullptr;
+  float eps = 0.f;
+  float* sum = nullptr;
+  int64_t ld_sum = 0;
+  uint16_t* xb = nullptr;
+  float* y = nullptr;
+  int64_t ldy = 0;
+  int M = 0, K = 0;
+};
+int32_t launch_rows(const RowsArgs& a, hipStream_t st);
+
+// x [M, K] dense bf16, W [N, K] (2N rows for EPI_SWIGLU) bf16; out fp32 [M, ldo], or for EPI_SWIGLU bf16 [M, ldo].
+// EPI_RESID: out = res + x W^T, where out and res must not overlap.  parts: scratch of part_cap floats for the partial
+// products of a contraction split over K.  `result` says where the fp32 result lies: in out, or still in pieces
+// (EPI_RESID: the residual rows and the partial products; EPI_PLAIN with split_ok: the partial products, without the
+// bias), for the next kernel to add.
+struct ContractArgs {
+  const void* x = nullptr;
+  const void* W = nullptr;
+  const float* bias = nullptr;   // EPI_PLAIN
+  RowSource res;                 // EPI_RESID, in one piece
+  void* out = nullptr;
+  int64_t ldo = 0;
+  float* parts = nullptr;
+  int64_t part_cap = 0;
+  int M = 0, N = 0, K = 0;
+  int epilogue = EPI_PLAIN;
+  bool split_ok = false;
+};
+int64_t contract_part_floats(int64_t rows, int D);     // scratch that lets every contraction of a D-wide module split as it would
+int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st);
 
 }  // namespace photon

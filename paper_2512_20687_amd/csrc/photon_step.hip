@@ -14,13 +14,13 @@ namespace photon {
 
 // ------------------------------------------------------------------ small kernels
 
-// out[i*out_mul + out_off] = rmsnorm(in[i*in_mul + in_off]) * g ; rows of D floats, D a multiple of 4.
-__global__ __launch_bounds__(256) void norm_rows_kernel(const float* __restrict__ in, int in_mul, int in_off,
+// out[i*out_mul + out_off] = rmsnorm(in[i * ld ..]) * g ; rows of D floats, D a multiple of 4.
+__global__ __launch_bounds__(256) void norm_rows_kernel(const float* __restrict__ in, int64_t ld,
                                                         const float* __restrict__ g, float eps, float* __restrict__ out,
                                                         int out_mul, int out_off, int D) {
   extern __shared__ float4_t xrow[];
   const int i = blockIdx.x, tid = threadIdx.x;
-  const float* x = in + ((int64_t)i * in_mul + in_off) * D;
+  const float* x = in + (int64_t)i * ld;
   float ss = 0.f;
   for (int d = tid * 4; d < D; d += 1024) {
     const float4_t v = *reinterpret_cast<const float4_t*>(x + d);
@@ -75,8 +75,9 @@ __global__ __launch_bounds__(256) void broadcast_rows_kernel(const float* __rest
 
 // Top-level STEP: position of sequence b is seq_len[b]-1 (the count already includes the new entry);
 // k, v go to cache[b, h, pos, :] of this layer, whose rows hold `pitch` >= d_h elements (the surplus is zeroed).
+// qkv: n_parts partial products, part_stride apart, that add up to the projection.
 template <typename TKV>
-__global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __restrict__ qkv, float* __restrict__ qrot,
+__global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __restrict__ qkv, int n_parts, int64_t part_stride, float* __restrict__ qrot,
                                                                  TKV* __restrict__ kc, TKV* __restrict__ vc,
                                                                  const int32_t* __restrict__ seq_len, int Bt, int H,
                                                                  int d_h, int pitch, int64_t S_max, float theta) {
@@ -90,8 +91,11 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
   float c, s;
   rope_angle(pos, i, d_h, theta, c, s);
   const float* src = qkv + (int64_t)b * 3 * D + h * d_h;
-  const float qa = src[i], qb = src[i + half];
-  const float ka = src[D + i], kb = src[D + i + half];
+  float qa = src[i], qb = src[i + half], ka = src[D + i], kb = src[D + i + half], va = src[2 * D + i], vb = src[2 * D + i + half];
+  for (int s2 = 1; s2 < n_parts; ++s2) {
+    src += part_stride;
+    qa += src[i]; qb += src[i + half]; ka += src[D + i]; kb += src[D + i + half]; va += src[2 * D + i]; vb += src[2 * D + i + half];
+  }
   float* qd = qrot + (int64_t)b * D + h * d_h;
   qd[i] = qa * c - qb * s;
   qd[i + half] = qb * c + qa * s;
@@ -99,8 +103,8 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
   const int64_t slot = (((int64_t)b * H + h) * S_max + pos) * pitch;
   kc[slot + i] = from_f32<TKV>(ka * c - kb * s);
   kc[slot + i + half] = from_f32<TKV>(kb * c + ka * s);
-  vc[slot + i] = from_f32<TKV>(src[2 * D + i]);
-  vc[slot + i + half] = from_f32<TKV>(src[2 * D + i + half]);
+  vc[slot + i] = from_f32<TKV>(va);
+  vc[slot + i + half] = from_f32<TKV>(vb);
   for (int p = d_h + i; p < pitch; p += half) { kc[slot + p] = TKV{}; vc[slot + p] = TKV{}; }
 }
 
@@ -198,13 +202,10 @@ static inline unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256
 
 // ------------------------------------------------------------------ workspace plan
 
-// From this many rows on a linear map goes to the tiled MFMA contraction instead of the few-row kernels
-// (which would re-read the weights once per 16 rows).
-constexpr int LINEAR_MANY_ROWS = 128;
-// Between the two, from this many rows on (more than one row tile of 16), the rows are normalised and rounded to
-// bf16 by the row kernel and the few-row kernel takes several row tiles per workgroup: the weights are then streamed
-// once per 32 or 64 rows instead of once per 16 (measured at 24 rows: QKV 17.2 -> 4.5 + 9.4 us, gate/up 23.7 -> 4.5 + 13.1).
-constexpr int LINEAR_MID_ROWS = 17;
+// From this many rows on (more than one row tile of 16) a bf16 pass runs on the tiled contractions (photon_gemm.hip): the
+// rows are normalised and rounded to bf16 by the row kernel, and no workgroup takes in all of K for all rows.  Below, the
+// few-row kernels, which keep the fp32 rows' remainders.
+constexpr int MANY_ROWS = 17;
 
 struct Plan {
   int L = 0;
@@ -216,9 +217,11 @@ struct Plan {
   size_t h2 = 0, attn2 = 0, qkv2 = 0, qrot2 = 0, act2 = 0;   // second set for the main line of a hierarchy (top-level decoder, then STEP)
   int64_t rows2 = 0;                             // its rows: Bt chunks x R_L converter rows
   size_t cond_top = 0;                           // conditioning latents of the level-(L-1) chunks (written on the main line)
-  size_t many = 0, many2 = 0;                    // scratch of the many-row linear path (0 rows: absent), main and STEP branch
+  size_t many = 0, many2 = 0;                    // bf16 rows of the tiled contractions (MANY_ROWS rows and up), main and STEP branch
+  size_t parts = 0, parts2 = 0;                  // their partial products
+  int64_t part_cap = 0, part_cap2 = 0;           // floats
   size_t hx[PHOTON_MAX_LEVELS] = {0}, hA = 0;    // hierarchical generation: encoder-side new units of level l, chunker outputs
-  int many_K = 0;                                // widest contraction it is sized for
+  int many_K = 0;                                // widest contraction they are sized for
   size_t bar = 0;                                // barrier slots of the persistent launches of one step, then the error word
   int bar_slots = 0;
   size_t fresh[PHOTON_MAX_LEVELS] = {0};         // fresh[l]: new level-l units, l = 0..L-1
@@ -266,8 +269,16 @@ static Plan make_plan(const photon_config& c, int Bt, int64_t S_max) {
   if (c.dt == PHOTON_BF16) {
     p.many_K = (int)(D > F ? D : F);
     if ((int64_t)c.C[c.L - 1] * D > p.many_K) p.many_K = (int)(c.C[c.L - 1] * D);   // the top chunker contracts over C_L * D
-    if (p.rows_max >= LINEAR_MID_ROWS) p.many = bump(cur, linear_many_workspace_bytes(p.rows_max, p.many_K, (int)(2 * F)));
-    if (p.rows2 >= LINEAR_MID_ROWS) p.many2 = bump(cur, linear_many_workspace_bytes(p.rows2, p.many_K, (int)(2 * F)));
+    if (p.rows_max >= MANY_ROWS) {
+      p.many = bump(cur, (size_t)p.rows_max * p.many_K * 2);
+      p.part_cap = contract_part_floats(p.rows_max, c.D);
+      p.parts = bump(cur, (size_t)p.part_cap * f);
+    }
+    if (p.rows2 >= MANY_ROWS) {
+      p.many2 = bump(cur, (size_t)p.rows2 * p.many_K * 2);
+      p.part_cap2 = contract_part_floats(p.rows2, c.D);
+      p.parts2 = bump(cur, (size_t)p.part_cap2 * f);
+    }
   }
   for (int l = 1; l <= c.L; ++l) {
     p.fresh[l - 1] = bump(cur, (size_t)p.chunks[l] * c.C[l - 1] * D * f);
@@ -326,7 +337,8 @@ struct Ctx {
   char* base;
   bool bf16;
   size_t o_h, o_attn, o_qkv, o_qrot, o_act;   // activation buffers of the branch this context drives
-  size_t o_many;                              // its many-row linear scratch
+  size_t o_many, o_parts;                     // its bf16 rows and partial products of the tiled contractions
+  int64_t part_cap;
   bool overlap;                               // run the top-level update beside the lower levels
   const photon_encoder_weights* ew = nullptr; // encoder-side weights (prefill, hierarchical generation)
   const photon_hier_state* hs = nullptr;      // lower-level encoder streams (hierarchical generation only)
@@ -337,65 +349,126 @@ struct Ctx {
 };
 
 
-// Rows entering a module pass: row i of the pass lives at in[i * ld] (D floats).
-struct RowsIn {
-  const float* ptr = nullptr;
-  int64_t ld = 0;
-};
+static bool many_rows(const Ctx& x, int64_t rows) { return x.bf16 && rows >= MANY_ROWS; }
 
-static int32_t linear(const Ctx& x, const float* in, int64_t ldx, const void* W, const float* gain, const float* bias,
-                      const float* res, int64_t ldres, float* out, int64_t ldo, int M, int N, int K, int epilogue,
-                      bool in_bf16 = false, bool out_bf16 = false) {
-  LinearArgs a;
-  a.x_bf16 = in_bf16; a.out_bf16 = out_bf16;
-  a.x = in; a.ldx = ldx; a.W = W; a.w_bf16 = x.bf16; a.gain = gain; a.eps = x.c->rms_eps; a.bias = bias; a.res = res;
-  a.ldres = ldres; a.out = out; a.ldo = ldo; a.M = M; a.N = N; a.K = K; a.epilogue = epilogue;
-  if (x.bf16 && M >= LINEAR_MANY_ROWS && K <= x.p.many_K && (epilogue != EPI_SWIGLU || 2 * N <= 2 * x.c->d_ff))
-    return launch_linear_many(a, x.base + x.o_many, x.p.many_K, x.st);
-  const int64_t w_bytes = (int64_t)(epilogue == EPI_SWIGLU ? 2 : 1) * N * K * 2;
-  if (x.bf16 && M >= LINEAR_MID_ROWS && K <= x.p.many_K && w_bytes < ((int64_t)1 << 32)) {
-    if (!in_bf16) {                                          // norm and rounding once, in front of the bf16-row kernel
-      void* rows_bf16 = x.base + x.o_many;
-      PHOTON_TRY(launch_norm_round_rows(in, ldx, gain, x.c->rms_eps, rows_bf16, M, K, x.st));
-      a.x = reinterpret_cast<const float*>(rows_bf16); a.ldx = K; a.x_bf16 = true; a.gain = nullptr;
-    }
-    return launch_linear(a, x.st);
+// Row kernel in front of a tiled contraction: `in` (summed up, if it comes in pieces, and the sum kept in `sum`),
+// normalised and rounded to bf16, into this branch's bf16 rows.
+static int32_t round_rows(const Ctx& x, const RowSource& in, const float* gain, float* sum, int64_t ld_sum, int rows, int K) {
+  RowsArgs a;
+  a.in = in; a.gain = gain; a.eps = x.c->rms_eps; a.sum = in.n_parts ? sum : nullptr; a.ld_sum = ld_sum;
+  a.xb = reinterpret_cast<uint16_t*>(x.base + x.o_many); a.M = rows; a.K = K;
+  return launch_rows(a, x.st);
+}
+
+// Tiled contraction of `rows` dense bf16 rows (nullptr: this branch's, as round_rows left them).
+static int32_t contract(const Ctx& x, const void* xb, const void* W, const float* bias, const RowSource& res, void* out, int64_t ldo, int rows,
+                        int N, int K, int epilogue, bool split_ok, RowSource* result) {
+  ContractArgs a;
+  a.x = xb != nullptr ? xb : x.base + x.o_many; a.W = W; a.bias = bias; a.res = res; a.out = out; a.ldo = ldo;
+  a.parts = x.f(x.o_parts); a.part_cap = x.part_cap; a.M = rows; a.N = N; a.K = K; a.epilogue = epilogue; a.split_ok = split_ok;
+  return launch_contract(a, result, x.st);
+}
+
+// out[M, N] = rmsnorm(in; gain) W^T + bias (gain, bias: nullptr for none).
+static int32_t linear(const Ctx& x, const RowSource& in, const void* W, const float* gain, const float* bias, float* out, int64_t ldo, int M,
+                      int N, int K) {
+  if (many_rows(x, M) && K <= x.p.many_K) {
+    RowSource whole;
+    PHOTON_TRY(round_rows(x, in, gain, nullptr, 0, M, K));
+    return contract(x, nullptr, W, bias, RowSource{}, out, ldo, M, N, K, EPI_PLAIN, false, &whole);
   }
+  LinearArgs a;
+  a.x = in.x; a.ldx = in.ld;
+  if (in.n_parts != 0) {                                   // a first sub-step with several converter rows had many rows, its items are few
+    RowsArgs sum;
+    sum.in = in; sum.sum = x.f(x.o_h); sum.ld_sum = K; sum.M = M; sum.K = K;
+    PHOTON_TRY(launch_rows(sum, x.st));
+    a.x = sum.sum; a.ldx = K;
+  }
+  a.W = W; a.w_bf16 = x.bf16; a.gain = gain; a.eps = x.c->rms_eps; a.bias = bias;
+  a.out = out; a.ldo = ldo; a.M = M; a.N = N; a.K = K;
   return launch_linear(a, x.st);
 }
 
-static int32_t norm(const Ctx& x, const float* in, int in_mul, int in_off, const float* g, float* out, int out_mul, int out_off,
-                    int rows) {
-  PHOTON_LAUNCH(KC_NORM, x.st, norm_rows_kernel, dim3(rows), dim3(256), x.c->D * sizeof(float), x.st, in, in_mul, in_off, g,
-                x.c->rms_eps, out, out_mul, out_off, x.c->D);
+// out[i * out_mul + out_off] = rmsnorm(in[i]) * g for `rows` rows of D floats.
+static int32_t norm(const Ctx& x, const RowSource& in, const float* g, float* out, int out_mul, int out_off, int rows) {
+  const int D = x.c->D;
+  if (in.n_parts != 0 || many_rows(x, rows)) {
+    RowsArgs a;
+    a.in = in; a.gain = g; a.eps = x.c->rms_eps; a.y = out + (int64_t)out_off * D; a.ldy = (int64_t)out_mul * D; a.M = rows; a.K = D;
+    return launch_rows(a, x.st);
+  }
+  PHOTON_LAUNCH(KC_NORM, x.st, norm_rows_kernel, dim3(rows), dim3(256), D * sizeof(float), x.st, in.x, in.ld, g, x.c->rms_eps, out, out_mul,
+                out_off, D);
   return check_launch("norm_rows_kernel");
 }
 
-// Tail of a block once the attention output sits in p.attn: O projection + residual, then the SwiGLU sub-layer,
-// leaving the residual stream in p.h.  `in` is the block's input (the residual stream before the block: p.h from
-// the second block on).  The stream between the two sub-layers lives in the q/k/v buffer, which the attention
-// has finished with: no projection then adds a residual in place, which the many-row contraction does not allow
-// (it requests residual values ahead of the stores of the tile before).
-static int32_t block_tail(const Ctx& x, const photon_layer_weights& lw, RowsIn in, int rows, bool attn_bf16) {
+static int32_t copy_rows(const Ctx& x, const float* src, float* dst, int64_t floats) {
+  PHOTON_LAUNCH(KC_MISC, x.st, copy_f32x4_kernel, dim3((unsigned)((floats / 4 + 255) / 256)), dim3(256), 0, x.st,
+                reinterpret_cast<const float4_t*>(src), reinterpret_cast<float4_t*>(dst), floats / 4);
+  return check_launch("copy_f32x4_kernel");
+}
+
+// One few-row linear map of a block: residual (res, may be nullptr) or SwiGLU epilogue, bf16 rows in / out by flag.
+static int32_t few_row_linear(const Ctx& x, const float* in, int64_t ldx, const void* W, const float* gain, const RowSource& res, float* out,
+                              int64_t ldo, int M, int N, int K, int epilogue, bool in_bf16, bool out_bf16) {
+  LinearArgs a;
+  a.x_bf16 = in_bf16; a.out_bf16 = out_bf16;
+  a.x = in; a.ldx = ldx; a.W = W; a.w_bf16 = x.bf16; a.gain = gain; a.eps = x.c->rms_eps; a.res = res.x; a.ldres = res.ld;
+  a.out = out; a.ldo = ldo; a.M = M; a.N = N; a.K = K; a.epilogue = epilogue;
+  return launch_linear(a, x.st);
+}
+
+// Tail of a block once the attention output sits in p.attn: O projection + residual, then the SwiGLU sub-layer.  `in` is
+// the block's input, in one piece (the residual stream before the block: p.h from the second block on); `out` says where
+// the residual stream lies afterwards: in p.h, or (tiled contractions) in pieces that the next row kernel adds up.
+// The stream between the two sub-layers lives in the q/k/v buffer, which the attention has finished with: no
+// projection then adds a residual in place, which the tiled contraction does not allow (it requests residual values
+// ahead of the stores of the tile before).
+static int32_t block_tail(const Ctx& x, const photon_layer_weights& lw, RowSource in, int rows, bool attn_bf16, RowSource* out) {
   const photon_config& c = *x.c;
+  const int D = c.D, F = c.d_ff;
   float *h = x.f(x.o_h), *attn = x.f(x.o_attn), *act = x.f(x.o_act), *mid = x.f(x.o_qkv);
-  PHOTON_TRY(linear(x, attn, c.D, lw.wo, nullptr, nullptr, in.ptr, in.ld, mid, c.D, rows, c.D, c.D, EPI_RESID, attn_bf16, false));
-  if (c.d_ff == 0) {
-    PHOTON_LAUNCH(KC_MISC, x.st, copy_f32x4_kernel, dim3((unsigned)(((int64_t)rows * c.D / 4 + 255) / 256)), dim3(256), 0, x.st,
-                  reinterpret_cast<const float4_t*>(mid), reinterpret_cast<float4_t*>(h), (int64_t)rows * c.D / 4);
-    return check_launch("copy_f32x4_kernel");
+  if (many_rows(x, rows)) {
+    RowSource m, none;
+    PHOTON_TRY(contract(x, attn, lw.wo, nullptr, in, mid, D, rows, D, D, EPI_RESID, false, &m));
+    if (F == 0) {
+      if (m.n_parts != 0) { *out = m; return PHOTON_OK; }
+      *out = RowSource{h, D};
+      return copy_rows(x, mid, h, (int64_t)rows * D);
+    }
+    PHOTON_TRY(round_rows(x, m, lw.g2, mid, D, rows, D));
+    PHOTON_TRY(contract(x, nullptr, lw.wgu, nullptr, RowSource{}, act, F, rows, F, D, EPI_SWIGLU, false, &none));
+    return contract(x, act, lw.wd, nullptr, RowSource{mid, D}, h, D, rows, D, F, EPI_RESID, false, out);
   }
+  *out = RowSource{h, D};
+  PHOTON_TRY(few_row_linear(x, attn, D, lw.wo, nullptr, in, mid, D, rows, D, D, EPI_RESID, attn_bf16, false));
+  if (F == 0) return copy_rows(x, mid, h, (int64_t)rows * D);
   // with bf16 matrices the hidden rows are kept as bf16: they are the down projection's MFMA operand as they stand
-  PHOTON_TRY(linear(x, mid, c.D, lw.wgu, lw.g2, nullptr, nullptr, 0, act, c.d_ff, rows, c.d_ff, c.D, EPI_SWIGLU, false, x.bf16));
-  return linear(x, act, c.d_ff, lw.wd, nullptr, nullptr, mid, c.D, h, c.D, rows, c.D, c.d_ff, EPI_RESID, x.bf16, false);
+  PHOTON_TRY(few_row_linear(x, mid, D, lw.wgu, lw.g2, RowSource{}, act, F, rows, F, D, EPI_SWIGLU, false, x.bf16));
+  return few_row_linear(x, act, F, lw.wd, nullptr, RowSource{mid, D}, h, D, rows, D, F, EPI_RESID, x.bf16, false);
+}
+
+// Head of a block: q, k, v of `rows` rows (fp32 [rows, 3D]).  `in` may come in pieces; it is in one piece (in p.h)
+// afterwards.  The projection itself may come in pieces (of row pitch 3D) where the kernel that reads it adds them up.
+static int32_t block_qkv(const Ctx& x, const photon_layer_weights& lw, RowSource* in, int rows, bool split_ok, RowSource* qkv) {
+  const int D = x.c->D;
+  float *h = x.f(x.o_h), *out = x.f(x.o_qkv);
+  if (many_rows(x, rows)) {
+    PHOTON_TRY(round_rows(x, *in, lw.g1, h, D, rows, D));
+    if (in->n_parts != 0) *in = RowSource{h, D};
+    return contract(x, nullptr, lw.wqkv, nullptr, RowSource{}, out, 3 * (int64_t)D, rows, 3 * D, D, EPI_PLAIN, split_ok, qkv);
+  }
+  *qkv = RowSource{out, 3 * (int64_t)D};
+  return few_row_linear(x, in->x, in->ld, lw.wqkv, lw.g1, RowSource{}, out, 3 * D, rows, 3 * D, D, EPI_PLAIN, false, false);
 }
 
 // All blocks of the level-`level` local decoder on n_chunks * q_len rows (window positions
-// q_pos .. q_pos+q_len-1 of every chunk).  Leaves the residual stream in p.h.
+// q_pos .. q_pos+q_len-1 of every chunk).  `out`: the residual stream afterwards (see block_tail).
 // alone: nothing else runs beside this pass (no STEP branch on the side stream).  The persistent kernel holds every
 // compute unit's registers and most of its LDS, so kernels of another stream cannot run beside it: where the
 // top-level update overlaps the lower levels, those levels keep the separate launches.
-static int32_t local_module_pass(const Ctx& x, int level, int64_t n_chunks, int q_len, int q_pos, RowsIn in, bool alone = true) {
+static int32_t local_module_pass(const Ctx& x, int level, int64_t n_chunks, int q_len, int q_pos, RowSource in, RowSource* out, bool alone = true) {
   const photon_config& c = *x.c;
   const photon_module_weights& mod = x.w->dec[level - 1];
   const int W = c.R[level - 1] + c.C[level - 1] - 1;
@@ -407,7 +480,7 @@ static int32_t local_module_pass(const Ctx& x, int level, int64_t n_chunks, int 
     // all blocks in one launch, the projections meeting at grid barriers instead of kernel boundaries
     PersistentModule pm;
     pm.layers = mod.layers; pm.n_layers = c.n_layers;
-    pm.x_in = in.ptr; pm.ld_in = in.ld;
+    pm.x_in = in.x; pm.ld_in = in.ld;
     pm.h = h; pm.qkv = qkv; pm.attn = attn; pm.act = x.f(x.o_act);
     pm.lk = x.f(x.p.lk[level - 1]); pm.lv = x.f(x.p.lv[level - 1]); pm.layer_cache = layer_cache;
     pm.bar = x.bar_words() + (size_t)(*x.bar_next) * PM_BAR_WORDS;
@@ -417,6 +490,7 @@ static int32_t local_module_pass(const Ctx& x, int level, int64_t n_chunks, int 
     pm.eps = c.rms_eps; pm.scale = scale; pm.theta = c.rope_theta;
     if (persistent_module_supported(pm)) {
       ++*x.bar_next;
+      *out = RowSource{h, c.D};
       return launch_persistent_module(pm, x.st);
     }
   }
@@ -424,12 +498,13 @@ static int32_t local_module_pass(const Ctx& x, int level, int64_t n_chunks, int 
     const photon_layer_weights& lw = mod.layers[i];
     float* lk = x.f(x.p.lk[level - 1]) + (size_t)i * layer_cache;
     float* lv = x.f(x.p.lv[level - 1]) + (size_t)i * layer_cache;
-    PHOTON_TRY(linear(x, in.ptr, in.ld, lw.wqkv, lw.g1, nullptr, nullptr, 0, qkv, 3 * c.D, rows, 3 * c.D, c.D, EPI_PLAIN));
+    RowSource qkv_rows;
+    PHOTON_TRY(block_qkv(x, lw, &in, rows, true, &qkv_rows));
     // with bf16 matrices the attention rows are written as bf16: the O projection's MFMA operand as they stand
-    PHOTON_TRY(launch_local_step_attn(c.d_h, qkv, lk, lv, attn, n_chunks, W, q_len, q_pos, c.H, scale, c.rope_theta, x.bf16, x.st));
-    PHOTON_TRY(block_tail(x, lw, in, rows, x.bf16));
-    in.ptr = h; in.ld = c.D;
+    PHOTON_TRY(launch_local_step_attn(c.d_h, qkv_rows, lk, lv, attn, n_chunks, W, q_len, q_pos, c.H, scale, c.rope_theta, x.bf16, x.st));
+    PHOTON_TRY(block_tail(x, lw, in, rows, x.bf16, &in));
   }
+  *out = in;
   return PHOTON_OK;
 }
 
@@ -437,10 +512,11 @@ static int32_t local_module_pass(const Ctx& x, int level, int64_t n_chunks, int 
 // stream's cache at position seq_len - 1 (the count already includes the new unit) and writes the new state
 // of sequence b to out[(b * out_mul + out_off) * D].
 static int32_t stream_step(const Ctx& x, const photon_module_weights& mod, void* k_cache, void* v_cache, const int32_t* seq_len,
-                           int64_t S_cap, RowsIn in, float* out, int out_mul, int out_off) {
+                           int64_t S_cap, RowSource in, float* out, int out_mul, int out_off) {
   const photon_config& c = *x.c;
   const int rows = x.Bt;
-  float *h = x.f(x.o_h), *qkv = x.f(x.o_qkv), *qrot = x.f(x.o_qrot), *attn = x.f(x.o_attn);
+  const bool many = many_rows(x, rows);
+  float *qrot = x.f(x.o_qrot), *attn = x.f(x.o_attn);
   const size_t esz = dtype_size(c.kv_dt);
   const int pitch = kv_row_elems(c.d_h);
   const size_t layer_cache = (size_t)x.Bt * c.H * S_cap * pitch * esz;
@@ -449,28 +525,30 @@ static int32_t stream_step(const Ctx& x, const photon_module_weights& mod, void*
     const photon_layer_weights& lw = mod.layers[i];
     char* kc = reinterpret_cast<char*>(k_cache) + (size_t)i * layer_cache;
     char* vc = reinterpret_cast<char*>(v_cache) + (size_t)i * layer_cache;
-    PHOTON_TRY(linear(x, in.ptr, in.ld, lw.wqkv, lw.g1, nullptr, nullptr, 0, qkv, 3 * c.D, rows, 3 * c.D, c.D, EPI_PLAIN));
+    RowSource qkv;
+    PHOTON_TRY(block_qkv(x, lw, &in, rows, true, &qkv));
+    const float* qkv0 = qkv.n_parts ? qkv.parts : qkv.x;
+    const int qkv_parts = qkv.n_parts ? qkv.n_parts : 1;
     const int64_t n_el = (int64_t)rows * c.H * (c.d_h / 2);
     if (c.kv_dt == PHOTON_FP8_E4M3)
-      PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<fp8_t>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv, qrot,
+      PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<fp8_t>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv0, qkv_parts, qkv.part_stride, qrot,
                     (fp8_t*)kc, (fp8_t*)vc, seq_len, x.Bt, c.H, c.d_h, pitch, S_cap, c.rope_theta);
     else if (x.bf16)
-      PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<bf16_t>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv, qrot,
+      PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<bf16_t>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv0, qkv_parts, qkv.part_stride, qrot,
                     (bf16_t*)kc, (bf16_t*)vc, seq_len, x.Bt, c.H, c.d_h, pitch, S_cap, c.rope_theta);
     else
-      PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<float>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv, qrot,
+      PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<float>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv0, qkv_parts, qkv.part_stride, qrot,
                     (float*)kc, (float*)vc, seq_len, x.Bt, c.H, c.d_h, pitch, S_cap, c.rope_theta);
     PHOTON_TRY(check_launch("rope_append_coarse_kernel"));
     PHOTON_TRY(launch_coarse_attn(c.kv_dt == PHOTON_FP8_E4M3 ? KV_FP8 : x.bf16 ? KV_BF16 : KV_F32, true, c.d_h, qrot, kc, vc, seq_len, attn, x.Bt, c.H, S_cap, scale,
-                                  x.p.n_splits, x.base + x.p.coarse_ws, x.st));
-    PHOTON_TRY(block_tail(x, lw, in, rows, false));      // the coarse attention writes fp32 rows
-    in.ptr = h; in.ld = c.D;
+                                  x.p.n_splits, x.base + x.p.coarse_ws, many, x.st));
+    PHOTON_TRY(block_tail(x, lw, in, rows, many, &in));  // few rows: fp32 attention rows, many: the O projection's bf16 operand
   }
-  return norm(x, h, 1, 0, mod.g_final, out, out_mul, out_off, rows);
+  return norm(x, in, mod.g_final, out, out_mul, out_off, rows);
 }
 
 // STEP of the top-level encoder; leaves X^(L)_{g+1} in state.x_top.
-static int32_t top_step(const Ctx& x, RowsIn in) {
+static int32_t top_step(const Ctx& x, RowSource in) {
   return stream_step(x, x.w->top, x.s->k_cache, x.s->v_cache, x.s->seq_len, x.s->S_max, in, x.s->x_top, 1, 0);
 }
 
@@ -503,17 +581,14 @@ static int32_t hier_reencode(const Ctx& x, const int32_t* tokens, const float** 
     per_seq /= C;                                          // new level-l units per sequence
     const int rows = (int)(Bt * per_seq);
     if (!(l == 1 && concat1))
-      PHOTON_TRY(linear(x, X, (int64_t)C * D, x.ew->chunker_w[l - 1], nullptr, x.ew->chunker_b[l - 1], nullptr, 0, A, D, rows, D, C * D,
-                        EPI_PLAIN));
+      PHOTON_TRY(linear(x, RowSource{X, (int64_t)C * D}, x.ew->chunker_w[l - 1], nullptr, x.ew->chunker_b[l - 1], A, D, rows, D, C * D));
     float* Xl = x.f(x.p.hx[l]);
     for (int j = 0; j < (int)per_seq; ++j) {
       PHOTON_LAUNCH(KC_MISC, x.st, step_begin_kernel, dim3(blocks_for(Bt)), dim3(256), 0, x.st, x.hs->seq_len[l - 1], Bt, x.hs->S_cap[l - 1],
                     x.s->status, (unsigned*)nullptr, 0);
       PHOTON_TRY(check_launch("step_begin_kernel"));
-      RowsIn in;
-      in.ptr = A + (int64_t)j * D; in.ld = per_seq * (int64_t)D;
-      PHOTON_TRY(stream_step(x, x.ew->enc[l - 1], x.hs->k_cache[l - 1], x.hs->v_cache[l - 1], x.hs->seq_len[l - 1], x.hs->S_cap[l - 1], in,
-                             Xl, (int)per_seq, j));
+      PHOTON_TRY(stream_step(x, x.ew->enc[l - 1], x.hs->k_cache[l - 1], x.hs->v_cache[l - 1], x.hs->seq_len[l - 1], x.hs->S_cap[l - 1],
+                             RowSource{A + (int64_t)j * D, per_seq * (int64_t)D}, Xl, (int)per_seq, j));
     }
     X = Xl;
   }
@@ -526,11 +601,8 @@ static int32_t chunk_and_step(const Ctx& x, const float* bottleneck, const photo
   const photon_config& c = *x.c;
   const int D = c.D, CL = c.C[c.L - 1];
   float* a_hat = (tr && tr->a_hat) ? tr->a_hat : x.f(x.p.a_hat);
-  PHOTON_TRY(linear(x, bottleneck, (int64_t)CL * D, x.w->chunker_w, nullptr, x.w->chunker_b, nullptr, 0, a_hat, D, x.Bt, D, CL * D,
-                    EPI_PLAIN));
-  RowsIn top_in;
-  top_in.ptr = a_hat; top_in.ld = D;
-  return top_step(x, top_in);
+  PHOTON_TRY(linear(x, RowSource{bottleneck, (int64_t)CL * D}, x.w->chunker_w, nullptr, x.w->chunker_b, a_hat, D, x.Bt, D, CL * D));
+  return top_step(x, RowSource{a_hat, D});
 }
 
 // The top-level update depends only on the level-L decoder's output, not on the lower levels that turn it into
@@ -549,33 +621,31 @@ static int32_t decode_level(const Ctx& x, int l, const float* cond_in, float* un
   const photon_module_weights& mod = x.w->dec[l - 1];
   float* h = x.f(x.o_h);
   // sub-step 0: the converter's R vectors at window positions 0..R-1 (row ch*R + r of a flat [n*R, D] view of h)
-  PHOTON_TRY(linear(x, cond_in, D, x.w->conv_w[l - 1], nullptr, x.w->conv_b[l - 1], nullptr, 0, h, (int64_t)R * D, (int)n, R * D, D,
-                    EPI_PLAIN));
+  PHOTON_TRY(linear(x, RowSource{cond_in, D}, x.w->conv_w[l - 1], nullptr, x.w->conv_b[l - 1], h, (int64_t)R * D, (int)n, R * D, D));
   if (after_converter != nullptr && hipEventRecord(after_converter, x.st) != hipSuccess)
     return fail(PHOTON_ERR_HIP, "decode step: cannot record the event that frees the conditioning buffer");
-  RowsIn in;
-  in.ptr = h; in.ld = D;
+  RowSource in{h, D};
   for (int j = 0; j < C; ++j) {
     const int q_len = (j == 0) ? R : 1;
     const int q_pos = (j == 0) ? 0 : R + j - 1;
-    PHOTON_TRY(local_module_pass(x, l, n, q_len, q_pos, in, alone));
+    RowSource last;
+    PHOTON_TRY(local_module_pass(x, l, n, q_len, q_pos, in, &last, alone));
+    last = last.pick(q_len, q_len - 1);                    // the last row of each chunk
     // item j = final norm of the last row of each chunk.  At the token level of a hierarchy the item only feeds the
     // vocabulary projection, which then applies the norm itself (one launch less per sub-step) unless the caller
     // asked to see the items.
     const bool norm_in_head = (l == 1 && L >= 2 && !(tr && tr->new_units[0]));
-    if (!norm_in_head) PHOTON_TRY(norm(x, h, q_len, q_len - 1, mod.g_final, units, C, j, (int)n));
+    if (!norm_in_head) PHOTON_TRY(norm(x, last, mod.g_final, units, C, j, (int)n));
     if (l >= 2) {                                          // Eq. 6: the module's own output is the next input
-      in.ptr = units + (int64_t)j * D; in.ld = (int64_t)C * D;
+      in = RowSource{units + (int64_t)j * D, (int64_t)C * D};
     } else {
       float* lg = (tr && tr->logits) ? tr->logits + (int64_t)j * c.vocab : x.f(x.p.logits);
       const int64_t ld = (tr && tr->logits) ? (int64_t)C * c.vocab : c.vocab;
       // logits of item j of every chunk: rows of `units` with pitch C*D
       if (norm_in_head)
-        PHOTON_TRY(linear(x, h + (int64_t)(q_len - 1) * D, (int64_t)q_len * D, x.w->W_lm, mod.g_final, nullptr, nullptr, 0, lg, ld, (int)n,
-                          c.vocab, D, EPI_PLAIN));
+        PHOTON_TRY(linear(x, last, x.w->W_lm, mod.g_final, nullptr, lg, ld, (int)n, c.vocab, D));
       else
-        PHOTON_TRY(linear(x, units + (int64_t)j * D, (int64_t)C * D, x.w->W_lm, nullptr, nullptr, nullptr, 0, lg, ld, (int)n, c.vocab, D,
-                          EPI_PLAIN));
+        PHOTON_TRY(linear(x, RowSource{units + (int64_t)j * D, (int64_t)C * D}, x.w->W_lm, nullptr, nullptr, lg, ld, (int)n, c.vocab, D));
       float* x_next = (j + 1 < C) ? h : nullptr;           // decoder-side embedding of the chosen token
       if (x.bf16)
         PHOTON_LAUNCH(KC_CHOOSE_TOKEN, x.st, choose_token_kernel<bf16_t>, dim3((unsigned)n), dim3(CHOOSE_THREADS), 0, x.st, lg, ld, c.vocab,
@@ -584,7 +654,7 @@ static int32_t decode_level(const Ctx& x, int l, const float* cond_in, float* un
         PHOTON_LAUNCH(KC_CHOOSE_TOKEN, x.st, choose_token_kernel<float>, dim3((unsigned)n), dim3(CHOOSE_THREADS), 0, x.st, lg, ld, c.vocab,
                       forced, out_tokens, C, j, (const float*)x.w->E_dec, x_next, D);
       PHOTON_TRY(check_launch("choose_token_kernel"));
-      in.ptr = h; in.ld = D;
+      in = RowSource{h, D};
     }
   }
   return PHOTON_OK;
@@ -637,7 +707,8 @@ static int32_t decode_step_impl(const Ctx& x, photon_state* st, const int32_t* f
   // previous) step work on the first set meanwhile
   Ctx top = x;
   if (L >= 2) {
-    top.o_h = x.p.h2; top.o_attn = x.p.attn2; top.o_qkv = x.p.qkv2; top.o_qrot = x.p.qrot2; top.o_act = x.p.act2; top.o_many = x.p.many2;
+    top.o_h = x.p.h2; top.o_attn = x.p.attn2; top.o_qkv = x.p.qkv2; top.o_qrot = x.p.qrot2; top.o_act = x.p.act2;
+    top.o_many = x.p.many2; top.o_parts = x.p.parts2; top.part_cap = x.p.part_cap2;
   }
   // level L: one chunk per sequence, conditioned on X^(L)_g.  Persistent launches only when nothing runs beside them
   // (a pipelined state keeps the separate launches also while a profiler holds the step on one stream, so that what
@@ -701,7 +772,8 @@ using namespace photon;
 struct PrefillPlan {
   int64_t M[PHOTON_MAX_LEVELS + 1] = {0};        // M[l]: level-l units per sequence, M[0] = T
   size_t X[PHOTON_MAX_LEVELS + 1] = {0};         // X[l]: level-l encoder states [Bt*M[l], D]; X[0] = embeddings; X[L] unused
-  size_t A = 0, h = 0, attn = 0, qkv = 0, act = 0, many = 0, ea = 0, pair = 0;
+  size_t A = 0, h = 0, attn = 0, qkv = 0, act = 0, many = 0, parts = 0, ea = 0, pair = 0;
+  int64_t part_cap = 0;
   int many_K = 0;
   size_t total = 0;
 };
@@ -725,7 +797,11 @@ static PrefillPlan make_prefill_plan(const photon_config& c, int Bt, int64_t T) 
     p.many_K = (int)(D > F ? D : F);
     for (int l = 1; l <= c.L; ++l)
       if ((int64_t)c.C[l - 1] * D > p.many_K) p.many_K = (int)(c.C[l - 1] * D);
-    if (rows >= LINEAR_MID_ROWS) p.many = bump(cur, linear_many_workspace_bytes(rows, p.many_K, (int)(2 * F)));
+    if (rows >= MANY_ROWS) {
+      p.many = bump(cur, (size_t)rows * p.many_K * 2);
+      p.part_cap = contract_part_floats(rows, c.D);
+      p.parts = bump(cur, (size_t)p.part_cap * f);
+    }
   }
   p.ea = bump(cur, encoder_attn_workspace_bytes(Bt, p.M[1], c.H, c.d_h, c.dt == PHOTON_BF16));
   p.total = cur;
@@ -740,7 +816,7 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
   const float scale = 1.0f / sqrtf((float)c.d_h);
   const size_t esz = dtype_size(c.kv_dt);
 
-  float *A = e.f(pp.A), *h = e.f(pp.h), *qkv = e.f(pp.qkv), *attn = e.f(pp.attn);
+  float *A = e.f(pp.A), *qkv = e.f(pp.qkv), *attn = e.f(pp.attn);
   float* pair = e.f(pp.pair);
   // X^(0): encoder-side embeddings.  Parameter-free level-1 chunker: they are D / C_1 wide, and C_1 of them side
   // by side are A^(1) itself.
@@ -755,14 +831,13 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
     const photon_module_weights& mod = ew.enc[l - 1];
     // Eq. 4: C consecutive level-(l-1) states are one row of C*D inputs (the states are contiguous per sequence)
     if (!(l == 1 && concat1))
-      PHOTON_TRY(linear(e, e.f(pp.X[l - 1]), (int64_t)C * D, ew.chunker_w[l - 1], nullptr, ew.chunker_b[l - 1], nullptr, 0, A, D, rows, D,
-                        C * D, EPI_PLAIN));
-    RowsIn in;
-    in.ptr = A; in.ld = D;
+      PHOTON_TRY(linear(e, RowSource{e.f(pp.X[l - 1]), (int64_t)C * D}, ew.chunker_w[l - 1], nullptr, ew.chunker_b[l - 1], A, D, rows, D, C * D));
+    RowSource in{A, D};
     const size_t layer_cache = (size_t)Bt * c.H * x.s->S_max * kv_row_elems(c.d_h) * esz;
     for (int i = 0; i < c.n_layers; ++i) {
       const photon_layer_weights& lw = mod.layers[i];
-      PHOTON_TRY(linear(e, in.ptr, in.ld, lw.wqkv, lw.g1, nullptr, nullptr, 0, qkv, 3 * D, rows, 3 * D, D, EPI_PLAIN));
+      RowSource qkv_rows;
+      PHOTON_TRY(block_qkv(e, lw, &in, rows, false, &qkv_rows));
       char *kc = nullptr, *vc = nullptr;
       int64_t cap = x.s->S_max;
       if (l == L) {
@@ -775,21 +850,20 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
         vc = reinterpret_cast<char*>(x.hs->v_cache[l - 1]) + (size_t)i * lc;
       }
       PHOTON_TRY(launch_encoder_attn(qkv, attn, Bt, M, c.H, c.d_h, c.rope_theta, scale, kc, vc, cap, e.base + pp.ea, x.bf16, c.kv_dt == PHOTON_FP8_E4M3, x.bf16, x.st));
-      PHOTON_TRY(block_tail(e, lw, in, rows, x.bf16));
-      in.ptr = h; in.ld = D;
+      PHOTON_TRY(block_tail(e, lw, in, rows, x.bf16, &in));
     }
     if (l < L) {
-      PHOTON_TRY(norm(e, in.ptr, 1, 0, mod.g_final, e.f(pp.X[l]), 1, 0, rows));
+      PHOTON_TRY(norm(e, in, mod.g_final, e.f(pp.X[l]), 1, 0, rows));
       if (x.hs != nullptr) {
         PHOTON_LAUNCH(KC_MISC, x.st, fill_i32_kernel, dim3(blocks_for(Bt)), dim3(256), 0, x.st, x.hs->seq_len[l - 1], (int32_t)M, Bt);
         PHOTON_TRY(check_launch("fill_i32_kernel"));
       }
     } else {
       // only two rows of X^(L) are ever used: the last one (the top state) and the one before it (conditions the carry decode)
-      PHOTON_TRY(norm(e, in.ptr, (int)M, (int)M - 1, mod.g_final, x.s->x_top, 1, 0, Bt));
+      PHOTON_TRY(norm(e, in.pick(M, M - 1), mod.g_final, x.s->x_top, 1, 0, Bt));
       if (L >= 2) {
         if (M >= 2) {
-          PHOTON_TRY(norm(e, in.ptr, (int)M, (int)M - 2, mod.g_final, pair, 1, 0, Bt));
+          PHOTON_TRY(norm(e, in.pick(M, M - 2), mod.g_final, pair, 1, 0, Bt));
         } else {
           PHOTON_LAUNCH(KC_MISC, x.st, broadcast_rows_kernel, dim3(blocks_for((int64_t)Bt * D)), dim3(256), 0, x.st, ew.x0[L - 1], pair, Bt, D);
           PHOTON_TRY(check_launch("broadcast_rows_kernel"));
@@ -814,21 +888,20 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
   for (int l = L; l >= 2; --l) {
     const int C = c.C[l - 1], R = c.R[l - 1];
     const photon_module_weights& mod = x.w->dec[l - 1];
-    PHOTON_TRY(linear(x, cond, cond_ld, x.w->conv_w[l - 1], nullptr, x.w->conv_b[l - 1], nullptr, 0, dh, (int64_t)R * D, Bt, R * D, D,
-                      EPI_PLAIN));
-    RowsIn in;
-    in.ptr = dh; in.ld = D;
+    PHOTON_TRY(linear(x, RowSource{cond, cond_ld}, x.w->conv_w[l - 1], nullptr, x.w->conv_b[l - 1], dh, (int64_t)R * D, Bt, R * D, D));
+    RowSource in{dh, D}, last;
     const float* teacher = e.f(pp.X[l - 1]) + (pp.M[l - 1] - C) * (int64_t)D;   // sequence b: + b * M[l-1] * D
     for (int j = 0; j < C; ++j) {
       const int q_len = (j == 0) ? R : 1;
       const int q_pos = (j == 0) ? 0 : R + j - 1;
-      PHOTON_TRY(local_module_pass(x, l, Bt, q_len, q_pos, in));
-      PHOTON_TRY(norm(x, dh, q_len, q_len - 1, mod.g_final, units, C, j, Bt));
-      in.ptr = teacher + (int64_t)j * D; in.ld = pp.M[l - 1] * (int64_t)D;
+      PHOTON_TRY(local_module_pass(x, l, Bt, q_len, q_pos, in, &last));
+      last = last.pick(q_len, q_len - 1);
+      PHOTON_TRY(norm(x, last, mod.g_final, units, C, j, Bt));
+      in = RowSource{teacher + (int64_t)j * D, pp.M[l - 1] * (int64_t)D};
     }
     // carry^(l-1) = the chunk's last item (C >= 2: the last sub-step had one row per sequence);
     // the item before it conditions the last chunk of the level below
-    PHOTON_TRY(norm(x, dh, 1, 0, mod.g_final, x.s->carry + (size_t)(l - 2) * Bt * D, 1, 0, Bt));
+    PHOTON_TRY(norm(x, last, mod.g_final, x.s->carry + (size_t)(l - 2) * Bt * D, 1, 0, Bt));
     cond = units + (int64_t)(C - 2) * D;
     cond_ld = (int64_t)C * D;
   }
@@ -938,7 +1011,8 @@ extern "C" int32_t photon_prefill(const photon_config* cfg, const photon_weights
   x.bf16 = (c.dt == PHOTON_BF16);
   x.overlap = false;
   x.ew = ew; x.hs = hst;
-  x.o_h = x.p.h; x.o_attn = x.p.attn; x.o_qkv = x.p.qkv; x.o_qrot = x.p.qrot; x.o_act = x.p.act; x.o_many = x.p.many;
+  x.o_h = x.p.h; x.o_attn = x.p.attn; x.o_qkv = x.p.qkv; x.o_qrot = x.p.qrot; x.o_act = x.p.act;
+  x.o_many = x.p.many; x.o_parts = x.p.parts; x.part_cap = x.p.part_cap;
   PHOTON_REQUIRE(st->workspace != nullptr && aligned16(st->workspace) && st->workspace_bytes >= x.p.total, PHOTON_ERR_WORKSPACE,
                  "%s: state workspace of %zu bytes needed (got %zu)", __func__, x.p.total, st->workspace_bytes);
   x.base = reinterpret_cast<char*>(st->workspace);
@@ -950,7 +1024,8 @@ extern "C" int32_t photon_prefill(const photon_config* cfg, const photon_weights
   Ctx e = x;                                               // same configuration and stream, the big buffers
   e.bar_next = nullptr;
   e.base = reinterpret_cast<char*>(workspace);
-  e.o_h = pp.h; e.o_attn = pp.attn; e.o_qkv = pp.qkv; e.o_qrot = 0; e.o_act = pp.act; e.o_many = pp.many;
+  e.o_h = pp.h; e.o_attn = pp.attn; e.o_qkv = pp.qkv; e.o_qrot = 0; e.o_act = pp.act;
+  e.o_many = pp.many; e.o_parts = pp.parts; e.part_cap = pp.part_cap;
   e.p.many_K = pp.many_K;
   return prefill_impl(x, e, pp, *ew, tokens);
 }
@@ -997,7 +1072,8 @@ static int32_t decode_entry(const char* fn, const photon_config* cfg, const phot
   PHOTON_REQUIRE(st->pipeline != 0 || st->lower_levels_pending == 0, PHOTON_ERR_INVALID_ARG,
                  "%s: the lower levels of a pipelined step are still outstanding: call photon_decode_join first", fn);
   x.ew = ew; x.hs = hst;
-  x.o_h = x.p.h; x.o_attn = x.p.attn; x.o_qkv = x.p.qkv; x.o_qrot = x.p.qrot; x.o_act = x.p.act; x.o_many = x.p.many;
+  x.o_h = x.p.h; x.o_attn = x.p.attn; x.o_qkv = x.p.qkv; x.o_qrot = x.p.qrot; x.o_act = x.p.act;
+  x.o_many = x.p.many; x.o_parts = x.p.parts; x.part_cap = x.p.part_cap;
   PHOTON_REQUIRE(st->workspace != nullptr && aligned16(st->workspace) && st->workspace_bytes >= x.p.total, PHOTON_ERR_WORKSPACE,
                  "%s: workspace of %zu bytes needed (got %zu)", fn, x.p.total, st->workspace_bytes);
   x.base = reinterpret_cast<char*>(st->workspace);

@@ -1,8 +1,10 @@
-"""Edges of the tiled bf16 contraction (photon_chunker_project, Eq. 4) against an fp32 product of the same bf16 inputs."""
+"""The tiled bf16 contractions: tile edges through photon_chunker_project (Eq. 4) against an fp32 product of the same
+bf16 inputs; splits over K and sums in pieces through decode steps against the oracle."""
 import pytest
 import torch
 
-from util import require_gpu
+import seeded_inputs as si
+from util import TOL, require_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -26,3 +28,27 @@ def test_tiled_contraction_edges(rows, K, N):
     err = (out[:rows].float() - ref).abs()
     bound = ref.abs() * 2.0 ** -8 + 1e-5 * K ** 0.5
     assert bool((err <= bound).all()), float((err - bound).max())
+
+
+# 16 rows below to hundreds above the switch to the tiled contractions, at every level; a first sub-step that is above it
+# while the others are below (12 sequences, two converter rows); split and unsplit K, attention-only blocks, padded heads,
+# tile columns partly empty.
+@pytest.mark.parametrize("kw,Bt", [
+    (dict(), 5),                                                    # level 1: 20 rows
+    (dict(D=1024, H=16, d_ff=2560, n_layers=1), 17),                # level 2: 17 rows, level 1: 68 (split K)
+    (dict(R=(2, 2)), 12),                                           # level 2: 24 rows, then 12
+    (dict(d_ff=0, R=(1, 2)), 18),
+    (dict(D=832, H=16, d_h=52, d_ff=1024, R=(2, 1), n_layers=1), 33),
+    (dict(D=448, H=8, d_h=56, d_ff=704, n_layers=1, L=3, C=(2, 3, 2), R=(1, 2, 1)), 40),
+    (dict(n_layers=1), 65),
+])
+def test_decode_step_at_many_rows(kw, Bt):
+    require_gpu()
+    from test_gpu_decode_step import check_against_oracle
+    base = dict(L=2, C=(4, 4), R=(1, 1), D=512, H=8, d_h=64, n_layers=2, d_ff=1280, vocab=1008, dtype="bf16")
+    base.update(kw)
+    cfg = si.PhotonConfig(**base)
+    S, S_max = 40, 48
+    st = si.make_decode_state(cfg, Bt, S, S_max, seed=3)
+    errs, _, _ = check_against_oracle(cfg, si.make_weights(cfg, 12), st, Bt, S_max, si.make_tokens(cfg.vocab, Bt, cfg.meta_context, 7), TOL["bf16"])
+    print(errs)
