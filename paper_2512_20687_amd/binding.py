@@ -500,6 +500,20 @@ class PhotonState:
         self.c_state = s
 
 
+    def keep_side_stream_apart(self) -> None:
+        """torch deals its streams from a pool of a few dozen: the caller's current stream (a graph-capture stream, say) can
+        turn out to be the very stream this state lends the step.  Lend another one then, ordered behind the first."""
+        if self.side_stream is None or self.side_stream.cuda_stream != _stream():
+            return
+        other = torch.cuda.Stream(device=self.model.device)
+        while other.cuda_stream == self.side_stream.cuda_stream:
+            other = torch.cuda.Stream(device=self.model.device)
+        if self.c_state.lower_levels_pending:
+            other.wait_stream(self.side_stream)
+        self.side_stream = other
+        self.c_state.side_stream = other.cuda_stream
+
+
 class PhotonHierState:
     """Encoder streams of the levels below the top (hierarchical generation only): per level l = 1..L-1 a K/V
     cache [n_layers, Bt, H, S_cap_l, photon_kv_row_elems(d_h)] and the per-sequence unit counts.  S_cap_l = S_max * prod(C_{l+1..L})."""
@@ -590,6 +604,7 @@ def photon_hiergen_step(model: PhotonModel, state: PhotonState, hier: PhotonHier
         tr.a_hat = _ptr(trace.get("a_hat"))
         for l, t in enumerate(trace.get("new_units", [])):
             tr.new_units[l] = _ptr(t)
+    state.keep_side_stream_apart()
     _check(lib.photon_hiergen_step(C.byref(model.c_cfg), C.byref(model.c_weights), C.byref(model.c_encoder_weights),
                                    C.byref(state.c_state), C.byref(hier.c_state), state.Bt, _ptr(forced_tokens), _ptr(out_tokens),
                                    C.byref(tr) if tr is not None else None, _stream()))
@@ -618,6 +633,7 @@ def photon_decode_step(model: PhotonModel, state: PhotonState, out_tokens: torch
         tr.a_hat = _ptr(trace.get("a_hat"))
         for l, t in enumerate(trace.get("new_units", [])):
             tr.new_units[l] = _ptr(t)
+    state.keep_side_stream_apart()
     _check(lib.photon_decode_step(C.byref(model.c_cfg), C.byref(model.c_weights), C.byref(state.c_state), state.Bt,
                                   _ptr(forced_tokens), _ptr(out_tokens), C.byref(tr) if tr is not None else None,
                                   _stream()))

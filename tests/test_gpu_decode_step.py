@@ -340,3 +340,40 @@ def test_logits_when_the_items_are_not_requested(kw, Bt):
     assert nerr(trace["logits"], otr["logits"]) <= tol
     assert nerr(state.x_top, otr["x_top"]) <= tol and nerr(state.carry, ost["carry"]) <= tol
     assert np.array_equal(toks.cpu().numpy(), np.asarray(forced))
+
+
+@pytest.mark.parametrize("pipeline", [False, True])
+def test_step_on_the_state_s_own_side_stream(pipeline):
+    """torch's streams come from a small pool: the caller's stream may be the one the state lends the step.  Eager on that
+    stream (second step only, so that a pipelined first step is outstanding on it) and captured on it."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(L=2, C=(4, 4), R=(1, 1), D=256, H=4, d_h=64, n_layers=1, d_ff=640, vocab=512, dtype="bf16")
+    Bt, S, S_max = 3, 40, 64
+    st = si.make_decode_state(cfg, Bt, S, S_max, seed=2)
+    model = ph.PhotonModel(cfg, si.make_weights(cfg, 4))
+    out = torch.zeros((2, 3, Bt, 16), dtype=torch.int32, device="cuda")
+
+    def fresh():
+        return ph.PhotonState(model, Bt, S_max, pipeline=pipeline, **{k: st[k] for k in ("k", "v", "seq_len", "x_top", "carry")})
+
+    ref, own = fresh(), fresh()
+    for i in range(3):
+        ph.photon_decode_step(model, ref, out[0, i])
+    ph.photon_decode_join(ref)
+    torch.cuda.synchronize()
+    lent = own.side_stream
+    ph.photon_decode_step(model, own, out[1, 0])
+    lent.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(lent):
+        ph.photon_decode_step(model, own, out[1, 1])
+        ph.photon_decode_join(own)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=own.side_stream):
+        ph.photon_decode_step(model, own, out[1, 2])
+        ph.photon_decode_join(own)
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    assert torch.equal(ref.x_top, own.x_top) and torch.equal(ref.k, own.k) and torch.equal(ref.carry, own.carry)
