@@ -416,14 +416,29 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
 #pragma unroll
       for (int t = 0; t < VEC; ++t) { qp[t] = head[partner[t]]; kp[t] = head[D + partner[t]]; }
     }
-    for (int s = 1; s < n_parts; ++s) {                      // further partial products of the projection
-      head += part_stride;
-      q4 += *reinterpret_cast<const float4_t*>(head + col);
-      k4 += *reinterpret_cast<const float4_t*>(head + col + D);
-      v4 += *reinterpret_cast<const float4_t*>(head + col + 2 * D);
-      if (PAD) {
+    // further partial products of the projection, three in flight
+    for (int s0 = 1; s0 < n_parts; s0 += 3) {
+      float4_t w[3][3];
+      float wq[3][VEC], wk[3][VEC];
 #pragma unroll
-        for (int t = 0; t < VEC; ++t) { qp[t] += head[partner[t]]; kp[t] += head[D + partner[t]]; }
+      for (int u = 0; u < 3; ++u) {
+        const float* more = head + (s0 + u < n_parts ? s0 + u : 0) * part_stride;   // past the last: loaded, not added
+        w[u][0] = *reinterpret_cast<const float4_t*>(more + col);
+        w[u][1] = *reinterpret_cast<const float4_t*>(more + col + D);
+        w[u][2] = *reinterpret_cast<const float4_t*>(more + col + 2 * D);
+        if (PAD) {
+#pragma unroll
+          for (int t = 0; t < VEC; ++t) { wq[u][t] = more[partner[t]]; wk[u][t] = more[D + partner[t]]; }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        if (s0 + u >= n_parts) continue;
+        q4 += w[u][0]; k4 += w[u][1]; v4 += w[u][2];
+        if (PAD) {
+#pragma unroll
+          for (int t = 0; t < VEC; ++t) { qp[t] += wq[u][t]; kp[t] += wk[u][t]; }
+        }
       }
     }
   };

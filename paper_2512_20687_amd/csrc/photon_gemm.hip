@@ -21,6 +21,7 @@
 namespace photon {
 
 constexpr int G_BK = 64;                                         // K must be a multiple of this
+constexpr int MAX_SPLITS = 8;                                    // over K
 
 // 16 bytes per lane from global memory straight into LDS: lane l lands at lds_base + 16 l (lds_base: byte offset in
 // LDS, wave-uniform).  Written as an instruction rather than through the compiler's builtin: the compiler treats
@@ -343,12 +344,12 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
     if (p.bias != nullptr) v += float4_t{p.bias[k], p.bias[k + 1], p.bias[k + 2], p.bias[k + 3]};
     return v;
   };
-  auto emit = [&](int k, const float4_t& v, float r) {
+  auto emit = [&](int k, const float4_t& v, const float4_t& g, float r) {
     if (p.xb != nullptr) {
-      const float4_t w = p.gain != nullptr ? v * *reinterpret_cast<const float4_t*>(p.gain + k) * r : v;
+      const float4_t w = p.gain != nullptr ? v * g * r : v;
       *reinterpret_cast<uint2*>(p.xb + (int64_t)row * K + k) = uint2{pack_bf16x2(w.x, w.y), pack_bf16x2(w.z, w.w)};
     }
-    if (p.y != nullptr) *reinterpret_cast<float4_t*>(p.y + (int64_t)row * p.ldy + k) = v * r * *reinterpret_cast<const float4_t*>(p.gain + k);
+    if (p.y != nullptr) *reinterpret_cast<float4_t*>(p.y + (int64_t)row * p.ldy + k) = v * r * g;
   };
   auto inv_rms = [&](float ss) {
     ss = group_sum<32>(ss);
@@ -363,18 +364,39 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
   };
   float ss = 0.f, r = 1.f;
   if constexpr (NV > 0) {
-    float4_t v[NV];
+    float4_t v[NV], g[NV];
+    // the gain is requested with the rows, not after the reduction
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int k = (i * TPR + t) * 4;
+      g[i] = p.gain != nullptr && k < K ? *reinterpret_cast<const float4_t*>(p.gain + k) : float4_t{1.f, 1.f, 1.f, 1.f};
+    }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int k = (i * TPR + t) * 4;
       v[i] = k < K && x != nullptr ? *reinterpret_cast<const float4_t*>(x + k) : float4_t{0.f, 0.f, 0.f, 0.f};
     }
-    for (int s = 0; s < p.in.n_parts; ++s) {
-      const float* ps = parts + s * p.in.part_stride;
+    // several partial products in flight: taken in one after the other, each costs a trip to memory
+    constexpr int PB = NV <= 2 ? MAX_SPLITS : NV <= 4 ? 4 : 2;
+    for (int s0 = 0; s0 < p.in.n_parts; s0 += PB) {
+      float4_t w[PB][NV];
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int k = (i * TPR + t) * 4;
-        if (k < K) v[i] += *reinterpret_cast<const float4_t*>(ps + k);
+      for (int u = 0; u < PB; ++u) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) w[u][i] = float4_t{0.f, 0.f, 0.f, 0.f};
+        if (s0 + u >= p.in.n_parts) continue;
+        const float* ps = parts + (s0 + u) * p.in.part_stride;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+          const int k = (i * TPR + t) * 4;
+          if (k < K) w[u][i] = *reinterpret_cast<const float4_t*>(ps + k);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < PB; ++u) {
+        if (s0 + u >= p.in.n_parts) continue;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[i] += w[u][i];
       }
     }
 #pragma unroll
@@ -389,7 +411,7 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int k = (i * TPR + t) * 4;
-      if (k < K) emit(k, v[i], r);
+      if (k < K) emit(k, v[i], g[i], r);
     }
   } else {
     if (p.gain != nullptr) {
@@ -402,7 +424,7 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
     for (int k = t * 4; k < K; k += TPR * 4) {
       const float4_t v = value(k);
       if (p.sum != nullptr) *reinterpret_cast<float4_t*>(p.sum + (int64_t)row * p.ld_sum + k) = v;
-      emit(k, v, r);
+      emit(k, v, p.gain != nullptr ? *reinterpret_cast<const float4_t*>(p.gain + k) : float4_t{1.f, 1.f, 1.f, 1.f}, r);
     }
   }
 }
@@ -443,7 +465,6 @@ struct TileShape { int bm, bn; float fixed, slab1, slabn; };
 constexpr TileShape TILES[T_KINDS] = {{64, 32, 1.6f, 0.21f, 0.17f},  {64, 64, 2.3f, 0.24f, 0.22f},    {128, 64, 2.8f, 0.34f, 0.34f},
                                       {128, 128, 3.5f, 0.50f, 0.59f}, {128, 256, 6.2f, 0.74f, 0.94f}, {256, 256, 8.6f, 1.00f, 1.36f}};
 constexpr float US_PER_MB_OUT = 0.18f, US_PER_MB_PARTS = 0.17f;      // writing the output; reading partial products back
-constexpr int MAX_SPLITS = 8;
 
 struct GemmPlan { int kind, splits, slabs; };
 

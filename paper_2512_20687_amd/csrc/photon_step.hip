@@ -88,14 +88,24 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
   const int h = (int)((idx / half) % H);
   const int b = (int)(idx / ((int64_t)half * H));
   const int pos = seq_len[b] - 1;
-  float c, s;
-  rope_angle(pos, i, d_h, theta, c, s);
   const float* src = qkv + (int64_t)b * 3 * D + h * d_h;
   float qa = src[i], qb = src[i + half], ka = src[D + i], kb = src[D + i + half], va = src[2 * D + i], vb = src[2 * D + i + half];
-  for (int s2 = 1; s2 < n_parts; ++s2) {
-    src += part_stride;
-    qa += src[i]; qb += src[i + half]; ka += src[D + i]; kb += src[D + i + half]; va += src[2 * D + i]; vb += src[2 * D + i + half];
+  for (int s0 = 1; s0 < n_parts; s0 += 3) {                    // three in flight
+    float w[3][6];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const float* more = src + (s0 + u < n_parts ? s0 + u : 0) * part_stride;   // past the last: loaded, not added
+      w[u][0] = more[i]; w[u][1] = more[i + half]; w[u][2] = more[D + i]; w[u][3] = more[D + i + half];
+      w[u][4] = more[2 * D + i]; w[u][5] = more[2 * D + i + half];
+    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      if (s0 + u >= n_parts) continue;
+      qa += w[u][0]; qb += w[u][1]; ka += w[u][2]; kb += w[u][3]; va += w[u][4]; vb += w[u][5];
+    }
   }
+  float c, s;
+  rope_angle(pos, i, d_h, theta, c, s);                        // under the loads
   float* qd = qrot + (int64_t)b * D + h * d_h;
   qd[i] = qa * c - qb * s;
   qd[i + half] = qb * c + qa * s;
