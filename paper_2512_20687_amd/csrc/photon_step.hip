@@ -58,6 +58,19 @@ __global__ __launch_bounds__(256) void embed_rows_kernel(const int32_t* __restri
   *reinterpret_cast<float4_t*>(rows + i * D + d) = v;
 }
 
+// The same rows as they are stored in a bf16 table, for a tiled contraction that takes bf16 rows: 16 bytes a thread, no
+// widening that a row kernel would only round back (131072 rows of 1024: 172 + 164 us for the two kernels).
+__global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restrict__ tokens, const uint4_t* __restrict__ table,
+                                                          uint4_t* __restrict__ rows, int64_t n, int per_row, int vocab) {
+  const int64_t first = (int64_t)blockIdx.x * 256, row0 = first / per_row;   // the same for the whole workgroup
+  const unsigned rest = (unsigned)(first - row0 * per_row) + threadIdx.x;
+  const int64_t i = row0 + rest / (unsigned)per_row;
+  if (i >= n) return;
+  int t = tokens[i];
+  t = t < 0 ? 0 : (t >= vocab ? vocab - 1 : t);                      // as in embed_rows_kernel
+  rows[first + threadIdx.x] = table[(int64_t)t * per_row + rest % (unsigned)per_row];
+}
+
 __global__ __launch_bounds__(256) void copy_f32x4_kernel(const float4_t* __restrict__ src, float4_t* __restrict__ dst, int64_t n4) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n4) dst[i] = src[i];
@@ -379,6 +392,12 @@ static int32_t contract(const Ctx& x, const void* xb, const void* W, const float
   return launch_contract(a, result, x.st);
 }
 
+// out[M, N] = W^T + bias of the bf16 rows that a row or gather kernel left in this branch's buffer.
+static int32_t linear_of_rounded(const Ctx& x, const void* W, const float* bias, float* out, int M, int N, int K) {
+  RowSource whole;
+  return contract(x, nullptr, W, bias, RowSource{}, out, N, M, N, K, EPI_PLAIN, false, &whole);
+}
+
 // out[M, N] = rmsnorm(in; gain) W^T + bias (gain, bias: nullptr for none).
 static int32_t linear(const Ctx& x, const RowSource& in, const void* W, const float* gain, const float* bias, float* out, int64_t ldo, int M,
                       int N, int K) {
@@ -575,6 +594,22 @@ static int32_t embed_rows(hipStream_t st, bool bf16, const int32_t* tokens, cons
   return check_launch("embed_rows_kernel");
 }
 
+// Level-1 chunker (Eq. 4) of n_tok tokens: their encoder-side embeddings, C of them side by side, into `rows` rows of `out`.
+// `scratch` takes the embeddings in fp32 where the rows are too few for the tiled contraction (or the tables fp32).
+static int32_t embed_and_chunk(const Ctx& x, const photon_encoder_weights& ew, const int32_t* tokens, int64_t n_tok, int rows, float* scratch,
+                               float* out) {
+  const photon_config& c = *x.c;
+  const int D = c.D, K = c.C[0] * D;
+  if (many_rows(x, rows) && K <= x.p.many_K) {
+    PHOTON_LAUNCH(KC_MISC, x.st, gather_rows_kernel, dim3(blocks_for(n_tok * (D / 8))), dim3(256), 0, x.st, tokens, (const uint4_t*)ew.E_enc,
+                  reinterpret_cast<uint4_t*>(x.base + x.o_many), n_tok, D / 8, c.vocab);
+    PHOTON_TRY(check_launch("gather_rows_kernel"));
+    return linear_of_rounded(x, ew.chunker_w[0], ew.chunker_b[0], out, rows, D, K);
+  }
+  PHOTON_TRY(embed_rows(x.st, x.bf16, tokens, ew.E_enc, scratch, n_tok, D, c.vocab));
+  return linear(x, RowSource{scratch, K}, ew.chunker_w[0], nullptr, ew.chunker_b[0], out, D, rows, D, K);
+}
+
 static int32_t hier_reencode(const Ctx& x, const int32_t* tokens, const float** bottleneck) {
   const photon_config& c = *x.c;
   const int D = c.D, L = c.L, Bt = x.Bt;
@@ -590,7 +625,9 @@ static int32_t hier_reencode(const Ctx& x, const int32_t* tokens, const float** 
     const int C = c.C[l - 1];
     per_seq /= C;                                          // new level-l units per sequence
     const int rows = (int)(Bt * per_seq);
-    if (!(l == 1 && concat1))
+    if (l == 1 && !concat1)
+      PHOTON_TRY(embed_and_chunk(x, *x.ew, tokens, n_tok, rows, X, A));
+    else if (l > 1)
       PHOTON_TRY(linear(x, RowSource{X, (int64_t)C * D}, x.ew->chunker_w[l - 1], nullptr, x.ew->chunker_b[l - 1], A, D, rows, D, C * D));
     float* Xl = x.f(x.p.hx[l]);
     for (int j = 0; j < (int)per_seq; ++j) {
@@ -840,7 +877,11 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
     const int rows = (int)(Bt * M);
     const photon_module_weights& mod = ew.enc[l - 1];
     // Eq. 4: C consecutive level-(l-1) states are one row of C*D inputs (the states are contiguous per sequence)
-    if (!(l == 1 && concat1))
+    if (l == 1 && !concat1)
+      PHOTON_TRY(embed_and_chunk(e, ew, tokens, n_tok, rows, e.f(pp.X[0]), A));
+    else if (l > 1 && rounded)
+      PHOTON_TRY(linear_of_rounded(e, ew.chunker_w[l - 1], ew.chunker_b[l - 1], A, rows, D, C * D));
+    else if (l > 1)
       PHOTON_TRY(linear(e, RowSource{e.f(pp.X[l - 1]), (int64_t)C * D}, ew.chunker_w[l - 1], nullptr, ew.chunker_b[l - 1], A, D, rows, D, C * D));
     RowSource in{A, D};
     const size_t layer_cache = (size_t)Bt * c.H * x.s->S_max * kv_row_elems(c.d_h) * esz;
@@ -863,7 +904,14 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
       PHOTON_TRY(block_tail(e, lw, in, rows, x.bf16, &in));
     }
     if (l < L) {
-      PHOTON_TRY(norm(e, in, mod.g_final, e.f(pp.X[l]), 1, 0, rows));
+      // the final norm; with a tiled contraction to follow, its operand in the same pass
+      const int next = (int)(Bt * pp.M[l + 1]);
+      rounded = many_rows(e, next) && c.C[l] * D <= e.p.many_K;
+      RowsArgs a;
+      a.in = in; a.gain = mod.g_final; a.eps = c.rms_eps; a.y = e.f(pp.X[l]); a.ldy = D; a.M = rows; a.K = D;
+      a.xb = reinterpret_cast<uint16_t*>(e.base + e.o_many);
+      if (rounded) PHOTON_TRY(launch_rows(a, x.st));
+      else PHOTON_TRY(norm(e, in, mod.g_final, e.f(pp.X[l]), 1, 0, rows));
       if (x.hs != nullptr) {
         PHOTON_LAUNCH(KC_MISC, x.st, fill_i32_kernel, dim3(blocks_for(Bt)), dim3(256), 0, x.st, x.hs->seq_len[l - 1], (int32_t)M, Bt);
         PHOTON_TRY(check_launch("fill_i32_kernel"));
