@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/photon.h"
+#include "photon_linear.h"
 
 namespace photon {
 
@@ -17,5 +18,11 @@ size_t encoder_attn_workspace_bytes(int Bt, int64_t M, int H, int d_h, bool bf16
 // bf16 only).  out_bf16 (with bf16 only): `out` holds bf16 values, the result rounded to nearest even.
 int32_t launch_encoder_attn(const float* qkv, float* out, int Bt, int64_t M, int H, int d_h, float theta, float scale, void* k_cache,
                             void* v_cache, int64_t S_max, void* workspace, bool bf16, bool kv_fp8, bool out_bf16, hipStream_t st);
+
+// The same in two parts, for bf16 heads of 64 whose projection writes the operands (launch_qkv_rope).  Begin lays the
+// operands out in `workspace`, fills `table` (M * 64 floats) and zeroes the rows behind the last position; it serves all
+// layers of a level.  The attention proper reads the operands (any head size up to 64).
+int32_t encoder_operands_begin(int Bt, int64_t M, int H, float theta, float scale, void* workspace, float* table, QkvOperands* ops, hipStream_t st);
+int32_t launch_encoder_attn_operands(const QkvOperands& o, float* out, int Bt, int d_h, bool out_bf16, hipStream_t st);
 
 }  // namespace photon

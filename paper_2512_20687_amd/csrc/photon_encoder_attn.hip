@@ -406,6 +406,28 @@ __global__ __launch_bounds__(EA_THREADS) void encoder_attn_mfma_kernel(const uin
     }
 }
 
+// Once per level in front of projections that write the operands themselves (launch_qkv_rope): cosines and sines of every
+// position's angles (row pos: 32 cosines, 32 sines), and zeros in the operands' rows behind the last position, which no
+// projection writes.
+__global__ __launch_bounds__(256) void encoder_operands_begin_kernel(const QkvOperands o, float* __restrict__ table, int streams, float theta) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx < (int64_t)o.M * 32) {
+    const int pos = (int)(idx >> 5), i = (int)(idx & 31);
+    float c, s;
+    rope_angle(pos, i, EA_DH, theta, c, s);
+    table[(int64_t)pos * 64 + i] = c;
+    table[(int64_t)pos * 64 + 32 + i] = s;
+  }
+  const int pad = o.Mp - o.M;                         // 0 .. 63
+  if (pad > 0 && idx < (int64_t)streams * EA_DH * pad) {
+    const int p = (int)(idx % pad), d = (int)(idx / pad % EA_DH);
+    const int64_t bh = idx / pad / EA_DH;
+    o.qh[(bh * o.Mp + o.M + p) * EA_DH + d] = 0;
+    o.kh[(bh * o.Mp + o.M + p) * EA_DH + d] = 0;
+    o.vt[(bh * EA_DH + d) * o.Mp + o.M + p] = 0;
+  }
+}
+
 // ---- fp32 configuration: plain tile kernel -----------------------------------------------------------
 // One workgroup = 64 queries of one (sequence, head); thread t owns query t and streams the keys 0..q
 // through LDS tiles of 32 keys (rotated as they are staged).
@@ -502,6 +524,25 @@ size_t encoder_attn_workspace_bytes(int Bt, int64_t M, int H, int d_h, bool bf16
   return (size_t)3 * Bt * H * round_up64(M) * EA_DH * sizeof(uint16_t);   // q, k, V^T
 }
 
+int32_t encoder_operands_begin(int Bt, int64_t M, int H, float theta, float scale, void* workspace, float* table, QkvOperands* ops, hipStream_t st) {
+  if ((int64_t)Bt * H > 65535) return fail(PHOTON_ERR_UNSUPPORTED, "encoder attention: Bt*H=%lld exceeds 65535", (long long)Bt * H);
+  QkvOperands o;
+  o.M = (int)M; o.Mp = (int)round_up64(M); o.H = H; o.qscale = scale * LOG2E; o.table = table;
+  const size_t arr = (size_t)Bt * H * o.Mp * EA_DH;
+  o.qh = reinterpret_cast<uint16_t*>(workspace); o.kh = o.qh + arr; o.vt = o.kh + arr;
+  const int64_t angles = M * 32, pads = (int64_t)Bt * H * EA_DH * (o.Mp - M), n = angles > pads ? angles : pads;
+  PHOTON_LAUNCH(KC_ROPE_APPEND, st, encoder_operands_begin_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, o, table, Bt * H, theta);
+  *ops = o;
+  return check_launch("encoder_operands_begin_kernel");
+}
+
+int32_t launch_encoder_attn_operands(const QkvOperands& o, float* out, int Bt, int d_h, bool out_bf16, hipStream_t st) {
+  const int n_qblocks = (o.M + EA_BQ - 1) / EA_BQ;
+  PHOTON_LAUNCH(KC_LOCAL_ATTN, st, encoder_attn_mfma_kernel, dim3(n_qblocks, Bt * o.H), dim3(EA_THREADS), 4 * EA_STAGE, st, o.qh, o.kh, o.vt, out,
+                (int64_t)o.M, o.H, d_h, n_qblocks, out_bf16 ? 1 : 0);
+  return check_launch("encoder_attn_mfma_kernel");
+}
+
 int32_t launch_encoder_attn(const float* qkv, float* out, int Bt, int64_t M, int H, int d_h, float theta, float scale, void* k_cache,
                             void* v_cache, int64_t S_max, void* workspace, bool bf16, bool kv_fp8, bool out_bf16, hipStream_t st) {
   if (Bt <= 0 || M <= 0) return PHOTON_OK;
@@ -545,10 +586,9 @@ int32_t launch_encoder_attn(const float* qkv, float* out, int Bt, int64_t M, int
   else { if (kv_fp8) PHOTON_EA_ROPE(true, fp8_t); else PHOTON_EA_ROPE(true, bf16_t); }
 #undef PHOTON_EA_ROPE
   PHOTON_TRY(check_launch("encoder_rope_split_kernel"));
-  const int n_qblocks = (int)((M + EA_BQ - 1) / EA_BQ);
-  PHOTON_LAUNCH(KC_LOCAL_ATTN, st, encoder_attn_mfma_kernel, dim3(n_qblocks, Bt * H), dim3(EA_THREADS), 4 * EA_STAGE, st, qh, kh, vt, out, M,
-                H, d_h, n_qblocks, out_bf16 ? 1 : 0);
-  return check_launch("encoder_attn_mfma_kernel");
+  QkvOperands o;
+  o.M = (int)M; o.H = H; o.qh = qh; o.kh = kh; o.vt = vt;
+  return launch_encoder_attn_operands(o, out, Bt, d_h, out_bf16, st);
 }
 
 }  // namespace photon

@@ -39,7 +39,7 @@ __device__ __forceinline__ void load16_to_lds(const void* gsrc, uint32_t lds_bas
 
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-enum GemmOut { GEMM_OUT_BF16 = 0, GEMM_OUT_F32 = 1, GEMM_OUT_SWIGLU = 2 };
+enum GemmOut { GEMM_OUT_BF16 = 0, GEMM_OUT_F32 = 1, GEMM_OUT_SWIGLU = 2, GEMM_OUT_QKV = 3 };
 
 // ---- shared by the tile kernels ------------------------------------------------------------------------------------------
 
@@ -50,6 +50,7 @@ struct GemmArgs {
   const bf16_t* x; const bf16_t* W; const float* bias; const float* res; void* out;
   int64_t ldres, ldo, split_stride;
   int M, N, K, tiles_m, tiles_n, group_m, slabs;
+  QkvOperands qkv;                                               // GEMM_OUT_QKV: where the columns go instead of `out`
 };
 
 // Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes a contiguous run of tiles (also when the count is
@@ -113,6 +114,67 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
       } else {
         *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)m * p.ldo + n) = uint2{pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w)};
       }
+    }
+  }
+}
+
+// Four consecutive cache entries.
+__device__ __forceinline__ void store_cache4(void* cache, int64_t at, const float4_t& y, bool fp8) {
+  if (fp8) *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(cache) + at) = pack_fp8x2(y.x, y.y) | (pack_fp8x2(y.z, y.w) << 16);
+  else *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(cache) + at) = uint2{pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w)};
+}
+
+// One row of a wave's 64 columns of a QKV projection, which are one head of q, k or v: q and k are rotated (element i and
+// i + 32 sit in accumulators j and j + 2 of the same lane), q scaled, everything rounded to fp16 and stored as the attention
+// kernel reads it; k and v also go to the cache.  Called by whole groups of four lanes (rows m .. m + 3) when positions come
+// in fours: they then exchange their v values and each stores four positions of one element instead of four single values.
+// 32768 x 3072 x 1024: 225 us, against 218 us for the fp32 projection and 135 us for the pass over it that this replaces.
+template <int TJ>
+__device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int col0, int fk) {
+  static_assert(TJ == 4, "a wave holds one head");
+  if (m >= p.M || col0 >= p.N) return;
+  const QkvOperands& o = p.qkv;
+  const int D = o.H * 64, section = col0 / D, h = (col0 - section * D) >> 6;
+  const int b = (int)((unsigned)m / (unsigned)o.M), pos = m - b * o.M;
+  const int64_t bh = (int64_t)b * o.H + h;
+  const bool cached = o.kc != nullptr && pos < o.S_max;
+  const int64_t slot = (bh * o.S_max + pos) * 64;
+  if (section < 2) {
+    uint16_t* dst = (section == 0 ? o.qh : o.kh) + (bh * o.Mp + pos) * 64;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int i = j * 16 + fk * 4;
+      const float4_t c = *reinterpret_cast<const float4_t*>(o.table + (int64_t)pos * 64 + i);
+      const float4_t s = *reinterpret_cast<const float4_t*>(o.table + (int64_t)pos * 64 + 32 + i);
+      float4_t y0 = acc[j] * c - acc[j + 2] * s, y1 = acc[j + 2] * c + acc[j] * s;
+      if (section == 0) {
+        y0 *= o.qscale; y1 *= o.qscale;
+      } else if (cached) {
+        store_cache4(o.kc, slot + i, y0, o.cache_fp8);
+        store_cache4(o.kc, slot + 32 + i, y1, o.cache_fp8);
+      }
+      *reinterpret_cast<uint2*>(dst + i) = uint2{pack_f16x2(y0.x, y0.y), pack_f16x2(y0.z, y0.w)};
+      *reinterpret_cast<uint2*>(dst + 32 + i) = uint2{pack_f16x2(y1.x, y1.y), pack_f16x2(y1.z, y1.w)};
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int d = j * 16 + fk * 4;
+    if (cached) store_cache4(o.vc, slot + d, acc[j], o.cache_fp8);
+    const uint32_t lo = pack_f16x2(acc[j].x, acc[j].y), hi = pack_f16x2(acc[j].z, acc[j].w);
+    uint16_t* dst = o.vt + (bh * 64 + d) * o.Mp;
+    if (o.M % 4 == 0) {
+      // a 4 x 4 transpose over the lanes q = 0..3 of the group: lane q ends up with element d + q of positions pos - q .. +3
+      const int q = threadIdx.x & 3;
+      const uint32_t lo1 = __builtin_amdgcn_update_dpp(0, lo, DPP_XOR1, 0xf, 0xf, false), hi1 = __builtin_amdgcn_update_dpp(0, hi, DPP_XOR1, 0xf, 0xf, false);
+      const uint32_t a = (q & 1) ? (lo1 >> 16) | (lo & 0xffff0000u) : (lo & 0xffffu) | (lo1 << 16);
+      const uint32_t c = (q & 1) ? (hi1 >> 16) | (hi & 0xffff0000u) : (hi & 0xffffu) | (hi1 << 16);
+      const uint32_t a2 = __builtin_amdgcn_update_dpp(0, a, DPP_XOR2, 0xf, 0xf, false), c2 = __builtin_amdgcn_update_dpp(0, c, DPP_XOR2, 0xf, 0xf, false);
+      *reinterpret_cast<uint2*>(dst + (int64_t)q * o.Mp + pos - q) = (q & 2) ? uint2{c2, c} : uint2{a, a2};
+    } else {
+      dst[pos] = (uint16_t)lo; dst[o.Mp + pos] = (uint16_t)(lo >> 16);
+      dst[2 * (int64_t)o.Mp + pos] = (uint16_t)hi; dst[3 * (int64_t)o.Mp + pos] = (uint16_t)(hi >> 16);
     }
   }
 }
@@ -190,7 +252,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // the surplus loads of the tail land before the workgroup ends
 #pragma unroll
-  for (int i = 0; i < TI; ++i) store_row<OUT, TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0, wn, fk, at.split);
+  for (int i = 0; i < TI; ++i) {
+    if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
+    else store_row<OUT, TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0, wn, fk, at.split);
+  }
 }
 
 // ---- large contractions: two groups of waves in counter-phase, 256 x 256 (TI = 4) or 128 x 256 (TI = 2) tile ------------
@@ -322,7 +387,11 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int i = 0; i < TI; ++i) store_row<OUT, TJ>(p, acc[h][i], m0 + (group * 2 + h) * HALF + i * 16 + fr, n0, wcol * 64, fk, at.split);
+    for (int i = 0; i < TI; ++i) {
+      const int m = m0 + (group * 2 + h) * HALF + i * 16 + fr;
+      if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
+      else store_row<OUT, TJ>(p, acc[h][i], m, n0, wcol * 64, fk, at.split);
+    }
 }
 
 // ---- row kernel between contractions --------------------------------------------------------------------------------------
@@ -470,12 +539,13 @@ struct GemmPlan { int kind, splits, slabs; };
 
 // part_cap: floats the scratch area for partial products holds (0: no splitting).  join_us: what reading the partial
 // products back costs beyond the bytes (a launch of its own, or nothing where the next kernel reads the result anyway).
-static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, int64_t part_cap, float join_us) {
+static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, int64_t part_cap, float join_us, int first_kind = 0,
+                          float* model_us = nullptr) {
   const int KT = K / G_BK;
   GemmPlan best{T_64x64, 1, KT};
   float best_us = 1e30f;
   const float out_mb = (float)M * N * (out_f32 ? 4e-6f : 2e-6f);
-  for (int k = 0; k < T_KINDS; ++k) {
+  for (int k = first_kind; k < T_KINDS; ++k) {
     const int bn = gate_up ? TILES[k].bn / 2 : TILES[k].bn;
     const int64_t tiles = (M + TILES[k].bm - 1) / TILES[k].bm * ((N + bn - 1) / bn);
     for (int s = 1; s <= MAX_SPLITS; ++s) {
@@ -489,6 +559,7 @@ static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, i
       if (tiles * s >= 512) break;                                // more splits only add bytes
     }
   }
+  if (model_us != nullptr) *model_us = best_us;
   return best;
 }
 
@@ -512,11 +583,20 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
   p.slabs = plan.slabs;
   const int64_t grid = (int64_t)p.tiles_m * p.tiles_n * plan.splits;
   if (grid > 0x7fffffffLL) return fail(PHOTON_ERR_UNSUPPORTED, "gemm: %lld workgroups are too many for one launch", (long long)grid);
-#define PHOTON_GEMM_CASE(KIND, KERN, THREADS, BUFS)                                                            case KIND: {                                                                                                   static bool attr_set = false;                                                                                return launch_kernel(KERN, &attr_set, (unsigned)grid, THREADS, (size_t)(BUFS) * (t.bm + t.bn) * 128, p, st);   }
+#define PHOTON_GEMM_CASE(KIND, KERN, THREADS, BUFS)                                                            \
+  case KIND: {                                                                                                 \
+    static bool attr_set = false;                                                                              \
+    return launch_kernel(KERN, &attr_set, (unsigned)grid, THREADS, (size_t)(BUFS) * (t.bm + t.bn) * 128, p, st); \
+  }
+  if constexpr (OUT != GEMM_OUT_QKV) {                           // a wave of the narrow tiles holds half a head
+    switch (plan.kind) {
+      PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT>), 256, 4)
+      PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT>), 256, 4)
+      PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT>), 512, 3)
+      default: break;
+    }
+  }
   switch (plan.kind) {
-    PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT>), 256, 4)
-    PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT>), 256, 4)
-    PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT>), 512, 3)
     PHOTON_GEMM_CASE(T_128x128, (gemm_tile_kernel<128, 128, 4, 2, 3, OUT>), 512, 3)
     PHOTON_GEMM_CASE(T_128x256, (gemm_pingpong_kernel<2, OUT>), PP_THREADS, 2)
     default:
@@ -560,6 +640,25 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
   rows.in = r; rows.bias = a.bias; rows.sum = reinterpret_cast<float*>(a.out); rows.ld_sum = a.ldo; rows.M = a.M; rows.K = a.N;
   *result = whole;
   return launch_rows(rows, st);
+}
+
+// The projection with the operands written by it (one of the wide tiles, K unsplit) against the best tile and the pass over
+// its fp32 result, which costs a launch and reads and writes 1.5 times that result at 4.5 bytes per ns (135 us at 32768 rows
+// of 3072).  Measured: 8192 rows of 3072 82 against 73 + 37 us; the model's margin matters below some hundred rows only.
+bool qkv_rope_pays(int64_t rows, int D, int d_h) {
+  if (d_h != 64) return false;
+  float fused = 0.f, best = 0.f;
+  plan_gemm(rows, 3 * D, D, false, false, 0, 0.f, T_128x128, &fused);
+  plan_gemm(rows, 3 * D, D, false, true, 0, 0.f, 0, &best);
+  return fused <= best + 4.f + 0.33f * (float)rows * 3 * D * 4e-6f;
+}
+
+int32_t launch_qkv_rope(const void* x, const void* W, int rows, int D, const QkvOperands& o, hipStream_t st) {
+  if (o.H * 64 != D || o.M <= 0 || rows % o.M != 0 || o.Mp % 64 != 0 || o.Mp < o.M)
+    return fail(PHOTON_ERR_UNSUPPORTED, "QKV projection: rows=%d D=%d do not match %d heads of 64 and %d positions", rows, D, o.H, o.M);
+  GemmArgs p{};
+  p.x = reinterpret_cast<const bf16_t*>(x); p.W = reinterpret_cast<const bf16_t*>(W); p.M = rows; p.N = 3 * D; p.K = D; p.qkv = o;
+  return launch_gemm<GEMM_OUT_QKV>(p, plan_gemm(rows, 3 * D, D, false, false, 0, 0.f, T_128x128), st);
 }
 
 static int32_t launch_chunker_gemm(const void* x, const void* w, const float* bias, void* out, int64_t M, int N, int K, hipStream_t st) {

@@ -99,4 +99,22 @@ struct ContractArgs {
 int64_t contract_part_floats(int64_t rows, int D);     // scratch that lets every contraction of a D-wide module split as it would
 int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st);
 
+// ---- QKV projection of an encoder (heads of 64) that writes the attention's operands itself ----
+
+// fp16 operands of the encoders' attention, per stream bh = sequence * H + head: qh, kh [bh][Mp][64] (rotated, q scaled),
+// vt [bh][64][Mp]; M positions per sequence, Mp: rounded up to 64.  kc, vc (both or neither): cache of S_max rows of 64 per
+// stream that receives the rotated keys and the values as bf16 or E4M3 bytes.  table: per position 32 cosines, 32 sines.
+struct QkvOperands {
+  uint16_t *qh = nullptr, *kh = nullptr, *vt = nullptr;
+  void *kc = nullptr, *vc = nullptr;
+  const float* table = nullptr;
+  int64_t S_max = 0;
+  int M = 0, Mp = 0, H = 0;
+  float qscale = 0.f;
+  bool cache_fp8 = false;
+};
+bool qkv_rope_pays(int64_t rows, int D, int d_h);
+// x [rows, D] dense bf16, rows = sequences * M; W [3D, D].
+int32_t launch_qkv_rope(const void* x, const void* W, int rows, int D, const QkvOperands& o, hipStream_t st);
+
 }  // namespace photon

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void embed_rows_kernel(const int32_t* __restri
 }
 
 // The same rows as they are stored in a bf16 table, for a tiled contraction that takes bf16 rows: 16 bytes a thread, no
-// widening that a row kernel would only round back (131072 rows of 1024: 172 + 164 us for the two kernels).
+// widening that a row kernel would only round back (131072 rows of 1024: 172 + 164 us for the two kernels, this one 90).
 __global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restrict__ tokens, const uint4_t* __restrict__ table,
                                                           uint4_t* __restrict__ rows, int64_t n, int per_row, int vocab) {
   const int64_t first = (int64_t)blockIdx.x * 256, row0 = first / per_row;   // the same for the whole workgroup
@@ -620,7 +620,7 @@ static int32_t hier_reencode(const Ctx& x, const int32_t* tokens, const float** 
   const bool concat1 = L >= 2 && x.ew->chunker_w[0] == nullptr;
   float* X = concat1 ? A : x.f(x.p.hx[0]);                 // encoder-side level-0 states of the new tokens
   const int64_t n_tok = (int64_t)Bt * per_seq;
-  PHOTON_TRY(embed_rows(x.st, x.bf16, tokens, x.ew->E_enc, X, n_tok, concat1 ? D / c.C[0] : D, c.vocab));
+  if (concat1 || L == 1) PHOTON_TRY(embed_rows(x.st, x.bf16, tokens, x.ew->E_enc, X, n_tok, concat1 ? D / c.C[0] : D, c.vocab));
   for (int l = 1; l < L; ++l) {
     const int C = c.C[l - 1];
     per_seq /= C;                                          // new level-l units per sequence
@@ -869,8 +869,9 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
   // by side are A^(1) itself.
   const bool concat1 = L >= 2 && ew.chunker_w[0] == nullptr;
   const int64_t n_tok = (int64_t)Bt * pp.M[0];
-  PHOTON_TRY(embed_rows(x.st, x.bf16, tokens, ew.E_enc, concat1 ? A : e.f(pp.X[0]), n_tok, concat1 ? D / c.C[0] : D, c.vocab));
+  if (concat1) PHOTON_TRY(embed_rows(x.st, x.bf16, tokens, ew.E_enc, A, n_tok, D / c.C[0], c.vocab));
 
+  bool rounded = false;                                    // the level below left its states in the bf16 rows as well
   for (int l = 1; l <= L; ++l) {
     const int C = c.C[l - 1];
     const int64_t M = pp.M[l];
@@ -885,10 +886,13 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
       PHOTON_TRY(linear(e, RowSource{e.f(pp.X[l - 1]), (int64_t)C * D}, ew.chunker_w[l - 1], nullptr, ew.chunker_b[l - 1], A, D, rows, D, C * D));
     RowSource in{A, D};
     const size_t layer_cache = (size_t)Bt * c.H * x.s->S_max * kv_row_elems(c.d_h) * esz;
+    // Where it pays, the projection writes the attention's operands itself; the angles' cosines and sines lie in the
+    // projection's own buffer meanwhile, behind the rows that the block's second half keeps there.
+    const bool fused = many_rows(e, rows) && qkv_rope_pays(rows, D, c.d_h);
+    QkvOperands ops;
+    if (fused) PHOTON_TRY(encoder_operands_begin(Bt, M, c.H, c.rope_theta, scale, e.base + pp.ea, qkv + (int64_t)rows * D, &ops, x.st));
     for (int i = 0; i < c.n_layers; ++i) {
       const photon_layer_weights& lw = mod.layers[i];
-      RowSource qkv_rows;
-      PHOTON_TRY(block_qkv(e, lw, &in, rows, false, &qkv_rows));
       char *kc = nullptr, *vc = nullptr;
       int64_t cap = x.s->S_max;
       if (l == L) {
@@ -900,7 +904,17 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
         kc = reinterpret_cast<char*>(x.hs->k_cache[l - 1]) + (size_t)i * lc;
         vc = reinterpret_cast<char*>(x.hs->v_cache[l - 1]) + (size_t)i * lc;
       }
-      PHOTON_TRY(launch_encoder_attn(qkv, attn, Bt, M, c.H, c.d_h, c.rope_theta, scale, kc, vc, cap, e.base + pp.ea, x.bf16, c.kv_dt == PHOTON_FP8_E4M3, x.bf16, x.st));
+      if (fused) {
+        PHOTON_TRY(round_rows(e, in, lw.g1, e.f(e.o_h), D, rows, D));
+        if (in.n_parts != 0) in = RowSource{e.f(e.o_h), D};
+        ops.kc = kc; ops.vc = vc; ops.S_max = cap; ops.cache_fp8 = c.kv_dt == PHOTON_FP8_E4M3;
+        PHOTON_TRY(launch_qkv_rope(e.base + e.o_many, lw.wqkv, rows, D, ops, x.st));
+        PHOTON_TRY(launch_encoder_attn_operands(ops, attn, Bt, c.d_h, true, x.st));
+      } else {
+        RowSource qkv_rows;
+        PHOTON_TRY(block_qkv(e, lw, &in, rows, false, &qkv_rows));
+        PHOTON_TRY(launch_encoder_attn(qkv, attn, Bt, M, c.H, c.d_h, c.rope_theta, scale, kc, vc, cap, e.base + pp.ea, x.bf16, c.kv_dt == PHOTON_FP8_E4M3, x.bf16, x.st));
+      }
       PHOTON_TRY(block_tail(e, lw, in, rows, x.bf16, &in));
     }
     if (l < L) {

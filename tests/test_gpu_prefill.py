@@ -243,6 +243,35 @@ def test_hierarchical_generation_two_steps(dtype, kw, Bt, T):
         check_hier(cfg, hier, ost, tol_kv)
 
 
+# Heads of 64 whose projection writes the attention's operands itself: positions that come in fours and that do not (5 x 67
+# and 3 x 7 at the second level, where row tiles straddle sequences), a last column tile of one head, all of a prompt's
+# streams kept, 128- and 256-wide tiles.
+@pytest.mark.parametrize("kw,Bt,T", [
+    (dict(D=320, H=5), 5, 16 * 67),
+    (dict(), 3, 16 * 7),
+    (dict(L=1, C=(4,), R=(1,)), 1, 4 * 130),
+    (dict(D=512, H=8, d_ff=1280, n_layers=1), 3, 16 * 341),
+])
+def test_bf16_prefill_operands_from_the_projection(kw, Bt, T):
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    base = dict(L=2, C=(4, 4), R=(1, 1), D=256, H=4, d_h=64, n_layers=2, d_ff=640, vocab=1024, dtype="bf16")
+    base.update(kw)
+    cfg = si.PhotonConfig(**base)
+    w = si.make_weights(cfg, 23)
+    toks = si.make_tokens(cfg.vocab, Bt, T, 4)
+    S_max = T // cfg.meta_context + 3
+    ost = po.hier_prefill(cfg, po.weights_to_f64(w), toks, S_max)
+    model = ph.PhotonModel(cfg, w)
+    state = ph.PhotonState(model, Bt, S_max)
+    hier = ph.PhotonHierState(model, Bt, S_max)
+    ws = torch.full((ph.photon_prefill_workspace_bytes(cfg, Bt, T),), 0xff, dtype=torch.uint8, device="cuda")   # NaN wherever it is read unwritten
+    ph.photon_prefill(model, state, dev(np.asarray(toks, np.int32)), hier=hier, workspace=ws)
+    torch.cuda.synchronize()
+    print(check_state(cfg, state, ost, Bt, TOL["bf16"], 2.0 ** -7))
+    check_hier(cfg, hier, ost, 2.0 ** -7)
+
+
 def test_bf16_prefill_with_8bit_cache_then_step():
     """Prefill into an 8-bit (E4M3) coarse cache, then a decode step from it, against the oracle doing the same."""
     require_gpu()
