@@ -118,6 +118,17 @@ template <int G> __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
+// Sum over the wave, the same in every lane: rows of 16 lanes by data-parallel moves, then rows and halves by exchanges of
+// whole rows (no trip through LDS).  The pairs added are those of lane distances 1, 2, 4, 8, 16, 32.
+__device__ __forceinline__ float wave_sum(float x) {
+  x = group_sum<16>(x);
+  typedef uint32_t uint2_native __attribute__((ext_vector_type(2)));
+  const uint2_native r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  const uint2_native h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
 // rotate a 128-bit register by 8 lanes inside every row of 16 lanes
 __device__ __forceinline__ uint4_t rotate8(const uint4_t& v) {
   constexpr int ROW_ROR8 = 0x128;

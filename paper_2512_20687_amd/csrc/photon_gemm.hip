@@ -421,8 +421,7 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
     if (p.y != nullptr) *reinterpret_cast<float4_t*>(p.y + (int64_t)row * p.ldy + k) = v * r * g;
   };
   auto inv_rms = [&](float ss) {
-    ss = group_sum<32>(ss);
-    ss += __shfl_xor(ss, 32);
+    ss = wave_sum(ss);
     if (TPR > 64) {
       __shared__ float partsum[4];
       if ((threadIdx.x & 63) == 0) partsum[threadIdx.x >> 6] = ss;

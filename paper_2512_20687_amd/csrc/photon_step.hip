@@ -27,8 +27,7 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(const float* __restrict_
     xrow[d >> 2] = v;
     ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss))));
   }
-  ss = group_sum<32>(ss);
-  ss += __shfl_xor(ss, 32);
+  ss = wave_sum(ss);
   __shared__ float partsum[4];
   if ((tid & 63) == 0) partsum[tid >> 6] = ss;
   __syncthreads();

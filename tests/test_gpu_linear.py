@@ -50,6 +50,17 @@ def test_linear_parity(dtype, M, N, K, epilogue, norm, bias):
     assert nerr(out, ref) <= TOL["f32"] * (1 if dtype == "f32" else 2)
 
 
+# fp32 matrices: the row counts on both sides of every power of two that the kernel is built for, K short of a wave's stride
+# and past it, a last workgroup with idle waves.
+@pytest.mark.parametrize("M", [2, 3, 5, 8, 9, 15, 33])
+@pytest.mark.parametrize("epilogue,norm", [(0, True), (1, False), (2, True)])
+def test_fp32_row_counts(M, epilogue, norm):
+    require_gpu()
+    for N, K in ((7, 20), (66, 300)):
+        out, ref = case("f32", M, N, K, epilogue, norm, True, seed=M)
+        assert nerr(out, ref) <= TOL["f32"]
+
+
 @pytest.mark.parametrize("M,N,K,epilogue,norm", [
     (16, 6144, 2048, 0, True),       # configuration 3: QKV with pre-norm, token level
     (4, 2048, 2048, 1, False),       # O projection + residual
