@@ -39,7 +39,7 @@ __device__ __forceinline__ void load16_to_lds(const void* gsrc, uint32_t lds_bas
 
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-enum GemmOut { GEMM_OUT_BF16 = 0, GEMM_OUT_F32 = 1, GEMM_OUT_SWIGLU = 2, GEMM_OUT_QKV = 3 };
+enum GemmOut { GEMM_OUT_BF16 = 0, GEMM_OUT_F32 = 1, GEMM_OUT_SWIGLU = 2, GEMM_OUT_QKV = 3, GEMM_OUT_LOGITS = 4 };
 
 // ---- shared by the tile kernels ------------------------------------------------------------------------------------------
 
@@ -50,6 +50,7 @@ struct GemmArgs {
   const bf16_t* x; const bf16_t* W; const float* bias; const float* res; void* out;
   int64_t ldres, ldo, split_stride;
   int M, N, K, tiles_m, tiles_n, group_m, slabs;
+  RowBest* best; int stretches;                                  // GEMM_OUT_LOGITS (fp32 output): see ContractArgs
   QkvOperands qkv;                                               // GEMM_OUT_QKV: where the columns go instead of `out`
 };
 
@@ -113,7 +114,7 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
       if (n >= p.N) continue;                                    // N is a multiple of 16
       float4_t y = acc[j];
       if (p.bias != nullptr) y += float4_t{p.bias[n], p.bias[n + 1], p.bias[n + 2], p.bias[n + 3]};
-      if constexpr (OUT == GEMM_OUT_F32) {
+      if constexpr (OUT == GEMM_OUT_F32 || OUT == GEMM_OUT_LOGITS) {
         if (p.res != nullptr) y += *reinterpret_cast<const float4_t*>(p.res + (int64_t)m * p.ldres + n);
         *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(p.out) + split * p.split_stride + (int64_t)m * p.ldo + n) = y;
       } else {
@@ -121,6 +122,30 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
       }
     }
   }
+}
+
+// Best column of a wave's 16 * TJ columns of row m, for the token choice: the choice then reads a pair per stretch instead
+// of all logits (1024 rows of 32000: 32 -> 7 us).  The four lanes that share a row are 16 and 32 apart.
+template <int TJ>
+__device__ __forceinline__ void store_best(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int col0, int fk) {
+  if (m >= p.M || col0 >= p.N) return;
+  float best = -INFINITY;
+  int column = 0x7fffffff;
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const int n = col0 + j * 16 + fk * 4;
+    if (n >= p.N) continue;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (acc[j][t] > best || column == 0x7fffffff) { best = acc[j][t]; column = n + t; }
+  }
+#pragma unroll
+  for (int mask = 16; mask < 64; mask <<= 1) {
+    const float v = __shfl_xor(best, mask);
+    const int c = __shfl_xor(column, mask);
+    if (v > best || (v == best && c < column)) { best = v; column = c; }
+  }
+  if (fk == 0) p.best[(int64_t)m * p.stretches + col0 / (16 * TJ)] = RowBest{best, column};
 }
 
 // Four consecutive cache entries.
@@ -260,6 +285,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
   for (int i = 0; i < TI; ++i) {
     if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
     else store_row<OUT, TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0, wn, fk, at.split);
+    if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
   }
 }
 
@@ -396,6 +422,7 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
       const int m = m0 + (group * 2 + h) * HALF + i * 16 + fr;
       if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
       else store_row<OUT, TJ>(p, acc[h][i], m, n0, wcol * 64, fk, at.split);
+      if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
     }
 }
 
@@ -614,7 +641,7 @@ int64_t contract_part_floats(int64_t rows, int D) {
   return (rows < 1024 ? rows : 1024) * 12 * (int64_t)D;
 }
 
-int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st) {
+int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st, int* best_stretches) {
   if (a.K % G_BK != 0 || a.N % 16 != 0 || a.ldo % 4 != 0) return fail(PHOTON_ERR_UNSUPPORTED, "contraction: K=%d must be a multiple of 64, N=%d of 16", a.K, a.N);
   GemmArgs p{};
   p.x = reinterpret_cast<const bf16_t*>(a.x); p.W = reinterpret_cast<const bf16_t*>(a.W); p.M = a.M; p.N = a.N; p.K = a.K;
@@ -624,6 +651,14 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
   const bool join = a.epilogue == EPI_PLAIN && !a.split_ok;
   const GemmPlan plan = plan_gemm(a.M, a.N, a.K, false, true, a.part_cap, join ? 3.5f : 0.f);
   const RowSource whole{reinterpret_cast<const float*>(a.out), a.ldo, nullptr, 0, 0, 0};
+  if (a.best != nullptr && plan.splits == 1) {
+    if (a.epilogue != EPI_PLAIN || a.bias != nullptr || best_stretches == nullptr)
+      return fail(PHOTON_ERR_INVALID_ARG, "contraction: the rows' best columns come with plain logits only");
+    const int wave_columns = plan.kind >= T_128x128 ? 64 : 32;
+    p.best = a.best; p.stretches = *best_stretches = (a.N + wave_columns - 1) / wave_columns;
+    *result = whole;
+    return launch_gemm<GEMM_OUT_LOGITS>(p, plan, st);
+  }
   if (plan.splits == 1) {
     if (a.epilogue == EPI_RESID) {
       if (a.res.n_parts != 0) return fail(PHOTON_ERR_INVALID_ARG, "contraction: the residual rows must be in one piece");

@@ -78,6 +78,12 @@ struct RowsArgs {
 };
 int32_t launch_rows(const RowsArgs& a, hipStream_t st);
 
+// The largest of a stretch of columns of one row and the column it sits in (the first, where several are equal).
+struct RowBest {
+  float value;
+  int column;
+};
+
 // x [M, K] dense bf16, W [N, K] (2N rows for EPI_SWIGLU) bf16; out fp32 [M, ldo], or for EPI_SWIGLU bf16 [M, ldo].
 // EPI_RESID: out = res + x W^T, where out and res must not overlap.  parts: scratch of part_cap floats for the partial
 // products of a contraction split over K.  `result` says where the fp32 result lies: in out, or still in pieces
@@ -95,9 +101,13 @@ struct ContractArgs {
   int M = 0, N = 0, K = 0;
   int epilogue = EPI_PLAIN;
   bool split_ok = false;
+  // EPI_PLAIN without bias: row m's best of every stretch of columns goes to best[m * stretches + stretch], where `best`
+  // holds M * best_stretches_max(N); launch_contract sets *best_stretches, and leaves it where K is split (nothing is written)
+  RowBest* best = nullptr;
 };
+inline int best_stretches_max(int N) { return (N + 31) / 32; }
 int64_t contract_part_floats(int64_t rows, int D);     // scratch that lets every contraction of a D-wide module split as it would
-int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st);
+int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st, int* best_stretches = nullptr);
 
 // ---- QKV projection of an encoder (heads of 64) that writes the attention's operands itself ----
 

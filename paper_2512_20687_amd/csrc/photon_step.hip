@@ -131,10 +131,12 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
 }
 
 // Token choice for one row of logits (greedy, lowest index on ties, or the forced token), then the
-// decoder-side embedding of that token as the next input row.
+// decoder-side embedding of that token as the next input row.  best: the row's best of `stretches` stretches of columns
+// (nullptr: all of the row's logits are read here).
 constexpr int CHOOSE_THREADS = 1024;
 template <typename TE>
 __global__ __launch_bounds__(CHOOSE_THREADS) void choose_token_kernel(const float* __restrict__ logits, int64_t ld_logits, int vocab,
+                                                           const RowBest* __restrict__ best_of, int stretches,
                                                            const int32_t* __restrict__ forced, int32_t* __restrict__ tokens,
                                                            int tok_mul, int tok_off, const TE* __restrict__ E,
                                                            float* __restrict__ x_next, int D) {
@@ -142,16 +144,38 @@ __global__ __launch_bounds__(CHOOSE_THREADS) void choose_token_kernel(const floa
   const float* lg = logits + (int64_t)row * ld_logits;
   float best = -INFINITY;
   int bi = 0x7fffffff;
-  for (int t0 = tid; t0 < vocab; t0 += 4 * CHOOSE_THREADS) {       // indices visited in increasing order: first maximum wins
-    float v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int t = t0 + u * CHOOSE_THREADS;
-      v[u] = t < vocab ? lg[t] : -INFINITY;
+  if (best_of != nullptr) {
+    for (int i = tid; i < stretches; i += blockDim.x) {
+      const RowBest r = best_of[(int64_t)row * stretches + i];       // in increasing order of columns
+      if (r.value > best || bi == 0x7fffffff) { best = r.value; bi = r.column; }
     }
+  } else if (vocab % 4 == 0 && ld_logits % 4 == 0 && (reinterpret_cast<uintptr_t>(lg) & 15) == 0) {
+    // 16 bytes a lane, 8 loads in flight: 32000 logits are one round of loads
+    for (int t0 = tid * 4; t0 < vocab; t0 += 32 * CHOOSE_THREADS) {  // indices visited in increasing order: first maximum wins
+      float4_t v[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (v[u] > best || (bi == 0x7fffffff && t0 + u * CHOOSE_THREADS < vocab)) { best = v[u]; bi = t0 + u * CHOOSE_THREADS; }
+      for (int u = 0; u < 8; ++u) {
+        const int t = t0 + u * 4 * CHOOSE_THREADS;
+        v[u] = t < vocab ? *reinterpret_cast<const float4_t*>(lg + t) : float4_t{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v[u][e] > best || (bi == 0x7fffffff && t0 + u * 4 * CHOOSE_THREADS < vocab)) { best = v[u][e]; bi = t0 + u * 4 * CHOOSE_THREADS + e; }
+    }
+  } else {
+    for (int t0 = tid; t0 < vocab; t0 += 4 * CHOOSE_THREADS) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = t0 + u * CHOOSE_THREADS;
+        v[u] = t < vocab ? lg[t] : -INFINITY;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (v[u] > best || (bi == 0x7fffffff && t0 + u * CHOOSE_THREADS < vocab)) { best = v[u]; bi = t0 + u * CHOOSE_THREADS; }
+    }
   }
 #pragma unroll
   for (int mask = 1; mask < 64; mask <<= 1) {
@@ -165,7 +189,7 @@ __global__ __launch_bounds__(CHOOSE_THREADS) void choose_token_kernel(const floa
   if ((tid & 63) == 0) { sv[tid >> 6] = best; si[tid >> 6] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < CHOOSE_THREADS / 64; ++w)
+    for (int w = 1; w < (int)blockDim.x / 64; ++w)
       if (sv[w] > best || (sv[w] == best && si[w] < bi)) { best = sv[w]; bi = si[w]; }
     const int64_t flat = (int64_t)row * tok_mul + tok_off;
     if (forced != nullptr) bi = forced[flat];
@@ -176,7 +200,7 @@ __global__ __launch_bounds__(CHOOSE_THREADS) void choose_token_kernel(const floa
   __syncthreads();
   if (x_next != nullptr) {
     const TE* e = E + (int64_t)chosen * D;
-    for (int d = tid; d < D; d += CHOOSE_THREADS) x_next[(int64_t)row * D + d] = to_f32<TE>(e[d]);
+    for (int d = tid; d < D; d += blockDim.x) x_next[(int64_t)row * D + d] = to_f32<TE>(e[d]);
   }
 }
 
@@ -241,6 +265,7 @@ struct Plan {
   size_t cond_top = 0;                           // conditioning latents of the level-(L-1) chunks (written on the main line)
   size_t many = 0, many2 = 0;                    // bf16 rows of the tiled contractions (MANY_ROWS rows and up), main and STEP branch
   size_t parts = 0, parts2 = 0;                  // their partial products
+  size_t best = 0;                               // best logits per stretch of the vocabulary (many rows at the token level)
   int64_t part_cap = 0, part_cap2 = 0;           // floats
   size_t hx[PHOTON_MAX_LEVELS] = {0}, hA = 0;    // hierarchical generation: encoder-side new units of level l, chunker outputs
   int many_K = 0;                                // widest contraction they are sized for
@@ -295,6 +320,7 @@ static Plan make_plan(const photon_config& c, int Bt, int64_t S_max) {
       p.many = bump(cur, (size_t)p.rows_max * p.many_K * 2);
       p.part_cap = contract_part_floats(p.rows_max, c.D);
       p.parts = bump(cur, (size_t)p.part_cap * f);
+      p.best = bump(cur, (size_t)p.chunks[1] * best_stretches_max(c.vocab) * sizeof(RowBest));
     }
     if (p.rows2 >= MANY_ROWS) {
       p.many2 = bump(cur, (size_t)p.rows2 * p.many_K * 2);
@@ -384,11 +410,12 @@ static int32_t round_rows(const Ctx& x, const RowSource& in, const float* gain, 
 
 // Tiled contraction of `rows` dense bf16 rows (nullptr: this branch's, as round_rows left them).
 static int32_t contract(const Ctx& x, const void* xb, const void* W, const float* bias, const RowSource& res, void* out, int64_t ldo, int rows,
-                        int N, int K, int epilogue, bool split_ok, RowSource* result) {
+                        int N, int K, int epilogue, bool split_ok, RowSource* result, RowBest* best = nullptr, int* stretches = nullptr) {
   ContractArgs a;
   a.x = xb != nullptr ? xb : x.base + x.o_many; a.W = W; a.bias = bias; a.res = res; a.out = out; a.ldo = ldo;
   a.parts = x.f(x.o_parts); a.part_cap = x.part_cap; a.M = rows; a.N = N; a.K = K; a.epilogue = epilogue; a.split_ok = split_ok;
-  return launch_contract(a, result, x.st);
+  a.best = best;
+  return launch_contract(a, result, x.st, stretches);
 }
 
 // out[M, N] = W^T + bias of the bf16 rows that a row or gather kernel left in this branch's buffer.
@@ -397,13 +424,14 @@ static int32_t linear_of_rounded(const Ctx& x, const void* W, const float* bias,
   return contract(x, nullptr, W, bias, RowSource{}, out, N, M, N, K, EPI_PLAIN, false, &whole);
 }
 
-// out[M, N] = rmsnorm(in; gain) W^T + bias (gain, bias: nullptr for none).
+// out[M, N] = rmsnorm(in; gain) W^T + bias (gain, bias: nullptr for none).  best (with stretches): the tiled contraction also
+// leaves the best columns of every row's stretches there; *stretches stays 0 where another kernel runs.
 static int32_t linear(const Ctx& x, const RowSource& in, const void* W, const float* gain, const float* bias, float* out, int64_t ldo, int M,
-                      int N, int K) {
+                      int N, int K, RowBest* best = nullptr, int* stretches = nullptr) {
   if (many_rows(x, M) && K <= x.p.many_K) {
     RowSource whole;
     PHOTON_TRY(round_rows(x, in, gain, nullptr, 0, M, K));
-    return contract(x, nullptr, W, bias, RowSource{}, out, ldo, M, N, K, EPI_PLAIN, false, &whole);
+    return contract(x, nullptr, W, bias, RowSource{}, out, ldo, M, N, K, EPI_PLAIN, false, &whole, best, stretches);
   }
   LinearArgs a;
   a.x = in.x; a.ldx = in.ld;
@@ -688,17 +716,21 @@ static int32_t decode_level(const Ctx& x, int l, const float* cond_in, float* un
       float* lg = (tr && tr->logits) ? tr->logits + (int64_t)j * c.vocab : x.f(x.p.logits);
       const int64_t ld = (tr && tr->logits) ? (int64_t)C * c.vocab : c.vocab;
       // logits of item j of every chunk: rows of `units` with pitch C*D
+      RowBest* best = x.p.best != 0 ? reinterpret_cast<RowBest*>(x.base + x.p.best) : nullptr;
+      int stretches = 0;
       if (norm_in_head)
-        PHOTON_TRY(linear(x, last, x.w->W_lm, mod.g_final, nullptr, lg, ld, (int)n, c.vocab, D));
+        PHOTON_TRY(linear(x, last, x.w->W_lm, mod.g_final, nullptr, lg, ld, (int)n, c.vocab, D, best, &stretches));
       else
-        PHOTON_TRY(linear(x, RowSource{units + (int64_t)j * D, (int64_t)C * D}, x.w->W_lm, nullptr, nullptr, lg, ld, (int)n, c.vocab, D));
+        PHOTON_TRY(linear(x, RowSource{units + (int64_t)j * D, (int64_t)C * D}, x.w->W_lm, nullptr, nullptr, lg, ld, (int)n, c.vocab, D, best, &stretches));
+      if (stretches == 0) best = nullptr;
+      const int threads = best != nullptr ? 256 : CHOOSE_THREADS;
       float* x_next = (j + 1 < C) ? h : nullptr;           // decoder-side embedding of the chosen token
       if (x.bf16)
-        PHOTON_LAUNCH(KC_CHOOSE_TOKEN, x.st, choose_token_kernel<bf16_t>, dim3((unsigned)n), dim3(CHOOSE_THREADS), 0, x.st, lg, ld, c.vocab,
-                      forced, out_tokens, C, j, (const bf16_t*)x.w->E_dec, x_next, D);
+        PHOTON_LAUNCH(KC_CHOOSE_TOKEN, x.st, choose_token_kernel<bf16_t>, dim3((unsigned)n), dim3(threads), 0, x.st, lg, ld, c.vocab,
+                      best, stretches, forced, out_tokens, C, j, (const bf16_t*)x.w->E_dec, x_next, D);
       else
-        PHOTON_LAUNCH(KC_CHOOSE_TOKEN, x.st, choose_token_kernel<float>, dim3((unsigned)n), dim3(CHOOSE_THREADS), 0, x.st, lg, ld, c.vocab,
-                      forced, out_tokens, C, j, (const float*)x.w->E_dec, x_next, D);
+        PHOTON_LAUNCH(KC_CHOOSE_TOKEN, x.st, choose_token_kernel<float>, dim3((unsigned)n), dim3(threads), 0, x.st, lg, ld, c.vocab,
+                      best, stretches, forced, out_tokens, C, j, (const float*)x.w->E_dec, x_next, D);
       PHOTON_TRY(check_launch("choose_token_kernel"));
       in = RowSource{h, D};
     }

@@ -52,3 +52,30 @@ def test_decode_step_at_many_rows(kw, Bt):
     st = si.make_decode_state(cfg, Bt, S, S_max, seed=3)
     errs, _, _ = check_against_oracle(cfg, si.make_weights(cfg, 12), st, Bt, S_max, si.make_tokens(cfg.vocab, Bt, cfg.meta_context, 7), TOL["bf16"])
     print(errs)
+
+
+# Greedy steps with enough rows that the vocabulary contraction leaves each row's best columns beside the logits: a narrow
+# and a wide wave tile, a last stretch of 16 columns, equal logits (the vocabulary's second half repeats the first: the
+# lower index wins), logits in the state's own buffer (no trace) as well.
+@pytest.mark.parametrize("Bt,vocab", [(5, 1008), (17, 4000), (65, 8016), (256, 16000)])
+def test_greedy_choice_at_many_rows(Bt, vocab):
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(L=2, C=(4, 4), R=(1, 1), D=256, H=4, d_h=64, n_layers=1, d_ff=640, vocab=vocab, dtype="bf16")
+    w = si.make_weights(cfg, 5)
+    w["W_lm"][vocab // 2:] = w["W_lm"][: vocab - vocab // 2]
+    st = si.make_decode_state(cfg, Bt, 20, 32, seed=2)
+    model = ph.PhotonModel(cfg, w)
+    tokens = []
+    for traced in (True, False):
+        state = ph.PhotonState(model, Bt, 32, k=st["k"], v=st["v"], seq_len=st["seq_len"], x_top=st["x_top"], carry=st["carry"])
+        out = torch.full((Bt, cfg.meta_context), -1, dtype=torch.int32, device="cuda")
+        logits = torch.full((Bt, cfg.meta_context, vocab), float("nan"), device="cuda")
+        ph.photon_decode_step(model, state, out, trace={"logits": logits} if traced else None)
+        torch.cuda.synchronize()
+        tokens.append(out)
+        if traced:
+            index = torch.arange(vocab, device="cuda").expand_as(logits)
+            first = torch.where(logits == logits.amax(-1, keepdim=True), index, vocab).amin(-1)
+            assert torch.equal(out.long(), first) and int(out.max()) < vocab - vocab // 2
+    assert torch.equal(tokens[0], tokens[1])
