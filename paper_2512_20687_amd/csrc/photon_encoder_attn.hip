@@ -29,8 +29,8 @@
 //   * the score accumulators start from minus a reference (kept as a register
 //     vector): the maximum of a query's first block, moved up to the running
 //     maximum only when a block's weights add up to more than 1024, which is
-//     far below fp16's range; until then weights above 1 are exact powers away
-//     from what they would be, in fp16 as in fp32.  The common path per score
+//     far below fp16's range (weights above 1 lose no more to its rounding
+//     than weights below).  The common path per score
 //     is exp2, one add into the row sum and the fp16 pack, with no maximum, no
 //     exchange and no branch between the score MFMAs and the exponentials; a
 //     block that does raise the reference forms its scores again (32 heads:

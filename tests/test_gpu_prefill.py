@@ -85,6 +85,11 @@ def test_small_fp32_prefill(kw, Bt, T):
     (dict(n_layers=1), 3, 16 * 1),
     (dict(D=832, H=16, d_h=52, d_ff=1024, n_layers=1, R=(2, 2), concat_level1=True), 2, 16 * 36),   # paper-like heads, MFMA attention on padded rows
     (dict(D=448, H=8, d_h=56, d_ff=640, n_layers=1), 2, 16 * 10),
+    # carries: windows of 80 rows of 16 sequences (fp32 rows, as a sub-step of 16 keeps them; more rows than any sub-step has)
+    # and of 85 rows of 17 (bf16 rows)
+    (dict(n_layers=1, R=(1, 2)), 16, 16 * 3),
+    (dict(n_layers=2, R=(1, 2)), 17, 16 * 2),
+    (dict(n_layers=1, L=3, C=(2, 5, 3), R=(1, 3, 2)), 4, 30 * 2),
 ])
 def test_bf16_prefill_then_step(kw, Bt, T):
     """bf16 weights and cache; then one decode step from the GPU-made state
