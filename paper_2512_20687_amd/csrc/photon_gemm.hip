@@ -49,7 +49,7 @@ enum GemmOut { GEMM_OUT_BF16 = 0, GEMM_OUT_F32 = 1, GEMM_OUT_SWIGLU = 2, GEMM_OU
 struct GemmArgs {
   const bf16_t* x; const bf16_t* W; const float* bias; const float* res; void* out;
   int64_t ldres, ldo, split_stride;
-  int M, N, K, tiles_m, tiles_n, group_m, slabs;
+  int M, N, K, tiles_m, tiles_n, group_m, slabs, tiles;          // tiles: of all splits
   RowBest* best; int stretches;                                  // GEMM_OUT_LOGITS (fp32 output): see ContractArgs
   QkvOperands qkv;                                               // GEMM_OUT_QKV: where the columns go instead of `out`
 };
@@ -58,8 +58,8 @@ struct GemmArgs {
 // not a multiple of 8), walked as bands of group_m row tiles, row tiles fastest: the 32 tiles resident on an XCD form a
 // patch of about group_m x 32 / group_m whose x rows and W rows that XCD's L2 holds once.
 struct TilePos { int tm, tn, split; };
-__device__ __forceinline__ TilePos tile_position(const GemmArgs& p) {
-  const int total = gridDim.x, id = blockIdx.x, xcd = id & 7, base = total >> 3, rem = total & 7;
+__device__ __forceinline__ TilePos tile_position(const GemmArgs& p, int id, int total) {
+  const int xcd = id & 7, base = total >> 3, rem = total & 7;
   const int logical = xcd * base + (xcd < rem ? xcd : rem) + (id >> 3);
   const int per_split = p.tiles_m * p.tiles_n;
   const int split = logical / per_split, t = logical - split * per_split;
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
   extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const TilePos at = tile_position(p);
+  const TilePos at = tile_position(p, blockIdx.x, gridDim.x);
   const int m0 = at.tm * BM, n0 = at.tn * (GU ? BN / 2 : BN);
   const int s0 = at.split * p.slabs;
   const int KT = min(p.slabs, p.K / G_BK - s0);
@@ -309,7 +309,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
 // 122 us (1.41 PFLOP/s) where a 16-wave kernel without the counter-phase takes 134 us.
 constexpr int PP_BN = 256, PP_THREADS = 512;
 
-template <int TI, int OUT>
+// WALK: a workgroup walks several tiles (launch_gemm says when), its loads running over the end of one into the next; else
+// one tile, whose slab addresses need no state of their own.
+template <int TI, int OUT, bool WALK = false>
 __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
   constexpr int TJ = 4;                                          // MFMA tiles of a wave's half: TI x 16 rows, 64 columns
@@ -321,56 +323,65 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave >> 2, wcol = wave & 3;                  // group 0: upper half of the tile's rows, group 1: lower half
-  const TilePos at = tile_position(p);
-  const int m0 = at.tm * PP_BM, n0 = at.tn * (GU ? PP_BN / 2 : PP_BN);
-  const int s0 = at.split * p.slabs;
-  const int KT = min(p.slabs, p.K / G_BK - s0);
+  const int fr = lane & 15, fk = lane >> 4;                      // operand fragment: row, 8-wide k group
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
 
   // one load instruction moves 64 lanes x 16 B = 8 staged rows; instruction i of wave w covers rows (i * 8 + w) * 8 .. +8
-  const char* src[PP_XI + PP_YI];
-#pragma unroll
-  for (int i = 0; i < PP_XI + PP_YI; ++i) {
+  auto source = [&](const TilePos& at, int i) {
     const int r = (i * 8 + wave) * 8 + (lane >> 3);
     const bf16_t* row;
     if ((i * 8 + wave) * 8 < PP_BN) {
-      row = p.W + (int64_t)weight_row<GU>(r, n0, p.N) * p.K;
+      row = p.W + (int64_t)weight_row<GU>(r, at.tn * (GU ? PP_BN / 2 : PP_BN), p.N) * p.K;
     } else {
       const int a = r - PP_BN, half = a / (2 * HALF), w = a % (2 * HALF);   // staged x row -> row of the tile
-      const int m = m0 + (w / HALF) * (2 * HALF) + half * HALF + w % HALF;
+      const int m = at.tm * PP_BM + (w / HALF) * (2 * HALF) + half * HALF + w % HALF;
       row = p.x + (int64_t)(m < p.M ? m : p.M - 1) * p.K;        // rows past the end repeat the last one: never stored
     }
-    src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8 + (int64_t)s0 * G_BK);
-  }
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
-  // past the end: the last slab again, into rows nobody reads any more (the number of loads in flight stays constant)
-  auto load = [&](int kt, auto first, auto last) {
-    const uint32_t to = lds0 + (kt & 1) * PP_STAGE;
-    const int64_t ko = (int64_t)(kt < KT ? kt : KT - 1) * (G_BK * 2);
+    return reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8 + (int64_t)at.split * p.slabs * G_BK);
+  };
+  auto slabs_of = [&](const TilePos& at) { return min(p.slabs, p.K / G_BK - at.split * p.slabs); };
+  // Loads run ahead of the slab that is contracted; each part has a place of its own in the sequence of all slabs.  After the
+  // last tile the last slab is loaded again, into rows nobody reads any more (the number of loads in flight stays constant).
+  struct Ahead { int id, left, slab; };                          // tile, slabs left in it, count of all slabs so far
+  Ahead ax{(int)blockIdx.x, 0, 0}, ay = ax;
+  const char* src[PP_XI + PP_YI];
+  auto enter = [&](Ahead& a, auto first, auto last) {
+    const TilePos to = tile_position(p, a.id, p.tiles);
+    a.left = slabs_of(to);
+#pragma unroll
+    for (int i = decltype(first)::value; i < decltype(last)::value; ++i) src[i] = source(to, i);
+  };
+  auto load = [&](Ahead& a, auto first, auto last) {
+    const uint32_t to = lds0 + (a.slab & 1) * PP_STAGE;
+    const int64_t ko = WALK ? 0 : (int64_t)(a.slab < a.left ? a.slab : a.left - 1) * (G_BK * 2);
+    ++a.slab;
 #pragma unroll
     for (int i = decltype(first)::value; i < decltype(last)::value; ++i) load16_to_lds(src[i] + ko, to + (i * 8 + wave) * 1024);
+    if constexpr (WALK) {
+      if (--a.left > 0) {
+#pragma unroll
+        for (int i = decltype(first)::value; i < decltype(last)::value; ++i) src[i] += G_BK * 2;
+      } else if (a.left == 0 && a.id + (int)gridDim.x < p.tiles) {
+        a.id += gridDim.x;
+        enter(a, first, last);
+      }
+    }
   };
   using I0 = std::integral_constant<int, 0>;
   using IX = std::integral_constant<int, PP_XI>;
   using IE = std::integral_constant<int, PP_XI + PP_YI>;
 
   float4_t acc[2][TI][TJ];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) acc[h][i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
-  const int fr = lane & 15, fk = lane >> 4;                      // operand fragment: row, 8-wide k group
   bf16x8_t xf[2][TI], wf[2][TJ];
-  auto read_w = [&](int kt) {
-    const char* s = lds + (kt & 1) * PP_STAGE;
+  auto read_w = [&](int slab) {
+    const char* s = lds + (slab & 1) * PP_STAGE;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int j = 0; j < TJ; ++j) wf[ks][j] = fragment(s, wcol * 64 + j * 16 + fr, ks * 4 + fk);
   };
-  auto read_x = [&](int kt, int half) {
-    const char* s = lds + (kt & 1) * PP_STAGE;
+  auto read_x = [&](int slab, int half) {
+    const char* s = lds + (slab & 1) * PP_STAGE;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -390,40 +401,60 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
     __builtin_amdgcn_sched_barrier(0);
   };
   // End of a read phase: own fragments in registers (part of the buffer may be overwritten from here on), own share of
-  // what the next read phase needs landed; after the barrier both hold for every wave.
+  // what the next read phase needs landed; after the barrier both hold for every wave.  (Behind a tile's stores, which
+  // count as well, the wait is longer than it has to be, never shorter.)
   auto read_done = [&] {
     __builtin_amdgcn_sched_barrier(0);
     wait_loads_and_barrier<PP_XI + PP_YI>();
   };
 
-  load(0, I0{}, IX{});
-  load(0, IX{}, IE{});
-  load(1, I0{}, IX{});
+  enter(ax, I0{}, IX{});
+  enter(ay, IX{}, IE{});
+  load(ax, I0{}, IX{});
+  load(ay, IX{}, IE{});
+  load(ax, I0{}, IX{});
   wait_loads_and_barrier<PP_XI + PP_YI>();                       // part X of slab 0
   if (group == 1) asm volatile("s_barrier" ::: "memory");        // half a phase behind group 0 from here on
-  for (int kt = 0; kt < KT; ++kt) {
-    read_w(kt);
-    read_x(kt, 0);
-    load(kt + 1, IX{}, IE{});                                    // part Y of the other buffer: last read in slab kt - 1
-    read_done();
-    mma(0);
-    read_x(kt, 1);
-    load(kt + 2, I0{}, IX{});                                    // part X of this buffer: both groups are past read 0
-    read_done();
-    mma(1);
-  }
-  if (group == 0) asm volatile("s_barrier" ::: "memory");
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // the surplus loads of the tail land before the workgroup ends
-
+  int slab = 0, id = blockIdx.x;
+  do {
+    const TilePos at = tile_position(p, id, p.tiles);
+    const int KT = slabs_of(at);
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      const int m = m0 + (group * 2 + h) * HALF + i * 16 + fr;
-      if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
-      else store_row<OUT, TJ>(p, acc[h][i], m, n0, wcol * 64, fk, at.split);
-      if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[h][i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int kt = 0; kt < KT; ++kt, ++slab) {
+      read_w(slab);
+      read_x(slab, 0);
+      load(ay, IX{}, IE{});                                      // part Y of the other buffer: last read one slab ago
+      read_done();
+      mma(0);
+      read_x(slab, 1);
+      load(ax, I0{}, IX{});                                      // part X of this buffer: both groups are past read 0
+      read_done();
+      mma(1);
     }
+    if constexpr (!WALK) {
+      if (group == 0) asm volatile("s_barrier" ::: "memory");
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // the surplus loads of the tail land before the workgroup ends
+    }
+    const int m0 = at.tm * PP_BM, n0 = at.tn * (GU ? PP_BN / 2 : PP_BN);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        const int m = m0 + (group * 2 + h) * HALF + i * 16 + fr;
+        if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
+        else store_row<OUT, TJ>(p, acc[h][i], m, n0, wcol * 64, fk, at.split);
+        if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
+      }
+  } while (WALK && (id += gridDim.x) < p.tiles);
+  if constexpr (WALK) {
+    if (group == 0) asm volatile("s_barrier" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
 }
 
 // ---- row kernel between contractions --------------------------------------------------------------------------------------
@@ -614,6 +645,7 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
   p.slabs = plan.slabs;
   const int64_t grid = (int64_t)p.tiles_m * p.tiles_n * plan.splits;
   if (grid > 0x7fffffffLL) return fail(PHOTON_ERR_UNSUPPORTED, "gemm: %lld workgroups are too many for one launch", (long long)grid);
+  p.tiles = (int)grid;
 #define PHOTON_GEMM_CASE(KIND, KERN, THREADS, BUFS)                                                            \
   case KIND: {                                                                                                 \
     static bool attr_set = false;                                                                              \
@@ -625,6 +657,19 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
       PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT>), 256, 4)
       PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT>), 512, 3)
       default: break;
+    }
+  }
+  // Gate/up over several rounds of short tiles: one workgroup per compute unit walks its tiles and loads the next one's first
+  // slabs under the last one's contraction, SiLU and stores.  Measured in prefills, dealt out / walked: 16 x 8192 tokens at K = 1024, four
+  // layers of two levels 1567 / 1469 us; 131072 tokens at K = 2048, eight layers of two levels 10.30 / 9.87 ms.  The
+  // other outputs lose by it (their stores and residual loads queue with the next tile's loads: 1024 columns of 32768 rows
+  // 147 / 166 us, QKV 228 / 264 us), and so do two rounds or long tiles, which have little to hide.
+  if constexpr (OUT == GEMM_OUT_SWIGLU) {
+    if (plan.kind >= T_128x256 && grid > 2 * 256 && p.K <= 2048) {
+      static bool attr_128 = false, attr_256 = false;
+      if (plan.kind == T_128x256)
+        return launch_kernel(gemm_pingpong_kernel<2, OUT, true>, &attr_128, 256, PP_THREADS, (size_t)2 * (t.bm + t.bn) * 128, p, st);
+      return launch_kernel(gemm_pingpong_kernel<4, OUT, true>, &attr_256, 256, PP_THREADS, (size_t)2 * (t.bm + t.bn) * 128, p, st);
     }
   }
   switch (plan.kind) {
