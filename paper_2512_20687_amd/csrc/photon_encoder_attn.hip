@@ -98,11 +98,14 @@ __device__ __forceinline__ int swz_k(int row, int col16) { return row * 128 + ((
 // the order of the contraction index); V keeps its own column order, so the output columns are the head's; all
 // other columns are zero.
 // TC: storage type of the cache (bf16_t or fp8_t).
+// table: row pos holds 32 cosines, 32 sines of the position's angles (as encoder_operands_begin leaves them); nullptr: they are
+// formed here, eight double-precision sines and cosines per thread, which every head repeats (4 x 268 positions of 32 heads of 52: 20 -> 17 us).
 template <bool PAD, typename TC>
 __global__ __launch_bounds__(256) void encoder_rope_split_kernel(const float* __restrict__ qkv, uint16_t* __restrict__ qh,
                                                                  uint16_t* __restrict__ kh, uint16_t* __restrict__ vt,
                                                                  TC* __restrict__ kc, TC* __restrict__ vc, int64_t M, int H,
-                                                                 int d_h_rt, int pitch, int64_t S_max, float theta, float qscale) {
+                                                                 int d_h_rt, int pitch, int64_t S_max, float theta, float qscale,
+                                                                 const float* __restrict__ table) {
   __shared__ uint16_t vtile[64][64 + 2];                // [d][position], padded
   const int tid = threadIdx.x;
   const int bh = blockIdx.y, b = bh / H, h = bh % H;
@@ -144,10 +147,22 @@ __global__ __launch_bounds__(256) void encoder_rope_split_kernel(const float* __
         if (i < hr) { q[j] = head[i]; q[8 + j] = head[i + hr]; k[j] = head[D + i]; k[8 + j] = head[D + i + hr]; }
       }
     }
+    float cs[8], sn[8];
+    if (table != nullptr) {
+      const float* t = table + pos * 64 + quarter * 8;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const float4_t a = *reinterpret_cast<const float4_t*>(t + c * 4), b = *reinterpret_cast<const float4_t*>(t + 32 + c * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { cs[c * 4 + e] = a[e]; sn[c * 4 + e] = b[e]; }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) rope_angle((int)pos, quarter * 8 + j, d_h, theta, cs[j], sn[j]);
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      float c, s;
-      rope_angle((int)pos, quarter * 8 + j, d_h, theta, c, s);
+      const float c = cs[j], s = sn[j];
       const float qa = q[j], qb = q[8 + j], ka = k[j], kb = k[8 + j];
       q[j] = (qa * c - qb * s) * qscale; q[8 + j] = (qb * c + qa * s) * qscale;
       k[j] = ka * c - kb * s; k[8 + j] = kb * c + ka * s;
@@ -421,15 +436,14 @@ __global__ __launch_bounds__(EA_THREADS) void encoder_attn_mfma_kernel(const uin
     }
 }
 
-// Once per level in front of projections that write the operands themselves (launch_qkv_rope): cosines and sines of every
-// position's angles (row pos: 32 cosines, 32 sines), and zeros in the operands' rows behind the last position, which no
-// projection writes.
-__global__ __launch_bounds__(256) void encoder_operands_begin_kernel(const QkvOperands o, float* __restrict__ table, int streams, float theta) {
+// Once per level: cosines and sines of every position's angles (row pos: 32 cosines, 32 sines), and zeros in the operands' rows
+// behind the last position, which a projection that writes the operands itself (launch_qkv_rope) leaves alone.
+__global__ __launch_bounds__(256) void encoder_operands_begin_kernel(const QkvOperands o, float* __restrict__ table, int streams, int d_h, float theta) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx < (int64_t)o.M * 32) {
     const int pos = (int)(idx >> 5), i = (int)(idx & 31);
     float c, s;
-    rope_angle(pos, i, EA_DH, theta, c, s);
+    rope_angle(pos, i, d_h, theta, c, s);
     table[(int64_t)pos * 64 + i] = c;
     table[(int64_t)pos * 64 + 32 + i] = s;
   }
@@ -539,14 +553,16 @@ size_t encoder_attn_workspace_bytes(int Bt, int64_t M, int H, int d_h, bool bf16
   return (size_t)3 * Bt * H * round_up64(M) * EA_DH * sizeof(uint16_t);   // q, k, V^T
 }
 
-int32_t encoder_operands_begin(int Bt, int64_t M, int H, float theta, float scale, void* workspace, float* table, QkvOperands* ops, hipStream_t st) {
+int32_t encoder_operands_begin(int Bt, int64_t M, int H, int d_h, float theta, float scale, bool zero_behind, void* workspace, float* table,
+                               QkvOperands* ops, hipStream_t st) {
   if ((int64_t)Bt * H > 65535) return fail(PHOTON_ERR_UNSUPPORTED, "encoder attention: Bt*H=%lld exceeds 65535", (long long)Bt * H);
   QkvOperands o;
   o.M = (int)M; o.Mp = (int)round_up64(M); o.H = H; o.qscale = scale * LOG2E; o.table = table;
   const size_t arr = (size_t)Bt * H * o.Mp * EA_DH;
   o.qh = reinterpret_cast<uint16_t*>(workspace); o.kh = o.qh + arr; o.vt = o.kh + arr;
-  const int64_t angles = M * 32, pads = (int64_t)Bt * H * EA_DH * (o.Mp - M), n = angles > pads ? angles : pads;
-  PHOTON_LAUNCH(KC_ROPE_APPEND, st, encoder_operands_begin_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, o, table, Bt * H, theta);
+  const int streams = zero_behind ? Bt * H : 0;
+  const int64_t angles = M * 32, pads = (int64_t)streams * EA_DH * (o.Mp - M), n = angles > pads ? angles : pads;
+  PHOTON_LAUNCH(KC_ROPE_APPEND, st, encoder_operands_begin_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, o, table, streams, d_h, theta);
   *ops = o;
   return check_launch("encoder_operands_begin_kernel");
 }
@@ -559,7 +575,7 @@ int32_t launch_encoder_attn_operands(const QkvOperands& o, float* out, int Bt, i
 }
 
 int32_t launch_encoder_attn(const float* qkv, float* out, int Bt, int64_t M, int H, int d_h, float theta, float scale, void* k_cache,
-                            void* v_cache, int64_t S_max, void* workspace, bool bf16, bool kv_fp8, bool out_bf16, hipStream_t st) {
+                            void* v_cache, int64_t S_max, void* workspace, bool bf16, bool kv_fp8, bool out_bf16, hipStream_t st, const float* table) {
   if (Bt <= 0 || M <= 0) return PHOTON_OK;
   if (out_bf16 && !bf16) return fail(PHOTON_ERR_UNSUPPORTED, "encoder attention: bf16 output rows come with the bf16 path only");
   if ((int64_t)Bt * H > 65535) return fail(PHOTON_ERR_UNSUPPORTED, "encoder attention: Bt*H=%lld exceeds 65535", (long long)Bt * H);
@@ -596,7 +612,7 @@ int32_t launch_encoder_attn(const float* qkv, float* out, int Bt, int64_t M, int
   uint16_t *kh = qh + arr, *vt = kh + arr;
 #define PHOTON_EA_ROPE(PAD, TC)                                                                                                        \
   PHOTON_LAUNCH(KC_ROPE_APPEND, st, (encoder_rope_split_kernel<PAD, TC>), dim3((unsigned)(Mp / 64), Bt * H), dim3(256), 0, st, qkv, qh, \
-                kh, vt, (TC*)k_cache, (TC*)v_cache, M, H, d_h, pitch, S_max, theta, scale * LOG2E)
+                kh, vt, (TC*)k_cache, (TC*)v_cache, M, H, d_h, pitch, S_max, theta, scale * LOG2E, table)
   if (d_h == EA_DH) { if (kv_fp8) PHOTON_EA_ROPE(false, fp8_t); else PHOTON_EA_ROPE(false, bf16_t); }
   else { if (kv_fp8) PHOTON_EA_ROPE(true, fp8_t); else PHOTON_EA_ROPE(true, bf16_t); }
 #undef PHOTON_EA_ROPE

@@ -861,7 +861,7 @@ using namespace photon;
 struct PrefillPlan {
   int64_t M[PHOTON_MAX_LEVELS + 1] = {0};        // M[l]: level-l units per sequence, M[0] = T
   size_t X[PHOTON_MAX_LEVELS + 1] = {0};         // X[l]: level-l encoder states [Bt*M[l], D]; X[0] = embeddings; X[L] unused
-  size_t A = 0, h = 0, attn = 0, qkv = 0, act = 0, many = 0, parts = 0, ea = 0, pair = 0;
+  size_t A = 0, h = 0, attn = 0, qkv = 0, act = 0, many = 0, parts = 0, ea = 0, table = 0, pair = 0;
   int64_t part_cap = 0;
   int many_K = 0;
   size_t total = 0;
@@ -892,6 +892,7 @@ static PrefillPlan make_prefill_plan(const photon_config& c, int Bt, int64_t T) 
       p.parts = bump(cur, (size_t)p.part_cap * f);
     }
   }
+  if (c.dt == PHOTON_BF16) p.table = bump(cur, (size_t)p.M[1] * 64 * f);   // rotary cosines and sines of a level's positions
   p.ea = bump(cur, encoder_attn_workspace_bytes(Bt, p.M[1], c.H, c.d_h, c.dt == PHOTON_BF16));
   p.total = cur;
   return p;
@@ -928,11 +929,12 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
       PHOTON_TRY(linear(e, RowSource{e.f(pp.X[l - 1]), (int64_t)C * D}, ew.chunker_w[l - 1], nullptr, ew.chunker_b[l - 1], A, D, rows, D, C * D));
     RowSource in{A, D};
     const size_t layer_cache = (size_t)Bt * c.H * x.s->S_max * kv_row_elems(c.d_h) * esz;
-    // Where it pays, the projection writes the attention's operands itself; the angles' cosines and sines lie in the
-    // projection's own buffer meanwhile, behind the rows that the block's second half keeps there.
+    // Where it pays, the projection writes the attention's operands itself; a separate pass over it takes the angles'
+    // cosines and sines from the same table.
     const bool fused = many_rows(e, rows) && qkv_rope_pays(rows, D, c.d_h);
     QkvOperands ops;
-    if (fused) PHOTON_TRY(encoder_operands_begin(Bt, M, c.H, c.rope_theta, scale, e.base + pp.ea, qkv + (int64_t)rows * D, &ops, x.st));
+    float* table = e.f(pp.table);
+    if (x.bf16) PHOTON_TRY(encoder_operands_begin(Bt, M, c.H, c.d_h, c.rope_theta, scale, fused, e.base + pp.ea, table, &ops, x.st));
     for (int i = 0; i < c.n_layers; ++i) {
       const photon_layer_weights& lw = mod.layers[i];
       char *kc = nullptr, *vc = nullptr;
@@ -955,7 +957,7 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
       } else {
         RowSource qkv_rows;
         PHOTON_TRY(block_qkv(e, lw, &in, rows, false, &qkv_rows));
-        PHOTON_TRY(launch_encoder_attn(qkv, attn, Bt, M, c.H, c.d_h, c.rope_theta, scale, kc, vc, cap, e.base + pp.ea, x.bf16, c.kv_dt == PHOTON_FP8_E4M3, x.bf16, x.st));
+        PHOTON_TRY(launch_encoder_attn(qkv, attn, Bt, M, c.H, c.d_h, c.rope_theta, scale, kc, vc, cap, e.base + pp.ea, x.bf16, c.kv_dt == PHOTON_FP8_E4M3, x.bf16, x.st, table));
       }
       PHOTON_TRY(block_tail(e, lw, in, rows, x.bf16, &in));
     }
