@@ -18,6 +18,11 @@ inline int kv_row_elems(int d_h) { return d_h < 1 ? 0 : d_h <= 32 ? 32 : d_h <= 
 int32_t launch_coarse_attn(KvType kv, bool q_f32, int d_h, const void* q, const void* kc, const void* vc,
                            const int32_t* seq_len, void* out, int Bt, int H, int64_t S_max, float scale,
                            int n_splits, void* ws, bool out_bf16, hipStream_t st);
+// The same for n_new new units per sequence in one launch: q and out have n_new rows per sequence (fp32 queries), row j attends
+// to the min(seq_len + j + 1, S_max) first entries (seq_len does not count the new units yet, their entries are in the
+// cache).  ws: photon_coarse_decode_attn_workspace_bytes(Bt * n_new, ..) bytes when n_splits > 1.
+int32_t launch_coarse_attn_units(KvType kv, int d_h, const float* q, const void* kc, const void* vc, const int32_t* seq_len, void* out, int Bt,
+                                 int n_new, int H, int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st);
 int32_t coarse_auto_splits(int Bt, int H, int64_t S_max);
 
 int32_t launch_local_attn(bool f32, int d_h, const void* q, const void* k, const void* v, void* out,

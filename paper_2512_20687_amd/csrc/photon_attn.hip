@@ -246,6 +246,192 @@ int32_t launch_coarse_attn(KvType kv, bool q_f32, int d_h, const void* q, const 
   return launch_coarse_dh<bf16_t, bf16_t>(d_h, q, kc, vc, seq_len, out, Bt, H, S_max, scale, n_splits, ws, out_bf16, st);
 }
 
+// Several queries of one stream (the new units of one sequence, n_new per sequence) in one launch: NQ of them share every K
+// and V row that a workgroup reads, so the cache is streamed once per NQ queries instead of once per query; the keys of the
+// later new units are masked for the earlier ones.  Otherwise as coarse_attn_kernel; half its loads in flight per buffer, as
+// the states of NQ queries take the registers (16 sequences x 16 heads x 2048 keys, 4 queries: 50 us against 4 x 22 us).
+constexpr int UNITS_NQ = 4;
+template <typename TKV, int DH, int COARSE_WAVES, int U, int NQ>
+__global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_units_kernel(
+    const float* __restrict__ q, const TKV* __restrict__ kc, const TKV* __restrict__ vc, const int32_t* __restrict__ seq_len,
+    float* __restrict__ out, float* __restrict__ ws, int H, int d_h, int64_t S_max, float scale_log2e, int n_splits, int n_new, int out_bf16) {
+  using M = RowMap<TKV, DH>;
+  constexpr int VEC = M::VEC, LPR = M::LPR, RPW = M::RPW;
+  constexpr int TILE = RPW * U;
+  const int split = blockIdx.x, bh = blockIdx.y, b = bh / H, h = bh - b * H;
+  const int j0 = blockIdx.z * NQ, live = min(NQ, n_new - j0);      // queries j0 .. j0 + live - 1 of this sequence
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int g = lane / LPR, c = lane % LPR;
+
+  int64_t old = seq_len[b];
+  old = old < 0 ? 0 : (old > S_max ? S_max : old);
+  auto length = [&](int i) { const int64_t n = old + j0 + i + 1; return n < S_max ? n : S_max; };
+  const int64_t n = length(live - 1);
+  int64_t per = (n + n_splits - 1) / n_splits;
+  per = (per + TILE - 1) / TILE * TILE;
+  const int64_t begin = (int64_t)split * per;
+  const int64_t end = begin + per < n ? begin + per : n;
+
+  float qf[NQ][VEC];
+  int64_t last[NQ];                                                // first key that query i does not see
+  SoftState<VEC> st[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    const float* qr = q + (((int64_t)b * n_new + j0 + (i < live ? i : live - 1)) * H + h) * d_h;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) qf[i][e] = c * VEC + e < d_h ? qr[c * VEC + e] * scale_log2e : 0.f;
+    last[i] = length(i);
+    if (last[i] > end) last[i] = end;
+    st[i].init();
+  }
+  const TKV* kb = kc + (int64_t)bh * S_max * DH + c * VEC;
+  const TKV* vb = vc + (int64_t)bh * S_max * DH + c * VEC;
+
+  auto load = [&](int64_t t0, uint4_t (&kr)[U], uint4_t (&vr)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int64_t key = t0 + u * RPW + g;
+      key = key < end ? key : end - 1;
+      kr[u] = load16_stream(kb + key * DH);
+      vr[u] = load16_stream(vb + key * DH);
+    }
+  };
+  auto consume = [&](int64_t t0, const uint4_t (&kr)[U], const uint4_t (&vr)[U]) {
+    float s[NQ][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float kf[VEC];
+      unpack16<TKV>(kr[u], kf);
+#pragma unroll
+      for (int i = 0; i < NQ; ++i) {
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc = fmaf(qf[i][e], kf[e], acc);
+        s[i][u] = group_sum<LPR>(acc);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      float mx = st[i].m;
+#pragma unroll
+      for (int u = 0; u < U; ++u) mx = fmaxf(mx, t0 + u * RPW + g < last[i] ? s[i][u] : NEG_BIG);
+      const float alpha = fast_exp2(st[i].m - mx);
+      st[i].m = mx;
+      st[i].l *= alpha;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) st[i].o[e] *= alpha;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        s[i][u] = t0 + u * RPW + g < last[i] ? fast_exp2(s[i][u] - mx) : 0.f;
+        st[i].l += s[i][u];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float vf[VEC];
+      unpack16<TKV>(vr[u], vf);
+#pragma unroll
+      for (int i = 0; i < NQ; ++i)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) st[i].o[e] = fmaf(s[i][u], vf[e], st[i].o[e]);
+    }
+  };
+
+  const int64_t stride = (int64_t)COARSE_WAVES * TILE;
+  int64_t t0 = begin + (int64_t)wave * TILE;
+  if (t0 < end) {
+    uint4_t ka[U], va[U], kb2[U], vb2[U];
+    load(t0, ka, va);
+    while (true) {
+      const int64_t t1 = t0 + stride;
+      const bool more1 = t1 < end;
+      if (more1) load(t1, kb2, vb2);
+      consume(t0, ka, va);
+      if (!more1) break;
+      const int64_t t2 = t1 + stride;
+      const bool more2 = t2 < end;
+      if (more2) load(t2, ka, va);
+      consume(t1, kb2, vb2);
+      if (!more2) break;
+      t0 = t2;
+    }
+  }
+
+  __shared__ float sm[NQ][COARSE_WAVES], sl[NQ][COARSE_WAVES], so[NQ][COARSE_WAVES][DH];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+#pragma unroll
+    for (int mask = LPR; mask < 64; mask <<= 1) {
+      const float m2 = __shfl_xor(st[i].m, mask);
+      const float mm = fmaxf(st[i].m, m2);
+      const float a1 = fast_exp2(st[i].m - mm), a2 = fast_exp2(m2 - mm);
+      st[i].l = st[i].l * a1 + __shfl_xor(st[i].l, mask) * a2;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) st[i].o[e] = st[i].o[e] * a1 + __shfl_xor(st[i].o[e], mask) * a2;
+      st[i].m = mm;
+    }
+    if (g == 0) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) so[i][wave][c * VEC + e] = st[i].o[e];
+      if (c == 0) { sm[i][wave] = st[i].m; sl[i][wave] = st[i].l; }
+    }
+  }
+  __syncthreads();
+  if (tid >= DH) return;
+  for (int i = 0; i < live; ++i) {
+    float mm = sm[i][0];
+#pragma unroll
+    for (int w = 1; w < COARSE_WAVES; ++w) mm = fmaxf(mm, sm[i][w]);
+    float l = 0.f, o = 0.f;
+#pragma unroll
+    for (int w = 0; w < COARSE_WAVES; ++w) {
+      const float a = fast_exp2(sm[i][w] - mm);
+      l = fmaf(sl[i][w], a, l);
+      o = fmaf(so[i][w][tid], a, o);
+    }
+    const int64_t row = ((int64_t)b * n_new + j0 + i) * H + h;
+    if (n_splits == 1) {
+      if (tid < d_h) store_out(out, row * d_h + tid, l > 0.f ? o / l : 0.f, out_bf16);
+    } else {
+      float* p = ws + (row * n_splits + split) * (DH + 2);
+      if (tid == 0) { p[0] = mm; p[1] = l; }
+      p[2 + tid] = o;
+    }
+  }
+}
+
+template <typename TKV, int DH>
+static int32_t launch_units_t(const float* q, const void* kc, const void* vc, const int32_t* seq_len, void* out, int Bt, int n_new, int H, int d_h,
+                              int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st) {
+  constexpr int WAVES = COARSE_WAVES_PER_WG, U = COARSE_UNROLL / 2;
+  const dim3 grid(n_splits, Bt * H, (n_new + UNITS_NQ - 1) / UNITS_NQ);
+  PHOTON_LAUNCH(KC_COARSE_ATTN, st, (coarse_attn_units_kernel<TKV, DH, WAVES, U, UNITS_NQ>), grid, dim3(WAVES * 64), 0, st, q, (const TKV*)kc,
+                (const TKV*)vc, seq_len, (float*)out, (float*)ws, H, d_h, S_max, scale * LOG2E, n_splits, n_new, out_bf16 ? 1 : 0);
+  int32_t rc = check_launch("coarse_attn_units_kernel");
+  if (rc != PHOTON_OK || n_splits == 1) return rc;
+  PHOTON_LAUNCH(KC_COARSE_MERGE, st, (coarse_merge_kernel<float, DH>), dim3((unsigned)(Bt * n_new * H)), dim3(DH), 0, st, (const float*)ws, (float*)out,
+                n_splits, d_h, out_bf16 ? 1 : 0);
+  return check_launch("coarse_merge_kernel");
+}
+
+template <typename TKV>
+static int32_t launch_units_dh(int d_h, const float* q, const void* kc, const void* vc, const int32_t* seq_len, void* out, int Bt, int n_new, int H,
+                               int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st) {
+  switch (kv_row_elems(d_h)) {
+    case 32: return launch_units_t<TKV, 32>(q, kc, vc, seq_len, out, Bt, n_new, H, d_h, S_max, scale, n_splits, ws, out_bf16, st);
+    case 64: return launch_units_t<TKV, 64>(q, kc, vc, seq_len, out, Bt, n_new, H, d_h, S_max, scale, n_splits, ws, out_bf16, st);
+    case 128: return launch_units_t<TKV, 128>(q, kc, vc, seq_len, out, Bt, n_new, H, d_h, S_max, scale, n_splits, ws, out_bf16, st);
+  }
+  return fail(PHOTON_ERR_UNSUPPORTED, "coarse attention: d_h=%d not in [1, 128]", d_h);
+}
+
+int32_t launch_coarse_attn_units(KvType kv, int d_h, const float* q, const void* kc, const void* vc, const int32_t* seq_len, void* out, int Bt,
+                                 int n_new, int H, int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st) {
+  if (kv == KV_F32) return launch_units_dh<float>(d_h, q, kc, vc, seq_len, out, Bt, n_new, H, S_max, scale, n_splits, ws, out_bf16, st);
+  if (kv == KV_FP8) return launch_units_dh<fp8_t>(d_h, q, kc, vc, seq_len, out, Bt, n_new, H, S_max, scale, n_splits, ws, out_bf16, st);
+  return launch_units_dh<bf16_t>(d_h, q, kc, vc, seq_len, out, Bt, n_new, H, S_max, scale, n_splits, ws, out_bf16, st);
+}
+
 int32_t coarse_auto_splits(int Bt, int H, int64_t S_max) {
   // Short streams (the benchmark shape: 128 streams x 8200 keys): about 768 workgroups (3 per CU), measured 80 %
   // of the HBM peak for any cache pitch (one workgroup per CU is as fast only when the pitch S_max*d_h is a

@@ -93,22 +93,25 @@ __global__ __launch_bounds__(256) void broadcast_rows_kernel(const float* __rest
   if (idx < (int64_t)rows * D) dst[idx] = src[idx % D];
 }
 
-// Top-level STEP: position of sequence b is seq_len[b]-1 (the count already includes the new entry);
+// New unit j of sequence b (row b * n_new + j) sits at position seq_len[b] + first + j (first = -1: the count already includes
+// the one new unit).  Past the last slot, the last new unit is written there, the others are not.
 // k, v go to cache[b, h, pos, :] of this layer, whose rows hold `pitch` >= d_h elements (the surplus is zeroed).
 // qkv: n_parts partial products, part_stride apart, that add up to the projection.
 template <typename TKV>
 __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __restrict__ qkv, int n_parts, int64_t part_stride, float* __restrict__ qrot,
                                                                  TKV* __restrict__ kc, TKV* __restrict__ vc,
-                                                                 const int32_t* __restrict__ seq_len, int Bt, int H,
+                                                                 const int32_t* __restrict__ seq_len, int rows, int n_new, int first, int H,
                                                                  int d_h, int pitch, int64_t S_max, float theta) {
   const int half = d_h >> 1, D = H * d_h;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)Bt * H * half) return;
+  if (idx >= (int64_t)rows * H * half) return;
   const int i = (int)(idx % half);
   const int h = (int)((idx / half) % H);
-  const int b = (int)(idx / ((int64_t)half * H));
-  const int pos = seq_len[b] - 1;
-  const float* src = qkv + (int64_t)b * 3 * D + h * d_h;
+  const int row = (int)(idx / ((int64_t)half * H)), b = row / n_new, j = row - b * n_new;
+  int pos = seq_len[b] + first + j;
+  bool kept = true;
+  if (n_new > 1 && pos >= S_max - 1) { kept = j == n_new - 1; pos = (int)(S_max - 1); }
+  const float* src = qkv + (int64_t)row * 3 * D + h * d_h;
   float qa = src[i], qb = src[i + half], ka = src[D + i], kb = src[D + i + half], va = src[2 * D + i], vb = src[2 * D + i + half];
   for (int s0 = 1; s0 < n_parts; s0 += 3) {                    // three in flight
     float w[3][6];
@@ -126,10 +129,10 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
   }
   float c, s;
   rope_angle(pos, i, d_h, theta, c, s);                        // under the loads
-  float* qd = qrot + (int64_t)b * D + h * d_h;
+  float* qd = qrot + (int64_t)row * D + h * d_h;
   qd[i] = qa * c - qb * s;
   qd[i + half] = qb * c + qa * s;
-  if (pos < 0 || pos >= S_max) return;                        // full cache: nothing is written out of bounds
+  if (!kept || pos < 0 || pos >= S_max) return;               // full cache: nothing is written out of bounds
   const int64_t slot = (((int64_t)b * H + h) * S_max + pos) * pitch;
   kc[slot + i] = from_f32<TKV>(ka * c - kb * s);
   kc[slot + i + half] = from_f32<TKV>(kb * c + ka * s);
@@ -234,12 +237,12 @@ __global__ __launch_bounds__(256) void shift_condition_kernel(const float* __res
 // A sequence whose cache is full (seq_len == S_cap on entry) keeps its count: its new entry then overwrites the last
 // one, in bounds, and the caller's status word gets bit 0 (its results of this step are not valid).
 __global__ __launch_bounds__(256) void step_begin_kernel(int32_t* __restrict__ seq_len, int Bt, int64_t S_cap, int32_t* __restrict__ status,
-                                                         unsigned* __restrict__ bar, int bar_words) {
+                                                         unsigned* __restrict__ bar, int bar_words, int add) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
   if (seq_len != nullptr && idx < Bt) {
     const int32_t n = seq_len[idx];
-    if (n < S_cap) seq_len[idx] = n + 1;
-    else if (status != nullptr) atomicOr(status, PHOTON_STATUS_CACHE_FULL);
+    if (n < S_cap) seq_len[idx] = n + add < S_cap ? n + add : (int32_t)S_cap;
+    if (n + (int64_t)add > S_cap && status != nullptr) atomicOr(status, PHOTON_STATUS_CACHE_FULL);
   }
   for (int i = idx; i < bar_words; i += gridDim.x * 256) bar[i] = 0u;
 }
@@ -577,11 +580,19 @@ static int32_t local_module_pass(const Ctx& x, int level, int64_t n_chunks, int 
 
 // STEP (Eq. 12-13) of one encoder stream on the Bt rows `in` (one new unit per sequence): appends K/V to the
 // stream's cache at position seq_len - 1 (the count already includes the new unit) and writes the new state
-// of sequence b to out[(b * out_mul + out_off) * D].
+// of sequence b to out[b * D].  n_new > 0: n_new consecutive new units per sequence (rows b * n_new + j) in one pass, each
+// attending to the units before it as if they had been appended one by one; the count does not include them yet, and `ws`
+// (ws_bytes) takes the split partials of their attention.
 static int32_t stream_step(const Ctx& x, const photon_module_weights& mod, void* k_cache, void* v_cache, const int32_t* seq_len,
-                           int64_t S_cap, RowSource in, float* out, int out_mul, int out_off) {
+                           int64_t S_cap, RowSource in, float* out, int n_new = 0, void* ws = nullptr, size_t ws_bytes = 0) {
   const photon_config& c = *x.c;
-  const int rows = x.Bt;
+  const int units = n_new > 0 ? n_new : 1, first = n_new > 0 ? 0 : -1;
+  const int rows = x.Bt * units;
+  int n_splits = x.p.n_splits;
+  if (n_new > 0) {                                           // one workgroup reads a stream for several units
+    n_splits = coarse_auto_splits(x.Bt, c.H, S_cap);
+    while (n_splits > 1 && photon_coarse_decode_attn_workspace_bytes(rows, c.H, c.d_h, n_splits) > ws_bytes) --n_splits;
+  }
   const bool many = many_rows(x, rows);
   float *qrot = x.f(x.o_qrot), *attn = x.f(x.o_attn);
   const size_t esz = dtype_size(c.kv_dt);
@@ -599,28 +610,31 @@ static int32_t stream_step(const Ctx& x, const photon_module_weights& mod, void*
     const int64_t n_el = (int64_t)rows * c.H * (c.d_h / 2);
     if (c.kv_dt == PHOTON_FP8_E4M3)
       PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<fp8_t>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv0, qkv_parts, qkv.part_stride, qrot,
-                    (fp8_t*)kc, (fp8_t*)vc, seq_len, x.Bt, c.H, c.d_h, pitch, S_cap, c.rope_theta);
+                    (fp8_t*)kc, (fp8_t*)vc, seq_len, rows, units, first, c.H, c.d_h, pitch, S_cap, c.rope_theta);
     else if (x.bf16)
       PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<bf16_t>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv0, qkv_parts, qkv.part_stride, qrot,
-                    (bf16_t*)kc, (bf16_t*)vc, seq_len, x.Bt, c.H, c.d_h, pitch, S_cap, c.rope_theta);
+                    (bf16_t*)kc, (bf16_t*)vc, seq_len, rows, units, first, c.H, c.d_h, pitch, S_cap, c.rope_theta);
     else
       PHOTON_LAUNCH(KC_ROPE_APPEND, x.st, rope_append_coarse_kernel<float>, dim3(blocks_for(n_el)), dim3(256), 0, x.st, qkv0, qkv_parts, qkv.part_stride, qrot,
-                    (float*)kc, (float*)vc, seq_len, x.Bt, c.H, c.d_h, pitch, S_cap, c.rope_theta);
+                    (float*)kc, (float*)vc, seq_len, rows, units, first, c.H, c.d_h, pitch, S_cap, c.rope_theta);
     PHOTON_TRY(check_launch("rope_append_coarse_kernel"));
-    PHOTON_TRY(launch_coarse_attn(c.kv_dt == PHOTON_FP8_E4M3 ? KV_FP8 : x.bf16 ? KV_BF16 : KV_F32, true, c.d_h, qrot, kc, vc, seq_len, attn, x.Bt, c.H, S_cap, scale,
-                                  x.p.n_splits, x.base + x.p.coarse_ws, many, x.st));
+    const KvType kv = c.kv_dt == PHOTON_FP8_E4M3 ? KV_FP8 : x.bf16 ? KV_BF16 : KV_F32;
+    if (n_new > 0)
+      PHOTON_TRY(launch_coarse_attn_units(kv, c.d_h, qrot, kc, vc, seq_len, attn, x.Bt, n_new, c.H, S_cap, scale, n_splits, ws, many, x.st));
+    else
+      PHOTON_TRY(launch_coarse_attn(kv, true, c.d_h, qrot, kc, vc, seq_len, attn, x.Bt, c.H, S_cap, scale, n_splits, x.base + x.p.coarse_ws, many, x.st));
     PHOTON_TRY(block_tail(x, lw, in, rows, many, &in));  // few rows: fp32 attention rows, many: the O projection's bf16 operand
   }
-  return norm(x, in, mod.g_final, out, out_mul, out_off, rows);
+  return norm(x, in, mod.g_final, out, 1, 0, rows);
 }
 
 // STEP of the top-level encoder; leaves X^(L)_{g+1} in state.x_top.
 static int32_t top_step(const Ctx& x, RowSource in) {
-  return stream_step(x, x.w->top, x.s->k_cache, x.s->v_cache, x.s->seq_len, x.s->S_max, in, x.s->x_top, 1, 0);
+  return stream_step(x, x.w->top, x.s->k_cache, x.s->v_cache, x.s->seq_len, x.s->S_max, in, x.s->x_top);
 }
 
 // Step 2 of hierarchical generation (Appendix A, Definition 1): re-encode the step's tokens bottom-up.  Every
-// level l < L advances its stream by its new units, one STEP per unit (they are causally ordered).  Returns the
+// level l < L advances its stream by its new units.  Returns the
 // encoder-side level-(L-1) block [Bt, C_L, D] (rows of sequence b contiguous).
 static int32_t embed_rows(hipStream_t st, bool bf16, const int32_t* tokens, const void* table, float* rows, int64_t n, int width, int vocab) {
   if (bf16)
@@ -667,14 +681,16 @@ static int32_t hier_reencode(const Ctx& x, const int32_t* tokens, const float** 
       PHOTON_TRY(embed_and_chunk(x, *x.ew, tokens, n_tok, rows, X, A));
     else if (l > 1)
       PHOTON_TRY(linear(x, RowSource{X, (int64_t)C * D}, x.ew->chunker_w[l - 1], nullptr, x.ew->chunker_b[l - 1], A, D, rows, D, C * D));
+    // The level's new units are causally ordered, but all their inputs are there: one pass takes them together, layer by
+    // layer, instead of one STEP each (16 sequences, 4 units, 4 layers: 816 -> 430 us).  Rows of a single STEP that stay in fp32 stay so.
     float* Xl = x.f(x.p.hx[l]);
-    for (int j = 0; j < (int)per_seq; ++j) {
-      PHOTON_LAUNCH(KC_MISC, x.st, step_begin_kernel, dim3(blocks_for(Bt)), dim3(256), 0, x.st, x.hs->seq_len[l - 1], Bt, x.hs->S_cap[l - 1],
-                    x.s->status, (unsigned*)nullptr, 0);
-      PHOTON_TRY(check_launch("step_begin_kernel"));
-      PHOTON_TRY(stream_step(x, x.ew->enc[l - 1], x.hs->k_cache[l - 1], x.hs->v_cache[l - 1], x.hs->seq_len[l - 1], x.hs->S_cap[l - 1],
-                             RowSource{A + (int64_t)j * D, per_seq * (int64_t)D}, Xl, (int)per_seq, j));
-    }
+    Ctx u = x;
+    u.few = Bt < MANY_ROWS;
+    PHOTON_TRY(stream_step(u, x.ew->enc[l - 1], x.hs->k_cache[l - 1], x.hs->v_cache[l - 1], x.hs->seq_len[l - 1], x.hs->S_cap[l - 1],
+                           RowSource{A, D}, Xl, (int)per_seq, x.f(x.p.logits), (size_t)x.p.chunks[1] * c.vocab * sizeof(float)));
+    PHOTON_LAUNCH(KC_MISC, x.st, step_begin_kernel, dim3(blocks_for(Bt)), dim3(256), 0, x.st, x.hs->seq_len[l - 1], Bt, x.hs->S_cap[l - 1],
+                  x.s->status, (unsigned*)nullptr, 0, (int)per_seq);
+    PHOTON_TRY(check_launch("step_begin_kernel"));
     X = Xl;
   }
   *bottleneck = X;
@@ -785,7 +801,7 @@ static int32_t decode_step_impl(const Ctx& x, photon_state* st, const int32_t* f
   const int L = c.L, Bt = x.Bt;
 
   PHOTON_LAUNCH(KC_MISC, x.st, step_begin_kernel, dim3(blocks_for(Bt)), dim3(256), 0, x.st, x.s->seq_len, Bt, x.s->S_max, x.s->status,
-                x.bar_words(), x.bar_word_count());
+                x.bar_words(), x.bar_word_count(), 1);
   PHOTON_TRY(check_launch("step_begin_kernel"));
 
   float* fresh[PHOTON_MAX_LEVELS];
@@ -997,7 +1013,7 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
   // 1103 -> 310 us).
   if (L >= 2) {
     PHOTON_LAUNCH(KC_MISC, x.st, step_begin_kernel, dim3(1), dim3(256), 0, x.st, (int32_t*)nullptr, 0, (int64_t)0, (int32_t*)nullptr,
-                  x.bar_words(), x.bar_word_count());
+                  x.bar_words(), x.bar_word_count(), 0);
     PHOTON_TRY(check_launch("step_begin_kernel"));
   }
   const float* cond = pair;                                // level-l latent before the last one, one row per sequence

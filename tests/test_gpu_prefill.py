@@ -206,6 +206,11 @@ def check_hier(cfg, hier, ost, tol_kv):
     ("bf16", dict(L=3, C=(2, 2, 4), R=(1, 1, 1), n_layers=1), 3, 16 * 5),
     ("f32", dict(D=208, H=4, d_h=52, concat_level1=True), 2, 16 * 3),
     ("bf16", dict(D=832, H=16, d_h=52, d_ff=1024, n_layers=1, concat_level1=True), 2, 16 * 6),
+    # new units of a step in one pass: 6 and 3 per sequence (a last group of 2 and of 3 queries), one prompt long enough for
+    # several workgroups per stream (their partials merged), rows above and below the switch to bf16 rows (17 sequences)
+    ("f32", dict(L=3, C=(2, 2, 3), R=(1, 1, 1), n_layers=1), 3, 12 * 300),
+    ("bf16", dict(L=3, C=(4, 2, 3), R=(1, 1, 1), n_layers=1), 2, 24 * 100),
+    ("bf16", dict(n_layers=1), 17, 16 * 2),
 ])
 def test_hierarchical_generation_two_steps(dtype, kw, Bt, T):
     """Prefill with every level's stream kept, then two steps of hierarchical generation (Definition 1)
@@ -275,6 +280,37 @@ def test_bf16_prefill_operands_from_the_projection(kw, Bt, T):
     torch.cuda.synchronize()
     print(check_state(cfg, state, ost, Bt, TOL["bf16"], 2.0 ** -7))
     check_hier(cfg, hier, ost, 2.0 ** -7)
+
+
+def test_hierarchical_step_with_a_stream_that_runs_full():
+    """The level-1 stream of one sequence has room for two of a step's four new units, the other's for all of them: the first is
+    flagged and clamped to its capacity, what lies in front of its last slot stays, and the second is as if it were alone."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(L=2, C=(4, 4), R=(1, 1), D=256, H=4, d_h=64, n_layers=1, d_ff=640, vocab=512, dtype="bf16")
+    w = si.make_weights(cfg, 3)
+    T, S_max = 16 * 4, 8                                               # 16 level-1 units; capacity 32
+    toks = si.make_tokens(cfg.vocab, 2, T, 2)
+    forced = dev(np.asarray(si.make_tokens(cfg.vocab, 2, cfg.meta_context, 4), np.int32))
+    model = ph.PhotonModel(cfg, w)
+    results = []
+    for full in (False, True):
+        state, hier = ph.PhotonState(model, 2, S_max), ph.PhotonHierState(model, 2, S_max)
+        ph.photon_prefill(model, state, dev(np.asarray(toks, np.int32)), hier=hier)
+        cap = hier.k[0].shape[3]
+        if full:
+            hier.seq_len[0][0] = cap - 2
+        out = torch.zeros((2, cfg.meta_context), dtype=torch.int32, device="cuda")
+        before = hier.k[0].clone()
+        ph.photon_hiergen_step(model, state, hier, out, forced_tokens=forced)
+        torch.cuda.synchronize()
+        results.append((state.x_top[1].clone(), hier.k[0][:, 1].clone(), int(state.status.item())))
+        if full:
+            assert hier.seq_len[0].tolist() == [cap, 20] and int(state.status.item()) & 1
+            assert torch.equal(hier.k[0][:, 0, :, :cap - 2], before[:, 0, :, :cap - 2])
+            assert float((hier.k[0][:, 0, :, cap - 1].float() - before[:, 0, :, cap - 1].float()).abs().max()) > 0
+    assert results[0][2] == 0
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
 def test_bf16_prefill_with_8bit_cache_then_step():
