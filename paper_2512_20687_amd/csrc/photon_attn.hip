@@ -249,7 +249,7 @@ int32_t launch_coarse_attn(KvType kv, bool q_f32, int d_h, const void* q, const 
 // Several queries of one stream (the new units of one sequence, n_new per sequence) in one launch: NQ of them share every K
 // and V row that a workgroup reads, so the cache is streamed once per NQ queries instead of once per query; the keys of the
 // later new units are masked for the earlier ones.  Otherwise as coarse_attn_kernel; half its loads in flight per buffer, as
-// the states of NQ queries take the registers (16 sequences x 16 heads x 2048 keys, 4 queries: 50 us against 4 x 22 us).
+// the states of NQ queries take the registers (16 sequences x 16 heads x 2048 keys, 4 queries: 33 us against 4 x 22 us).
 constexpr int UNITS_NQ = 4;
 template <typename TKV, int DH, int COARSE_WAVES, int U, int NQ>
 __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_units_kernel(
@@ -263,17 +263,20 @@ __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_units_kernel(
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int g = lane / LPR, c = lane % LPR;
 
-  int64_t old = seq_len[b];
-  old = old < 0 ? 0 : (old > S_max ? S_max : old);
-  auto length = [&](int i) { const int64_t n = old + j0 + i + 1; return n < S_max ? n : S_max; };
-  const int64_t n = length(live - 1);
-  int64_t per = (n + n_splits - 1) / n_splits;
+  // counts are 32-bit, so positions are too
+  const int cap = S_max < 0x7fff0000 ? (int)S_max : 0x7fff0000;
+  int old = seq_len[b];
+  old = old < 0 ? 0 : (old > cap ? cap : old);
+  auto length = [&](int i) { const int n = old + j0 + i + 1; return n < cap ? n : cap; };
+  const int n = length(live - 1);
+  int per = (n + n_splits - 1) / n_splits;
   per = (per + TILE - 1) / TILE * TILE;
-  const int64_t begin = (int64_t)split * per;
-  const int64_t end = begin + per < n ? begin + per : n;
+  const int64_t begin64 = (int64_t)split * per;
+  const int begin = begin64 < n ? (int)begin64 : n;
+  const int end = n - begin > per ? begin + per : n;
 
   float qf[NQ][VEC];
-  int64_t last[NQ];                                                // first key that query i does not see
+  int last[NQ];                                                // first key that query i does not see
   SoftState<VEC> st[NQ];
 #pragma unroll
   for (int i = 0; i < NQ; ++i) {
@@ -287,16 +290,16 @@ __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_units_kernel(
   const TKV* kb = kc + (int64_t)bh * S_max * DH + c * VEC;
   const TKV* vb = vc + (int64_t)bh * S_max * DH + c * VEC;
 
-  auto load = [&](int64_t t0, uint4_t (&kr)[U], uint4_t (&vr)[U]) {
+  auto load = [&](int t0, uint4_t (&kr)[U], uint4_t (&vr)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int64_t key = t0 + u * RPW + g;
+      int key = t0 + u * RPW + g;
       key = key < end ? key : end - 1;
-      kr[u] = load16_stream(kb + key * DH);
-      vr[u] = load16_stream(vb + key * DH);
+      kr[u] = load16_stream(kb + (int64_t)key * DH);
+      vr[u] = load16_stream(vb + (int64_t)key * DH);
     }
   };
-  auto consume = [&](int64_t t0, const uint4_t (&kr)[U], const uint4_t (&vr)[U]) {
+  auto consume = [&](int t0, const uint4_t (&kr)[U], const uint4_t (&vr)[U]) {
     float s[NQ][U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -337,18 +340,18 @@ __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_units_kernel(
     }
   };
 
-  const int64_t stride = (int64_t)COARSE_WAVES * TILE;
-  int64_t t0 = begin + (int64_t)wave * TILE;
+  constexpr int stride = COARSE_WAVES * TILE;
+  int t0 = begin + wave * TILE;
   if (t0 < end) {
     uint4_t ka[U], va[U], kb2[U], vb2[U];
     load(t0, ka, va);
     while (true) {
-      const int64_t t1 = t0 + stride;
+      const int t1 = t0 + stride;
       const bool more1 = t1 < end;
       if (more1) load(t1, kb2, vb2);
       consume(t0, ka, va);
       if (!more1) break;
-      const int64_t t2 = t1 + stride;
+      const int t2 = t1 + stride;
       const bool more2 = t2 < end;
       if (more2) load(t2, ka, va);
       consume(t1, kb2, vb2);
@@ -403,7 +406,8 @@ __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_units_kernel(
 template <typename TKV, int DH>
 static int32_t launch_units_t(const float* q, const void* kc, const void* vc, const int32_t* seq_len, void* out, int Bt, int n_new, int H, int d_h,
                               int64_t S_max, float scale, int n_splits, void* ws, bool out_bf16, hipStream_t st) {
-  constexpr int WAVES = COARSE_WAVES_PER_WG, U = COARSE_UNROLL / 2;
+  // workgroups of 4 waves: the states of 4 queries leave a SIMD room for 3 waves, which workgroups of 8 do not fill (50 -> 33 us)
+  constexpr int WAVES = 4, U = COARSE_UNROLL / 2;
   const dim3 grid(n_splits, Bt * H, (n_new + UNITS_NQ - 1) / UNITS_NQ);
   PHOTON_LAUNCH(KC_COARSE_ATTN, st, (coarse_attn_units_kernel<TKV, DH, WAVES, U, UNITS_NQ>), grid, dim3(WAVES * 64), 0, st, q, (const TKV*)kc,
                 (const TKV*)vc, seq_len, (float*)out, (float*)ws, H, d_h, S_max, scale * LOG2E, n_splits, n_new, out_bf16 ? 1 : 0);
