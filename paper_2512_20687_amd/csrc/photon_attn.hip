@@ -544,7 +544,9 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_attn_kernel(
 // DH: 4 * lanes of a group.  PAD: the head size d_h is smaller than DH (a multiple of 4): surplus lanes carry
 // zeros, and the rotary partner of an element (d_h/2 away, in general not a whole number of lanes) is read from
 // memory instead of from a neighbour lane.
-template <int DH, int NK, bool PAD>
+// PARTS: the projection comes as several partial products.  Code of its own: with few rows this launch is latency only, and
+// fetching its instructions is part of that (two steps of 4 sequences at 128k tokens 6474 us with one code for both, 6448).
+template <int DH, int NK, bool PAD, bool PARTS>
 __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
     const float* __restrict__ qkv, int n_parts, int64_t part_stride, float* __restrict__ lk, float* __restrict__ lv, float* __restrict__ out,
     int64_t n_units, int H, int d_h_rt, int W, int q_len, int q_pos, float scale_log2e, double freq_ratio, int out_bf16) {
@@ -607,7 +609,7 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
       for (int t = 0; t < VEC; ++t) { qp[t] = head[partner[t]]; kp[t] = head[D + partner[t]]; }
     }
     // further partial products of the projection, three in flight
-    for (int s0 = 1; s0 < n_parts; s0 += 3) {
+    for (int s0 = 1; PARTS && s0 < n_parts; s0 += 3) {
       float4_t w[3][3];
       float wq[3][VEC], wk[3][VEC];
 #pragma unroll
@@ -705,8 +707,8 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
   }
 }
 
-template <int DH, bool PAD>
-static int32_t launch_local_step_dh(const RowSource& qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,
+template <int DH, bool PAD, bool PARTS>
+static int32_t launch_local_step_parts(const RowSource& qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,
                                     int q_pos, int H, int d_h, float scale, float theta, bool out_bf16, hipStream_t st) {
   const double freq_ratio = theta == 0.f ? 0.0 : pow((double)theta, -2.0 / (double)d_h);
   const int64_t n_units = n_chunks * H;
@@ -715,7 +717,7 @@ static int32_t launch_local_step_dh(const RowSource& qkv, float* lk, float* lv, 
   if (blocks > 0x7fffffffLL) return fail(PHOTON_ERR_UNSUPPORTED, "chunk-local attention: too many chunks for one launch");
 #define PHOTON_LS_CASE(N)                                                                                                   \
   case N:                                                                                                                   \
-    PHOTON_LAUNCH(KC_LOCAL_ATTN, st, (local_step_attn_kernel<DH, N, PAD>), dim3((unsigned)blocks), dim3(LOCAL_THREADS), 0, st, \
+    PHOTON_LAUNCH(KC_LOCAL_ATTN, st, (local_step_attn_kernel<DH, N, PAD, PARTS>), dim3((unsigned)blocks), dim3(LOCAL_THREADS), 0, st, \
                   qkv.n_parts ? qkv.parts : qkv.x, qkv.n_parts ? qkv.n_parts : 1, qkv.part_stride, lk, lv, out, n_units, H, d_h, W, q_len, q_pos, scale * LOG2E, freq_ratio, out_bf16 ? 1 : 0);                                    \
     break;
   switch (q_pos + q_len) {
@@ -727,6 +729,13 @@ static int32_t launch_local_step_dh(const RowSource& qkv, float* lk, float* lv, 
   }
 #undef PHOTON_LS_CASE
   return check_launch("local_step_attn_kernel");
+}
+
+template <int DH, bool PAD>
+static int32_t launch_local_step_dh(const RowSource& qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,
+                                    int q_pos, int H, int d_h, float scale, float theta, bool out_bf16, hipStream_t st) {
+  if (qkv.n_parts > 1) return launch_local_step_parts<DH, PAD, true>(qkv, lk, lv, out, n_chunks, W, q_len, q_pos, H, d_h, scale, theta, out_bf16, st);
+  return launch_local_step_parts<DH, PAD, false>(qkv, lk, lv, out, n_chunks, W, q_len, q_pos, H, d_h, scale, theta, out_bf16, st);
 }
 
 int32_t launch_local_step_attn(int d_h, const RowSource& qkv, float* lk, float* lv, float* out, int64_t n_chunks, int W, int q_len,

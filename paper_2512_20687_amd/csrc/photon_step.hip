@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
   if (idx >= (int64_t)rows * H * half) return;
   const int i = (int)(idx % half);
   const int h = (int)((idx / half) % H);
-  const int row = (int)(idx / ((int64_t)half * H)), b = row / n_new, j = row - b * n_new;
+  const int row = (int)(idx / ((int64_t)half * H)), b = n_new == 1 ? row : row / n_new, j = row - b * n_new;
   int pos = seq_len[b] + first + j;
   bool kept = true;
   if (n_new > 1 && pos >= S_max - 1) { kept = j == n_new - 1; pos = (int)(S_max - 1); }
