@@ -149,6 +149,21 @@ def test_bf16_prefill_ragged_widths():
     print(errs)
 
 
+def test_bf16_prefill_with_more_tiles_than_units():
+    """3060 rows, SwiGLU width 5696: 540 tiles of the gate/up projection, two per compute unit and for some three, which one
+    workgroup per unit walks; the last row tile and the last column tile are partly empty.  The second block's keys and
+    values see every row of the first block's feed-forward."""
+    require_gpu()
+    cfg = si.PhotonConfig(L=1, C=(4,), R=(1,), D=512, H=8, d_h=64, n_layers=2, d_ff=5696, vocab=512, dtype="bf16")
+    w = si.make_weights(cfg, 47)
+    Bt, T = 12, 1020
+    toks = si.make_tokens(cfg.vocab, Bt, T, 10)
+    S_max = T // 4 + 1
+    ost = po.prefill(cfg, po.weights_to_f64(w), toks, S_max)
+    model, state = gpu_prefill(cfg, w, toks, S_max)
+    print(check_state(cfg, state, ost, Bt, TOL["bf16"], 2.0 ** -7))
+
+
 def test_encoder_attn_long_sequence_sampled_queries():
     """8192 positions (the top encoder's length in configuration 3); the oracle computes a sample of the queries."""
     require_gpu()
