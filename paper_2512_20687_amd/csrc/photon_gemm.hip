@@ -9,9 +9,9 @@
 // K is walked in slabs of 64: rows of x and W move global -> LDS directly (no staging registers), several slabs ahead
 // of the one that the matrix cores contract, and MFMA 16x16x32 tiles accumulate in registers.  Two kernels: one group of
 // waves with three or four slab buffers (tiles of 64 x 32 to 128 x 128), and two groups in counter-phase (128 x 256 and
-// 256 x 256).  A contraction too small to fill the chip is split over K as well: the fp32 partial products go to a
-// scratch area and are added, in a fixed order, by the kernel that reads the result anyway (the row kernel in front of
-// the next contraction, the attention kernels).  The gate/up projection forms SwiGLU in the accumulators.
+// 256 x 256).  A contraction of fewer than 128 rows is too small to fill the chip and is split over K as well: the fp32
+// partial products go to a scratch area and are added, in a fixed order, by the kernel that reads the result anyway (the row
+// kernel in front of the next contraction, the attention kernels).  The gate/up projection forms SwiGLU in the accumulators.
 #include <type_traits>
 
 #include "photon_device.h"
@@ -21,7 +21,10 @@
 namespace photon {
 
 constexpr int G_BK = 64;                                         // K must be a multiple of this
-constexpr int MAX_SPLITS = 8;                                    // over K
+// Order of a sum over K.  From ORDERED_ROWS rows on the products are added up along K.  Below, in the order of the few-row
+// kernels: K in chunks of 128, chunk c in class c % 8, each class added up along K, then the classes' sums in order.  A row's
+// result then depends neither on the other rows of the pass nor on the tile and the split that plan_gemm finds fastest.
+constexpr int ORDERED_ROWS = 128, K_CLASSES = 8, CHUNK_SLABS = 2;
 
 // 16 bytes per lane from global memory straight into LDS: lane l lands at lds_base + 16 l (lds_base: byte offset in
 // LDS, wave-uniform).  Written as an instruction rather than through the compiler's builtin: the compiler treats
@@ -44,12 +47,13 @@ enum GemmOut { GEMM_OUT_BF16 = 0, GEMM_OUT_F32 = 1, GEMM_OUT_SWIGLU = 2, GEMM_OU
 // ---- shared by the tile kernels ------------------------------------------------------------------------------------------
 
 // One contraction as the kernels take it: out[m, n] (bf16, fp32 or the SwiGLU product as bf16) = x[m, :] . W[n, :]
-// (+ bias[n] + res[m, n]).  fp32 output may be split over K: split s contracts slabs s * slabs .. +slabs and writes its
-// partial product to out + s * split_stride (no bias or residual then).  group_m: row tiles that are walked together.
+// (+ bias[n] + res[m, n]).  fp32 output in classes may be split over K: split s contracts classes s * split_classes ..
+// + split_classes; the first writes their sum, the others each class's sum, to the partial products out + part *
+// part_stride (no bias or residual then).  group_m: row tiles that are walked together.
 struct GemmArgs {
   const bf16_t* x; const bf16_t* W; const float* bias; const float* res; void* out;
-  int64_t ldres, ldo, split_stride;
-  int M, N, K, tiles_m, tiles_n, group_m, slabs, tiles;          // tiles: of all splits
+  int64_t ldres, ldo, part_stride;
+  int M, N, K, tiles_m, tiles_n, group_m, split_classes, tiles;  // tiles: of all splits
   RowBest* best; int stretches;                                  // GEMM_OUT_LOGITS (fp32 output): see ContractArgs
   QkvOperands qkv;                                               // GEMM_OUT_QKV: where the columns go instead of `out`
 };
@@ -96,7 +100,7 @@ __device__ __forceinline__ float silu_to_bf16(float g) { return g * __builtin_am
 // One row of a wave's accumulators: the MFMAs take W as their row operand, so a lane holds 4 consecutive columns of
 // output row m: acc[j] is columns wave_col + j * 16 + 4 fk .. +3 of the tile's staged W rows.
 template <int OUT, int TJ>
-__device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int n0, int wave_col, int fk, int split) {
+__device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int n0, int wave_col, int fk, int part) {
   if (m >= p.M) return;
   if constexpr (OUT == GEMM_OUT_SWIGLU) {
 #pragma unroll
@@ -116,7 +120,7 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
       if (p.bias != nullptr) y += float4_t{p.bias[n], p.bias[n + 1], p.bias[n + 2], p.bias[n + 3]};
       if constexpr (OUT == GEMM_OUT_F32 || OUT == GEMM_OUT_LOGITS) {
         if (p.res != nullptr) y += *reinterpret_cast<const float4_t*>(p.res + (int64_t)m * p.ldres + n);
-        *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(p.out) + split * p.split_stride + (int64_t)m * p.ldo + n) = y;
+        *reinterpret_cast<float4_t*>(reinterpret_cast<float*>(p.out) + part * p.part_stride + (int64_t)m * p.ldo + n) = y;
       } else {
         *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)m * p.ldo + n) = uint2{pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w)};
       }
@@ -219,7 +223,9 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // Measured against the kernels it replaces (MI355X): 64 rows, 2048 x 5120: 28 -> 7.0 us (8 splits); 64 rows, 6144 x 2048:
 // 16.4 -> 8.3 us (2 splits); 64 rows, SwiGLU 2 x 2560 x 1024: 12.3 -> 5.4 us; 512 rows, 2048 x 5120: 32 -> 18 us; 512 rows,
 // SwiGLU 2 x 5120 x 2048: 42 -> 31 us.
-template <int BM, int BN, int WM, int WN, int NB, int OUT>
+// CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
+// in the classes' order, which costs a few scalar instructions per slab.
+template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
   constexpr int WAVES = WM * WN, STAGE = (BM + BN) * 128;
@@ -232,8 +238,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const TilePos at = tile_position(p, blockIdx.x, gridDim.x);
   const int m0 = at.tm * BM, n0 = at.tn * (GU ? BN / 2 : BN);
-  const int s0 = at.split * p.slabs;
-  const int KT = min(p.slabs, p.K / G_BK - s0);
+  const int KT = p.K / G_BK, chunks = (KT + CHUNK_SLABS - 1) / CHUNK_SLABS;
+  const int classes = chunks < K_CLASSES ? chunks : K_CLASSES;
+  const int class0 = CLASSES ? at.split * p.split_classes : 0;
+  const int class1 = CLASSES ? min(class0 + p.split_classes, classes) : 1;
 
   const char* src[LPS];
 #pragma unroll
@@ -242,50 +250,89 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
     const bf16_t* row;
     if ((i * WAVES + wave) * 8 < BM) row = p.x + (int64_t)(m0 + r < p.M ? m0 + r : p.M - 1) * p.K;   // past the end: never stored
     else row = p.W + (int64_t)weight_row<GU>(r - BM, n0, p.N) * p.K;
-    src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8 + (int64_t)s0 * G_BK);
+    src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8);
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
-  auto load = [&](int kt, int buf) {                             // past the end: the last slab again, into a buffer nobody reads
-    const int64_t ko = (int64_t)(kt < KT ? kt : KT - 1) * (G_BK * 2);
+  // Slab that is loaded next, and its class.  Past the end: the last slab again, into a buffer nobody reads.
+  int ahead = CLASSES ? class0 * CHUNK_SLABS : 0, ahead_class = class0;
+  auto load = [&](int buf) {
+    const int64_t ko = (int64_t)ahead * (G_BK * 2);
 #pragma unroll
     for (int i = 0; i < LPS; ++i) load16_to_lds(src[i] + ko, lds0 + buf * STAGE + (i * WAVES + wave) * 1024);
+    if constexpr (!CLASSES) {
+      if (ahead + 1 < KT) ++ahead;
+    } else {
+      const int next_chunk = ahead / CHUNK_SLABS + K_CLASSES;
+      if (ahead % CHUNK_SLABS + 1 < CHUNK_SLABS && ahead + 1 < KT) ++ahead;
+      else if (next_chunk < chunks) ahead = next_chunk * CHUNK_SLABS;
+      else if (ahead_class + 1 < class1) ahead = ++ahead_class * CHUNK_SLABS;
+    }
   };
-  float4_t acc[TI][TJ];
+  // slabs of class c: whole chunks, but for the last one of K
+  auto class_slabs = [&](int c) {
+    if (!CLASSES) return KT;
+    const int n = (chunks - c + K_CLASSES - 1) / K_CLASSES;
+    return n * CHUNK_SLABS - ((chunks - 1) % K_CLASSES == c ? chunks * CHUNK_SLABS - KT : 0);
+  };
+  float4_t acc[TI][TJ], sum[CLASSES ? TI : 1][CLASSES ? TJ : 1];
+  auto clear = [&] {
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < TJ; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
+  };
   const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
   const int fr = lane & 15, fk = lane >> 4;                      // operand fragment: row, 8-wide k group
+  auto store = [&](const float4_t (&y)[TI][TJ], int part) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, y[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
+      else store_row<OUT, TJ>(p, y[i], m0 + wm + i * 16 + fr, n0, wn, fk, part);
+      if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, y[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
+    }
+  };
 
 #pragma unroll
-  for (int s = 0; s < NB - 1; ++s) load(s, s);
+  for (int s = 0; s < NB - 1; ++s) load(s);
   int buf = 0, next = NB - 1;
-  for (int kt = 0; kt < KT; ++kt) {
-    wait_loads_and_barrier<(NB - 2) * LPS>();
-    load(kt + NB - 1, next);
-    const char* s = lds + buf * STAGE;
+  for (int c = class0; c < class1; ++c) {
+    clear();
+    for (int left = class_slabs(c); left > 0; --left) {
+      wait_loads_and_barrier<(NB - 2) * LPS>();                  // (behind a class's stores, which count as well, longer than it has to be)
+      load(next);
+      const char* s = lds + buf * STAGE;
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      bf16x8_t xf[TI], wf[TJ];
+      for (int ks = 0; ks < 2; ++ks) {
+        bf16x8_t xf[TI], wf[TJ];
 #pragma unroll
-      for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
+        for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
 #pragma unroll
-      for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
+        for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
 #pragma unroll
-      for (int i = 0; i < TI; ++i)
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+          for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+      }
+      buf = buf + 1 < NB ? buf + 1 : 0;
+      next = next + 1 < NB ? next + 1 : 0;
     }
-    buf = buf + 1 < NB ? buf + 1 : 0;
-    next = next + 1 < NB ? next + 1 : 0;
+    if constexpr (CLASSES) {
+      if (class0 == 0) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) sum[i][j] = c == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
+      } else if (OUT == GEMM_OUT_F32 && c + 1 < class1) {
+        store(acc, c + 1 - p.split_classes);
+      }
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // the surplus loads of the tail land before the workgroup ends
-#pragma unroll
-  for (int i = 0; i < TI; ++i) {
-    if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
-    else store_row<OUT, TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0, wn, fk, at.split);
-    if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, acc[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
+  if constexpr (CLASSES) {
+    if (class0 == 0) store(sum, 0);
+    else store(acc, class1 - p.split_classes);
+  } else {
+    store(acc, 0);
   }
 }
 
@@ -337,9 +384,9 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
       const int m = at.tm * PP_BM + (w / HALF) * (2 * HALF) + half * HALF + w % HALF;
       row = p.x + (int64_t)(m < p.M ? m : p.M - 1) * p.K;        // rows past the end repeat the last one: never stored
     }
-    return reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8 + (int64_t)at.split * p.slabs * G_BK);
+    return reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8);
   };
-  auto slabs_of = [&](const TilePos& at) { return min(p.slabs, p.K / G_BK - at.split * p.slabs); };
+  const int KT = p.K / G_BK;
   // Loads run ahead of the slab that is contracted; each part has a place of its own in the sequence of all slabs.  After the
   // last tile the last slab is loaded again, into rows nobody reads any more (the number of loads in flight stays constant).
   struct Ahead { int id, left, slab; };                          // tile, slabs left in it, count of all slabs so far
@@ -347,7 +394,7 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
   const char* src[PP_XI + PP_YI];
   auto enter = [&](Ahead& a, auto first, auto last) {
     const TilePos to = tile_position(p, a.id, p.tiles);
-    a.left = slabs_of(to);
+    a.left = KT;
 #pragma unroll
     for (int i = decltype(first)::value; i < decltype(last)::value; ++i) src[i] = source(to, i);
   };
@@ -418,7 +465,6 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
   int slab = 0, id = blockIdx.x;
   do {
     const TilePos at = tile_position(p, id, p.tiles);
-    const int KT = slabs_of(at);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -447,7 +493,7 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
       for (int i = 0; i < TI; ++i) {
         const int m = m0 + (group * 2 + h) * HALF + i * 16 + fr;
         if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
-        else store_row<OUT, TJ>(p, acc[h][i], m, n0, wcol * 64, fk, at.split);
+        else store_row<OUT, TJ>(p, acc[h][i], m, n0, wcol * 64, fk, 0);
         if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, acc[h][i], m, n0 + wcol * 64, fk);
       }
   } while (WALK && (id += gridDim.x) < p.tiles);
@@ -459,10 +505,12 @@ __global__ __launch_bounds__(PP_THREADS) void gemm_pingpong_kernel(const GemmArg
 
 // ---- row kernel between contractions --------------------------------------------------------------------------------------
 //
-// Per row: add up what the value consists of (residual row, the partial products of a split contraction, bias), write
-// the sum if asked, normalise (RMS with gain) and write it as bf16 (the next contraction's operand, rounded to nearest
-// even) or fp32.  TPR threads hold a row in registers, NV float4 each (one read of the row; loads of all sources in flight
-// together); NV == 0: rows longer than the registers hold, read again for the second pass.
+// Per row: add up what the value consists of (the partial products of a split contraction, bias, residual row, in this
+// order, as a contraction in one piece does), write the sum if asked, normalise (RMS with gain) and write it as bf16 (the
+// next contraction's operand, rounded to nearest even) or fp32.  TPR threads hold a row in registers, NV float4 each (one
+// read of the row; loads of all sources in flight together); NV == 0: rows longer than the registers hold, read again for
+// the second pass.  The squares are added up as by 256 threads at every TPR, so that a row's result does not depend on how
+// many rows there are.
 template <int TPR, int NV>
 __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
   const int row = blockIdx.x * (256 / TPR) + threadIdx.x / TPR, t = threadIdx.x % TPR;
@@ -471,21 +519,28 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
   const float* x = p.in.x != nullptr ? p.in.x + (int64_t)row * p.in.ld : nullptr;
   const float* parts = p.in.parts + (int64_t)row * p.in.part_ld;
   auto value = [&](int k) {
-    float4_t v = x != nullptr ? *reinterpret_cast<const float4_t*>(x + k) : float4_t{0.f, 0.f, 0.f, 0.f};
+    float4_t v = float4_t{0.f, 0.f, 0.f, 0.f};
     for (int s = 0; s < p.in.n_parts; ++s) v += *reinterpret_cast<const float4_t*>(parts + s * p.in.part_stride + k);
     if (p.bias != nullptr) v += float4_t{p.bias[k], p.bias[k + 1], p.bias[k + 2], p.bias[k + 3]};
+    if (x != nullptr) v += *reinterpret_cast<const float4_t*>(x + k);
     return v;
   };
+  // with fp32 rows asked for as well, the bf16 rows are those rounded
   auto emit = [&](int k, const float4_t& v, const float4_t& g, float r) {
-    if (p.xb != nullptr) {
-      const float4_t w = p.gain != nullptr ? v * g * r : v;
-      *reinterpret_cast<uint2*>(p.xb + (int64_t)row * K + k) = uint2{pack_bf16x2(w.x, w.y), pack_bf16x2(w.z, w.w)};
+    float4_t w = p.gain != nullptr ? v * g * r : v;
+    if (p.y != nullptr) {
+      w = v * r * g;
+      *reinterpret_cast<float4_t*>(p.y + (int64_t)row * p.ldy + k) = w;
     }
-    if (p.y != nullptr) *reinterpret_cast<float4_t*>(p.y + (int64_t)row * p.ldy + k) = v * r * g;
+    if (p.xb != nullptr)
+      *reinterpret_cast<uint2*>(p.xb + (int64_t)row * K + k) = uint2{pack_bf16x2(w.x, w.y), pack_bf16x2(w.z, w.w)};
   };
-  auto inv_rms = [&](float ss) {
-    ss = wave_sum(ss);
-    if (TPR > 64) {
+  auto inv_rms = [&](const float (&of)[4]) {
+    float ss;
+    if constexpr (TPR == 64) {
+      ss = (wave_sum(of[0]) + wave_sum(of[1])) + (wave_sum(of[2]) + wave_sum(of[3]));
+    } else {
+      ss = wave_sum(of[0]);
       __shared__ float partsum[4];
       if ((threadIdx.x & 63) == 0) partsum[threadIdx.x >> 6] = ss;
       __syncthreads();
@@ -493,9 +548,9 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
     }
     return 1.0f / sqrtf(ss / (float)K + p.eps);
   };
-  float ss = 0.f, r = 1.f;
+  float ss[4] = {0.f, 0.f, 0.f, 0.f}, r = 1.f;                   // TPR == 64: of the four waves that 256 threads would be
   if constexpr (NV > 0) {
-    float4_t v[NV], g[NV];
+    float4_t v[NV], g[NV], whole[NV];
     // the gain is requested with the rows, not after the reduction
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -505,10 +560,11 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int k = (i * TPR + t) * 4;
-      v[i] = k < K && x != nullptr ? *reinterpret_cast<const float4_t*>(x + k) : float4_t{0.f, 0.f, 0.f, 0.f};
+      whole[i] = k < K && x != nullptr ? *reinterpret_cast<const float4_t*>(x + k) : float4_t{0.f, 0.f, 0.f, 0.f};
+      v[i] = float4_t{0.f, 0.f, 0.f, 0.f};
     }
     // several partial products in flight: taken in one after the other, each costs a trip to memory
-    constexpr int PB = NV <= 2 ? MAX_SPLITS : NV <= 4 ? 4 : 2;
+    constexpr int PB = NV <= 2 ? K_CLASSES : NV <= 4 ? 4 : 2;
     for (int s0 = 0; s0 < p.in.n_parts; s0 += PB) {
       float4_t w[PB][NV];
 #pragma unroll
@@ -535,8 +591,10 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
       const int k = (i * TPR + t) * 4;
       if (k >= K) continue;
       if (p.bias != nullptr) v[i] += float4_t{p.bias[k], p.bias[k + 1], p.bias[k + 2], p.bias[k + 3]};
+      v[i] += whole[i];
       if (p.sum != nullptr) *reinterpret_cast<float4_t*>(p.sum + (int64_t)row * p.ld_sum + k) = v[i];
-      ss = fmaf(v[i].x, v[i].x, fmaf(v[i].y, v[i].y, fmaf(v[i].z, v[i].z, fmaf(v[i].w, v[i].w, ss))));
+      float& to = ss[TPR == 64 ? i & 3 : 0];
+      to = fmaf(v[i].x, v[i].x, fmaf(v[i].y, v[i].y, fmaf(v[i].z, v[i].z, fmaf(v[i].w, v[i].w, to))));
     }
     if (p.gain != nullptr) r = inv_rms(ss);
 #pragma unroll
@@ -548,7 +606,7 @@ __global__ __launch_bounds__(256) void rows_kernel(const RowsArgs p) {
     if (p.gain != nullptr) {
       for (int k = t * 4; k < K; k += TPR * 4) {
         const float4_t v = value(k);
-        ss = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss))));
+        ss[0] = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, ss[0]))));
       }
       r = inv_rms(ss);
     }
@@ -586,7 +644,7 @@ __global__ __launch_bounds__(256) void copy_bytes16_kernel(const uint4_t* __rest
 
 // ---- which tile, how many splits ------------------------------------------------------------------------------------------
 
-enum TileKind { T_64x32 = 0, T_64x64, T_128x64, T_128x128, T_128x256, T_256x256, T_KINDS };
+enum TileKind { T_64x32 = 0, T_64x64, T_128x64, T_128x128, T_CLASS_KINDS, T_128x256 = T_CLASS_KINDS, T_256x256, T_KINDS };
 struct TileShape { int bm, bn; float fixed, slab1, slabn; };
 // Time model behind the choice, in us: fixed + slabs per split * (slab1 if every compute unit has one workgroup at most,
 // slabn * workgroups per unit otherwise) + what the output bytes cost.  Fitted to sweeps of all tiles and splits over
@@ -597,28 +655,31 @@ constexpr TileShape TILES[T_KINDS] = {{64, 32, 1.6f, 0.21f, 0.17f},  {64, 64, 2.
                                       {128, 128, 3.5f, 0.50f, 0.59f}, {128, 256, 6.2f, 0.74f, 0.94f}, {256, 256, 8.6f, 1.00f, 1.36f}};
 constexpr float US_PER_MB_OUT = 0.18f, US_PER_MB_PARTS = 0.17f;      // writing the output; reading partial products back
 
-struct GemmPlan { int kind, splits, slabs; };
+// parts: partial products (1: none); split_classes: classes of K per split (0: the sum runs along K, unsplit)
+struct GemmPlan { int kind, splits, parts, split_classes; };
 
+// classes: the sum is formed in classes of K (then not by the counter-phase kernels), and may be split between them.
 // part_cap: floats the scratch area for partial products holds (0: no splitting).  join_us: what reading the partial
 // products back costs beyond the bytes (a launch of its own, or nothing where the next kernel reads the result anyway).
-static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, int64_t part_cap, float join_us, int first_kind = 0,
-                          float* model_us = nullptr) {
-  const int KT = K / G_BK;
-  GemmPlan best{T_64x64, 1, KT};
+static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, bool classes, int64_t part_cap, float join_us,
+                          int first_kind = 0, float* model_us = nullptr) {
+  const int KT = K / G_BK, chunks = (KT + CHUNK_SLABS - 1) / CHUNK_SLABS, n_classes = chunks < K_CLASSES ? chunks : K_CLASSES;
+  GemmPlan best{T_64x64, 1, 1, classes ? K_CLASSES : 0};
   float best_us = 1e30f;
   const float out_mb = (float)M * N * (out_f32 ? 4e-6f : 2e-6f);
-  for (int k = first_kind; k < T_KINDS; ++k) {
+  for (int k = first_kind; k < (classes ? T_CLASS_KINDS : T_KINDS); ++k) {
     const int bn = gate_up ? TILES[k].bn / 2 : TILES[k].bn;
     const int64_t tiles = (M + TILES[k].bm - 1) / TILES[k].bm * ((N + bn - 1) / bn);
-    for (int s = 1; s <= MAX_SPLITS; ++s) {
-      if (s > 1 && (s * M * N > part_cap || KT < 2 * s)) break;
-      const int slabs = (KT + s - 1) / s;
-      if (s > 1 && (KT + slabs - 1) / slabs != s) continue;       // the same slabs per split as with fewer splits
-      const float rounds = (float)((tiles * s + 255) / 256);
+    for (int per = K_CLASSES; per >= 1; per /= 2) {               // classes per split: the first split's come in one part, every other class is one
+      const int splits = (n_classes + per - 1) / per, parts = splits > 1 ? 1 + n_classes - per : 1;
+      if (per < K_CLASSES && (splits == 1 || !classes)) continue;
+      if (parts > 1 && parts * M * N > part_cap) break;
+      const int slabs = splits == 1 ? KT : per * ((chunks + K_CLASSES - 1) / K_CLASSES) * CHUNK_SLABS;
+      const float rounds = (float)((tiles * splits + 255) / 256);
       const float us = TILES[k].fixed + slabs * (rounds <= 1.f ? TILES[k].slab1 : TILES[k].slabn * rounds) +
-                       out_mb * s * US_PER_MB_OUT + (s > 1 ? out_mb * s * US_PER_MB_PARTS + join_us : 0.f);
-      if (us < best_us) { best_us = us; best = GemmPlan{k, s, slabs}; }
-      if (tiles * s >= 512) break;                                // more splits only add bytes
+                       out_mb * parts * US_PER_MB_OUT + (parts > 1 ? out_mb * parts * US_PER_MB_PARTS + join_us : 0.f);
+      if (us < best_us) { best_us = us; best = GemmPlan{k, splits, parts, classes ? per : 0}; }
+      if (tiles * splits >= 512) break;                           // more splits only add bytes
     }
   }
   if (model_us != nullptr) *model_us = best_us;
@@ -642,7 +703,7 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
   p.tiles_m = (p.M + t.bm - 1) / t.bm;
   p.tiles_n = (p.N + bn - 1) / bn;
   p.group_m = p.tiles_m < 8 ? p.tiles_m : 8;
-  p.slabs = plan.slabs;
+  p.split_classes = plan.split_classes;
   const int64_t grid = (int64_t)p.tiles_m * p.tiles_n * plan.splits;
   if (grid > 0x7fffffffLL) return fail(PHOTON_ERR_UNSUPPORTED, "gemm: %lld workgroups are too many for one launch", (long long)grid);
   p.tiles = (int)grid;
@@ -652,10 +713,21 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
     return launch_kernel(KERN, &attr_set, (unsigned)grid, THREADS, (size_t)(BUFS) * (t.bm + t.bn) * 128, p, st); \
   }
   if constexpr (OUT != GEMM_OUT_QKV) {                           // a wave of the narrow tiles holds half a head
+    if constexpr (OUT != GEMM_OUT_BF16) {                        // (the chunker's sum always runs along K)
+      if (plan.split_classes != 0) {
+        switch (plan.kind) {
+          PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT, true>), 256, 4)
+          PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT, true>), 256, 4)
+          PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT, true>), 512, 3)
+          default:
+          PHOTON_GEMM_CASE(T_128x128, (gemm_tile_kernel<128, 128, 4, 2, 3, OUT, true>), 512, 3)
+        }
+      }
+    }
     switch (plan.kind) {
-      PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT>), 256, 4)
-      PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT>), 256, 4)
-      PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT>), 512, 3)
+      PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT, false>), 256, 4)
+      PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT, false>), 256, 4)
+      PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT, false>), 512, 3)
       default: break;
     }
   }
@@ -673,7 +745,7 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
     }
   }
   switch (plan.kind) {
-    PHOTON_GEMM_CASE(T_128x128, (gemm_tile_kernel<128, 128, 4, 2, 3, OUT>), 512, 3)
+    PHOTON_GEMM_CASE(T_128x128, (gemm_tile_kernel<128, 128, 4, 2, 3, OUT, false>), 512, 3)
     PHOTON_GEMM_CASE(T_128x256, (gemm_pingpong_kernel<2, OUT>), PP_THREADS, 2)
     default:
     PHOTON_GEMM_CASE(T_256x256, (gemm_pingpong_kernel<4, OUT>), PP_THREADS, 2)
@@ -682,8 +754,8 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
 }
 
 int64_t contract_part_floats(int64_t rows, int D) {
-  // 8 splits of a D-wide result, 4 of a 3D-wide one, at up to 1024 rows (more rows have enough tiles)
-  return (rows < 1024 ? rows : 1024) * 12 * (int64_t)D;
+  // 8 parts of a D-wide result, 5 of a 3D-wide one, at up to 512 rows (more rows have enough tiles)
+  return (rows < 512 ? rows : 512) * 15 * (int64_t)D;
 }
 
 int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st, int* best_stretches) {
@@ -691,10 +763,11 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
   GemmArgs p{};
   p.x = reinterpret_cast<const bf16_t*>(a.x); p.W = reinterpret_cast<const bf16_t*>(a.W); p.M = a.M; p.N = a.N; p.K = a.K;
   p.bias = a.bias; p.out = a.out; p.ldo = a.ldo;
-  if (a.epilogue == EPI_SWIGLU) return launch_gemm<GEMM_OUT_SWIGLU>(p, plan_gemm(a.M, a.N, a.K, true, false, 0, 0.f), st);
+  const bool classes = (a.order_rows > 0 ? a.order_rows : a.M) < ORDERED_ROWS;
+  if (a.epilogue == EPI_SWIGLU) return launch_gemm<GEMM_OUT_SWIGLU>(p, plan_gemm(a.M, a.N, a.K, true, false, classes, 0, 0.f), st);
   // a plain result that the caller needs in one piece is joined by a launch of the row kernel
   const bool join = a.epilogue == EPI_PLAIN && !a.split_ok;
-  const GemmPlan plan = plan_gemm(a.M, a.N, a.K, false, true, a.part_cap, join ? 3.5f : 0.f);
+  const GemmPlan plan = plan_gemm(a.M, a.N, a.K, false, true, classes, a.part_cap, join ? 3.5f : 0.f);
   const RowSource whole{reinterpret_cast<const float*>(a.out), a.ldo, nullptr, 0, 0, 0};
   if (a.best != nullptr && plan.splits == 1) {
     if (a.epilogue != EPI_PLAIN || a.bias != nullptr || best_stretches == nullptr)
@@ -715,9 +788,9 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
     *result = whole;
     return launch_gemm<GEMM_OUT_F32>(p, plan, st);
   }
-  p.bias = nullptr; p.out = a.parts; p.ldo = a.N; p.split_stride = (int64_t)a.M * a.N;
+  p.bias = nullptr; p.out = a.parts; p.ldo = a.N; p.part_stride = (int64_t)a.M * a.N;
   PHOTON_TRY(launch_gemm<GEMM_OUT_F32>(p, plan, st));
-  RowSource r{nullptr, 0, a.parts, plan.splits, a.N, p.split_stride};
+  RowSource r{nullptr, 0, a.parts, plan.parts, a.N, p.part_stride};
   if (a.epilogue == EPI_RESID) { r.x = a.res.x; r.ld = a.res.ld; }
   if (!join) { *result = r; return PHOTON_OK; }
   RowsArgs rows{};
@@ -730,10 +803,10 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
 // its fp32 result, which costs a launch and reads and writes 1.5 times that result at 4.5 bytes per ns (135 us at 32768 rows
 // of 3072).  Measured: 8192 rows of 3072 82 against 73 + 37 us; the model's margin matters below some hundred rows only.
 bool qkv_rope_pays(int64_t rows, int D, int d_h) {
-  if (d_h != 64) return false;
+  if (d_h != 64 || rows < ORDERED_ROWS) return false;
   float fused = 0.f, best = 0.f;
-  plan_gemm(rows, 3 * D, D, false, false, 0, 0.f, T_128x128, &fused);
-  plan_gemm(rows, 3 * D, D, false, true, 0, 0.f, 0, &best);
+  plan_gemm(rows, 3 * D, D, false, false, false, 0, 0.f, T_128x128, &fused);
+  plan_gemm(rows, 3 * D, D, false, true, false, 0, 0.f, 0, &best);
   return fused <= best + 4.f + 0.33f * (float)rows * 3 * D * 4e-6f;
 }
 
@@ -742,13 +815,13 @@ int32_t launch_qkv_rope(const void* x, const void* W, int rows, int D, const Qkv
     return fail(PHOTON_ERR_UNSUPPORTED, "QKV projection: rows=%d D=%d do not match %d heads of 64 and %d positions", rows, D, o.H, o.M);
   GemmArgs p{};
   p.x = reinterpret_cast<const bf16_t*>(x); p.W = reinterpret_cast<const bf16_t*>(W); p.M = rows; p.N = 3 * D; p.K = D; p.qkv = o;
-  return launch_gemm<GEMM_OUT_QKV>(p, plan_gemm(rows, 3 * D, D, false, false, 0, 0.f, T_128x128), st);
+  return launch_gemm<GEMM_OUT_QKV>(p, plan_gemm(rows, 3 * D, D, false, false, false, 0, 0.f, T_128x128), st);
 }
 
 static int32_t launch_chunker_gemm(const void* x, const void* w, const float* bias, void* out, int64_t M, int N, int K, hipStream_t st) {
   GemmArgs p{};
   p.x = (const bf16_t*)x; p.W = (const bf16_t*)w; p.bias = bias; p.out = out; p.ldo = N; p.M = (int)M; p.N = N; p.K = K;
-  return launch_gemm<GEMM_OUT_BF16>(p, plan_gemm(M, N, K, false, false, 0, 0.f), st);
+  return launch_gemm<GEMM_OUT_BF16>(p, plan_gemm(M, N, K, false, false, false, 0, 0.f), st);
 }
 
 }  // namespace photon

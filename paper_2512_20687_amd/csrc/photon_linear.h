@@ -43,8 +43,8 @@ bool launch_linear_resident_x2(const LinearArgs& a, hipStream_t st);
 
 // ---- 17 rows and up with bf16 weights: row kernel (norm, rounding to bf16) + tiled MFMA contraction ----
 
-// Rows as a sum: x[row * ld ..] (nullptr: nothing) plus n_parts partial products of a contraction split over K,
-// parts[s * part_stride + row * part_ld ..], added in order.
+// Rows as a sum: n_parts partial products of a contraction split over K, parts[s * part_stride + row * part_ld ..], added
+// in order, plus x[row * ld ..] (nullptr: nothing).
 struct RowSource {
   const float* x = nullptr;
   int64_t ld = 0;
@@ -88,7 +88,8 @@ struct RowBest {
 // EPI_RESID: out = res + x W^T, where out and res must not overlap.  parts: scratch of part_cap floats for the partial
 // products of a contraction split over K.  `result` says where the fp32 result lies: in out, or still in pieces
 // (EPI_RESID: the residual rows and the partial products; EPI_PLAIN with split_ok: the partial products, without the
-// bias), for the next kernel to add.
+// bias), for the next kernel to add.  order_rows: the row count whose order of the sum over K is kept (0: M); passes that take
+// the rows of several smaller passes together give a row the result it has there.
 struct ContractArgs {
   const void* x = nullptr;
   const void* W = nullptr;
@@ -99,7 +100,7 @@ struct ContractArgs {
   float* parts = nullptr;
   int64_t part_cap = 0;
   int M = 0, N = 0, K = 0;
-  int epilogue = EPI_PLAIN;
+  int epilogue = EPI_PLAIN, order_rows = 0;
   bool split_ok = false;
   // EPI_PLAIN without bias: row m's best of every stretch of columns goes to best[m * stretches + stretch], where `best`
   // holds M * best_stretches_max(N); launch_contract sets *best_stretches, and leaves it where K is split (nothing is written)

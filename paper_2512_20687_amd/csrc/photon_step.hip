@@ -130,12 +130,12 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
   float c, s;
   rope_angle(pos, i, d_h, theta, c, s);                        // under the loads
   float* qd = qrot + (int64_t)row * D + h * d_h;
-  qd[i] = qa * c - qb * s;
-  qd[i + half] = qb * c + qa * s;
+  qd[i] = fmaf(qa, c, -(qb * s));                              // which product is rounded is part of the result: written out
+  qd[i + half] = fmaf(qa, s, qb * c);
   if (!kept || pos < 0 || pos >= S_max) return;               // full cache: nothing is written out of bounds
   const int64_t slot = (((int64_t)b * H + h) * S_max + pos) * pitch;
-  kc[slot + i] = from_f32<TKV>(ka * c - kb * s);
-  kc[slot + i + half] = from_f32<TKV>(kb * c + ka * s);
+  kc[slot + i] = from_f32<TKV>(fmaf(ka, c, -(kb * s)));
+  kc[slot + i + half] = from_f32<TKV>(fmaf(ka, s, kb * c));
   vc[slot + i] = from_f32<TKV>(va);
   vc[slot + i + half] = from_f32<TKV>(vb);
   for (int p = d_h + i; p < pitch; p += half) { kc[slot + p] = TKV{}; vc[slot + p] = TKV{}; }
@@ -398,6 +398,7 @@ struct Ctx {
   char* base;
   bool bf16;
   bool few = false;                           // this pass keeps the few-row kernels (and their fp32 rows) at any row count
+  int order_rows = 0;                         // row count whose order of summation the blocks' contractions keep (0: their own)
   size_t o_h, o_attn, o_qkv, o_qrot, o_act;   // activation buffers of the branch this context drives
   size_t o_many, o_parts;                     // its bf16 rows and partial products of the tiled contractions
   int64_t part_cap;
@@ -428,7 +429,7 @@ static int32_t contract(const Ctx& x, const void* xb, const void* W, const float
   ContractArgs a;
   a.x = xb != nullptr ? xb : x.base + x.o_many; a.W = W; a.bias = bias; a.res = res; a.out = out; a.ldo = ldo;
   a.parts = x.f(x.o_parts); a.part_cap = x.part_cap; a.M = rows; a.N = N; a.K = K; a.epilogue = epilogue; a.split_ok = split_ok;
-  a.best = best;
+  a.best = best; a.order_rows = x.order_rows;
   return launch_contract(a, result, x.st, stretches);
 }
 
@@ -682,10 +683,12 @@ static int32_t hier_reencode(const Ctx& x, const int32_t* tokens, const float** 
     else if (l > 1)
       PHOTON_TRY(linear(x, RowSource{X, (int64_t)C * D}, x.ew->chunker_w[l - 1], nullptr, x.ew->chunker_b[l - 1], A, D, rows, D, C * D));
     // The level's new units are causally ordered, but all their inputs are there: one pass takes them together, layer by
-    // layer, instead of one STEP each (16 sequences, 4 units, 4 layers: 816 -> 370 us).  Rows of a single STEP that stay in fp32 stay so.
+    // layer, instead of one STEP each (16 sequences, 4 units, 4 layers: 816 -> 370 us).
     float* Xl = x.f(x.p.hx[l]);
+    // A row's result stays that of a single STEP: same precision, same order of every sum over the width.
     Ctx u = x;
     u.few = Bt < MANY_ROWS;
+    u.order_rows = Bt;
     PHOTON_TRY(stream_step(u, x.ew->enc[l - 1], x.hs->k_cache[l - 1], x.hs->v_cache[l - 1], x.hs->seq_len[l - 1], x.hs->S_cap[l - 1],
                            RowSource{A, D}, Xl, (int)per_seq, x.f(x.p.logits), (size_t)x.p.chunks[1] * c.vocab * sizeof(float)));
     PHOTON_LAUNCH(KC_MISC, x.st, step_begin_kernel, dim3(blocks_for(Bt)), dim3(256), 0, x.st, x.hs->seq_len[l - 1], Bt, x.hs->S_cap[l - 1],

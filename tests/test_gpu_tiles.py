@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import seeded_inputs as si
-from util import TOL, require_gpu
+from util import TOL, dev, require_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +79,59 @@ def test_greedy_choice_at_many_rows(Bt, vocab):
             first = torch.where(logits == logits.amax(-1, keepdim=True), index, vocab).amin(-1)
             assert torch.equal(out.long(), first) and int(out.max()) < vocab - vocab // 2
     assert torch.equal(tokens[0], tokens[1])
+
+
+def step_of_first(cfg, w, st, Bt, forced):
+    """One step of the first Bt sequences of `st`: the state afterwards and the trace."""
+    from test_gpu_decode_step import run_step
+    part = dict(k=st["k"][:, :Bt], v=st["v"][:, :Bt], seq_len=st["seq_len"][:Bt], x_top=st["x_top"][:Bt], carry=st["carry"][:, :Bt])
+    _, state, _, trace = run_step(cfg, w, part, Bt, st["k"].shape[3], forced[:Bt])
+    return state, trace
+
+
+# A sequence's step does not depend on how many others it is decoded with, as long as every level stays on the same side of
+# 17 and of 128 rows (where rows are rounded, and where the order of the sums over the width changes): bit for bit, over
+# different tiles and splits.  Widths with whole and half chunks of 128, more and fewer than 8 of them.
+@pytest.mark.parametrize("kw,batches", [
+    (dict(L=1, C=(4,), R=(1,), D=512, d_ff=1280), (17, 64, 127)),
+    (dict(L=1, C=(3,), R=(1,), D=1344, H=21, d_ff=2560), (17, 65, 120)),
+    (dict(L=1, C=(2,), R=(1,), D=320, H=5, d_ff=704), (128, 300, 1100)),
+    (dict(L=2, C=(4, 4), R=(1, 1), D=1024, H=16, d_ff=2560), (128, 257)),
+    (dict(L=2, C=(4, 4), R=(1, 1), D=1024, H=16, d_ff=2560), (5, 16)),
+])
+def test_a_sequence_s_step_does_not_depend_on_the_batch(kw, batches):
+    require_gpu()
+    base = dict(H=8, d_h=64, n_layers=2, vocab=1008, dtype="bf16")
+    base.update(kw)
+    cfg = si.PhotonConfig(**base)
+    w, st = si.make_weights(cfg, 12), si.make_decode_state(cfg, batches[-1], 20, 64, seed=3)
+    forced = si.make_tokens(cfg.vocab, batches[-1], cfg.meta_context, 7)
+    ref = None
+    for Bt in batches:
+        state, trace = step_of_first(cfg, w, st, Bt, forced)
+        got = [trace["logits"][:batches[0]], state.x_top[:batches[0]], state.k[:, :batches[0]], state.v[:, :batches[0]]]
+        if ref is None:
+            ref = got
+        for a, b in zip(ref, got):
+            assert torch.equal(a, b), Bt
+
+
+# The order of a contraction's sum: below 128 rows that of the few-row kernel on the same bf16 rows, from 128 on that of the
+# chunker entry point (whose result is rounded to bf16): the top chunker of a step against both, bit for bit.
+@pytest.mark.parametrize("Bt,C,D", [(17, 4, 512), (64, 3, 448), (100, 2, 64), (127, 8, 1024), (128, 4, 512), (333, 3, 448)])
+def test_order_of_a_contraction_s_sum(Bt, C, D):
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(L=1, C=(C,), R=(1,), D=D, H=D // 64, d_h=64, n_layers=1, d_ff=64, vocab=1008, dtype="bf16")
+    w, st = si.make_weights(cfg, 2), si.make_decode_state(cfg, Bt, 10, 64, seed=1)
+    _, trace = step_of_first(cfg, w, st, Bt, si.make_tokens(cfg.vocab, Bt, C, 7))
+    rows = trace["new_units"][0].reshape(Bt, C * D).to(torch.bfloat16)
+    W, b = dev(w["enc"][0]["chunker"]["w"], "bf16"), dev(w["enc"][0]["chunker"]["b"])
+    if Bt < 128:
+        out = torch.zeros((Bt, D), device="cuda")
+        ph.photon_linear(rows, W, out, bias=b)
+        assert torch.equal(out, trace["a_hat"])
+    else:
+        out = torch.zeros((Bt, D), dtype=torch.bfloat16, device="cuda")
+        ph.photon_chunker_project(rows.reshape(Bt * C, D), W, b, out, C)
+        assert torch.equal(out, trace["a_hat"].to(torch.bfloat16))
