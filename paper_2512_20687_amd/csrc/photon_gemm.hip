@@ -92,11 +92,6 @@ template <int VM> __device__ __forceinline__ void wait_loads_and_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM) : "memory");
 }
 
-// SiLU in front of a rounding to bf16: the reciprocal instruction (1 ulp) instead of an IEEE division, whose dozen
-// instructions per value showed most where the accumulators' work is small (256 rows, 2 x 2560 x 1024: 11.3 -> 10.3 us; 1024
-// rows: 20.2 -> 19.8 us; 512 rows, 2 x 5120 x 2048: 34.2 -> 33.3 us).
-__device__ __forceinline__ float silu_to_bf16(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
-
 // One row of a wave's accumulators: the MFMAs take W as their row operand, so a lane holds 4 consecutive columns of
 // output row m: acc[j] is columns wave_col + j * 16 + 4 fk .. +3 of the tile's staged W rows.
 template <int OUT, int TJ>
@@ -109,7 +104,7 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
       if (n >= p.N) continue;
       const float4_t g = acc[j], u = acc[j + 1];
       *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)m * p.ldo + n) =
-          uint2{pack_bf16x2(silu_to_bf16(g.x) * u.x, silu_to_bf16(g.y) * u.y), pack_bf16x2(silu_to_bf16(g.z) * u.z, silu_to_bf16(g.w) * u.w)};
+          uint2{pack_bf16x2(silu(g.x) * u.x, silu(g.y) * u.y), pack_bf16x2(silu(g.z) * u.z, silu(g.w) * u.w)};
     }
   } else {
 #pragma unroll

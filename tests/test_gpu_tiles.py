@@ -1,5 +1,6 @@
 """The tiled bf16 contractions: tile edges through photon_chunker_project (Eq. 4) against an fp32 product of the same
 bf16 inputs; splits over K and sums in pieces through decode steps against the oracle."""
+import numpy as np
 import pytest
 import torch
 
@@ -135,3 +136,31 @@ def test_order_of_a_contraction_s_sum(Bt, C, D):
         out = torch.zeros((Bt, D), dtype=torch.bfloat16, device="cuda")
         ph.photon_chunker_project(rows.reshape(Bt * C, D), W, b, out, C)
         assert torch.equal(out, trace["a_hat"].to(torch.bfloat16))
+
+
+# SwiGLU of many rows against the few-row kernel's on the same bf16 rows.  Identity converter, no attention, a down projection
+# that adds up every D-th hidden column: the new unit is the norm of (row of +-1) + those sums.  One hidden value rounded
+# to the other side (2^-8 of it) would show at 1e-4; fp32 sums and the norm leave 1e-6.
+@pytest.mark.parametrize("Bt", [40, 127])
+def test_swiglu_of_many_rows_is_that_of_the_few_row_kernel(Bt):
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    D, F = 1024, 4096
+    cfg = si.PhotonConfig(L=1, C=(1,), R=(1,), D=D, H=16, d_h=64, n_layers=1, d_ff=F, vocab=1008, dtype="bf16")
+    w, st = si.make_weights(cfg, 6), si.make_decode_state(cfg, Bt, 4, 16, seed=5)
+    dec, eye = w["dec"][0], np.eye(D, dtype=np.float32)
+    dec["converter"]["w"], dec["converter"]["b"] = eye, np.zeros((D,), np.float32)
+    layer = dec["module"]["layers"][0]
+    layer["wv"] = np.zeros((D, D), np.float32)
+    layer["g2"], dec["module"]["g_final"] = np.ones((D,), np.float32), np.ones((D,), np.float32)
+    layer["wd"] = np.tile(eye, (1, F // D))
+    st["x_top"] = np.where(st["x_top"] < 0, -1.0, 1.0).astype(np.float32)
+    _, trace = step_of_first(cfg, w, st, Bt, si.make_tokens(cfg.vocab, Bt, 1, 7))
+    rows = dev(st["x_top"])
+    wgu, hidden = dev(np.concatenate([layer["wg"], layer["wu"]]), "bf16"), torch.zeros((Bt, F), dtype=torch.bfloat16, device="cuda")
+    for m in range(0, Bt, 16):
+        ph.photon_linear(rows[m:m + 16].to(torch.bfloat16), wgu, hidden[m:m + 16], epilogue=2)
+    ref = rows.double() + hidden.double().reshape(Bt, F // D, D).sum(1)
+    ref = ref / (ref.pow(2).mean(1, keepdim=True) + cfg.rms_eps).sqrt()
+    err = (trace["new_units"][0].reshape(Bt, D).double() - ref).abs().max()
+    assert float(err) <= 1e-5, float(err)
