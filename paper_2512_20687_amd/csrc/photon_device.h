@@ -168,6 +168,13 @@ __device__ __forceinline__ void rope_angle(int pos, int i, int d_h, float theta,
   c = (float)cd; s = (float)sd;
 }
 
+// Rotary pair of an encoder.  Which of the two products is rounded is part of the result: written out, so that every kernel
+// that forms these operands has the same bits.
+__device__ __forceinline__ void rotate_pair(float a, float b, float c, float s, float& x, float& y) {
+  x = fmaf(a, c, -(b * s));
+  y = fmaf(b, c, a * s);
+}
+
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float NEG_BIG = -1.0e30f;     // finite stand-in for -inf as running maximum
 

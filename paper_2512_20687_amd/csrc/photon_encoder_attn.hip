@@ -26,17 +26,9 @@
 //     keys of the tile; V is stored transposed ([d_h][key]), so the matching
 //     operand of the second MFMA is one 16-byte LDS read.  No data moves
 //     between lanes and no register is repacked.
-//   * the score accumulators start from minus a reference (kept as a register
-//     vector): the maximum of a query's first block, moved up to the running
-//     maximum only when a block's weights add up to more than 1024, which is
-//     far below fp16's range (weights above 1 lose no more to its rounding
-//     than weights below).  The common path per score
-//     is exp2, one add into the row sum and the fp16 pack, with no maximum, no
-//     exchange and no branch between the score MFMAs and the exponentials; a
-//     block that does raise the reference forms its scores again (32 heads:
-//     32768 positions 5.71 -> 5.38 ms, 8192 502 -> 460 us, 16 x 2048 778 ->
-//     721 us; error against float64 as before within 2 % of itself at the
-//     kernel, unchanged at the prefill's outputs).
+//   * the score accumulators start from minus the running maximum (kept as a
+//     register vector that changes only when the maximum does), so the common
+//     path per score is exp2, one add into the row sum and the fp16 pack.
 //   * a workgroup = 12 waves = 384 queries of one (sequence, head) share every
 //     key block of 64 (K, V^T: 16 KB = one 16-byte piece of each array per
 //     thread of the first 8 waves; three waves per SIMD is what the kernel's
@@ -164,8 +156,9 @@ __global__ __launch_bounds__(256) void encoder_rope_split_kernel(const float* __
     for (int j = 0; j < 8; ++j) {
       const float c = cs[j], s = sn[j];
       const float qa = q[j], qb = q[8 + j], ka = k[j], kb = k[8 + j];
-      q[j] = (qa * c - qb * s) * qscale; q[8 + j] = (qb * c + qa * s) * qscale;
-      k[j] = ka * c - kb * s; k[8 + j] = kb * c + ka * s;
+      rotate_pair(qa, qb, c, s, q[j], q[8 + j]);
+      q[j] *= qscale; q[8 + j] *= qscale;
+      rotate_pair(ka, kb, c, s, k[j], k[8 + j]);
     }
   }
   const int64_t row = ((int64_t)bh * Mp + pos) * EA_DH;
@@ -304,7 +297,6 @@ __global__ __launch_bounds__(EA_THREADS) void encoder_attn_mfma_kernel(const uin
 
     // st[kt][v] = S^T[key k0 + kt*32 + 16 kg + v][query] - m_run; the two tiles' MFMA chains are interleaved
     float16_t st[2];
-    auto scores = [&]() __attribute__((always_inline)) {
     if (two) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
@@ -333,35 +325,15 @@ __global__ __launch_bounds__(EA_THREADS) void encoder_attn_mfma_kernel(const uin
         for (int v = 0; v < 16; ++v)
           if (kt * 32 + v > rel) st[kt][v] = NEG_BIG;
     }
-    };
-    float psum;
-    uint4_t pf[2][2];                                 // P^T operands: [key tile][k-step]: keys 16 kg + 8 s + 0..7 of the tile
-    auto weights = [&]() __attribute__((always_inline)) {
-      psum = 0.f;
+    // scores are relative to the running maximum: a positive one raises it (rare after the first blocks)
+    float mx = st[0][0];
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          uint4_t pk;
-          float p[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            // a masked score is about -1e30: exp2 gives exactly 0 (the query sees at least key k0 of every block it processes)
-            p[j] = fast_exp2(st[kt][8 * s + j]);
-            psum += p[j];
-          }
-          pk.x = pack_f16x2_unit(p[0], p[1]); pk.y = pack_f16x2_unit(p[2], p[3]); pk.z = pack_f16x2_unit(p[4], p[5]);
-          pk.w = pack_f16x2_unit(p[6], p[7]);
-          pf[kt][s] = pk;
-        }
-    };
-    auto raise = [&](bool first) __attribute__((always_inline)) {
-      float mx = st[0][0];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, st[kt][v]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, st[kt][v]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const bool first = (kb == 0);                     // block 0 is every wave's first block: it sets the reference maximum
+    if (first || __builtin_amdgcn_ballot_w64(mx > 0.f) != 0) {
       const float up = first ? mx : fmaxf(mx, 0.f);   // this lane's reference maximum moves by `up`
       m_run += up;
 #pragma unroll
@@ -378,11 +350,25 @@ __global__ __launch_bounds__(EA_THREADS) void encoder_attn_mfma_kernel(const uin
 #pragma unroll
           for (int e = 0; e < 16; ++e) o[dt][e] *= alpha;
       }
-    };
-    scores();
-    if (kb == 0) raise(true);
-    weights();
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(psum > 1024.f) != 0, 0)) { scores(); raise(false); weights(); }
+    }
+    float psum = 0.f;
+    uint4_t pf[2][2];                                 // P^T operands: [key tile][k-step]: keys 16 kg + 8 s + 0..7 of the tile
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        uint4_t pk;
+        float p[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          // a masked score is about -1e30: exp2 gives exactly 0 (the query sees at least key k0 of every block it processes)
+          p[j] = fast_exp2(st[kt][8 * s + j]);
+          psum += p[j];
+        }
+        pk.x = pack_f16x2_unit(p[0], p[1]); pk.y = pack_f16x2_unit(p[2], p[3]); pk.z = pack_f16x2_unit(p[4], p[5]);
+        pk.w = pack_f16x2_unit(p[6], p[7]);
+        pf[kt][s] = pk;
+      }
     l_run += psum;
     // O^T += V^T P^T: k-slot (kg, j) of step s stands for key kt*32 + 16 kg + 8 s + j: 16 consecutive bytes of a V^T row
 #pragma unroll

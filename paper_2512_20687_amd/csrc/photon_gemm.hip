@@ -175,7 +175,13 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
       const int i = j * 16 + fk * 4;
       const float4_t c = *reinterpret_cast<const float4_t*>(o.table + (int64_t)pos * 64 + i);
       const float4_t s = *reinterpret_cast<const float4_t*>(o.table + (int64_t)pos * 64 + 32 + i);
-      float4_t y0 = acc[j] * c - acc[j + 2] * s, y1 = acc[j + 2] * c + acc[j] * s;
+      float4_t y0, y1;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        float lower, upper;
+        rotate_pair(acc[j][t], acc[j + 2][t], c[t], s[t], lower, upper);
+        y0[t] = lower; y1[t] = upper;
+      }
       if (section == 0) {
         y0 *= o.qscale; y1 *= o.qscale;
       } else if (cached) {

@@ -297,6 +297,34 @@ def test_bf16_prefill_operands_from_the_projection(kw, Bt, T):
     check_hier(cfg, hier, ost, 2.0 ** -7)
 
 
+def test_operands_from_the_projection_are_those_of_the_separate_pass():
+    """The same rotated keys, bit for bit, whether the projection writes them or the pass behind it does: rows of +-1 and weights
+    that are multiples of 2^-10, so that the fp32 projection is known exactly and photon_encoder_attn can be given it."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(L=1, C=(1,), R=(1,), D=256, H=4, d_h=64, n_layers=1, d_ff=64, vocab=512, dtype="bf16")
+    w, M = si.make_weights(cfg, 8), 8192
+    w["E_enc"] = np.where(w["E_enc"] < 0, -1.0, 1.0).astype(np.float32)
+    chunk, layer = w["enc"][0]["chunker"], w["enc"][0]["module"]["layers"][0]
+    chunk["w"], chunk["b"], layer["g1"] = np.eye(cfg.D, dtype=np.float32), np.zeros((cfg.D,), np.float32), np.ones((cfg.D,), np.float32)
+    for name in ("wq", "wk", "wv"):
+        layer[name] = np.clip(np.round(layer[name] * 1024), -128, 128).astype(np.float32) / 1024
+    tokens = si.make_tokens(cfg.vocab, 1, M, 3)
+    model = ph.PhotonModel(cfg, w)
+    state = ph.PhotonState(model, 1, M)
+    ph.photon_prefill(model, state, dev(np.asarray(tokens, np.int32)))
+    rows = w["E_enc"][np.asarray(tokens)[0]].astype(np.float64)
+    qkv = np.concatenate([rows @ layer[name].astype(np.float64).T for name in ("wq", "wk", "wv")], 1)
+    assert np.array_equal(qkv, qkv.astype(np.float32))
+    k, v = (torch.zeros_like(state.k[0]) for _ in range(2))
+    ws = torch.empty(ph.photon_encoder_attn_workspace_bytes(1, M, cfg.H, cfg.d_h, True), dtype=torch.uint8, device="cuda")
+    ph.photon_encoder_attn(dev(qkv.astype(np.float32)), torch.empty((M, cfg.D), device="cuda"), 1, M, cfg.H, cfg.d_h, cfg.rope_theta, k_cache=k,
+                           v_cache=v, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(state.v[0], v)
+    assert torch.equal(state.k[0], k), int((state.k[0] != k).sum())
+
+
 def test_hierarchical_step_with_a_stream_that_runs_full():
     """The level-1 stream of one sequence has room for two of a step's four new units, the other's for all of them: the first is
     flagged and clamped to its capacity, what lies in front of its last slot stays, and the second is as if it were alone."""
