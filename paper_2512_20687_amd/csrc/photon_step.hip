@@ -451,8 +451,9 @@ static int32_t linear(const Ctx& x, const RowSource& in, const void* W, const fl
   LinearArgs a;
   a.x = in.x; a.ldx = in.ld;
   if (in.n_parts != 0) {                                   // a first sub-step with several converter rows had many rows, its items are few
+    // into the attention rows, which nobody reads any more: without a feed-forward the whole part is p.h itself, at another pitch
     RowsArgs sum;
-    sum.in = in; sum.sum = x.f(x.o_h); sum.ld_sum = K; sum.M = M; sum.K = K;
+    sum.in = in; sum.sum = x.f(x.o_attn); sum.ld_sum = K; sum.M = M; sum.K = K;
     PHOTON_TRY(launch_rows(sum, x.st));
     a.x = sum.sum; a.ldx = K;
   }

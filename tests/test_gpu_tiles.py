@@ -55,6 +55,19 @@ def test_decode_step_at_many_rows(kw, Bt):
     print(errs)
 
 
+# Attention-only blocks whose first token sub-step has more than 16 rows and whose items are fewer: the last block's result
+# comes in pieces, the whole one of which is the buffer the next rows enter through, and is joined for the few-row head.
+@pytest.mark.parametrize("kw,Bt", [
+    (dict(D=512, H=8, R=(2, 1)), 3),
+    (dict(D=1024, H=16, R=(3, 2), n_layers=1), 4),
+    (dict(D=256, H=4, R=(9, 1), C=(4, 2)), 2),
+])
+def test_attention_only_blocks_joined_for_a_few_row_head(kw, Bt):
+    require_gpu()
+    from test_gpu_decode_step import test_logits_when_the_items_are_not_requested as check
+    check(dict(dict(L=2, C=(4, 4), d_ff=0, vocab=1008, dtype="bf16"), **kw), Bt)
+
+
 # Greedy steps with enough rows that the vocabulary contraction leaves each row's best columns beside the logits: a narrow
 # and a wide wave tile, a last stretch of 16 columns, equal logits (the vocabulary's second half repeats the first: the
 # lower index wins), logits in the state's own buffer (no trace) as well.
