@@ -329,14 +329,28 @@ __global__ __launch_bounds__(COARSE_WAVES * 64) void coarse_attn_units_kernel(
         st[i].l += s[i][u];
       }
     }
+    // A key that a query does not see must not reach it through 0 * v either (a later unit may hold infinities or NaN): only
+    // the last keys of a stream are seen by some queries and not by others.
+    if (t0 + TILE <= last[0]) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float vf[VEC];
-      unpack16<TKV>(vr[u], vf);
+      for (int u = 0; u < U; ++u) {
+        float vf[VEC];
+        unpack16<TKV>(vr[u], vf);
 #pragma unroll
-      for (int i = 0; i < NQ; ++i)
+        for (int i = 0; i < NQ; ++i)
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) st[i].o[e] = fmaf(s[i][u], vf[e], st[i].o[e]);
+          for (int e = 0; e < VEC; ++e) st[i].o[e] = fmaf(s[i][u], vf[e], st[i].o[e]);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float vf[VEC];
+        unpack16<TKV>(vr[u], vf);
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) st[i].o[e] = fmaf(s[i][u], t0 + u * RPW + g < last[i] ? vf[e] : 0.f, st[i].o[e]);
+      }
     }
   };
 

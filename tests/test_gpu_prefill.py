@@ -325,6 +325,32 @@ def test_operands_from_the_projection_are_those_of_the_separate_pass():
     assert torch.equal(state.k[0], k), int((state.k[0] != k).sum())
 
 
+@pytest.mark.parametrize("dtype,bad", [("bf16", float("nan")), ("f32", float("inf"))])
+def test_a_new_unit_does_not_reach_the_units_before_it(dtype, bad):
+    """Four new units of a level in one pass, the third made of a token whose embedding is not finite: the two before it are
+    what they are with any other token there, and it is not finite."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(L=2, C=(4, 4), R=(1, 1), D=256, H=4, d_h=64, n_layers=2, d_ff=640, vocab=512, dtype=dtype)
+    w, T, S_max = si.make_weights(cfg, 3), 16 * 4, 8
+    w["E_enc"][7] = bad
+    prompt = np.maximum(np.asarray(si.make_tokens(cfg.vocab, 2, T, 2)), 8)
+    tokens = np.maximum(np.asarray(si.make_tokens(cfg.vocab, 2, cfg.meta_context, 4)), 8)
+    model, units = ph.PhotonModel(cfg, w), []
+    for token in (7, 9):
+        tokens[:, 9] = token
+        state, hier = ph.PhotonState(model, 2, S_max), ph.PhotonHierState(model, 2, S_max)
+        ph.photon_prefill(model, state, dev(np.asarray(prompt, np.int32)), hier=hier)
+        out = torch.zeros((2, cfg.meta_context), dtype=torch.int32, device="cuda")
+        ph.photon_hiergen_step(model, state, hier, out, forced_tokens=dev(np.asarray(tokens, np.int32)))
+        torch.cuda.synchronize()
+        units.append([t[:, :, :, 16:20].clone() for t in (hier.k[0], hier.v[0])])
+    for poisoned, clean in zip(*units):
+        assert bool(torch.isfinite(clean.float()).all())
+        assert torch.equal(poisoned[:, :, :, :2], clean[:, :, :, :2])
+        assert not bool(torch.isfinite(poisoned[:, :, :, 2].float()).any())
+
+
 def test_hierarchical_step_with_a_stream_that_runs_full():
     """The level-1 stream of one sequence has room for two of a step's four new units, the other's for all of them: the first is
     flagged and clamped to its capacity, what lies in front of its last slot stays, and the second is as if it were alone."""
