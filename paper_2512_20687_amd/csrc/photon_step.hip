@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
   const int row = (int)(idx / ((int64_t)half * H)), b = n_new == 1 ? row : row / n_new, j = row - b * n_new;
   int pos = seq_len[b] + first + j;
   bool kept = true;
-  if (n_new > 1 && pos >= S_max - 1) { kept = j == n_new - 1; pos = (int)(S_max - 1); }
+  if (first == 0 && pos >= S_max - 1) { kept = j == n_new - 1; pos = (int)(S_max - 1); }
   const float* src = qkv + (int64_t)row * 3 * D + h * d_h;
   float qa = src[i], qb = src[i + half], ka = src[D + i], kb = src[D + i + half], va = src[2 * D + i], vb = src[2 * D + i + half];
   for (int s0 = 1; s0 < n_parts; s0 += 3) {                    // three in flight

@@ -382,6 +382,28 @@ def test_hierarchical_step_with_a_stream_that_runs_full():
     assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
 
 
+def test_hierarchical_step_of_one_unit_on_a_full_stream():
+    """One new unit per step and level (a top chunk of 1): on a full stream it takes the last slot, as if the entry there had not
+    been counted yet, and the sequence is flagged."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(L=2, C=(4, 1), R=(1, 2), D=256, H=4, d_h=64, n_layers=2, d_ff=640, vocab=512, dtype="bf16")
+    w, S_max = si.make_weights(cfg, 3), 8
+    st = si.make_decode_state(cfg, 2, 4, S_max, seed=9)
+    model, results = ph.PhotonModel(cfg, w), []
+    level1 = [si.make_normal((cfg.n_layers, 2, cfg.H, S_max, cfg.d_h), s) for s in (21, 22)]
+    forced = dev(np.asarray(si.make_tokens(cfg.vocab, 2, cfg.meta_context, 4), np.int32))
+    for count in (S_max, S_max - 1):
+        state = ph.PhotonState(model, 2, S_max, **{k: st[k] for k in ("k", "v", "seq_len", "x_top", "carry")})
+        hier = ph.PhotonHierState(model, 2, S_max, k=[level1[0]], v=[level1[1]], seq_len=[np.array([count, 3], np.int32)])
+        ph.photon_hiergen_step(model, state, hier, torch.zeros((2, cfg.meta_context), dtype=torch.int32, device="cuda"), forced_tokens=forced)
+        torch.cuda.synchronize()
+        assert hier.seq_len[0].tolist() == [S_max, 4] and bool(int(state.status.item()) & 1) == (count == S_max)
+        results.append((state.x_top, state.k, state.v, hier.k[0], hier.v[0]))
+    for full, room in zip(*results):
+        assert torch.equal(full, room)
+
+
 def test_bf16_prefill_with_8bit_cache_then_step():
     """Prefill into an 8-bit (E4M3) coarse cache, then a decode step from it, against the oracle doing the same."""
     require_gpu()
