@@ -732,17 +732,17 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
       default: break;
     }
   }
-  // Gate/up over several rounds of short tiles: one workgroup per compute unit walks its tiles and loads the next one's first
-  // slabs under the last one's contraction, SiLU and stores.  Measured in prefills, dealt out / walked: 16 x 8192 tokens at K = 1024, four
-  // layers of two levels 1567 / 1469 us; 131072 tokens at K = 2048, eight layers of two levels 10.30 / 9.87 ms.  The
-  // other outputs lose by it (their stores and residual loads queue with the next tile's loads: 1024 columns of 32768 rows
-  // 147 / 166 us, QKV 228 / 264 us), and so do two rounds or long tiles, which have little to hide.
+  // Gate/up over several rounds of short 256 x 256 tiles: one workgroup per compute unit walks its tiles and loads the next
+  // one's first slabs under the last one's contraction, SiLU and stores.  Measured in prefills, dealt out / walked: 16 x 8192
+  // tokens at K = 1024, four layers of two levels 1567 / 1469 us; 131072 tokens at K = 2048, eight layers of two levels
+  // 10.30 / 9.87 ms.  128 x 256 tiles gain nothing by it (eight layers, 627 to 710 tiles at K = 256 to 1536: 2097 / 2108,
+  // 2456 / 2438, 1349 / 1345, 1397 / 1399, 1624 / 1622 us).  The other outputs lose (their stores and residual loads queue with
+  // the next tile's loads: 1024 columns of 32768 rows 147 / 166 us, QKV 228 / 264 us), and so do two rounds or long tiles,
+  // which have little to hide.
   if constexpr (OUT == GEMM_OUT_SWIGLU) {
-    if (plan.kind >= T_128x256 && grid > 2 * 256 && p.K <= 2048) {
-      static bool attr_128 = false, attr_256 = false;
-      if (plan.kind == T_128x256)
-        return launch_kernel(gemm_pingpong_kernel<2, OUT, true>, &attr_128, 256, PP_THREADS, (size_t)2 * (t.bm + t.bn) * 128, p, st);
-      return launch_kernel(gemm_pingpong_kernel<4, OUT, true>, &attr_256, 256, PP_THREADS, (size_t)2 * (t.bm + t.bn) * 128, p, st);
+    if (plan.kind == T_256x256 && grid > 2 * 256 && p.K <= 2048) {
+      static bool attr_set = false;
+      return launch_kernel(gemm_pingpong_kernel<4, OUT, true>, &attr_set, 256, PP_THREADS, (size_t)2 * (t.bm + t.bn) * 128, p, st);
     }
   }
   switch (plan.kind) {
