@@ -350,6 +350,16 @@ PHOTON_API int32_t photon_persistent_trace(uint64_t* stamps);
  * leave the kernel normally.  Meant for tests of that path (a limit of a few ticks makes the first real wait run out). */
 PHOTON_API int32_t photon_set_barrier_wait_limit(int64_t ticks);
 
+/* Which tile a bf16 contraction of rows x N x K takes, for tests that mean a particular one (host only): its rows and output
+ * columns, over how many workgroups K is split, and whether one workgroup per compute unit walks the tiles.  Outputs: fp32
+ * (the block projections; K split as far as the scratch of an N wide module allows), bf16 (photon_chunker_project) and SwiGLU
+ * (N: columns of the product). */
+#define PHOTON_CONTRACT_F32 0
+#define PHOTON_CONTRACT_CHUNKER 1
+#define PHOTON_CONTRACT_SWIGLU 2
+PHOTON_API int32_t photon_contract_tile(int64_t rows, int32_t N, int32_t K, int32_t output, int32_t* tile_rows, int32_t* tile_columns,
+                                        int32_t* splits, int32_t* walked);
+
 /* --------------------------------------------------------------------------
  * Hierarchical prefill of a batch of prompts (paper Section 2.3.3, first
  * paragraph; encoder Eq. 3-4): embeds the tokens, runs chunker + encoder

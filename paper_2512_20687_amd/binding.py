@@ -240,6 +240,19 @@ def photon_persistent_trace(stamps: Optional[torch.Tensor]) -> None:
     _check(lib.photon_persistent_trace(_ptr(stamps)))
 
 
+PHOTON_CONTRACT_F32, PHOTON_CONTRACT_CHUNKER, PHOTON_CONTRACT_SWIGLU = 0, 1, 2
+
+
+def photon_contract_tile(rows: int, N: int, K: int, output: int):
+    """(tile rows, tile columns, splits of K, walked) of a bf16 contraction (host only)."""
+    lib = load_library()
+    lib.photon_contract_tile.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int32] + [C.POINTER(C.c_int32)] * 4
+    lib.photon_contract_tile.restype = C.c_int32
+    res = [C.c_int32() for _ in range(4)]
+    _check(lib.photon_contract_tile(rows, N, K, output, *[C.byref(r) for r in res]))
+    return res[0].value, res[1].value, res[2].value, bool(res[3].value)
+
+
 def photon_set_barrier_wait_limit(ticks: int) -> None:
     """Bound of a grid-barrier wait of a persistent launch in 10 ns ticks (default 10**9)."""
     lib = load_library()

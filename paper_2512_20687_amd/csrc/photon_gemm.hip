@@ -697,6 +697,18 @@ static int32_t launch_kernel(void (*kern)(GemmArgs), bool* attr_set, unsigned gr
   return check_launch("gemm kernel");
 }
 
+// Gate/up over several rounds of short 256 x 256 tiles: one workgroup per compute unit walks its tiles and loads the next
+// one's first slabs under the last one's contraction, SiLU and stores.  Measured in prefills, dealt out / walked: 16 x 8192
+// tokens at K = 1024, four layers of two levels 1567 / 1469 us; 131072 tokens at K = 2048, eight layers of two levels
+// 10.30 / 9.87 ms.  128 x 256 tiles gain nothing by it (eight layers, 627 to 710 tiles at K = 256 to 1536: 2097 / 2108,
+// 2456 / 2438, 1349 / 1345, 1397 / 1399, 1624 / 1622 us).  The other outputs lose (their stores and residual loads queue with
+// the next tile's loads: 1024 columns of 32768 rows 147 / 166 us, QKV 228 / 264 us), and so do two rounds or long tiles,
+// which have little to hide.
+static bool walks(const GemmPlan& plan, int64_t M, int N, int K) {
+  const int bn = TILES[T_256x256].bn / 2;
+  return plan.kind == T_256x256 && (M + 255) / 256 * ((N + bn - 1) / bn) > 2 * 256 && K <= 2048;
+}
+
 template <int OUT>
 static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
   const TileShape& t = TILES[plan.kind];
@@ -732,15 +744,8 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
       default: break;
     }
   }
-  // Gate/up over several rounds of short 256 x 256 tiles: one workgroup per compute unit walks its tiles and loads the next
-  // one's first slabs under the last one's contraction, SiLU and stores.  Measured in prefills, dealt out / walked: 16 x 8192
-  // tokens at K = 1024, four layers of two levels 1567 / 1469 us; 131072 tokens at K = 2048, eight layers of two levels
-  // 10.30 / 9.87 ms.  128 x 256 tiles gain nothing by it (eight layers, 627 to 710 tiles at K = 256 to 1536: 2097 / 2108,
-  // 2456 / 2438, 1349 / 1345, 1397 / 1399, 1624 / 1622 us).  The other outputs lose (their stores and residual loads queue with
-  // the next tile's loads: 1024 columns of 32768 rows 147 / 166 us, QKV 228 / 264 us), and so do two rounds or long tiles,
-  // which have little to hide.
   if constexpr (OUT == GEMM_OUT_SWIGLU) {
-    if (plan.kind == T_256x256 && grid > 2 * 256 && p.K <= 2048) {
+    if (walks(plan, p.M, p.N, p.K)) {
       static bool attr_set = false;
       return launch_kernel(gemm_pingpong_kernel<4, OUT, true>, &attr_set, 256, PP_THREADS, (size_t)2 * (t.bm + t.bn) * 128, p, st);
     }
@@ -828,6 +833,23 @@ static int32_t launch_chunker_gemm(const void* x, const void* w, const float* bi
 }  // namespace photon
 
 using namespace photon;
+
+extern "C" int32_t photon_contract_tile(int64_t rows, int32_t N, int32_t K, int32_t output, int32_t* tile_rows, int32_t* tile_columns,
+                                        int32_t* splits, int32_t* walked) {
+  clear_error();
+  PHOTON_REQUIRE(rows >= 1 && rows <= (1LL << 24) && N >= 16 && N % 16 == 0 && K >= G_BK && K % G_BK == 0 && K <= (1 << 24), PHOTON_ERR_INVALID_ARG,
+                 "%s: rows=%lld N=%d K=%d invalid", __func__, (long long)rows, N, K);
+  PHOTON_REQUIRE(output >= PHOTON_CONTRACT_F32 && output <= PHOTON_CONTRACT_SWIGLU, PHOTON_ERR_INVALID_ARG, "%s: unknown output %d", __func__, output);
+  PHOTON_REQUIRE(tile_rows && tile_columns && splits && walked, PHOTON_ERR_INVALID_ARG, "%s: null result", __func__);
+  const bool gate_up = output == PHOTON_CONTRACT_SWIGLU, f32 = output == PHOTON_CONTRACT_F32;
+  const GemmPlan plan = plan_gemm(rows, N, K, gate_up, f32, output != PHOTON_CONTRACT_CHUNKER && rows < ORDERED_ROWS,
+                                  f32 ? contract_part_floats(rows, N) : 0, 0.f);
+  *tile_rows = TILES[plan.kind].bm;
+  *tile_columns = TILES[plan.kind].bn / (gate_up ? 2 : 1);
+  *splits = plan.splits;
+  *walked = gate_up && walks(plan, rows, N, K) ? 1 : 0;
+  return PHOTON_OK;
+}
 
 extern "C" int32_t photon_chunker_project(const void* x, const void* w, const float* bias, void* out, int64_t rows,
                                           int32_t C, int32_t d_in, int32_t d_out, photon_dtype dt, void* stream) {

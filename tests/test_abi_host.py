@@ -100,3 +100,21 @@ def test_schedule_controls_validate_on_the_host(lib):
     assert lib.photon_set_persistent(0) == 0 and lib.photon_set_persistent(1) == 0
     lib.photon_persistent_trace.argtypes = [ctypes.c_void_p]
     assert lib.photon_persistent_trace(None) == 0
+
+
+def test_contract_tile_validates_on_the_host(lib):
+    from paper_2512_20687_amd import binding as b
+    res = [ctypes.c_int32() for _ in range(4)]
+    refs = [ctypes.byref(r) for r in res]
+    b.photon_contract_tile(64, 64, 64, 0)                        # declares the arguments
+    for rows, N, K, output in [(0, 64, 64, 0), (64, 60, 64, 0), (64, 64, 96, 0), (64, 64, 0, 0), (64, 64, 64, 3), (64, 64, 64, -1)]:
+        assert lib.photon_contract_tile(rows, N, K, output, *refs) == -1
+    assert lib.photon_contract_tile(64, 64, 64, 0, None, *refs[1:]) == -1
+    # a sum that runs along K is in one piece: the chunker's always, every other from 128 rows on
+    for rows in (1, 17, 127, 128, 1000, 40000):
+        for N, K in ((64, 4096), (1024, 1024), (5120, 2048)):
+            assert b.photon_contract_tile(rows, N, K, b.PHOTON_CONTRACT_CHUNKER)[2] == 1
+            assert b.photon_contract_tile(rows, N, K, b.PHOTON_CONTRACT_SWIGLU)[2] == 1
+            tile = b.photon_contract_tile(rows, N, K, b.PHOTON_CONTRACT_F32)
+            assert 1 <= tile[2] <= min(8, (K + 127) // 128) and (rows < 128 or tile[2] == 1)
+            assert rows >= 128 or tile[1] <= 128                 # the counter-phase tiles know no classes

@@ -155,6 +155,8 @@ def test_bf16_prefill_with_more_tiles_than_units():
     values see every row of the first block's feed-forward."""
     require_gpu()
     cfg = si.PhotonConfig(L=1, C=(4,), R=(1,), D=512, H=8, d_h=64, n_layers=2, d_ff=5696, vocab=512, dtype="bf16")
+    from paper_2512_20687_amd.binding import PHOTON_CONTRACT_SWIGLU, photon_contract_tile
+    assert photon_contract_tile(3060, cfg.d_ff, cfg.D, PHOTON_CONTRACT_SWIGLU) == (256, 128, 1, True)
     w = si.make_weights(cfg, 47)
     Bt, T = 12, 1020
     toks = si.make_tokens(cfg.vocab, Bt, T, 10)

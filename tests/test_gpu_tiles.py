@@ -10,10 +10,14 @@ from util import TOL, dev, require_gpu
 pytestmark = pytest.mark.gpu
 
 
-# 192 tiles of 256 x 256 and up: the counter-phase kernel.  One row more and one less than whole row tiles, a last
-# column tile of 16 columns, one to three K slabs, a tile count that is no multiple of 8.
+# A row more and a row less than whole row tiles, a last column tile of 16 columns, one to five K slabs (which tile each of
+# them takes is left to the time model; test_every_tile_kind names its tiles).
 @pytest.mark.parametrize("rows,K,N", [(6144, 64, 2048), (6145, 128, 2048), (6143, 192, 2048), (49409, 64, 256), (6100, 320, 2064)])
 def test_tiled_contraction_edges(rows, K, N):
+    check_chunker(rows, K, N)
+
+
+def check_chunker(rows, K, N):
     require_gpu()
     import paper_2512_20687_amd as ph
     g = torch.Generator(device="cuda").manual_seed(rows + K)
@@ -29,6 +33,24 @@ def test_tiled_contraction_edges(rows, K, N):
     err = (out[:rows].float() - ref).abs()
     bound = ref.abs() * 2.0 ** -8 + 1e-5 * K ** 0.5
     assert bool((err <= bound).all()), float((err - bound).max())
+
+
+# Every tile of the contraction at one, two and three K slabs, fewer and more than it loads ahead: a row more or less than whole
+# row tiles, a last column tile of 16 columns, a tile count that is no multiple of the 8 XCDs.
+@pytest.mark.parametrize("tile,rows,K,N", [
+    ((64, 32), 63, 64, 48), ((64, 32), 65, 128, 80), ((64, 32), 193, 192, 144),
+    ((64, 64), 9473, 64, 592), ((64, 64), 11777, 128, 208), ((64, 64), 9855, 192, 144),
+    ((128, 64), 62719, 64, 144), ((128, 64), 29697, 128, 144), ((128, 64), 19711, 192, 144),
+    ((128, 128), 28927, 64, 1040), ((128, 128), 25855, 128, 528), ((128, 128), 23553, 192, 400),
+    ((128, 256), 20481, 64, 4624), ((128, 256), 7425, 128, 6416), ((128, 256), 14337, 192, 2064), ((128, 256), 641, 704, 8208),
+    ((256, 256), 42495, 64, 2064), ((256, 256), 13313, 128, 3344), ((256, 256), 25599, 192, 1040), ((256, 256), 1537, 320, 7696),
+])
+def test_every_tile_kind(tile, rows, K, N):
+    import paper_2512_20687_amd as ph
+    from paper_2512_20687_amd.binding import PHOTON_CONTRACT_CHUNKER
+    assert ph.photon_contract_tile(rows, N, K, PHOTON_CONTRACT_CHUNKER) == (*tile, 1, False)
+    assert -(-rows // tile[0]) * -(-N // tile[1]) % 8 != 0
+    check_chunker(rows, K, N)
 
 
 # 16 rows below to hundreds above the switch to the tiled contractions, at every level; a first sub-step that is above it
@@ -132,10 +154,15 @@ def test_a_sequence_s_step_does_not_depend_on_the_batch(kw, batches):
 
 # The order of a contraction's sum: below 128 rows that of the few-row kernel on the same bf16 rows, from 128 on that of the
 # chunker entry point (whose result is rounded to bf16): the top chunker of a step against both, bit for bit.
-@pytest.mark.parametrize("Bt,C,D", [(17, 4, 512), (64, 3, 448), (100, 2, 64), (127, 8, 1024), (128, 4, 512), (333, 3, 448)])
-def test_order_of_a_contraction_s_sum(Bt, C, D):
+@pytest.mark.parametrize("Bt,C,D,tile", [
+    (17, 4, 512, (64, 32, 8)), (64, 3, 448, (64, 32, 8)), (100, 2, 64, (64, 32, 1)), (127, 8, 1024, (64, 64, 8)), (127, 1, 1024, (64, 32, 4)),
+    (127, 1, 2048, (64, 64, 4)), (128, 4, 512, (64, 32, 1)), (333, 3, 448, (64, 32, 1)),
+])
+def test_order_of_a_contraction_s_sum(Bt, C, D, tile):
     require_gpu()
     import paper_2512_20687_amd as ph
+    from paper_2512_20687_amd.binding import PHOTON_CONTRACT_F32
+    assert ph.photon_contract_tile(Bt, D, C * D, PHOTON_CONTRACT_F32) == (*tile, False)
     cfg = si.PhotonConfig(L=1, C=(C,), R=(1,), D=D, H=D // 64, d_h=64, n_layers=1, d_ff=64, vocab=1008, dtype="bf16")
     w, st = si.make_weights(cfg, 2), si.make_decode_state(cfg, Bt, 10, 64, seed=1)
     _, trace = step_of_first(cfg, w, st, Bt, si.make_tokens(cfg.vocab, Bt, C, 7))
