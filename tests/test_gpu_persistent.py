@@ -190,6 +190,14 @@ def test_pipelined_steps_equal_joined_steps(kw, Bt):
         ph.photon_set_persistent(True)
 
 
+# The main line itself on the tiled contractions (more than 16 sequences: rows and partial products of its own) beside lower
+# levels that still run: split and unsplit sums, two converter rows at the top, attention-only blocks, four blocks over five steps.
+@pytest.mark.parametrize("kw,Bt", [(dict(R=(1, 2)), 20), (dict(D=512, H=8, d_ff=1280, n_layers=4), 24), (dict(d_ff=0, n_layers=3), 18),
+                                   (dict(L=3, C=(2, 2, 2), R=(2, 1, 1), D=320, H=5, d_ff=704), 65), (dict(n_layers=1, C=(2, 2)), 130)])
+def test_pipelined_steps_equal_joined_steps_at_many_rows(kw, Bt):
+    test_pipelined_steps_equal_joined_steps(kw, Bt)
+
+
 def test_pipelined_state_refuses_unjoined_use():
     """A state with outstanding lower levels may only take further pipelined steps or the join."""
     require_gpu()
