@@ -880,8 +880,8 @@ using namespace photon;
 
 struct PrefillPlan {
   int64_t M[PHOTON_MAX_LEVELS + 1] = {0};        // M[l]: level-l units per sequence, M[0] = T
-  size_t X[PHOTON_MAX_LEVELS + 1] = {0};         // X[l]: level-l encoder states [Bt*M[l], D]; X[0] = embeddings; X[L] unused
-  size_t A = 0, h = 0, attn = 0, qkv = 0, act = 0, many = 0, parts = 0, ea = 0, table = 0, pair = 0;
+  size_t X[PHOTON_MAX_LEVELS + 1] = {0};         // X[l]: level-l encoder states [Bt*M[l], D]; X[0]: embeddings in fp32, where needed; X[L] unused
+  size_t A = 0, h = 0, attn = 0, qkv = 0, act = 0, many = 0, parts = 0, ea = 0, table = 0, before_last = 0;
   int64_t part_cap = 0;
   int many_K = 0;
   size_t total = 0;
@@ -894,14 +894,16 @@ static PrefillPlan make_prefill_plan(const photon_config& c, int Bt, int64_t T) 
   p.M[0] = T;
   for (int l = 1; l <= c.L; ++l) p.M[l] = p.M[l - 1] / c.C[l - 1];
   size_t cur = 0;
-  for (int l = 0; l < c.L; ++l) p.X[l] = bump(cur, (size_t)Bt * p.M[l] * D * f);
   const int64_t rows = (int64_t)Bt * p.M[1];     // the widest level
+  const bool gathered = c.dt == PHOTON_BF16 && rows >= MANY_ROWS;   // embed_and_chunk: the embeddings go to the bf16 rows
+  if (!gathered) p.X[0] = bump(cur, (size_t)Bt * T * D * f);
+  for (int l = 1; l < c.L; ++l) p.X[l] = bump(cur, (size_t)Bt * p.M[l] * D * f);
   p.A = bump(cur, rows * D * f);
   p.h = bump(cur, rows * D * f);
   p.attn = bump(cur, rows * D * f);
   p.qkv = bump(cur, rows * 3 * D * f);
   p.act = bump(cur, rows * F * f);
-  p.pair = bump(cur, (size_t)2 * Bt * D * f);    // conditioning latent of the carry decode, and a spare
+  p.before_last = bump(cur, (size_t)Bt * D * f); // conditioning latent of the carry decode
   if (c.dt == PHOTON_BF16) {
     p.many_K = (int)(D > F ? D : F);
     for (int l = 1; l <= c.L; ++l)
@@ -927,7 +929,7 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
   const size_t esz = dtype_size(c.kv_dt);
 
   float *A = e.f(pp.A), *qkv = e.f(pp.qkv), *attn = e.f(pp.attn);
-  float* pair = e.f(pp.pair);
+  float* before_last = e.f(pp.before_last);                // X^(L) in front of the last one, one row per sequence
   // X^(0): encoder-side embeddings.  Parameter-free level-1 chunker: they are D / C_1 wide, and C_1 of them side
   // by side are A^(1) itself.
   const bool concat1 = L >= 2 && ew.chunker_w[0] == nullptr;
@@ -999,9 +1001,9 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
       PHOTON_TRY(norm(e, in.pick(M, M - 1), mod.g_final, x.s->x_top, 1, 0, Bt));
       if (L >= 2) {
         if (M >= 2) {
-          PHOTON_TRY(norm(e, in.pick(M, M - 2), mod.g_final, pair, 1, 0, Bt));
+          PHOTON_TRY(norm(e, in.pick(M, M - 2), mod.g_final, before_last, 1, 0, Bt));
         } else {
-          PHOTON_LAUNCH(KC_MISC, x.st, broadcast_rows_kernel, dim3(blocks_for((int64_t)Bt * D)), dim3(256), 0, x.st, ew.x0[L - 1], pair, Bt, D);
+          PHOTON_LAUNCH(KC_MISC, x.st, broadcast_rows_kernel, dim3(blocks_for((int64_t)Bt * D)), dim3(256), 0, x.st, ew.x0[L - 1], before_last, Bt, D);
           PHOTON_TRY(check_launch("broadcast_rows_kernel"));
         }
       }
@@ -1020,7 +1022,7 @@ static int32_t prefill_impl(const Ctx& x, Ctx e, const PrefillPlan& pp, const ph
                   x.bar_words(), x.bar_word_count(), 0);
     PHOTON_TRY(check_launch("step_begin_kernel"));
   }
-  const float* cond = pair;                                // level-l latent before the last one, one row per sequence
+  const float* cond = before_last;                         // level-l latent before the last one, one row per sequence
   float* dh = x.f(x.o_h);
   float* units = x.f(x.p.fresh[0]);                        // [Bt, D]: the item before the last one
   Ctx window = x;

@@ -118,3 +118,14 @@ def test_contract_tile_validates_on_the_host(lib):
             tile = b.photon_contract_tile(rows, N, K, b.PHOTON_CONTRACT_F32)
             assert 1 <= tile[2] <= min(8, (K + 127) // 128) and (rows < 128 or tile[2] == 1)
             assert rows >= 128 or tile[1] <= 128                 # the counter-phase tiles know no classes
+
+
+def test_prefill_workspace_holds_no_fp32_embeddings_where_they_are_gathered(lib):
+    """Attention-only blocks, chunks of 8: per level-1 row and column 4 + 4 + 4 + 12 bytes of fp32 rows, 8 * 2 of bf16 rows and 6
+    of attention operands, where fp32 embeddings would be 8 * 4 more."""
+    import paper_2512_20687_amd as ph
+    import seeded_inputs as si
+    T, D = 1 << 20, 512
+    cfg = si.PhotonConfig(L=1, C=(8,), R=(1,), D=D, H=8, d_h=64, n_layers=1, d_ff=0, vocab=512, dtype="bf16")
+    per_row = ph.photon_prefill_workspace_bytes(cfg, 1, T) / (T // 8 * D)
+    assert 46 <= per_row < 48, per_row
