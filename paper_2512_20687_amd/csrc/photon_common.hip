@@ -31,7 +31,7 @@ std::mutex g_prof_mu;
 std::vector<ProfRec> g_prof;
 const char* const kClassNames[KC_COUNT] = {
     "coarse_attn_kernel", "coarse_merge_kernel", "local_attn_kernel", "linear_bf16_kernels", "gemm_f32_kernel",
-    "reduce_splits_kernel", "chunker_gemm_bf16_kernel", "norm_rows_kernel", "rope_append_kernel", "silu_mul_kernel",
+    "chunker_gemm_bf16_kernel", "norm_rows_kernel", "rope_append_kernel",
     "choose_token_kernel", "misc", "persistent_module_kernel"};
 }  // namespace
 
