@@ -224,14 +224,16 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // Measured against the kernels it replaces (MI355X): 64 rows, 2048 x 5120: 28 -> 7.0 us (8 splits); 64 rows, 6144 x 2048:
 // 16.4 -> 8.3 us (2 splits); 64 rows, SwiGLU 2 x 2560 x 1024: 12.3 -> 5.4 us; 512 rows, 2048 x 5120: 32 -> 18 us; 512 rows,
 // SwiGLU 2 x 5120 x 2048: 42 -> 31 us.
+// PER: slabs per barrier, all of them read behind it (chosen in launch_gemm).
 // CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
 // in the classes' order, which costs a few scalar instructions per slab.
-template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES>
+template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, int PER = 1>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
   constexpr int WAVES = WM * WN, STAGE = (BM + BN) * 128;
   constexpr int LPS = (BM + BN) / 8 / WAVES;                     // load instructions per wave and slab
   constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;            // MFMA tiles of a wave
+  static_assert(PER == 1 || (PER == 2 && !CLASSES), "pairs of slabs along K");
   static_assert((BM + BN) / 8 % WAVES == 0, "every wave moves the same number of rows");
   static_assert(!GU || TJ % 2 == 0, "a wave holds gate and up columns in pairs");
   extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows]
@@ -294,28 +296,44 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
   };
 
 #pragma unroll
-  for (int s = 0; s < NB - 1; ++s) load(s);
-  int buf = 0, next = NB - 1;
+  for (int s = 0; s < NB - PER; ++s) load(s);
+  int buf = 0, next = NB - PER;
+  auto contract_slab = [&] {
+    const char* s = lds + buf * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8_t xf[TI], wf[TJ];
+#pragma unroll
+      for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+    }
+    buf = buf + 1 < NB ? buf + 1 : 0;
+  };
+  // The next PER slabs have landed (NB - 2 PER younger ones may be in flight), everybody is done with the last PER.
+  auto enter_slabs = [&] {
+    wait_loads_and_barrier<(NB - 2 * PER) * LPS>();              // (behind a class's stores, which count as well, longer than it has to be)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      load(next);
+      next = next + 1 < NB ? next + 1 : 0;
+    }
+  };
   for (int c = class0; c < class1; ++c) {
     clear();
-    for (int left = class_slabs(c); left > 0; --left) {
-      wait_loads_and_barrier<(NB - 2) * LPS>();                  // (behind a class's stores, which count as well, longer than it has to be)
-      load(next);
-      const char* s = lds + buf * STAGE;
+    int left = class_slabs(c);
+    for (; left >= PER; left -= PER) {
+      enter_slabs();
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        bf16x8_t xf[TI], wf[TJ];
-#pragma unroll
-        for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-          for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
-      }
-      buf = buf + 1 < NB ? buf + 1 : 0;
-      next = next + 1 < NB ? next + 1 : 0;
+      for (int u = 0; u < PER; ++u) contract_slab();
+    }
+    if (PER > 1 && left > 0) {                                   // PER == 2, the last slab of an odd number
+      enter_slabs();
+      contract_slab();
     }
     if constexpr (CLASSES) {
       if (class0 == 0) {
@@ -735,6 +753,15 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
           default:
           PHOTON_GEMM_CASE(T_128x128, (gemm_tile_kernel<128, 128, 4, 2, 3, OUT, true>), 512, 3)
         }
+      }
+    }
+    // A workgroup that has its compute unit to itself takes two slabs per barrier: a barrier and the operand reads behind it are
+    // most of what a slab of a 64 x 32 tile costs (one / two: 1 row 16384 x 2048 57 / 44 us, 64 rows 8192 x 2048 30.2 / 24.0 us, 512
+    // rows 2048 x 512 9.8 / 8.3 us).  64 x 64 tiles lose by it (1000 rows 2048 x 1024 10.8 / 11.5 us).
+    if constexpr (OUT == GEMM_OUT_BF16) {
+      if (plan.kind == T_64x32 && grid <= 256) {
+        static bool attr_set = false;
+        return launch_kernel(gemm_tile_kernel<64, 32, 4, 1, 6, OUT, false, 2>, &attr_set, (unsigned)grid, 256, (size_t)6 * (t.bm + t.bn) * 128, p, st);
       }
     }
     switch (plan.kind) {
