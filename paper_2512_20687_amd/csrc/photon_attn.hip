@@ -558,8 +558,10 @@ __global__ __launch_bounds__(LOCAL_THREADS) void local_attn_kernel(
 // DH: 4 * lanes of a group.  PAD: the head size d_h is smaller than DH (a multiple of 4): surplus lanes carry
 // zeros, and the rotary partner of an element (d_h/2 away, in general not a whole number of lanes) is read from
 // memory instead of from a neighbour lane.
-// PARTS: the projection comes as several partial products.  Code of its own: with few rows this launch is latency only, and
-// fetching its instructions is part of that (two steps of 4 sequences at 128k tokens 6474 us with one code for both, 6448).
+// PARTS: the projection comes as several partial products.  Code of its own: with few rows this launch is latency only.  Two
+// codes / one for both, timed in turn four times: two steps of 4 sequences at 128k tokens 6428 - 6444 / 6459 - 6477 us, a step
+// of one sequence at 32k 1068 / 1073 us, where the runs of one side differ by 0.2 %.  (Traced launch by launch, which keeps
+// the two streams apart, the two are alike: 3.9 - 4.6 us.)
 template <int DH, int NK, bool PAD, bool PARTS>
 __global__ __launch_bounds__(LOCAL_THREADS) void local_step_attn_kernel(
     const float* __restrict__ qkv, int n_parts, int64_t part_stride, float* __restrict__ lk, float* __restrict__ lv, float* __restrict__ out,
