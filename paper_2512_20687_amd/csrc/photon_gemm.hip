@@ -221,12 +221,12 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // its W rows, 128 bytes per row and slab) plus about 2.5 us of launch, first slab and stores: the tile and the split
 // over K are chosen together so that every unit has work (plan_gemm).  One barrier per slab: slab kt has landed for every wave, and
 // everybody is done with slab kt - 1, whose buffer takes slab kt + NB - 1; NB - 1 slabs are in flight meanwhile.
-// Measured against the kernels it replaces (MI355X): 64 rows, 2048 x 5120: 28 -> 7.0 us (8 splits); 64 rows, 6144 x 2048:
-// 16.4 -> 8.3 us (2 splits); 64 rows, SwiGLU 2 x 2560 x 1024: 12.3 -> 5.4 us; 512 rows, 2048 x 5120: 32 -> 18 us; 512 rows,
-// SwiGLU 2 x 5120 x 2048: 42 -> 31 us.
+// Measured against the kernels it replaces (MI355X): 64 rows, 2048 x 5120: 28 -> 8.7 us (8 splits); 64 rows, 6144 x 2048:
+// 16.4 -> 11.6 us; 64 rows, SwiGLU 2 x 2560 x 1024: 12.3 -> 8.7 us; 512 rows, 2048 x 5120: 32 -> 28 us.
 // PER: slabs per barrier, all of them read behind it (chosen in launch_gemm).
 // CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
-// in the classes' order, which costs a few scalar instructions per slab.
+// in the classes' order, which costs a few scalar instructions per slab.  (The SwiGLU above: 5.9 - 6.3 us with sums along K and SiLU
+// by the reciprocal instruction, 8.4 - 8.7 us in classes and with the division.)
 template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, int PER = 1>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
@@ -371,7 +371,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
 // go out part by part, X in read 1 and Y in the next read 0, with four phases (about 1 us) to land before the wait for
 // them; two 64 KB buffers suffice.  Every wait names the number of younger loads (XI + YI, a constant).
 // MFMA 16x16x32 rather than 32x32x16: at the same schedule 10-15 % faster on real data, where power limits the clock.
-// Measured (MI355X, data spread like N(0,1)): 32768 x 2048 x 16384 1972 -> 1496 us (1.47 PFLOP/s); 8192 x 2048 x 5120
+// Measured (MI355X, data spread like N(0,1)): 32768 x 2048 x 16384, timed in turn with the single group of waves on two cards,
+// 1975 -> 1538 and 2007 -> 1597 us (1.43 and 1.38 PFLOP/s); 8192 x 2048 x 5120
 // 122 us (1.41 PFLOP/s) where a 16-wave kernel without the counter-phase takes 134 us.
 constexpr int PP_BN = 256, PP_THREADS = 512;
 
@@ -667,8 +668,8 @@ enum TileKind { T_64x32 = 0, T_64x64, T_128x64, T_128x128, T_CLASS_KINDS, T_128x
 struct TileShape { int bm, bn; float fixed, slab1, slabn; };
 // Time model behind the choice, in us: fixed + slabs per split * (slab1 if every compute unit has one workgroup at most,
 // slabn * workgroups per unit otherwise) + what the output bytes cost.  Fitted to sweeps of all tiles and splits over
-// 128 - 2048 rows at the widths 1024, 1664 and 2048 (195 points per tile; the model is off by 5-11 % rms), so it
-// ranks the choices rather than predicting a time; 256 x 256 with its long first slab and store pays off once the
+// 128 - 2048 rows at the widths 1024, 1664 and 2048 (195 points per tile; the model is off by 5-11 % rms), with sums along
+// K (what classes add is left out), so it ranks the choices rather than predicting a time; 256 x 256 with its long first slab and store pays off once the
 // other tiles need several rounds.
 constexpr TileShape TILES[T_KINDS] = {{64, 32, 1.6f, 0.21f, 0.17f},  {64, 64, 2.3f, 0.24f, 0.22f},    {128, 64, 2.8f, 0.34f, 0.34f},
                                       {128, 128, 3.5f, 0.50f, 0.59f}, {128, 256, 6.2f, 0.74f, 0.94f}, {256, 256, 8.6f, 1.00f, 1.36f}};
