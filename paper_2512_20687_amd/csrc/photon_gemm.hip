@@ -223,17 +223,18 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // everybody is done with slab kt - 1, whose buffer takes slab kt + NB - 1; NB - 1 slabs are in flight meanwhile.
 // Measured against the kernels it replaces (MI355X): 64 rows, 2048 x 5120: 28 -> 8.7 us (8 splits); 64 rows, 6144 x 2048:
 // 16.4 -> 11.6 us; 64 rows, SwiGLU 2 x 2560 x 1024: 12.3 -> 8.7 us; 512 rows, 2048 x 5120: 32 -> 28 us.
-// PER: slabs per barrier, all of them read behind it (chosen in launch_gemm).
+// AHEAD: a barrier in the middle of each slab, behind which the next slab's first operands are read under the MFMAs of this one's
+// second half, and NB slabs in flight: for workgroups that have their unit to themselves (launch_gemm).
 // CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
 // in the classes' order, which costs a few scalar instructions per slab.  (The SwiGLU above: 5.9 - 6.3 us with sums along K and SiLU
 // by the reciprocal instruction, 8.4 - 8.7 us in classes and with the division.)
-template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, int PER = 1>
+template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, bool AHEAD = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
   constexpr int WAVES = WM * WN, STAGE = (BM + BN) * 128;
   constexpr int LPS = (BM + BN) / 8 / WAVES;                     // load instructions per wave and slab
   constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;            // MFMA tiles of a wave
-  static_assert(PER == 1 || (PER == 2 && !CLASSES), "pairs of slabs along K");
+  static_assert(!(AHEAD && CLASSES), "read ahead along K");
   static_assert((BM + BN) / 8 % WAVES == 0, "every wave moves the same number of rows");
   static_assert(!GU || TJ % 2 == 0, "a wave holds gate and up columns in pairs");
   extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows]
@@ -295,54 +296,72 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
     }
   };
 
+  if constexpr (AHEAD) {
+    bf16x8_t xf[2][TI], wf[2][TJ];                               // [k step of the slab]
+    auto read = [&](int buf, int ks) {
+      const char* s = lds + buf * STAGE;
 #pragma unroll
-  for (int s = 0; s < NB - PER; ++s) load(s);
-  int buf = 0, next = NB - PER;
-  auto contract_slab = [&] {
-    const char* s = lds + buf * STAGE;
+      for (int i = 0; i < TI; ++i) xf[ks][i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      bf16x8_t xf[TI], wf[TJ];
-#pragma unroll
-      for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
+      for (int j = 0; j < TJ; ++j) wf[ks][j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mma = [&](int ks) {
 #pragma unroll
       for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
-    }
-    buf = buf + 1 < NB ? buf + 1 : 0;
-  };
-  // The next PER slabs have landed (NB - 2 PER younger ones may be in flight), everybody is done with the last PER.
-  auto enter_slabs = [&] {
-    wait_loads_and_barrier<(NB - 2 * PER) * LPS>();              // (behind a class's stores, which count as well, longer than it has to be)
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      load(next);
-      next = next + 1 < NB ? next + 1 : 0;
-    }
-  };
-  for (int c = class0; c < class1; ++c) {
+        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][j], xf[ks][i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
     clear();
-    int left = class_slabs(c);
-    for (; left >= PER; left -= PER) {
-      enter_slabs();
 #pragma unroll
-      for (int u = 0; u < PER; ++u) contract_slab();
+    for (int s = 0; s < NB; ++s) load(s);
+    wait_loads_and_barrier<(NB - 1) * LPS>();                    // slab 0
+    read(0, 0);
+    int buf = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      read(buf, 1);
+      mma(0);
+      wait_loads_and_barrier<(NB - 2) * LPS>();                  // slab kt + 1 has landed, everybody holds the rest of slab kt in registers
+      load(buf);                                                 // slab kt + NB
+      buf = buf + 1 < NB ? buf + 1 : 0;
+      read(buf, 0);                                              // (after the last slab: a landed buffer, not used)
+      mma(1);
     }
-    if (PER > 1 && left > 0) {                                   // PER == 2, the last slab of an odd number
-      enter_slabs();
-      contract_slab();
-    }
-    if constexpr (CLASSES) {
-      if (class0 == 0) {
+  } else {
 #pragma unroll
-        for (int i = 0; i < TI; ++i)
+    for (int s = 0; s < NB - 1; ++s) load(s);
+    int buf = 0, next = NB - 1;
+    for (int c = class0; c < class1; ++c) {
+      clear();
+      for (int left = class_slabs(c); left > 0; --left) {
+        wait_loads_and_barrier<(NB - 2) * LPS>();                // (behind a class's stores, which count as well, longer than it has to be)
+        load(next);
+        const char* s = lds + buf * STAGE;
 #pragma unroll
-          for (int j = 0; j < TJ; ++j) sum[i][j] = c == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
-      } else if (OUT == GEMM_OUT_F32 && c + 1 < class1) {
-        store(acc, c + 1 - p.split_classes);
+        for (int ks = 0; ks < 2; ++ks) {
+          bf16x8_t xf[TI], wf[TJ];
+#pragma unroll
+          for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
+#pragma unroll
+          for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+        }
+        buf = buf + 1 < NB ? buf + 1 : 0;
+        next = next + 1 < NB ? next + 1 : 0;
+      }
+      if constexpr (CLASSES) {
+        if (class0 == 0) {
+#pragma unroll
+          for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) sum[i][j] = c == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
+        } else if (OUT == GEMM_OUT_F32 && c + 1 < class1) {
+          store(acc, c + 1 - p.split_classes);
+        }
       }
     }
   }
@@ -669,8 +688,8 @@ struct TileShape { int bm, bn; float fixed, slab1, slabn; };
 // Time model behind the choice, in us: fixed + slabs per split * (slab1 if every compute unit has one workgroup at most,
 // slabn * workgroups per unit otherwise) + what the output bytes cost.  Fitted to sweeps of all tiles and splits over
 // 128 - 2048 rows at the widths 1024, 1664 and 2048 (195 points per tile; the model is off by 5-11 % rms), with sums along
-// K (what classes add is left out), so it ranks the choices rather than predicting a time; 256 x 256 with its long first slab and store pays off once the
-// other tiles need several rounds.
+// K (what classes add is left out), so it ranks the choices rather than predicting a time; 256 x 256 with its long first slab
+// and store pays off once the other tiles need several rounds.
 constexpr TileShape TILES[T_KINDS] = {{64, 32, 1.6f, 0.21f, 0.17f},  {64, 64, 2.3f, 0.24f, 0.22f},    {128, 64, 2.8f, 0.34f, 0.34f},
                                       {128, 128, 3.5f, 0.50f, 0.59f}, {128, 256, 6.2f, 0.74f, 0.94f}, {256, 256, 8.6f, 1.00f, 1.36f}};
 constexpr float US_PER_MB_OUT = 0.18f, US_PER_MB_PARTS = 0.17f;      // writing the output; reading partial products back
@@ -756,13 +775,16 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
         }
       }
     }
-    // A workgroup that has its compute unit to itself takes two slabs per barrier: a barrier and the operand reads behind it are
-    // most of what a slab of a 64 x 32 tile costs (one / two: 1 row 16384 x 2048 57 / 44 us, 64 rows 8192 x 2048 30.2 / 24.0 us, 512
-    // rows 2048 x 512 9.8 / 8.3 us).  64 x 64 tiles lose by it (1000 rows 2048 x 1024 10.8 / 11.5 us).
+    // The chunker's tiles that have a compute unit each: the barrier and the operand reads behind it are most of what a slab costs,
+    // so the reads go ahead (behind the barrier / ahead: 1 row 16384 x 2048 57.2 / 36.4 us, 64 rows 8192 x 2048 30.2 / 20.1 us, 512 rows
+    // 2048 x 512 9.8 / 7.5 us; 64 x 64 tiles: 400 rows 8192 x 2048 32.4 / 28.9 us, 1000 rows 2048 x 1024 11.2 / 10.3 us).
     if constexpr (OUT == GEMM_OUT_BF16) {
-      if (plan.kind == T_64x32 && grid <= 256) {
-        static bool attr_set = false;
-        return launch_kernel(gemm_tile_kernel<64, 32, 4, 1, 6, OUT, false, 2>, &attr_set, (unsigned)grid, 256, (size_t)6 * (t.bm + t.bn) * 128, p, st);
+      if (grid <= 256) {
+        switch (plan.kind) {
+          PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 6, OUT, false, true>), 256, 6)
+          PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT, false, true>), 256, 4)
+          default: break;
+        }
       }
     }
     switch (plan.kind) {

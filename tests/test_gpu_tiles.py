@@ -37,11 +37,12 @@ def check_chunker(rows, K, N):
 
 # Every tile of the contraction at one, two and three K slabs, fewer and more than it loads ahead: a row more or less than whole
 # row tiles, a last column tile of 16 columns, a tile count that is no multiple of the 8 XCDs.
-# The narrowest also at odd and even numbers of slabs above that, with and without a unit to itself (one or two slabs per barrier).
+# The narrow ones also at odd and even numbers of slabs above that, with and without a unit to themselves (operands read ahead or not).
 @pytest.mark.parametrize("tile,rows,K,N", [
     ((64, 32), 63, 64, 48), ((64, 32), 65, 128, 80), ((64, 32), 193, 192, 144), ((64, 32), 1, 704, 80), ((64, 32), 129, 768, 2000),
     ((64, 32), 77, 320, 4944), ((64, 32), 127, 384, 4944),
     ((64, 64), 9473, 64, 592), ((64, 64), 11777, 128, 208), ((64, 64), 9855, 192, 144),
+    ((64, 64), 191, 704, 3216), ((64, 64), 255, 768, 3856), ((64, 64), 2369, 768, 336),
     ((128, 64), 62719, 64, 144), ((128, 64), 29697, 128, 144), ((128, 64), 19711, 192, 144),
     ((128, 128), 28927, 64, 1040), ((128, 128), 25855, 128, 528), ((128, 128), 23553, 192, 400),
     ((128, 256), 20481, 64, 4624), ((128, 256), 7425, 128, 6416), ((128, 256), 14337, 192, 2064), ((128, 256), 641, 704, 8208),
