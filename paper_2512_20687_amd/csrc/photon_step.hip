@@ -9,6 +9,7 @@
 #include "photon_host.h"
 #include "photon_linear.h"
 #include "photon_persistent.h"
+#include "photon_small.h"
 
 namespace photon {
 
@@ -701,11 +702,43 @@ static int32_t hier_reencode(const Ctx& x, const int32_t* tokens, const float** 
   return PHOTON_OK;
 }
 
+// A decode level, or chunker and STEP, of a small fp32 model in one launch (photon_small.hip).
+static SmallLevel small_level(const Ctx& x, int l, const float* cond_in, float* units, const int32_t* forced, int32_t* out_tokens,
+                              const photon_trace* tr) {
+  const photon_config& c = *x.c;
+  SmallLevel a;
+  a.mod = &x.w->dec[l - 1]; a.conv_w = x.w->conv_w[l - 1]; a.conv_b = x.w->conv_b[l - 1]; a.cond = cond_in; a.units = units;
+  a.n_chunks = x.p.chunks[l]; a.n_layers = c.n_layers; a.D = c.D; a.F = c.d_ff; a.H = c.H; a.C = c.C[l - 1]; a.R = c.R[l - 1];
+  a.eps = c.rms_eps; a.theta = c.rope_theta;
+  if (l == 1) {
+    const bool traced = tr && tr->logits;
+    a.W_lm = x.w->W_lm; a.E = x.w->E_dec; a.vocab = c.vocab; a.forced = forced; a.tokens = out_tokens;
+    a.logits = traced ? tr->logits : x.f(x.p.logits);
+    a.ld_logits = traced ? (int64_t)a.C * c.vocab : c.vocab;
+    a.ld_item = traced ? c.vocab : 0;
+    if (c.L >= 2 && !(tr && tr->new_units[0])) a.units = nullptr;   // nobody reads the token level's items
+  }
+  return a;
+}
+
+static SmallStep small_step(const Ctx& x, const float* bottleneck, float* a_hat) {
+  const photon_config& c = *x.c;
+  SmallStep a;
+  a.mod = &x.w->top; a.chunker_w = x.w->chunker_w; a.chunker_b = x.w->chunker_b; a.bottleneck = bottleneck; a.a_hat = a_hat;
+  a.x_top = x.s->x_top; a.k_cache = (float*)x.s->k_cache; a.v_cache = (float*)x.s->v_cache; a.seq_len = x.s->seq_len; a.S_max = x.s->S_max;
+  a.Bt = x.Bt; a.n_layers = c.n_layers; a.D = c.D; a.F = c.d_ff; a.H = c.H; a.CL = c.C[c.L - 1]; a.eps = c.rms_eps; a.theta = c.rope_theta;
+  return a;
+}
+
+static bool takes_small(const Ctx& x, const SmallLevel& a) { return !x.bf16 && !g_no_persistent && small_level_pays(a); }
+static bool takes_small(const Ctx& x, const SmallStep& a) { return !x.bf16 && !g_no_persistent && small_step_pays(a); }
+
 // (ii) top chunker (Eq. 4) on the C_L new level-(L-1) units of every sequence, (iii) STEP (Eq. 13).
 static int32_t chunk_and_step(const Ctx& x, const float* bottleneck, const photon_trace* tr) {
   const photon_config& c = *x.c;
   const int D = c.D, CL = c.C[c.L - 1];
   float* a_hat = (tr && tr->a_hat) ? tr->a_hat : x.f(x.p.a_hat);
+  if (const SmallStep a = small_step(x, bottleneck, a_hat); takes_small(x, a)) return launch_small_step(a, x.st);
   PHOTON_TRY(linear(x, RowSource{bottleneck, (int64_t)CL * D}, x.w->chunker_w, nullptr, x.w->chunker_b, a_hat, D, x.Bt, D, CL * D));
   return top_step(x, RowSource{a_hat, D});
 }
@@ -725,6 +758,12 @@ static int32_t decode_level(const Ctx& x, int l, const float* cond_in, float* un
   const int64_t n = x.p.chunks[l];
   const photon_module_weights& mod = x.w->dec[l - 1];
   float* h = x.f(x.o_h);
+  if (const SmallLevel a = small_level(x, l, cond_in, units, forced, out_tokens, tr); takes_small(x, a)) {
+    PHOTON_TRY(launch_small_level(a, x.st));
+    if (after_converter != nullptr && hipEventRecord(after_converter, x.st) != hipSuccess)
+      return fail(PHOTON_ERR_HIP, "decode step: cannot record the event that frees the conditioning buffer");
+    return PHOTON_OK;
+  }
   // sub-step 0: the converter's R vectors at window positions 0..R-1 (row ch*R + r of a flat [n*R, D] view of h)
   PHOTON_TRY(linear(x, RowSource{cond_in, D}, x.w->conv_w[l - 1], nullptr, x.w->conv_b[l - 1], h, (int64_t)R * D, (int)n, R * D, D));
   if (after_converter != nullptr && hipEventRecord(after_converter, x.st) != hipSuccess)
@@ -831,7 +870,10 @@ static int32_t decode_step_impl(const Ctx& x, photon_state* st, const int32_t* f
         hipStreamWaitEvent(x.st, (hipEvent_t)st->free_event, 0) != hipSuccess)      // the previous step's lower levels have read cond_top
       return fail(PHOTON_ERR_HIP, "decode step: cannot wait for the conditioning buffer");
     PHOTON_TRY(condition_lower(top, L, fresh[L - 1], cond_top));
-    if (x.overlap && x.hs == nullptr) {
+    // Where a joined step's STEP and token level are a launch each, the fork and the join cost more than they hide.
+    const bool two_launches = !pipelined && L == 2 && takes_small(x, small_level(x, 1, cond_top, fresh[0], forced, out_tokens, tr)) &&
+                              takes_small(top, small_step(top, fresh[L - 1], nullptr));
+    if (x.overlap && x.hs == nullptr && !two_launches) {
       if (hipEventRecord((hipEvent_t)st->fork_event, x.st) != hipSuccess || hipStreamWaitEvent(side_st, (hipEvent_t)st->fork_event, 0) != hipSuccess)
         return fail(PHOTON_ERR_HIP, "decode step: cannot fork the lower levels");
       Ctx side = x;

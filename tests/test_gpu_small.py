@@ -1,0 +1,80 @@
+"""Small fp32 models: a decode level, and the chunker with the STEP behind it, as one launch each, against the oracle and against
+the separate launches they replace."""
+import numpy as np
+import pytest
+import torch
+
+import seeded_inputs as si
+from test_gpu_decode_step import check_against_oracle
+from util import TOL, nerr, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _profiled_launches(cfg, w, st, Bt, S_max, persistent):
+    import paper_2512_20687_amd as ph
+    ph.photon_set_persistent(persistent)
+    try:
+        model = ph.PhotonModel(cfg, w)
+        state = ph.PhotonState(model, Bt, S_max, k=st["k"], v=st["v"], seq_len=st["seq_len"], x_top=st["x_top"], carry=st["carry"])
+        logits = torch.empty((Bt, cfg.meta_context, cfg.vocab), device="cuda")
+        toks = torch.empty((Bt, cfg.meta_context), dtype=torch.int32, device="cuda")
+        ph.photon_profile_reset()
+        ph.photon_profile_enable(True)
+        ph.photon_decode_step(model, state, toks, trace={"logits": logits})
+        torch.cuda.synchronize()
+        ph.photon_profile_enable(False)
+        n = sum(launches for launches, _ in ph.photon_profile_get().values())
+        ph.photon_profile_reset()
+        return state, toks, logits, n
+    finally:
+        ph.photon_set_persistent(True)
+        ph.photon_profile_enable(False)
+
+
+@pytest.mark.parametrize("kw,Bt,S0,S_max", [
+    (dict(), 1, 16, 128),                                        # the tiny configuration
+    (dict(D=16, H=1, d_h=16, d_ff=40, vocab=500), 2, 1, 5),      # narrower than a k step, one head, odd cache, one entry
+    (dict(D=20, H=5, d_h=4, d_ff=4, vocab=1), 3, 5, 6),          # smallest heads, one column
+    (dict(D=96, H=3, d_h=32, d_ff=240, vocab=1000), 8, 37, 40),  # heads that do not divide the waves, several k steps
+    (dict(D=128, H=2, d_h=64, d_ff=320, R=(2, 2), C=(4, 3)), 2, 100, 131),
+    (dict(D=128, H=1, d_h=128, d_ff=320, vocab=300), 2, 9, 64),  # widest head
+    (dict(D=120, H=10, d_h=12, d_ff=0, n_layers=2), 3, 20, 33),  # more heads than waves, no feed-forward
+    (dict(n_layers=8, d_ff=64), 1, 3, 7),                        # as many blocks as the arguments hold
+    (dict(L=3, C=(2, 3, 2), R=(1, 2, 1), n_layers=2), 3, 9, 24),
+    (dict(L=1, C=(4,), R=(2,)), 2, 9, 24),
+    (dict(rope_theta=0.0, C=(2, 5)), 2, 9, 24),
+])
+def test_small_step_against_oracle_and_separate_launches(kw, Bt, S0, S_max):
+    require_gpu()
+    base = dict(L=2, C=(4, 4), R=(1, 1), D=64, H=2, d_h=32, n_layers=1, d_ff=160, vocab=512, dtype="f32")
+    base.update(kw)
+    cfg = si.PhotonConfig(**base)
+    w = si.make_weights(cfg, 21)
+    st = si.make_decode_state(cfg, Bt, S0, S_max, seed=5)
+    st["seq_len"] = np.array([max(1, S0 - 3 * b) for b in range(Bt)], np.int32)
+    if cfg.vocab > 1:
+        check_against_oracle(cfg, w, st, Bt, S_max, None, TOL["f32"])
+    one, toks1, logits1, n1 = _profiled_launches(cfg, w, st, Bt, S_max, True)
+    sep, toks0, logits0, n0 = _profiled_launches(cfg, w, st, Bt, S_max, False)
+    assert n1 == 2 * cfg.L + 1 < n0, (n1, n0)                    # begin, levels, conditioning, chunker with STEP
+    assert torch.equal(toks1, toks0)
+    # both are sums of at most a few thousand fp32 products in another order: 1e-6 of the largest value each
+    for a, b in ((logits1, logits0), (one.x_top, sep.x_top), (one.carry, sep.carry), (one.k, sep.k), (one.v, sep.v)):
+        if a.numel():
+            assert nerr(a, b.double().cpu().numpy()) < 5e-6
+
+
+def test_small_step_full_cache():
+    """A full cache: the new entry overwrites the last one, as with separate launches, and nothing is written behind it."""
+    require_gpu()
+    cfg = si.PhotonConfig(L=2, C=(4, 4), R=(1, 1), D=64, H=2, d_h=32, n_layers=2, d_ff=160, vocab=96, dtype="f32")
+    w = si.make_weights(cfg, 3)
+    S_max = 9
+    st = si.make_decode_state(cfg, 2, 9, S_max, seed=5)
+    st["seq_len"] = np.array([9, 8], np.int32)
+    one, toks1, logits1, _ = _profiled_launches(cfg, w, st, 2, S_max, True)
+    sep, toks0, logits0, _ = _profiled_launches(cfg, w, st, 2, S_max, False)
+    assert torch.equal(one.seq_len, sep.seq_len) and torch.equal(one.status, sep.status) and int(one.status) == 1
+    for a, b in ((logits1, logits0), (one.x_top, sep.x_top), (one.k, sep.k), (one.v, sep.v)):
+        assert nerr(a, b.double().cpu().numpy()) < 5e-6
