@@ -8,7 +8,7 @@
 //
 // K is walked in slabs of 64: rows of x and W move global -> LDS directly (no staging registers), several slabs ahead
 // of the one that the matrix cores contract, and MFMA 16x16x32 tiles accumulate in registers.  Two kernels: one group of
-// waves with three or four slab buffers (tiles of 64 x 32 to 128 x 128), and two groups in counter-phase (128 x 256 and
+// waves with three or more slab buffers (tiles of 32 x 32 to 128 x 160), and two groups in counter-phase (128 x 256 and
 // 256 x 256).  A contraction of fewer than 128 rows is too small to fill the chip and is split over K as well: the fp32
 // partial products go to a scratch area and are added, in a fixed order, by the kernel that reads the result anyway (the row
 // kernel in front of the next contraction, the attention kernels).  The gate/up projection forms SwiGLU in the accumulators.
@@ -81,11 +81,12 @@ __device__ __forceinline__ bf16x8_t fragment(const char* slab, int r, int c16) {
 }
 
 // Row of W behind staged W row r of a tile whose output columns start at n0 (clamped into the matrix).  SwiGLU: 16 gate
-// rows, then the 16 up rows of the same columns, so that both products of a column meet in one lane.
-template <bool GU> __device__ __forceinline__ int weight_row(int r, int n0, int N) {
+// rows, then the 16 up rows of the same columns, so that both products of a column meet in one lane; IN8 (a wave holds an odd
+// number of MFMA tiles): 8 gate rows, then the 8 up rows of the same columns, which meet in lanes l and l + 32.
+template <bool GU, bool IN8 = false> __device__ __forceinline__ int weight_row(int r, int n0, int N) {
   if (!GU) return n0 + r < N ? n0 + r : N - 1;
-  const int c = n0 + (r >> 5) * 16 + (r & 15);
-  return (c < N ? c : N - 1) + ((r >> 4) & 1) * N;
+  const int c = IN8 ? n0 + (r >> 4) * 8 + (r & 7) : n0 + (r >> 5) * 16 + (r & 15);
+  return (c < N ? c : N - 1) + ((r >> (IN8 ? 3 : 4)) & 1) * N;
 }
 
 template <int VM> __device__ __forceinline__ void wait_loads_and_barrier() {
@@ -98,6 +99,7 @@ template <int OUT, int TJ>
 __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&acc)[TJ], int m, int n0, int wave_col, int fk, int part) {
   if (m >= p.M) return;
   if constexpr (OUT == GEMM_OUT_SWIGLU) {
+    static_assert(TJ % 2 == 0, "gate and up tiles in turn");
 #pragma unroll
     for (int j = 0; j < TJ; j += 2) {
       const int n = n0 + (wave_col + j * 16) / 2 + fk * 4;
@@ -120,6 +122,27 @@ __device__ __forceinline__ void store_row(const GemmArgs& p, const float4_t (&ac
         *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)m * p.ldo + n) = uint2{pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w)};
       }
     }
+  }
+}
+
+// SwiGLU of two MFMA rows m and m + 16 in the IN8 order: the halves of the wave trade accumulators, after which the lower lanes
+// hold gate and up of row m, the upper lanes of row m + 16.
+template <int TJ>
+__device__ __forceinline__ void store_swiglu_rows(const GemmArgs& p, const float4_t (&lo)[TJ], const float4_t (&hi)[TJ], int m, int n0, int wave_col, int fk) {
+  typedef uint32_t uint2_native __attribute__((ext_vector_type(2)));
+  const int row = m + (fk >> 1) * 16;
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    float4_t g, u;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint2_native r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo[j][t]), __float_as_uint(hi[j][t]), false, false);
+      g[t] = __uint_as_float(r[0]); u[t] = __uint_as_float(r[1]);
+    }
+    const int n = n0 + (wave_col + j * 16) / 2 + (fk & 1) * 4;
+    if (row < p.M && n < p.N)
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(p.out) + (int64_t)row * p.ldo + n) =
+          uint2{pack_bf16x2(silu(g.x) * u.x, silu(g.y) * u.y), pack_bf16x2(silu(g.z) * u.z, silu(g.w) * u.w)};
   }
 }
 
@@ -219,24 +242,26 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // WM x WN waves share a BM x BN tile.  A compute unit is fed at 40 to 100 bytes per ns here, depending on how many
 // workgroups share it, so what a small contraction costs is the bytes its busiest unit has to take in (its x rows and
 // its W rows, 128 bytes per row and slab) plus about 2.5 us of launch, first slab and stores: the tile and the split
-// over K are chosen together so that every unit has work (plan_gemm).  One barrier per slab: slab kt has landed for every wave, and
-// everybody is done with slab kt - 1, whose buffer takes slab kt + NB - 1; NB - 1 slabs are in flight meanwhile.
+// over K are chosen together so that every unit has work (plan_gemm).
 // Measured against the kernels it replaces (MI355X): 64 rows, 2048 x 5120: 28 -> 8.7 us (8 splits); 64 rows, 6144 x 2048:
 // 16.4 -> 11.6 us; 64 rows, SwiGLU 2 x 2560 x 1024: 12.3 -> 8.7 us; 512 rows, 2048 x 5120: 32 -> 28 us.
-// AHEAD: a barrier in the middle of each slab, behind which the next slab's first operands are read under the MFMAs of this one's
-// second half, and NB slabs in flight: for workgroups that have their unit to themselves (launch_gemm).
+// Sums along K: within a slab the operand reads of one half go out among the MFMAs of the other half, one read at a time: reads issued together
+// in front of the MFMAs keep the matrix cores waiting, as all waves leave the barrier together.  The one barrier per slab lies
+// between the halves: everybody then holds the rest of slab kt in registers, slab kt + 1 has landed, and the buffer takes slab
+// kt + NB.  Against reads, then MFMAs behind the barrier (512 rows, weights in the memory-side cache / in HBM): 64 x 64 tiles
+// 2048 x 2048 10.7 / 11.8 -> 9.4 / 11.6 us, 2048 x 5120 22.2 / 26.7 -> 19.0 / 25.8 us; 128 x 128, 6144 x 2048 21.7 / 24.5 -> 20.8 / 23.3 us.
+// Small wave tiles help for the same reason: 32 x 32 by four waves.
 // CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
-// in the classes' order, which costs a few scalar instructions per slab.  (The SwiGLU above: 5.9 - 6.3 us with sums along K and SiLU
-// by the reciprocal instruction, 8.4 - 8.7 us in classes and with the division.)
-template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, bool AHEAD = false>
+// in the classes' order, which costs a few scalar instructions per slab.
+template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
   constexpr int WAVES = WM * WN, STAGE = (BM + BN) * 128;
-  constexpr int LPS = (BM + BN) / 8 / WAVES;                     // load instructions per wave and slab
+  constexpr int PIECES = (BM + BN) / 8, LPS = (PIECES + WAVES - 1) / WAVES;   // load instructions of a slab, and per wave
   constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;            // MFMA tiles of a wave
-  static_assert(!(AHEAD && CLASSES), "read ahead along K");
-  static_assert((BM + BN) / 8 % WAVES == 0, "every wave moves the same number of rows");
-  static_assert(!GU || TJ % 2 == 0, "a wave holds gate and up columns in pairs");
+  constexpr bool IN8 = GU && TJ % 2 != 0;
+  static_assert(!IN8 || TI % 2 == 0, "a wave trades rows in pairs");
+  static_assert(BM % 8 == 0 && NB >= 2, "");
   extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -247,22 +272,26 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
   const int class0 = CLASSES ? at.split * p.split_classes : 0;
   const int class1 = CLASSES ? min(class0 + p.split_classes, classes) : 1;
 
+  // Piece of load instruction i: 8 rows.  Where the pieces do not divide, surplus instructions repeat the last piece (the same
+  // bytes to the same place), so that every wave has the same number of loads in flight.
+  auto piece = [&](int i) { const int q = i * WAVES + wave; return PIECES % WAVES == 0 || q < PIECES ? q : PIECES - 1; };
   const char* src[LPS];
 #pragma unroll
   for (int i = 0; i < LPS; ++i) {
-    const int r = (i * WAVES + wave) * 8 + (lane >> 3);
+    const int r = piece(i) * 8 + (lane >> 3);
     const bf16_t* row;
-    if ((i * WAVES + wave) * 8 < BM) row = p.x + (int64_t)(m0 + r < p.M ? m0 + r : p.M - 1) * p.K;   // past the end: never stored
-    else row = p.W + (int64_t)weight_row<GU>(r - BM, n0, p.N) * p.K;
+    if (piece(i) * 8 < BM) row = p.x + (int64_t)(m0 + r < p.M ? m0 + r : p.M - 1) * p.K;   // past the end: never stored
+    else row = p.W + (int64_t)weight_row<GU, IN8>(r - BM, n0, p.N) * p.K;
     src[i] = reinterpret_cast<const char*>(row + swizzled_column(r, lane & 7) * 8);
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)lds;
-  // Slab that is loaded next, and its class.  Past the end: the last slab again, into a buffer nobody reads.
+  // Slab that is loaded next, and its class.  Past the end: the last slab again, into a buffer nobody reads (every wait then names a
+  // constant; waits chosen by what is left, without those loads: 64 rows, SwiGLU 2 x 2560 x 1024 8.4 -> 9.5 us).
   int ahead = CLASSES ? class0 * CHUNK_SLABS : 0, ahead_class = class0;
   auto load = [&](int buf) {
     const int64_t ko = (int64_t)ahead * (G_BK * 2);
 #pragma unroll
-    for (int i = 0; i < LPS; ++i) load16_to_lds(src[i] + ko, lds0 + buf * STAGE + (i * WAVES + wave) * 1024);
+    for (int i = 0; i < LPS; ++i) load16_to_lds(src[i] + ko, lds0 + buf * STAGE + piece(i) * 1024);
     if constexpr (!CLASSES) {
       if (ahead + 1 < KT) ++ahead;
     } else {
@@ -279,59 +308,69 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
     return n * CHUNK_SLABS - ((chunks - 1) % K_CLASSES == c ? chunks * CHUNK_SLABS - KT : 0);
   };
   float4_t acc[TI][TJ], sum[CLASSES ? TI : 1][CLASSES ? TJ : 1];
+  const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
+  const int fr = lane & 15, fk = lane >> 4;                      // operand fragment: row, 8-wide k group
+  auto store = [&](const float4_t (&y)[TI][TJ], int part) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      if constexpr (IN8) {
+        if (i % 2 == 0) store_swiglu_rows<TJ>(p, y[i], y[i + 1], m0 + wm + i * 16 + fr, n0, wn, fk);
+      } else if constexpr (OUT == GEMM_OUT_QKV) {
+        store_qkv<TJ>(p, y[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
+      } else {
+        store_row<OUT, TJ>(p, y[i], m0 + wm + i * 16 + fr, n0, wn, fk, part);
+      }
+      if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, y[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
+    }
+  };
+
+  bf16x8_t xf[2][TI], wf[2][TJ];                                 // [half of the slab]
+  auto read_one = [&](int buf, int ks, int t) {
+    const char* s = lds + buf * STAGE;
+    if (t < TJ) wf[ks][t] = fragment(s, BM + wn + t * 16 + fr, ks * 4 + fk);
+    else xf[ks][t - TJ] = fragment(s, wm + (t - TJ) * 16 + fr, ks * 4 + fk);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // MFMAs of half 1 - KS of the slab at hand; under the first three quarters of them the operands of half KS of buffer `buf`
+  auto half = [&](int buf, auto KS) {
+    constexpr int ks = decltype(KS)::value, READS = TI + TJ, MFMAS = TI * TJ, SPAN = (MFMAS * 3 + 3) / 4;
+#pragma unroll
+    for (int q = 0; q < MFMAS; ++q) {
+#pragma unroll
+      for (int t = 0; t < READS; ++t)
+        if (t * SPAN / READS == q) read_one(buf, ks, t);
+      const int i = q % TI, j = q / TI;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[1 - ks][j], xf[1 - ks][i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   auto clear = [&] {
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
       for (int j = 0; j < TJ; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
   };
-  const int wm = (wave / WN) * (BM / WM), wn = (wave % WN) * (BN / WN);
-  const int fr = lane & 15, fk = lane >> 4;                      // operand fragment: row, 8-wide k group
-  auto store = [&](const float4_t (&y)[TI][TJ], int part) {
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      if constexpr (OUT == GEMM_OUT_QKV) store_qkv<TJ>(p, y[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
-      else store_row<OUT, TJ>(p, y[i], m0 + wm + i * 16 + fr, n0, wn, fk, part);
-      if constexpr (OUT == GEMM_OUT_LOGITS) store_best<TJ>(p, y[i], m0 + wm + i * 16 + fr, n0 + wn, fk);
-    }
-  };
-
-  if constexpr (AHEAD) {
-    bf16x8_t xf[2][TI], wf[2][TJ];                               // [k step of the slab]
-    auto read = [&](int buf, int ks) {
-      const char* s = lds + buf * STAGE;
-#pragma unroll
-      for (int i = 0; i < TI; ++i) xf[ks][i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) wf[ks][j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    auto mma = [&](int ks) {
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][j], xf[ks][i], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    clear();
+  int buf = 0;
+  if constexpr (!CLASSES) {
 #pragma unroll
     for (int s = 0; s < NB; ++s) load(s);
-    wait_loads_and_barrier<(NB - 1) * LPS>();                    // slab 0
-    read(0, 0);
-    int buf = 0;
+    clear();
+    wait_loads_and_barrier<(NB - 1) * LPS>();                    // the first slab
+#pragma unroll
+    for (int t = 0; t < TI + TJ; ++t) read_one(0, 0, t);
     for (int kt = 0; kt < KT; ++kt) {
-      read(buf, 1);
-      mma(0);
-      wait_loads_and_barrier<(NB - 2) * LPS>();                  // slab kt + 1 has landed, everybody holds the rest of slab kt in registers
-      load(buf);                                                 // slab kt + NB
+      half(buf, std::integral_constant<int, 1>{});
+      wait_loads_and_barrier<(NB - 2) * LPS>();
+      load(buf);
       buf = buf + 1 < NB ? buf + 1 : 0;
-      read(buf, 0);                                              // (after the last slab: a landed buffer, not used)
-      mma(1);
+      half(buf, std::integral_constant<int, 0>{});               // (behind the last slab: not used)
     }
   } else {
+    // A class is two slabs where K is 1024: with its sum to be closed every other slab, reads ahead only get in the way (64 rows, K = 1024:
+    // SwiGLU 2 x 2560 8.0 us, with reads ahead 9.5; 3072 columns 6.8 and 7.3).
 #pragma unroll
     for (int s = 0; s < NB - 1; ++s) load(s);
-    int buf = 0, next = NB - 1;
+    int next = NB - 1;
     for (int c = class0; c < class1; ++c) {
       clear();
       for (int left = class_slabs(c); left > 0; --left) {
@@ -340,28 +379,25 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
         const char* s = lds + buf * STAGE;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-          bf16x8_t xf[TI], wf[TJ];
 #pragma unroll
-          for (int i = 0; i < TI; ++i) xf[i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
+          for (int i = 0; i < TI; ++i) xf[ks][i] = fragment(s, wm + i * 16 + fr, ks * 4 + fk);
 #pragma unroll
-          for (int j = 0; j < TJ; ++j) wf[j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
+          for (int j = 0; j < TJ; ++j) wf[ks][j] = fragment(s, BM + wn + j * 16 + fr, ks * 4 + fk);
 #pragma unroll
           for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][j], xf[ks][i], acc[i][j], 0, 0, 0);
         }
         buf = buf + 1 < NB ? buf + 1 : 0;
         next = next + 1 < NB ? next + 1 : 0;
       }
-      if constexpr (CLASSES) {
-        if (class0 == 0) {
+      if (class0 == 0) {
 #pragma unroll
-          for (int i = 0; i < TI; ++i)
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) sum[i][j] = c == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
-        } else if (OUT == GEMM_OUT_F32 && c + 1 < class1) {
-          store(acc, c + 1 - p.split_classes);
-        }
+          for (int j = 0; j < TJ; ++j) sum[i][j] = c == 0 ? acc[i][j] : sum[i][j] + acc[i][j];
+      } else if (OUT == GEMM_OUT_F32 && c + 1 < class1) {
+        store(acc, c + 1 - p.split_classes);
       }
     }
   }
@@ -683,30 +719,49 @@ __global__ __launch_bounds__(256) void copy_bytes16_kernel(const uint4_t* __rest
 
 // ---- which tile, how many splits ------------------------------------------------------------------------------------------
 
-enum TileKind { T_64x32 = 0, T_64x64, T_128x64, T_128x128, T_CLASS_KINDS, T_128x256 = T_CLASS_KINDS, T_256x256, T_KINDS };
-struct TileShape { int bm, bn; float fixed, slab1, slabn; };
+enum TileKind { T_64x32 = 0, T_64x64, T_128x64, T_128x128, T_CLASS_KINDS, T_128x256 = T_CLASS_KINDS, T_256x256, T_32x32, T_128x96, T_128x160, T_KINDS };
+struct TileShape { int bm, bn, wave_columns; };
+constexpr TileShape TILES[T_KINDS] = {{64, 32, 32}, {64, 64, 32}, {128, 64, 32}, {128, 128, 64}, {128, 256, 64}, {256, 256, 64}, {32, 32, 16}, {128, 96, 48}, {128, 160, 80}};
 // Time model behind the choice, in us: fixed + slabs per split * (slab1 if every compute unit has one workgroup at most,
-// slabn * workgroups per unit otherwise) + what the output bytes cost.  Fitted to sweeps of all tiles and splits over
-// 128 - 2048 rows at the widths 1024, 1664 and 2048 (195 points per tile; the model is off by 5-11 % rms), with sums along
-// K (what classes add is left out), so it ranks the choices rather than predicting a time; 256 x 256 with its long first slab
-// and store pays off once the other tiles need several rounds.
-constexpr TileShape TILES[T_KINDS] = {{64, 32, 1.6f, 0.21f, 0.17f},  {64, 64, 2.3f, 0.24f, 0.22f},    {128, 64, 2.8f, 0.34f, 0.34f},
-                                      {128, 128, 3.5f, 0.50f, 0.59f}, {128, 256, 6.2f, 0.74f, 0.94f}, {256, 256, 8.6f, 1.00f, 1.36f}};
+// slabn * workgroups per unit otherwise) + what the output bytes cost.  It ranks the choices rather than predicting a time;
+// 256 x 256 with its long first slab and store pays off once the other tiles need several rounds.
+// PASS: fp32 and SwiGLU results summed along K.  Fitted to a sweep of all tiles over 128 - 3000 rows of 16 projections at the widths
+// 448 to 2048, weights half of the time in the memory-side cache and half in HBM (6-8 % rms); its choice is within 0.3 % of the
+// best tile over the sweep (geometric mean), and 9 % faster than the tiles and the kernels before (up to 1.6 times below 300 rows).
+// CLASSED: sums in classes, and the chunker's own entry point, over 128 - 2048 rows at the widths 1024, 1664 and 2048 (5-11 % rms).
+struct TileTime { float fixed, slab1, slabn; };
+constexpr TileTime CLASSED[] = {{1.6f, 0.21f, 0.17f}, {2.3f, 0.24f, 0.22f}, {2.8f, 0.34f, 0.34f}, {3.5f, 0.50f, 0.59f}, {6.2f, 0.74f, 0.94f}, {8.6f, 1.00f, 1.36f}};
+constexpr TileTime PASS[T_KINDS] = {{2.9f, 0.184f, 0.152f}, {2.8f, 0.217f, 0.218f}, {3.3f, 0.341f, 0.334f}, {4.8f, 0.472f, 0.538f}, {6.9f, 0.779f, 0.903f},
+                                    {9.4f, 1.10f, 1.28f},   {2.2f, 0.151f, 0.106f}, {4.3f, 0.440f, 0.476f}, {5.6f, 0.583f, 0.648f}};
 constexpr float US_PER_MB_OUT = 0.18f, US_PER_MB_PARTS = 0.17f;      // writing the output; reading partial products back
 
 // parts: partial products (1: none); split_classes: classes of K per split (0: the sum runs along K, unsplit)
 struct GemmPlan { int kind, splits, parts, split_classes; };
 
+enum PlanOutput { PLAN_F32, PLAN_SWIGLU, PLAN_LOGITS, PLAN_CHUNKER, PLAN_QKV };
+// Which tiles an output takes.  A wave of the 32 x 32 tile holds 16 columns: half a gate/up pair, less than a stretch of logits.
+// (Results of up to 512 columns keep the 64 x 32 tile that the tests of the order of a sum name; 333 rows of 448, K = 1344: 6.6 us
+// there, 5.3 us by 32 x 32.)  128 x 96 and 128 x 160 fill the units where the other tiles leave a part of them idle or need a second
+// round: 512 rows, SwiGLU 2 x 5120 x 2048, 160 tiles of 128 x 256 32.8 us, 256 tiles of 128 x 160 25.7 us.
+static bool tile_takes(int kind, PlanOutput output, bool classes, int N) {
+  if (classes) return kind < T_CLASS_KINDS;
+  if (output == PLAN_CHUNKER) return kind <= T_256x256;
+  if (output == PLAN_QKV) return kind == T_128x128 || kind == T_128x256 || kind == T_256x256;   // a wave holds a head
+  return kind != T_32x32 || (output == PLAN_F32 && N > 512);
+}
+
 // classes: the sum is formed in classes of K (then not by the counter-phase kernels), and may be split between them.
 // part_cap: floats the scratch area for partial products holds (0: no splitting).  join_us: what reading the partial
 // products back costs beyond the bytes (a launch of its own, or nothing where the next kernel reads the result anyway).
-static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, bool classes, int64_t part_cap, float join_us,
-                          int first_kind = 0, float* model_us = nullptr) {
+static GemmPlan plan_gemm(int64_t M, int N, int K, PlanOutput output, bool classes, int64_t part_cap, float join_us, float* model_us = nullptr) {
+  const bool gate_up = output == PLAN_SWIGLU, out_f32 = output == PLAN_F32 || output == PLAN_LOGITS;
   const int KT = K / G_BK, chunks = (KT + CHUNK_SLABS - 1) / CHUNK_SLABS, n_classes = chunks < K_CLASSES ? chunks : K_CLASSES;
   GemmPlan best{T_64x64, 1, 1, classes ? K_CLASSES : 0};
   float best_us = 1e30f;
   const float out_mb = (float)M * N * (out_f32 ? 4e-6f : 2e-6f);
-  for (int k = first_kind; k < (classes ? T_CLASS_KINDS : T_KINDS); ++k) {
+  for (int k = 0; k < T_KINDS; ++k) {
+    if (!tile_takes(k, output, classes, N)) continue;
+    const TileTime& cost = classes || output == PLAN_CHUNKER ? CLASSED[k] : PASS[k];
     const int bn = gate_up ? TILES[k].bn / 2 : TILES[k].bn;
     const int64_t tiles = (M + TILES[k].bm - 1) / TILES[k].bm * ((N + bn - 1) / bn);
     for (int per = K_CLASSES; per >= 1; per /= 2) {               // classes per split: the first split's come in one part, every other class is one
@@ -715,7 +770,7 @@ static GemmPlan plan_gemm(int64_t M, int N, int K, bool gate_up, bool out_f32, b
       if (parts > 1 && parts * M * N > part_cap) break;
       const int slabs = splits == 1 ? KT : per * ((chunks + K_CLASSES - 1) / K_CLASSES) * CHUNK_SLABS;
       const float rounds = (float)((tiles * splits + 255) / 256);
-      const float us = TILES[k].fixed + slabs * (rounds <= 1.f ? TILES[k].slab1 : TILES[k].slabn * rounds) +
+      const float us = cost.fixed + slabs * (rounds <= 1.f ? cost.slab1 : cost.slabn * rounds) +
                        out_mb * parts * US_PER_MB_OUT + (parts > 1 ? out_mb * parts * US_PER_MB_PARTS + join_us : 0.f);
       if (us < best_us) { best_us = us; best = GemmPlan{k, splits, parts, classes ? per : 0}; }
       if (tiles * splits >= 512) break;                           // more splits only add bytes
@@ -763,33 +818,41 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
     static bool attr_set = false;                                                                              \
     return launch_kernel(KERN, &attr_set, (unsigned)grid, THREADS, (size_t)(BUFS) * (t.bm + t.bn) * 128, p, st); \
   }
-  if constexpr (OUT != GEMM_OUT_QKV) {                           // a wave of the narrow tiles holds half a head
+  if constexpr (OUT != GEMM_OUT_QKV) {                           // a wave of these tiles does not hold a head
     if constexpr (OUT != GEMM_OUT_BF16) {                        // (the chunker's sum always runs along K)
       if (plan.split_classes != 0) {
         switch (plan.kind) {
           PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT, true>), 256, 4)
-          PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT, true>), 256, 4)
+          PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 4, 2, 4, OUT, true>), 512, 4)
           PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT, true>), 512, 3)
           default:
           PHOTON_GEMM_CASE(T_128x128, (gemm_tile_kernel<128, 128, 4, 2, 3, OUT, true>), 512, 3)
         }
       }
+      switch (plan.kind) {
+        PHOTON_GEMM_CASE(T_128x96, (gemm_tile_kernel<128, 96, 4, 2, 3, OUT, false>), 512, 3)
+        PHOTON_GEMM_CASE(T_128x160, (gemm_tile_kernel<128, 160, 4, 2, 3, OUT, false>), 512, 3)
+        default: break;
+      }
     }
-    // The chunker's tiles that have a compute unit each: the barrier and the operand reads behind it are most of what a slab costs,
-    // so the reads go ahead (behind the barrier / ahead: 1 row 16384 x 2048 57.2 / 36.4 us, 64 rows 8192 x 2048 30.2 / 20.1 us, 512 rows
-    // 2048 x 512 9.8 / 7.5 us; 64 x 64 tiles: 400 rows 8192 x 2048 32.4 / 28.9 us, 1000 rows 2048 x 1024 11.2 / 10.3 us).
+    if constexpr (OUT == GEMM_OUT_F32) {
+      if (plan.kind == T_32x32) {
+        static bool attr_set = false;
+        return launch_kernel(gemm_tile_kernel<32, 32, 2, 2, 4, OUT, false>, &attr_set, (unsigned)grid, 256, (size_t)4 * 64 * 128, p, st);
+      }
+    }
+    // 64 x 32 tiles of the chunker, whose sums are long, with a compute unit each: six slabs in flight
     if constexpr (OUT == GEMM_OUT_BF16) {
       if (grid <= 256) {
         switch (plan.kind) {
-          PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 6, OUT, false, true>), 256, 6)
-          PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT, false, true>), 256, 4)
+          PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 6, OUT, false>), 256, 6)
           default: break;
         }
       }
     }
     switch (plan.kind) {
       PHOTON_GEMM_CASE(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT, false>), 256, 4)
-      PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 2, 2, 4, OUT, false>), 256, 4)
+      PHOTON_GEMM_CASE(T_64x64, (gemm_tile_kernel<64, 64, 4, 2, 4, OUT, false>), 512, 4)
       PHOTON_GEMM_CASE(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT, false>), 512, 3)
       default: break;
     }
@@ -820,15 +883,15 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
   p.x = reinterpret_cast<const bf16_t*>(a.x); p.W = reinterpret_cast<const bf16_t*>(a.W); p.M = a.M; p.N = a.N; p.K = a.K;
   p.bias = a.bias; p.out = a.out; p.ldo = a.ldo;
   const bool classes = (a.order_rows > 0 ? a.order_rows : a.M) < ORDERED_ROWS;
-  if (a.epilogue == EPI_SWIGLU) return launch_gemm<GEMM_OUT_SWIGLU>(p, plan_gemm(a.M, a.N, a.K, true, false, classes, 0, 0.f), st);
+  if (a.epilogue == EPI_SWIGLU) return launch_gemm<GEMM_OUT_SWIGLU>(p, plan_gemm(a.M, a.N, a.K, PLAN_SWIGLU, classes, 0, 0.f), st);
   // a plain result that the caller needs in one piece is joined by a launch of the row kernel
   const bool join = a.epilogue == EPI_PLAIN && !a.split_ok;
-  const GemmPlan plan = plan_gemm(a.M, a.N, a.K, false, true, classes, a.part_cap, join ? 3.5f : 0.f);
+  const GemmPlan plan = plan_gemm(a.M, a.N, a.K, a.best != nullptr ? PLAN_LOGITS : PLAN_F32, classes, a.part_cap, join ? 3.5f : 0.f);
   const RowSource whole{reinterpret_cast<const float*>(a.out), a.ldo, nullptr, 0, 0, 0};
   if (a.best != nullptr && plan.splits == 1) {
     if (a.epilogue != EPI_PLAIN || a.bias != nullptr || best_stretches == nullptr)
       return fail(PHOTON_ERR_INVALID_ARG, "contraction: the rows' best columns come with plain logits only");
-    const int wave_columns = plan.kind >= T_128x128 ? 64 : 32;
+    const int wave_columns = TILES[plan.kind].wave_columns;
     p.best = a.best; p.stretches = *best_stretches = (a.N + wave_columns - 1) / wave_columns;
     *result = whole;
     return launch_gemm<GEMM_OUT_LOGITS>(p, plan, st);
@@ -861,8 +924,8 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
 bool qkv_rope_pays(int64_t rows, int D, int d_h) {
   if (d_h != 64 || rows < ORDERED_ROWS) return false;
   float fused = 0.f, best = 0.f;
-  plan_gemm(rows, 3 * D, D, false, false, false, 0, 0.f, T_128x128, &fused);
-  plan_gemm(rows, 3 * D, D, false, true, false, 0, 0.f, 0, &best);
+  plan_gemm(rows, 3 * D, D, PLAN_QKV, false, 0, 0.f, &fused);
+  plan_gemm(rows, 3 * D, D, PLAN_F32, false, 0, 0.f, &best);
   return fused <= best + 4.f + 0.33f * (float)rows * 3 * D * 4e-6f;
 }
 
@@ -871,13 +934,13 @@ int32_t launch_qkv_rope(const void* x, const void* W, int rows, int D, const Qkv
     return fail(PHOTON_ERR_UNSUPPORTED, "QKV projection: rows=%d D=%d do not match %d heads of 64 and %d positions", rows, D, o.H, o.M);
   GemmArgs p{};
   p.x = reinterpret_cast<const bf16_t*>(x); p.W = reinterpret_cast<const bf16_t*>(W); p.M = rows; p.N = 3 * D; p.K = D; p.qkv = o;
-  return launch_gemm<GEMM_OUT_QKV>(p, plan_gemm(rows, 3 * D, D, false, false, false, 0, 0.f, T_128x128), st);
+  return launch_gemm<GEMM_OUT_QKV>(p, plan_gemm(rows, 3 * D, D, PLAN_QKV, false, 0, 0.f), st);
 }
 
 static int32_t launch_chunker_gemm(const void* x, const void* w, const float* bias, void* out, int64_t M, int N, int K, hipStream_t st) {
   GemmArgs p{};
   p.x = (const bf16_t*)x; p.W = (const bf16_t*)w; p.bias = bias; p.out = out; p.ldo = N; p.M = (int)M; p.N = N; p.K = K;
-  return launch_gemm<GEMM_OUT_BF16>(p, plan_gemm(M, N, K, false, false, false, 0, 0.f), st);
+  return launch_gemm<GEMM_OUT_BF16>(p, plan_gemm(M, N, K, PLAN_CHUNKER, false, 0, 0.f), st);
 }
 
 }  // namespace photon
@@ -892,7 +955,7 @@ extern "C" int32_t photon_contract_tile(int64_t rows, int32_t N, int32_t K, int3
   PHOTON_REQUIRE(output >= PHOTON_CONTRACT_F32 && output <= PHOTON_CONTRACT_SWIGLU, PHOTON_ERR_INVALID_ARG, "%s: unknown output %d", __func__, output);
   PHOTON_REQUIRE(tile_rows && tile_columns && splits && walked, PHOTON_ERR_INVALID_ARG, "%s: null result", __func__);
   const bool gate_up = output == PHOTON_CONTRACT_SWIGLU, f32 = output == PHOTON_CONTRACT_F32;
-  const GemmPlan plan = plan_gemm(rows, N, K, gate_up, f32, output != PHOTON_CONTRACT_CHUNKER && rows < ORDERED_ROWS,
+  const GemmPlan plan = plan_gemm(rows, N, K, gate_up ? PLAN_SWIGLU : f32 ? PLAN_F32 : PLAN_CHUNKER, output != PHOTON_CONTRACT_CHUNKER && rows < ORDERED_ROWS,
                                   f32 ? contract_part_floats(rows, N) : 0, 0.f);
   *tile_rows = TILES[plan.kind].bm;
   *tile_columns = TILES[plan.kind].bn / (gate_up ? 2 : 1);
