@@ -38,6 +38,9 @@ constexpr int ORDERED_ROWS = 128, K_CLASSES = 8, CHUNK_SLABS = 2;
 __device__ __forceinline__ void load16_to_lds(const void* gsrc, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(lds_base) : "memory", "m0");
 }
+__device__ __forceinline__ void load4_to_lds(const void* gsrc, uint32_t lds_base) {   // 4 bytes per lane
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(gsrc), "s"(lds_base) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 typedef __attribute__((address_space(3))) void* lptr_t;
@@ -54,9 +57,14 @@ struct GemmArgs {
   const bf16_t* x; const bf16_t* W; const float* bias; const float* res; void* out;
   int64_t ldres, ldo, part_stride;
   int M, N, K, tiles_m, tiles_n, group_m, split_classes, tiles;  // tiles: of all splits
+  bool cold;                                                     // W comes from HBM: see ContractArgs
   RowBest* best; int stretches;                                  // GEMM_OUT_LOGITS (fp32 output): see ContractArgs
   QkvOperands qkv;                                               // GEMM_OUT_QKV: where the columns go instead of `out`
 };
+
+// Workgroups that share W rows on an XCD, from which on touching their lines pays: 2 of them 19.2 -> 20.4 us (256 rows, 4992 x 1664), 4 and
+// more as measured at the kernel.
+constexpr int TOUCH_SHARERS = 4;
 
 // Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes a contiguous run of tiles (also when the count is
 // not a multiple of 8), walked as bands of group_m row tiles, row tiles fastest: the 32 tiles resident on an XCD form a
@@ -251,10 +259,16 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // kt + NB.  Against reads, then MFMAs behind the barrier (512 rows, weights in the memory-side cache / in HBM): 64 x 64 tiles
 // 2048 x 2048 10.7 / 11.8 -> 9.4 / 11.6 us, 2048 x 5120 22.2 / 26.7 -> 19.0 / 25.8 us; 128 x 128, 6144 x 2048 21.7 / 24.5 -> 20.8 / 23.3 us.
 // Small wave tiles help for the same reason: 32 x 32 by four waves.
+// TOUCH: one more wave, which requests four bytes of every line of W ahead of the others: its workgroup's share of what the workgroups
+// with the same columns read together on an XCD.  A unit holds about 64 KB of requests in flight and returns them in order, so x
+// rows that lie in L2 wait behind W lines that come from HBM, and every sharer waits for itself; a line that is touched once is
+// in L2 when they ask.  Weights in the memory-side cache / in HBM, without and with it: 256 rows, 1664 x 4096 by 64 x 32 12.8 / 16.6 and
+// 12.0 / 13.9 us, 1664 x 1664 6.9 / 8.5 and 6.6 / 7.9; 512 rows, 2048 x 5120 by 64 x 64 20.0 / 26.7 and 21.8 / 23.0; 1024 rows, 1664 x 4096 by 128 x 64
+// 23.4 / 29.6 and 25.4 / 26.2; 128 x 96 tiles lose (21.6 -> 25.1).
 // CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
 // in the classes' order, which costs a few scalar instructions per slab.
-template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs p) {
+template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, bool TOUCH = false>
+__global__ __launch_bounds__((WM * WN + TOUCH) * 64) void gemm_tile_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
   constexpr int WAVES = WM * WN, STAGE = (BM + BN) * 128;
   constexpr int PIECES = (BM + BN) / 8, LPS = (PIECES + WAVES - 1) / WAVES;   // load instructions of a slab, and per wave
@@ -262,11 +276,26 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(const GemmArgs 
   constexpr bool IN8 = GU && TJ % 2 != 0;
   static_assert(!IN8 || TI % 2 == 0, "a wave trades rows in pairs");
   static_assert(BM % 8 == 0 && NB >= 2, "");
-  extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows]
+  extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows], TOUCH: 256 bytes nobody reads
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const TilePos at = tile_position(p, blockIdx.x, gridDim.x);
   const int m0 = at.tm * BM, n0 = at.tn * (GU ? BN / 2 : BN);
+  if constexpr (TOUCH) {
+    static_assert(!GU && !CLASSES, "plain columns, summed along K");
+    if (wave == WAVES) {                                         // (a wave that has ended takes no part in the barriers)
+      const int band = at.tm / p.group_m, sharers = min(p.group_m, p.tiles_m - band * p.group_m);
+      const int share = (BN + sharers - 1) / sharers, first = n0 + (at.tm - band * p.group_m) * share, lines = sharers < TOUCH_SHARERS ? 0 : share * (p.K / G_BK);
+      const uint32_t sink = (uint32_t)(uintptr_t)(lptr_t)lds + NB * STAGE;
+      for (int l0 = 0; l0 < lines; l0 += 64) {
+        const int l = l0 + lane < lines ? l0 + lane : lines - 1, r = first + l % share;
+        load4_to_lds(reinterpret_cast<const char*>(p.W + (int64_t)(r < p.N ? r : p.N - 1) * p.K) + (l / share) * (G_BK * 2), sink);
+        asm volatile("s_waitcnt vmcnt(2)" ::: "memory");         // three requests of 64 lines in flight: ahead of the others, not far
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      return;
+    }
+  }
   const int KT = p.K / G_BK, chunks = (KT + CHUNK_SLABS - 1) / CHUNK_SLABS;
   const int classes = chunks < K_CLASSES ? chunks : K_CLASSES;
   const int class0 = CLASSES ? at.split * p.split_classes : 0;
@@ -818,6 +847,11 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
     static bool attr_set = false;                                                                              \
     return launch_kernel(KERN, &attr_set, (unsigned)grid, THREADS, (size_t)(BUFS) * (t.bm + t.bn) * 128, p, st); \
   }
+#define PHOTON_GEMM_TOUCH(KIND, KERN, THREADS, BUFS)                                                           \
+  case KIND: {                                                                                                 \
+    static bool attr_set = false;                                                                              \
+    return launch_kernel(KERN, &attr_set, (unsigned)grid, THREADS + 64, (size_t)(BUFS) * (t.bm + t.bn) * 128 + 256, p, st); \
+  }
   if constexpr (OUT != GEMM_OUT_QKV) {                           // a wave of these tiles does not hold a head
     if constexpr (OUT != GEMM_OUT_BF16) {                        // (the chunker's sum always runs along K)
       if (plan.split_classes != 0) {
@@ -839,6 +873,16 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
       if (plan.kind == T_32x32) {
         static bool attr_set = false;
         return launch_kernel(gemm_tile_kernel<32, 32, 2, 2, 4, OUT, false>, &attr_set, (unsigned)grid, 256, (size_t)4 * 64 * 128, p, st);
+      }
+      // W lines touched ahead: tiles that share their columns with others, one round of them (with several workgroups on a unit others
+      // ask for other lines meanwhile), and the wide ones only where W comes from HBM (both sides measured at the kernel)
+      if (p.tiles_m >= TOUCH_SHARERS && grid <= 256) {
+        switch (plan.kind == T_64x32 || p.cold ? plan.kind : T_KINDS) {
+          PHOTON_GEMM_TOUCH(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT, false, true>), 256, 4)
+          PHOTON_GEMM_TOUCH(T_64x64, (gemm_tile_kernel<64, 64, 4, 2, 4, OUT, false, true>), 512, 4)
+          PHOTON_GEMM_TOUCH(T_128x64, (gemm_tile_kernel<128, 64, 4, 2, 3, OUT, false, true>), 512, 3)
+          default: break;
+        }
       }
     }
     // 64 x 32 tiles of the chunker, whose sums are long, with a compute unit each: six slabs in flight
@@ -870,6 +914,7 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
     PHOTON_GEMM_CASE(T_256x256, (gemm_pingpong_kernel<4, OUT>), PP_THREADS, 2)
   }
 #undef PHOTON_GEMM_CASE
+#undef PHOTON_GEMM_TOUCH
 }
 
 int64_t contract_part_floats(int64_t rows, int D) {
@@ -881,7 +926,7 @@ int32_t launch_contract(const ContractArgs& a, RowSource* result, hipStream_t st
   if (a.K % G_BK != 0 || a.N % 16 != 0 || a.ldo % 4 != 0) return fail(PHOTON_ERR_UNSUPPORTED, "contraction: K=%d must be a multiple of 64, N=%d of 16", a.K, a.N);
   GemmArgs p{};
   p.x = reinterpret_cast<const bf16_t*>(a.x); p.W = reinterpret_cast<const bf16_t*>(a.W); p.M = a.M; p.N = a.N; p.K = a.K;
-  p.bias = a.bias; p.out = a.out; p.ldo = a.ldo;
+  p.bias = a.bias; p.out = a.out; p.ldo = a.ldo; p.cold = a.cold;
   const bool classes = (a.order_rows > 0 ? a.order_rows : a.M) < ORDERED_ROWS;
   if (a.epilogue == EPI_SWIGLU) return launch_gemm<GEMM_OUT_SWIGLU>(p, plan_gemm(a.M, a.N, a.K, PLAN_SWIGLU, classes, 0, 0.f), st);
   // a plain result that the caller needs in one piece is joined by a launch of the row kernel

@@ -102,6 +102,7 @@ struct ContractArgs {
   int M = 0, N = 0, K = 0;
   int epilogue = EPI_PLAIN, order_rows = 0;
   bool split_ok = false;
+  bool cold = false;             // W is not in the memory-side cache: the matrices in use between two reads of it exceed that
   // EPI_PLAIN without bias: row m's best of every stretch of columns goes to best[m * stretches + stretch], where `best`
   // holds M * best_stretches_max(N); launch_contract sets *best_stretches, and leaves it where K is split (nothing is written)
   RowBest* best = nullptr;

@@ -398,6 +398,7 @@ struct Ctx {
   Plan p;
   char* base;
   bool bf16;
+  bool cold = false;                          // a module's matrices do not stay in the memory-side cache between two passes
   bool few = false;                           // this pass keeps the few-row kernels (and their fp32 rows) at any row count
   int order_rows = 0;                         // row count whose order of summation the blocks' contractions keep (0: their own)
   size_t o_h, o_attn, o_qkv, o_qrot, o_act;   // activation buffers of the branch this context drives
@@ -412,6 +413,12 @@ struct Ctx {
   float* f(size_t off) const { return reinterpret_cast<float*>(base + off); }
 };
 
+
+// Between two reads of a matrix a step streams the module it belongs to, the vocabulary's matrix and, beside them, the other line's
+// module: from about half of the 256 MB of the memory-side cache per module on the matrices come from HBM.
+static bool cold_modules(const photon_config& c) {
+  return c.dt == PHOTON_BF16 && (int64_t)c.n_layers * (4 * (int64_t)c.D * c.D + 3 * (int64_t)c.D * c.d_ff) * 2 > ((int64_t)128 << 20);
+}
 
 static bool many_rows(const Ctx& x, int64_t rows) { return x.bf16 && !x.few && rows >= MANY_ROWS; }
 
@@ -430,7 +437,7 @@ static int32_t contract(const Ctx& x, const void* xb, const void* W, const float
   ContractArgs a;
   a.x = xb != nullptr ? xb : x.base + x.o_many; a.W = W; a.bias = bias; a.res = res; a.out = out; a.ldo = ldo;
   a.parts = x.f(x.o_parts); a.part_cap = x.part_cap; a.M = rows; a.N = N; a.K = K; a.epilogue = epilogue; a.split_ok = split_ok;
-  a.best = best; a.order_rows = x.order_rows;
+  a.best = best; a.order_rows = x.order_rows; a.cold = x.cold;
   return launch_contract(a, result, x.st, stretches);
 }
 
@@ -1188,6 +1195,7 @@ extern "C" int32_t photon_prefill(const photon_config* cfg, const photon_weights
   x.c = cfg; x.w = w; x.s = st; x.Bt = Bt; x.st = (hipStream_t)stream;
   x.p = make_plan(c, Bt, st->S_max);
   x.bf16 = (c.dt == PHOTON_BF16);
+  x.cold = cold_modules(c);
   x.overlap = false;
   x.ew = ew; x.hs = hst;
   x.o_h = x.p.h; x.o_attn = x.p.attn; x.o_qkv = x.p.qkv; x.o_qrot = x.p.qrot; x.o_act = x.p.act;
@@ -1240,6 +1248,7 @@ static int32_t decode_entry(const char* fn, const photon_config* cfg, const phot
   x.c = cfg; x.w = w; x.s = st; x.Bt = Bt; x.st = (hipStream_t)stream;
   x.p = make_plan(c, Bt, st->S_max);
   x.bf16 = (c.dt == PHOTON_BF16);
+  x.cold = cold_modules(c);
   // the top-level update runs beside the lower levels when the caller lent a second stream and two events
   // (per-kernel timing wants one stream: concurrency would inflate the bracketed times)
   x.overlap = !g_profile_on && st->side_stream != nullptr && st->fork_event != nullptr && st->join_event != nullptr;

@@ -61,3 +61,24 @@ def test_greedy_choice_from_wide_stretches(Bt):
     index = torch.arange(V, device="cuda").expand_as(logits)
     first = torch.where(logits == logits.amax(-1, keepdim=True), index, V).amin(-1)
     assert torch.equal(out.long(), first) and int(out.max()) < V - V // 2
+
+
+def test_steps_agree_with_weights_touched_ahead():
+    """A module of 160 MB, whose wide tiles have a wave that touches the weights ahead: 64 x 64 tiles of nine row tiles (a band of
+    eight and one by itself), 128 x 64 tiles of eight, the last ones partly empty; 128 rows take neither."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    from paper_2512_20687_amd.binding import PHOTON_CONTRACT_F32
+    D, F = 1344, 3200
+    assert [ph.photon_contract_tile(r, D, K, PHOTON_CONTRACT_F32)[:2] for r, K in ((128, D), (520, D), (520, F), (1000, D), (1000, F))] == [
+        (32, 32), (64, 64), (64, 64), (128, 64), (128, 64)]
+    cfg = si.PhotonConfig(L=1, C=(1,), R=(1,), D=D, H=21, d_h=64, n_layers=4, d_ff=F, vocab=1008, dtype="bf16")
+    w, st = si.make_weights(cfg, 12, encoders=False), si.make_decode_state(cfg, 1000, 4, 16, seed=3)
+    forced = si.make_tokens(cfg.vocab, 1000, cfg.meta_context, 7)
+    ref = None
+    for Bt in (128, 520, 1000):
+        state, trace = step_of_first(cfg, w, st, Bt, forced)
+        got = [trace["logits"][:128], state.x_top[:128], state.k[:, :128], state.v[:, :128]]
+        ref = ref or got
+        for a, b in zip(ref, got):
+            assert torch.equal(a, b), Bt
