@@ -265,10 +265,13 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // in L2 when they ask.  Weights in the memory-side cache / in HBM, without and with it: 256 rows, 1664 x 4096 by 64 x 32 12.8 / 16.6 and
 // 12.0 / 13.9 us, 1664 x 1664 6.9 / 8.5 and 6.6 / 7.9; 512 rows, 2048 x 5120 by 64 x 64 20.0 / 26.7 and 21.8 / 23.0; 1024 rows, 1664 x 4096 by 128 x 64
 // 23.4 / 29.6 and 25.4 / 26.2; 128 x 96 tiles lose (21.6 -> 25.1).
+// The launch bounds name two waves per SIMD also where four make a workgroup: with all 512 registers to deal the compiler keeps
+// accumulators in the accumulation registers and moves them about in every slab, behind the MFMAs (64 x 32, 64 rows, 8192 x 2048:
+// 24.6 us instead of 20.1).
 // CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
 // in the classes' order, which costs a few scalar instructions per slab.
 template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, bool TOUCH = false>
-__global__ __launch_bounds__((WM * WN + TOUCH) * 64) void gemm_tile_kernel(const GemmArgs p) {
+__global__ __launch_bounds__((WM * WN + TOUCH) * 64, 2) void gemm_tile_kernel(const GemmArgs p) {
   constexpr bool GU = (OUT == GEMM_OUT_SWIGLU);
   constexpr int WAVES = WM * WN, STAGE = (BM + BN) * 128;
   constexpr int PIECES = (BM + BN) / 8, LPS = (PIECES + WAVES - 1) / WAVES;   // load instructions of a slab, and per wave
@@ -360,9 +363,10 @@ __global__ __launch_bounds__((WM * WN + TOUCH) * 64) void gemm_tile_kernel(const
     else xf[ks][t - TJ] = fragment(s, wm + (t - TJ) * 16 + fr, ks * 4 + fk);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // MFMAs of half 1 - KS of the slab at hand; under the first three quarters of them the operands of half KS of buffer `buf`
+  // MFMAs of half 1 - KS of the slab at hand; under the first three quarters of them the operands of half KS of buffer `buf` (in front
+  // of them where there are only one or two: a read between two MFMAs would come late; 6 rows, 3072 x 1664: 9.0 / 10.7 us)
   auto half = [&](int buf, auto KS) {
-    constexpr int ks = decltype(KS)::value, READS = TI + TJ, MFMAS = TI * TJ, SPAN = (MFMAS * 3 + 3) / 4;
+    constexpr int ks = decltype(KS)::value, READS = TI + TJ, MFMAS = TI * TJ, SPAN = MFMAS <= 2 ? 1 : (MFMAS * 3 + 3) / 4;
 #pragma unroll
     for (int q = 0; q < MFMAS; ++q) {
 #pragma unroll
@@ -756,11 +760,11 @@ constexpr TileShape TILES[T_KINDS] = {{64, 32, 32}, {64, 64, 32}, {128, 64, 32},
 // 256 x 256 with its long first slab and store pays off once the other tiles need several rounds.
 // PASS: fp32 and SwiGLU results summed along K.  Fitted to a sweep of all tiles over 128 - 3000 rows of 16 projections at the widths
 // 448 to 2048, weights half of the time in the memory-side cache and half in HBM (6-8 % rms); its choice is within 0.3 % of the
-// best tile over the sweep (geometric mean), and 9 % faster than the tiles and the kernels before (up to 1.6 times below 300 rows).
+// best tile over the sweep (geometric mean), and 11 % faster than the tiles and the kernels before (up to 1.6 times below 300 rows).
 // CLASSED: sums in classes, and the chunker's own entry point, over 128 - 2048 rows at the widths 1024, 1664 and 2048 (5-11 % rms).
 struct TileTime { float fixed, slab1, slabn; };
 constexpr TileTime CLASSED[] = {{1.6f, 0.21f, 0.17f}, {2.3f, 0.24f, 0.22f}, {2.8f, 0.34f, 0.34f}, {3.5f, 0.50f, 0.59f}, {6.2f, 0.74f, 0.94f}, {8.6f, 1.00f, 1.36f}};
-constexpr TileTime PASS[T_KINDS] = {{2.9f, 0.184f, 0.152f}, {2.8f, 0.217f, 0.218f}, {3.3f, 0.341f, 0.334f}, {4.8f, 0.472f, 0.538f}, {6.9f, 0.779f, 0.903f},
+constexpr TileTime PASS[T_KINDS] = {{2.8f, 0.165f, 0.150f}, {3.0f, 0.212f, 0.216f}, {3.3f, 0.341f, 0.334f}, {4.8f, 0.472f, 0.538f}, {6.9f, 0.779f, 0.903f},
                                     {9.4f, 1.10f, 1.28f},   {2.2f, 0.151f, 0.106f}, {4.3f, 0.440f, 0.476f}, {5.6f, 0.583f, 0.648f}};
 constexpr float US_PER_MB_OUT = 0.18f, US_PER_MB_PARTS = 0.17f;      // writing the output; reading partial products back
 

@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 
 D, F, V = 832, 2112, 8016
 # projections of a pass of `rows` rows: q/k/v, O, gate/up, down, vocabulary
-TILES = {128: [(32, 32), (32, 32), (64, 32), (32, 32), (64, 64)],
-         300: [(64, 64), (32, 32), (128, 32), (64, 32), (128, 96)],
+TILES = {128: [(64, 32), (32, 32), (64, 32), (32, 32), (64, 64)],
+         300: [(64, 64), (64, 32), (128, 32), (64, 32), (128, 96)],
          600: [(128, 64), (32, 32), (128, 48), (32, 32), (128, 160)],
          1030: [(128, 96), (64, 64), (128, 80), (64, 64), (128, 160)]}
 
