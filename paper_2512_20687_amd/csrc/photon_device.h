@@ -178,4 +178,53 @@ __device__ __forceinline__ void rotate_pair(float a, float b, float c, float s, 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float NEG_BIG = -1.0e30f;     // finite stand-in for -inf as running maximum
 
+// Greedy choice among a row of logits by CHOOSE_THREADS threads: every thread's best column, lowest index on ties, is met in
+// waves, then over the waves in order.  A NaN is never greater than another value, and nothing is greater than it: the choice in
+// a row that holds one follows from this order of comparisons, which every kernel that chooses keeps.
+constexpr int CHOOSE_THREADS = 1024, NO_COLUMN = 0x7fffffff;
+__device__ __forceinline__ void take_better(float value, int column, float& best, int& best_column) {
+  if (value > best || (value == best && column < best_column)) { best = value; best_column = column; }
+}
+// Thread tid's columns of the row (ld: distance of rows), visited in increasing order: the first maximum wins.
+__device__ __forceinline__ void best_of_share(const float* lg, int64_t ld, int vocab, int tid, float& best, int& column) {
+  best = -INFINITY;
+  column = NO_COLUMN;
+  if (vocab % 4 == 0 && ld % 4 == 0 && (reinterpret_cast<uintptr_t>(lg) & 15) == 0) {
+    // 16 bytes a lane, 8 loads in flight: 32000 logits are one round of loads
+    for (int t0 = tid * 4; t0 < vocab; t0 += 32 * CHOOSE_THREADS) {
+      float4_t v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int t = t0 + u * 4 * CHOOSE_THREADS;
+        v[u] = t < vocab ? *reinterpret_cast<const float4_t*>(lg + t) : float4_t{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v[u][e] > best || (column == NO_COLUMN && t0 + u * 4 * CHOOSE_THREADS < vocab)) { best = v[u][e]; column = t0 + u * 4 * CHOOSE_THREADS + e; }
+    }
+  } else {
+    for (int t0 = tid; t0 < vocab; t0 += 4 * CHOOSE_THREADS) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = t0 + u * CHOOSE_THREADS;
+        v[u] = t < vocab ? lg[t] : -INFINITY;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (v[u] > best || (column == NO_COLUMN && t0 + u * CHOOSE_THREADS < vocab)) { best = v[u]; column = t0 + u * CHOOSE_THREADS; }
+    }
+  }
+}
+__device__ __forceinline__ void best_of_wave(float& best, int& column) {   // in lane 0
+#pragma unroll
+  for (int mask = 1; mask < 64; mask <<= 1) {
+    const float ov = __shfl_xor(best, mask);
+    const int oi = __shfl_xor(column, mask);
+    take_better(ov, oi, best, column);
+  }
+}
+
 }  // namespace photon

@@ -21,6 +21,7 @@ namespace photon {
 namespace {
 
 constexpr int SM_THREADS = 512, SM_WAVES = SM_THREADS / 64, SM_GROUPS = SM_THREADS / 16;
+constexpr int CHOOSE_WAVES = CHOOSE_THREADS / 64;
 constexpr int SM_MAX_LAYERS = 8, SM_MAX_D = 128;
 constexpr int SM_AHEAD = 8;                              // float4 per lane requested a phase ahead
 constexpr size_t SM_LDS_LIMIT = 64 * 1024;
@@ -209,7 +210,7 @@ __host__ __device__ inline SmallLds small_lds(int rows, int D, int F, int layers
   s.act = take(rows * s.FP); s.qkv = take(rows * 3 * s.DP);
   s.kc = take(layers * window * s.WP); s.vc = take(layers * window * s.WP);
   s.rot = take(2 * angles);
-  s.red = take(2 * SM_WAVES + 4);
+  s.red = take(2 * CHOOSE_WAVES + 4);
   s.extra = take(extra_floats);
   s.total = at;
   return s;
@@ -370,27 +371,44 @@ __global__ __launch_bounds__(SM_THREADS) void small_level_kernel(const SmallLeve
       for (int d = tid; d < D; d += SM_THREADS) p.units[(chunk * p.C + j) * D + d] = h[at * s.DP + d] * rf * gains[2 * p.n_layers * s.DP + d];
     if (token_level) {
       float best = -INFINITY;
-      int column = 0x7fffffff;
+      int column = NO_COLUMN;
       float* lg = p.logits + chunk * p.ld_logits + j * p.ld_item;
       contract_rows<KS, 1>(head, xn + at * s.DP, s.DP, 1, a, [&] { request<KS>(wqkv(0), 0, 0, b); }, [&](int n, int, float y, float) {
         const float v = y * rf;
         lg[n] = v;
-        if (v > best || column == 0x7fffffff) { best = v; column = n; }   // a lane's columns come in increasing order
+        if (v > best || v != v || column == NO_COLUMN) { best = v; column = n; }   // columns come in increasing order; a NaN stays
       });
       auto meet = [&] {                                  // the wave's best value, and the first column that has it
         const float top = wave_max(best);
-        column = (int)wave_min(best == top ? (uint32_t)column : 0x7fffffffu);
+        column = (int)wave_min(best == top ? (uint32_t)column : (uint32_t)NO_COLUMN);
         best = top;
       };
+      const bool nan_here = __any(best != best);
       meet();
       float* bv = lds + s.red;
-      int *bc = reinterpret_cast<int*>(bv + SM_WAVES), *chosen = bc + SM_WAVES;
-      if (lane == 0) { bv[wave] = best; bc[wave] = column; }
+      int *bc = reinterpret_cast<int*>(bv + CHOOSE_WAVES), *chosen = bc + CHOOSE_WAVES;
+      if (lane == 0) { bv[wave] = nan_here ? NAN : best; bc[wave] = column; }
       lds_barrier();
+      best = bv[lane & (SM_WAVES - 1)];
+      const bool nan_row = __any(best != best);
+      if (nan_row) {                                     // a NaN among the logits: read them again, in the order that decides then
+        __syncthreads();
+#pragma unroll 1
+        for (int w = wave; w < CHOOSE_WAVES; w += SM_WAVES) {
+          best_of_share(lg, p.ld_logits, p.vocab, w * 64 + lane, best, column);
+          best_of_wave(best, column);
+          if (lane == 0) { bv[w] = best; bc[w] = column; }
+        }
+        lds_barrier();
+      }
       if (wave == 0) {
-        best = bv[lane & (SM_WAVES - 1)];
-        column = bc[lane & (SM_WAVES - 1)];
-        meet();
+        if (nan_row) {
+          best = bv[0]; column = bc[0];
+          for (int w = 1; w < CHOOSE_WAVES; ++w) take_better(bv[w], bc[w], best, column);
+        } else {
+          column = bc[lane & (SM_WAVES - 1)];
+          meet();
+        }
         if (lane == 0) {
           const int64_t flat = chunk * p.C + j;
           if (p.forced != nullptr) column = p.forced[flat];

@@ -145,7 +145,6 @@ __global__ __launch_bounds__(256) void rope_append_coarse_kernel(const float* __
 // Token choice for one row of logits (greedy, lowest index on ties, or the forced token), then the
 // decoder-side embedding of that token as the next input row.  best: the row's best of `stretches` stretches of columns
 // (nullptr: all of the row's logits are read here).
-constexpr int CHOOSE_THREADS = 1024;
 template <typename TE>
 __global__ __launch_bounds__(CHOOSE_THREADS) void choose_token_kernel(const float* __restrict__ logits, int64_t ld_logits, int vocab,
                                                            const RowBest* __restrict__ best_of, int stretches,
@@ -155,54 +154,23 @@ __global__ __launch_bounds__(CHOOSE_THREADS) void choose_token_kernel(const floa
   const int row = blockIdx.x, tid = threadIdx.x;
   const float* lg = logits + (int64_t)row * ld_logits;
   float best = -INFINITY;
-  int bi = 0x7fffffff;
+  int bi = NO_COLUMN;
   if (best_of != nullptr) {
     for (int i = tid; i < stretches; i += blockDim.x) {
       const RowBest r = best_of[(int64_t)row * stretches + i];       // in increasing order of columns
-      if (r.value > best || bi == 0x7fffffff) { best = r.value; bi = r.column; }
-    }
-  } else if (vocab % 4 == 0 && ld_logits % 4 == 0 && (reinterpret_cast<uintptr_t>(lg) & 15) == 0) {
-    // 16 bytes a lane, 8 loads in flight: 32000 logits are one round of loads
-    for (int t0 = tid * 4; t0 < vocab; t0 += 32 * CHOOSE_THREADS) {  // indices visited in increasing order: first maximum wins
-      float4_t v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = t0 + u * 4 * CHOOSE_THREADS;
-        v[u] = t < vocab ? *reinterpret_cast<const float4_t*>(lg + t) : float4_t{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (v[u][e] > best || (bi == 0x7fffffff && t0 + u * 4 * CHOOSE_THREADS < vocab)) { best = v[u][e]; bi = t0 + u * 4 * CHOOSE_THREADS + e; }
+      if (r.value > best || bi == NO_COLUMN) { best = r.value; bi = r.column; }
     }
   } else {
-    for (int t0 = tid; t0 < vocab; t0 += 4 * CHOOSE_THREADS) {
-      float v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int t = t0 + u * CHOOSE_THREADS;
-        v[u] = t < vocab ? lg[t] : -INFINITY;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (v[u] > best || (bi == 0x7fffffff && t0 + u * CHOOSE_THREADS < vocab)) { best = v[u]; bi = t0 + u * CHOOSE_THREADS; }
-    }
+    best_of_share(lg, ld_logits, vocab, tid, best, bi);
   }
-#pragma unroll
-  for (int mask = 1; mask < 64; mask <<= 1) {
-    const float ov = __shfl_xor(best, mask);
-    const int oi = __shfl_xor(bi, mask);
-    if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-  }
+  best_of_wave(best, bi);
   __shared__ float sv[CHOOSE_THREADS / 64];
   __shared__ int si[CHOOSE_THREADS / 64];
   __shared__ int chosen;
   if ((tid & 63) == 0) { sv[tid >> 6] = best; si[tid >> 6] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < (int)blockDim.x / 64; ++w)
-      if (sv[w] > best || (sv[w] == best && si[w] < bi)) { best = sv[w]; bi = si[w]; }
+    for (int w = 1; w < (int)blockDim.x / 64; ++w) take_better(sv[w], si[w], best, bi);
     const int64_t flat = (int64_t)row * tok_mul + tok_off;
     if (forced != nullptr) bi = forced[flat];
     bi = bi < 0 ? 0 : (bi >= vocab ? vocab - 1 : bi);

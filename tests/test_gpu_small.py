@@ -78,3 +78,37 @@ def test_small_step_full_cache():
     assert torch.equal(one.seq_len, sep.seq_len) and torch.equal(one.status, sep.status) and int(one.status) == 1
     for a, b in ((logits1, logits0), (one.x_top, sep.x_top), (one.k, sep.k), (one.v, sep.v)):
         assert nerr(a, b.double().cpu().numpy()) < 5e-6
+
+
+def _greedy(cfg, w, st, Bt, S_max, persistent):
+    """Tokens and logits of a greedy step, with one launch a level or with separate launches."""
+    state, toks, logits, n = _profiled_launches(cfg, w, st, Bt, S_max, persistent)
+    assert (n == 2 * cfg.L + 1) == persistent
+    return toks, logits
+
+
+@pytest.mark.parametrize("vocab,bad", [
+    (512, range(512)), (333, range(333)),                        # every logit a NaN
+    (512, [0]), (512, [3, 4, 130]), (512, range(256, 512)), (512, [511]), (333, [0]), (333, [1, 64]), (333, range(64, 333)),
+    (3000, [2048, 2999]), (3000, range(0, 3000, 7)), (3001, [1030]),
+    (512, ()), (333, ()),                                        # none: equal logits alone
+])
+def test_token_choice_with_equal_logits_and_nan(vocab, bad):
+    """The choice of the separate kernel: the lowest of equal columns, and the same token where logits are NaN (columns of
+    W_lm that are; 0 where all are)."""
+    require_gpu()
+    cfg = si.PhotonConfig(L=2, C=(2, 2), R=(1, 1), D=64, H=2, d_h=32, n_layers=1, d_ff=160, vocab=vocab, dtype="f32")
+    Bt = 3
+    w, st = si.make_weights(cfg, 8), si.make_decode_state(cfg, Bt, 9, 16, seed=4)
+    w["W_lm"][vocab // 2: vocab // 2 * 2] = w["W_lm"][: vocab // 2]   # values come twice
+    w["W_lm"][list(bad)] = np.nan
+    one, logits1 = _greedy(cfg, w, st, Bt, 16, True)
+    sep, logits0 = _greedy(cfg, w, st, Bt, 16, False)
+    assert torch.equal(one, sep), (one, sep)
+    assert torch.equal(logits1.isnan(), logits0.isnan())
+    if len(bad) == vocab:
+        assert not bool(one.any())
+    elif len(bad) == 0:
+        index = torch.arange(vocab, device="cuda").expand_as(logits1)
+        first = torch.where(logits1 == logits1.amax(-1, keepdim=True), index, vocab).amin(-1)
+        assert torch.equal(one.long(), first)
