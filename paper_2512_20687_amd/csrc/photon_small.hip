@@ -5,7 +5,7 @@
 // takes a chunk through everything the level does: activations, window and rotary angles stay in LDS, phases meet at
 // workgroup barriers, and the matrices (a few hundred KB) stream from the caches.  Sixteen lanes hold a matrix row, the 32
 // groups of a workgroup take 32 rows a pass; the first rows of a phase's matrix are requested a phase ahead.  A compute unit
-// takes in about 60 bytes per ns, which is what limits the sizes this pays for (small_bytes_pay).  A step of the tiny
+// takes in 60 to 75 bytes per ns, which is what limits the sizes this pays for (SmallTimes).  A step of the tiny
 // configuration (D = 64, one block): 297 us enqueued launch by launch, 100 us so (levels 34 and 43, chunker and STEP 14).
 // Eight waves with 8 pieces each in flight: 44 us for the token level alone; four with 16 52 us, sixteen with 4 60 us.
 #include "photon_small.h"
@@ -600,14 +600,52 @@ bool small_shape(int n_layers, int D, int H, int64_t workgroups) {
   return n_layers <= SM_MAX_LAYERS && D <= SM_MAX_D && D % 4 == 0 && D / H % 4 == 0 && workgroups <= 256;
 }
 
-// One workgroup streams `bytes` at about 60 bytes per ns and needs about 0.5 us per phase; the launches it replaces take 3.5 us
-// each with one chunk in flight and up to 7 with 32.  Measured, whole steps, this path / separate launches: D = 64, one block, 1 and
-// 8 sequences 100 / 232 and 101 / 442 us; D = 96, two blocks, 1000 columns 232 / 695; D = 128, one block 151 / 268; D = 128, two
-// blocks, 8 sequences 266 / 802; D = 32 with 1000 entries in the cache 105 / 405.  Rows beyond 128 wide have 1.7 MB a block
-// (28 us) and more, which the launches deal over the chip.
-bool small_bytes_pay(double bytes, int phases, int launches) { return bytes / 60e3 + 0.5 * phases < 4.0 * launches; }
+// Batches that a workgroup takes in one after the other: of rows padded to whole k steps (ks of 64), and of rows of any length.
+int row_batches(int N, int ks, bool pair = false) {
+  const int passes = (N + SM_GROUPS - 1) / SM_GROUPS * (pair ? 2 : 1), per = SM_AHEAD / ks;
+  return (passes + per - 1) / per;
+}
+int long_batches(int N, int K) { return row_batches(N, 4) * ((K + 255) / 256); }
 
-double layer_bytes(int D, int F) { return 4.0 * (4.0 * D * D + 3.0 * D * F); }
+// Time of the one launch and of the launches it replaces, in us.  Fitted to steps of 838 models replayed from a graph, with either
+// part in either form (widths 8 - 128, 1 - 8 blocks, 100 - 32000 columns, 1 - 256 chunks, caches of 32 - 2048 entries; 9.6 % rms): what
+// a workgroup takes is its batches (64 KB each, padding included, at 75 bytes per ns), barriers and heads in turn; a separate launch
+// takes 2.4 us and more with every doubling of its rows.  A level is one launch where that is faster by a twentieth, STEP where it is
+// slower by a tenth at most: enqueued call by call, separate launches take an eighth more.  Of the 838 steps four are then slower than
+// separate launches (by 2 to 10 %), and the geometric mean is 0.5 % above the best choice for every model.  (By true bytes and 4 us a
+// launch 51 were slower: four blocks 32 wide, 8 items, 32000 columns, one sequence 1299 us instead of 558; one block 72 wide, 4000 columns,
+// 512 entries 78 instead of 44.)  Whole steps, one launch / separate, enqueued: D = 64, one block, 1 and 8 sequences 100 / 232 and 101 / 442 us;
+// D = 128, two blocks, 8 sequences 266 / 802.  Rows beyond 128 wide have 1.7 MB a block and more, which the launches deal over the chip.
+struct SmallTimes { double one, separate; };
+
+double layer_megabytes(int D, int F) { return 4e-6 * (4.0 * D * D + 3.0 * D * F); }
+int layer_batches(int D, int F) {
+  const int ks = D <= 64 ? 1 : 2;
+  return row_batches(3 * D, ks) + row_batches(D, ks) + (F > 0 ? row_batches(F, ks, true) + long_batches(D, F) : 0);
+}
+int head_rounds(int H) { return (H + SM_WAVES - 1) / SM_WAVES; }
+
+SmallTimes level_times(const SmallLevel& a) {
+  const int ks = a.D <= 64 ? 1 : 2, vocab = a.E != nullptr ? a.vocab : 0;
+  const double rows = (double)a.n_chunks, phases = a.C * ((a.F > 0 ? 5 : 3) * a.n_layers + (vocab > 0 ? 2 : 1));
+  const double batches = a.C * (a.n_layers * layer_batches(a.D, a.F) + row_batches(vocab, ks)) + row_batches(a.R * a.D, ks);
+  const double head_mb = 4e-6 * vocab * a.D;
+  return {2.5 + 0.16 * phases + 0.84 * batches + 1.34 * a.n_layers * head_rounds(a.H) * (a.C + a.R - 1),
+          phases * (2.4 + 1.17 * log2(rows)) +
+              a.C * (0.043 * rows * (a.n_layers * layer_megabytes(a.D, a.F) + head_mb) + 0.35 * head_mb + 38e-6 * rows * vocab)};
+}
+
+SmallTimes step_times(const SmallStep& a) {
+  const int pitch = kv_row_elems(a.D / a.H), per_head = a.H < SM_WAVES ? SM_WAVES / a.H : 1, entries = 4 * per_head * (256 / pitch);
+  const int block = a.F > 0 ? 5 : 3;
+  const double rows = (double)a.Bt, launches = (block + 1) * a.n_layers + 2;
+  const double kv_rounds = (double)head_rounds(a.H) * (double)((a.S_max + entries - 1) / entries);
+  const double score_rounds = (double)head_rounds(a.H) * (double)((a.S_max + 63) / 64);
+  return {6.3 + 0.65 * ((block + 2) * a.n_layers + 2) + 0.55 * (a.n_layers * layer_batches(a.D, a.F) + long_batches(a.D, a.CL * a.D)) +
+              a.n_layers * (1.66 * kv_rounds + 0.12 * score_rounds),
+          launches * (2.2 + 0.96 * log2(rows)) + a.n_layers * (0.061 * rows * layer_megabytes(a.D, a.F) + 0.29 * (double)a.S_max / 64 +
+                                                               0.12 * rows * 8e-6 * (double)a.S_max * a.H * pitch)};
+}
 
 size_t level_lds(const SmallLevel& a) {
   return sizeof(float) * small_lds(a.R <= 1 ? 1 : 2, a.D, a.F, a.n_layers, a.R + a.C - 1, (a.R + a.C - 1) * (a.D / a.H / 2), 0).total;
@@ -622,8 +660,9 @@ size_t step_lds(const SmallStep& a) {
 
 bool small_level_pays(const SmallLevel& a) {
   if (!small_shape(a.n_layers, a.D, a.H, a.n_chunks) || a.R > 2) return false;
-  const double head = a.E != nullptr ? 4.0 * a.vocab * a.D : 0.0;
-  return level_lds(a) <= SM_LDS_LIMIT && small_bytes_pay(a.n_layers * layer_bytes(a.D, a.F) + head, 5 * a.n_layers + 2, 5 * a.n_layers + 2);
+  if ((int64_t)a.vocab * a.D > ((int64_t)1 << 27)) return false;   // a matrix view takes offsets below 1 GiB
+  const SmallTimes t = level_times(a);
+  return level_lds(a) <= SM_LDS_LIMIT && 1.05 * t.one < t.separate;
 }
 
 int32_t launch_small_level(const SmallLevel& a, hipStream_t st) {
@@ -645,9 +684,8 @@ int32_t launch_small_level(const SmallLevel& a, hipStream_t st) {
 
 bool small_step_pays(const SmallStep& a) {
   if (!small_shape(a.n_layers, a.D, a.H, a.Bt) || a.S_max > (1 << 14)) return false;
-  const double kv = 8.0 * a.S_max * a.H * kv_row_elems(a.D / a.H);
-  return step_lds(a) <= SM_LDS_LIMIT &&
-         small_bytes_pay(a.n_layers * (layer_bytes(a.D, a.F) + kv) + 4.0 * a.CL * a.D * a.D, 7 * a.n_layers + 2, 6 * a.n_layers + 2);
+  const SmallTimes t = step_times(a);
+  return step_lds(a) <= SM_LDS_LIMIT && 0.9 * t.one < t.separate;
 }
 
 int32_t launch_small_step(const SmallStep& a, hipStream_t st) {

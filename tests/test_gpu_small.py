@@ -112,3 +112,32 @@ def test_token_choice_with_equal_logits_and_nan(vocab, bad):
         index = torch.arange(vocab, device="cuda").expand_as(logits1)
         first = torch.where(logits1 == logits1.amax(-1, keepdim=True), index, vocab).amin(-1)
         assert torch.equal(one.long(), first)
+
+
+@pytest.mark.parametrize("kw,Bt,S_max,level,step", [
+    # a long vocabulary: 558 us with separate launches, 1264 with the level in one
+    (dict(D=32, H=1, C=(8,), n_layers=4, d_ff=128, vocab=32000), 1, 64, False, True),
+    (dict(D=16, H=1, d_h=16, C=(8,), n_layers=2, d_ff=40, vocab=32000), 2, 32, False, True),     # 353 and 881 us
+    # few launches to save: 44 us separate, 61 with the level in one, 78 with STEP in one
+    (dict(D=72, H=9, d_h=8, C=(1,), d_ff=288, vocab=4000), 1, 512, False, False),
+    (dict(D=120, H=6, d_h=20, C=(2,), n_layers=3, d_ff=0, vocab=16000), 2, 512, False, False),   # STEP 139 and 181 us
+    (dict(C=(4,)), 1, 128, True, True),
+])
+def test_one_launch_only_where_it_is_faster(kw, Bt, S_max, level, step):
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(**dict(dict(L=1, R=(1,), D=64, H=2, d_h=32, n_layers=1, d_ff=160, vocab=512, dtype="f32"), **kw))
+    w, st = si.make_weights(cfg, 21), si.make_decode_state(cfg, Bt, 9, S_max, seed=5)
+    model = ph.PhotonModel(cfg, w)
+    state = ph.PhotonState(model, Bt, S_max, k=st["k"], v=st["v"], seq_len=st["seq_len"], x_top=st["x_top"], carry=st["carry"])
+    toks = torch.empty((Bt, cfg.meta_context), dtype=torch.int32, device="cuda")
+    ph.photon_profile_reset()
+    ph.photon_profile_enable(True)
+    try:
+        ph.photon_decode_step(model, state, toks)
+        torch.cuda.synchronize()
+    finally:
+        ph.photon_profile_enable(False)
+    classes = ph.photon_profile_get()
+    ph.photon_profile_reset()
+    assert ("local_attn_kernel" not in classes) == level and ("coarse_attn_kernel" not in classes) == step, classes
