@@ -272,6 +272,8 @@ struct SmallLevelArgs {
   double freq_ratio;                                     // theta^(-2 / d_h); 0: no rotation
 };
 
+static_assert(PHOTON_MAX_WINDOW * 4 <= 64, "four lanes of a wave hold a window position");
+
 // KS: 64-wide k steps of a row of D.  MR: rows of the first sub-step (converter length R <= MR); further sub-steps have one row.
 template <int KS, int MR>
 __global__ __launch_bounds__(SM_THREADS) void small_level_kernel(const SmallLevelArgs p) {

@@ -44,6 +44,10 @@ def _profiled_launches(cfg, w, st, Bt, S_max, persistent):
     (dict(L=3, C=(2, 3, 2), R=(1, 2, 1), n_layers=2), 3, 9, 24),
     (dict(L=1, C=(4,), R=(2,)), 2, 9, 24),
     (dict(rope_theta=0.0, C=(2, 5)), 2, 9, 24),
+    (dict(C=(16, 2)), 2, 9, 24),                                 # windows of 16 positions: every lane of the softmax
+    (dict(C=(15, 2), R=(2, 1)), 2, 9, 24),
+    (dict(D=16, H=4, d_h=4, d_ff=40, C=(15, 2), R=(2, 1)), 3, 9, 24),
+    (dict(D=128, H=4, d_ff=320, n_layers=3, C=(16, 1)), 2, 9, 24),   # 62 of 64 KB of LDS
 ])
 def test_small_step_against_oracle_and_separate_launches(kw, Bt, S0, S_max):
     require_gpu()
