@@ -62,9 +62,13 @@ struct GemmArgs {
   QkvOperands qkv;                                               // GEMM_OUT_QKV: where the columns go instead of `out`
 };
 
-// Workgroups that share W rows on an XCD, from which on touching their lines pays: 2 of them 19.2 -> 20.4 us (256 rows, 4992 x 1664), 4 and
-// more as measured at the kernel.
-constexpr int TOUCH_SHARERS = 4;
+// Workgroups that share W rows on an XCD, from which on touching their lines pays.  Geometric means over 11 projections, weights in the
+// memory-side cache / in HBM, by 64 x 32, 64 x 64 and 128 x 64: of 2 row tiles 1.01 / 1.07, 0.90 / 0.99 and 0.98 / 1.05 times as fast as without, of
+// 3 1.01 / 1.12, 0.96 / 1.08 and 0.99 / 1.13, of 4 and more 1.02 / 1.10, 0.96 / 1.08 and 1.00 / 1.10.
+constexpr int TOUCH_SHARERS = 3;
+// Slabs whose lines are requested ahead of the barrier at hand: 8, 16, 32 and all 1.08, 1.09, 1.09 and 1.10 times as fast from HBM, 0.96, 0.96, 0.95 and
+// 0.95 from the memory-side cache (64 x 64 tiles); by 128 x 64 1.10 each, and 1.00, 0.99, 0.99 and 0.99.
+constexpr int TOUCH_AHEAD = 8;
 
 // Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes a contiguous run of tiles (also when the count is
 // not a multiple of 8), walked as bands of group_m row tiles, row tiles fastest: the 32 tiles resident on an XCD form a
@@ -259,12 +263,13 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // kt + NB.  Against reads, then MFMAs behind the barrier (512 rows, weights in the memory-side cache / in HBM): 64 x 64 tiles
 // 2048 x 2048 10.7 / 11.8 -> 9.4 / 11.6 us, 2048 x 5120 22.2 / 26.7 -> 19.0 / 25.8 us; 128 x 160, 10240 x 2048 29.2 / 33.7 -> 27.4 / 31.9 us.
 // Small wave tiles help for the same reason: 32 x 32 by four waves.
-// TOUCH: one more wave, which requests four bytes of every line of W ahead of the others: its workgroup's share of what the workgroups
-// with the same columns read together on an XCD.  A unit holds about 64 KB of requests in flight and returns them in order, so x
-// rows that lie in L2 wait behind W lines that come from HBM, and every sharer waits for itself; a line that is touched once is
-// in L2 when they ask.  Weights in the memory-side cache / in HBM, without and with it: 256 rows, 1664 x 4096 by 64 x 32 12.8 / 16.6 and
-// 12.0 / 13.9 us, 1664 x 1664 6.9 / 8.5 and 6.6 / 7.9; 512 rows, 2048 x 5120 by 64 x 64 20.0 / 26.7 and 21.8 / 23.0; 1024 rows, 1664 x 4096 by 128 x 64
-// 23.4 / 29.6 and 25.4 / 26.2; 128 x 96 tiles lose (21.6 -> 25.1).
+// TOUCH: one more wave, which requests four bytes of every line of W some slabs ahead of the others: its workgroup's share of what the
+// workgroups with the same columns read together on an XCD.  A unit holds about 64 KB of requests in flight and returns them in order, so
+// x rows that lie in L2 wait behind W lines that come from HBM, and every sharer waits for itself; a line that is touched once is in L2
+// when they ask.  Weights in the memory-side cache / in HBM, without and with it: 256 rows, 1664 x 4096 by 64 x 32 12.5 / 17.4 and 12.5 / 14.3 us,
+// 1664 x 1664 6.9 / 8.9 and 6.7 / 7.8; 512 rows, 2048 x 5120 by 64 x 64 19.4 / 26.8 and 21.0 / 22.4; 1024 rows, 1664 x 4096 by 128 x 64 24.6 / 30.9 and
+// 25.4 / 25.8.  (A wave that met no barrier held the others at their first one until it had touched all its lines: from HBM 14.9, 8.3, 24.9 and
+// 27.3 us.)  128 x 96 and 128 x 160 gain less and stay without it (34 and 32 projections: 0.99 / 1.04 and 0.99 / 1.03).
 // The launch bounds name two waves per SIMD also where four make a workgroup: with all 512 registers to deal the compiler keeps
 // accumulators in the accumulation registers and moves them about in every slab, behind the MFMAs (64 x 32, 64 rows, 8192 x 2048:
 // 24.6 us instead of 20.1).
@@ -277,6 +282,10 @@ __global__ __launch_bounds__((WM * WN + TOUCH) * 64, 2) void gemm_tile_kernel(co
   constexpr int PIECES = (BM + BN) / 8, LPS = (PIECES + WAVES - 1) / WAVES;   // load instructions of a slab, and per wave
   constexpr int TI = BM / WM / 16, TJ = BN / WN / 16;            // MFMA tiles of a wave
   constexpr bool IN8 = GU && TJ % 2 != 0;
+  // 128 x 64 and 128 x 128 tiles gain little by the reads ahead (1024 rows, 1664 x 4096 by 128 x 64 27.5 / 26.7 us; 2048 rows, 1664 x 1664 by
+  // 128 x 128 19.9 / 19.7), and the one slab more that is requested past the end costs where K is short (1200 rows, 768 x 1600 by
+  // 128 x 64 8.1 / 8.3 us; a prefill at the width 384 3280 / 3319 us).
+  constexpr bool READS_AHEAD = !CLASSES && !(BM == 128 && (BN == 64 || BN == 128));
   static_assert(!IN8 || TI % 2 == 0, "a wave trades rows in pairs");
   static_assert(BM % 8 == 0 && NB >= 2, "");
   extern __shared__ __align__(16) char lds[];                    // [NB buffers][BM x rows | BN W rows], TOUCH: 256 bytes nobody reads
@@ -290,10 +299,14 @@ __global__ __launch_bounds__((WM * WN + TOUCH) * 64, 2) void gemm_tile_kernel(co
       const int band = at.tm / p.group_m, sharers = min(p.group_m, p.tiles_m - band * p.group_m);
       const int share = (BN + sharers - 1) / sharers, first = n0 + (at.tm - band * p.group_m) * share, lines = sharers < TOUCH_SHARERS ? 0 : share * (p.K / G_BK);
       const uint32_t sink = (uint32_t)(uintptr_t)(lptr_t)lds + NB * STAGE;
-      for (int l0 = 0; l0 < lines; l0 += 64) {
-        const int l = l0 + lane < lines ? l0 + lane : lines - 1, r = first + l % share;
-        load4_to_lds(reinterpret_cast<const char*>(p.W + (int64_t)(r < p.N ? r : p.N - 1) * p.K) + (l / share) * (G_BK * 2), sink);
-        asm volatile("s_waitcnt vmcnt(2)" ::: "memory");         // three requests of 64 lines in flight: ahead of the others, not far
+      // The workgroup's barriers wait for this wave too: it meets each of them.
+      int l0 = 0;
+      for (int met = 0; met < p.K / G_BK + (READS_AHEAD ? 1 : 0); ++met) {
+        for (const int until = min(lines, (met + TOUCH_AHEAD) * share); l0 < until; l0 += 64) {
+          const int l = l0 + lane < lines ? l0 + lane : lines - 1, r = first + l % share;
+          load4_to_lds(reinterpret_cast<const char*>(p.W + (int64_t)(r < p.N ? r : p.N - 1) * p.K) + (l / share) * (G_BK * 2), sink);
+        }
+        asm volatile("s_barrier" ::: "memory");
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       return;
@@ -384,11 +397,7 @@ __global__ __launch_bounds__((WM * WN + TOUCH) * 64, 2) void gemm_tile_kernel(co
       for (int j = 0; j < TJ; ++j) acc[i][j] = float4_t{0.f, 0.f, 0.f, 0.f};
   };
   int buf = 0;
-  // 128 x 64 and 128 x 128 tiles gain little by the reads ahead (1024 rows, 1664 x 4096 by 128 x 64 27.5 / 26.7 us; 2048 rows, 1664 x 1664 by
-  // 128 x 128 19.9 / 19.7), and the one slab more that is requested past the end costs where K is short (1200 rows, 768 x 1600 by
-  // 128 x 64 8.1 / 8.3 us; a prefill at the width 384 3280 / 3319 us).
-  constexpr bool AHEAD = !CLASSES && !(BM == 128 && (BN == 64 || BN == 128));
-  if constexpr (AHEAD) {
+  if constexpr (READS_AHEAD) {
 #pragma unroll
     for (int s = 0; s < NB; ++s) load(s);
     clear();
