@@ -790,14 +790,14 @@ struct GemmPlan { int kind, splits, parts, split_classes; };
 
 enum PlanOutput { PLAN_F32, PLAN_SWIGLU, PLAN_LOGITS, PLAN_CHUNKER, PLAN_QKV };
 // Which tiles an output takes.  A wave of the 32 x 32 tile holds 16 columns: half a gate/up pair, less than a stretch of logits.
-// (Results of up to 512 columns keep the 64 x 32 tile that the tests of the order of a sum name; 333 rows of 448, K = 1344: 6.6 us
-// there, 5.3 us by 32 x 32.)  128 x 96 and 128 x 160 fill the units where the other tiles leave a part of them idle or need a second
+// (By 32 x 32, 64 - 512 columns: 505 shapes of 128 - 4096 rows, medians 5.2 -> 4.2 us at K = 1024, 11.3 -> 8.7 at K = 4096.)
+// 128 x 96 and 128 x 160 fill the units where the other tiles leave a part of them idle or need a second
 // round: 512 rows, SwiGLU 2 x 5120 x 2048, 160 tiles of 128 x 256 32.8 us, 256 tiles of 128 x 160 25.7 us.
-static bool tile_takes(int kind, PlanOutput output, bool classes, int64_t M, int N) {
+static bool tile_takes(int kind, PlanOutput output, bool classes, int64_t M) {
   if (classes) return kind < T_CLASS_KINDS;
   if (output == PLAN_QKV) return kind == T_128x128 || kind == T_128x256 || kind == T_256x256;   // a wave holds a head
   if (output == PLAN_CHUNKER || M > PASS_ROWS) return kind <= T_256x256;
-  return kind != T_32x32 || (output == PLAN_F32 && N > 512);
+  return kind != T_32x32 || output == PLAN_F32;
 }
 
 // classes: the sum is formed in classes of K (then not by the counter-phase kernels), and may be split between them.
@@ -810,7 +810,7 @@ static GemmPlan plan_gemm(int64_t M, int N, int K, PlanOutput output, bool class
   float best_us = 1e30f;
   const float out_mb = (float)M * N * (out_f32 ? 4e-6f : 2e-6f);
   for (int k = 0; k < T_KINDS; ++k) {
-    if (!tile_takes(k, output, classes, M, N)) continue;
+    if (!tile_takes(k, output, classes, M)) continue;
     const TileTime& cost = classes || output == PLAN_CHUNKER || M > PASS_ROWS ? CLASSED[k] : PASS[k];
     const int bn = gate_up ? TILES[k].bn / 2 : TILES[k].bn;
     const int64_t tiles = (M + TILES[k].bm - 1) / TILES[k].bm * ((N + bn - 1) / bn);

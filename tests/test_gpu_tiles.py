@@ -37,7 +37,7 @@ def check_chunker(rows, K, N):
 
 # Every tile of the contraction at one, two and three K slabs, fewer and more than it loads ahead: a row more or less than whole
 # row tiles, a last column tile of 16 columns, a tile count that is no multiple of the 8 XCDs.
-# The narrow ones also at odd and even numbers of slabs above that, with and without a unit to themselves (operands read ahead or not).
+# The narrow ones also at odd and even numbers of slabs above that, in grids of up to 256 tiles and of more (64 x 32: six or four slab buffers).
 @pytest.mark.parametrize("tile,rows,K,N", [
     ((64, 32), 63, 64, 48), ((64, 32), 65, 128, 80), ((64, 32), 193, 192, 144), ((64, 32), 1, 704, 80), ((64, 32), 129, 768, 2000),
     ((64, 32), 77, 320, 4944), ((64, 32), 127, 384, 4944),
@@ -159,7 +159,7 @@ def test_a_sequence_s_step_does_not_depend_on_the_batch(kw, batches):
 # chunker entry point (whose result is rounded to bf16): the top chunker of a step against both, bit for bit.
 @pytest.mark.parametrize("Bt,C,D,tile", [
     (17, 4, 512, (64, 32, 8)), (64, 3, 448, (64, 32, 8)), (100, 2, 64, (64, 32, 1)), (127, 8, 1024, (64, 64, 8)), (127, 1, 1024, (64, 32, 4)),
-    (127, 1, 2048, (64, 64, 4)), (128, 4, 512, (64, 32, 1)), (333, 3, 448, (64, 32, 1)),
+    (127, 1, 2048, (64, 64, 4)), (128, 4, 512, (32, 32, 1)), (333, 3, 448, (32, 32, 1)), (333, 2, 1024, (64, 32, 1)), (1000, 3, 448, (64, 32, 1)),
 ])
 def test_order_of_a_contraction_s_sum(Bt, C, D, tile):
     require_gpu()
