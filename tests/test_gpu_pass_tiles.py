@@ -75,6 +75,28 @@ def test_greedy_choice_from_wide_stretches(Bt):
     assert torch.equal(out.long(), first) and int(out.max()) < V - V // 2
 
 
+# Contractions of one to three K slabs, fewer than the tiles load ahead, and their last row tiles partly empty.
+@pytest.mark.parametrize("D,F,V,Bt,tiles", [
+    (64, 64, 1008, 333, dict(qkv=(32, 32), down=(32, 32))),
+    (128, 128, 1008, 301, dict(qkv=(32, 32), down=(32, 32))),
+    (128, 128, 7008, 3457, dict(logits=(128, 96))),
+    (128, 192, 16016, 3081, dict(logits=(128, 160))),
+    (192, 2688, 7008, 833, dict(logits=(128, 96))),
+    (192, 2688, 1008, 3841, dict(gate_up=(128, 48))),
+    (192, 7616, 1008, 1537, dict(gate_up=(128, 80))),
+])
+def test_steps_agree_at_few_slabs(D, F, V, Bt, tiles):
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    from paper_2512_20687_amd.binding import PHOTON_CONTRACT_F32, PHOTON_CONTRACT_SWIGLU
+    tile = lambda N, K, output=PHOTON_CONTRACT_F32: ph.photon_contract_tile(Bt, N, K, output)[:2]
+    taken = dict(qkv=tile(3 * D, D), down=tile(D, F), logits=tile(V, D), gate_up=tile(F, D, PHOTON_CONTRACT_SWIGLU))
+    assert {k: taken[k] for k in tiles} == tiles
+    cfg = si.PhotonConfig(L=1, C=(1,), R=(1,), D=D, H=D // 64, d_h=64, n_layers=2, d_ff=F, vocab=V, dtype="bf16")
+    st, forced, which = repeating(cfg, Bt, 4, 16)
+    check_rows_agree(cfg, si.make_weights(cfg, 12, encoders=False), st, forced, which, (128, Bt))
+
+
 def test_steps_agree_with_weights_touched_ahead():
     """A module of 160 MB, whose wide tiles have a wave that touches the weights ahead: 64 x 64 tiles of three row tiles and of nine (a band
     of eight and one by itself), 128 x 64 tiles of eight, the last ones partly empty; 128 rows take neither."""
