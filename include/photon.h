@@ -226,7 +226,9 @@ PHOTON_API int32_t photon_linear(const void* x, const void* w, const float* gain
  * hidden rows and the attention rows of the local decoders and of the prefill
  * are kept in bf16, and so are the rows entering a projection once
  * a pass holds 17 rows or more (below that they enter as a bf16 head plus a
- * bf16 remainder, i.e. with fp32 accuracy).
+ * bf16 remainder, i.e. with fp32 accuracy).  dt = fp32: everything in fp32; how
+ * a sum is ordered follows the kernels, which the number of sequences and S_max
+ * help to choose, so a sequence's last bits can change with them.
  * -------------------------------------------------------------------------- */
 typedef struct photon_config {
   int32_t L;                     /* levels, 1..PHOTON_MAX_LEVELS */
@@ -333,7 +335,11 @@ PHOTON_API int32_t photon_decode_join(photon_state* st, void* stream);
  * it holds at most 16 rows of a bf16 configuration: on != 0 (the default) runs it as ONE persistent launch, one
  * workgroup per compute unit, whose phases meet at grid barriers (bounded waits; needs head size 64 or 128, a window
  * of at most 8 positions, at most 16 blocks per module and one of the compiled width classes, else the separate
- * launches are used); on == 0 always uses separate launches.  Process-wide; results agree to the last bit.
+ * launches are used); on == 0 always uses separate launches.  Results agree to the last bit.
+ * In an fp32 configuration of up to 128 columns the switch concerns whole levels, and the chunker with the STEP behind
+ * it: on != 0 runs each as one launch, a workgroup per chunk or sequence, where that is faster (up to 256 of them, 8
+ * blocks and two converter rows), on == 0 as separate launches.  The sums are the same fp32 sums in another order:
+ * results agree to about 1e-6 of the largest value (5e-7 at most over 221 models).  Process-wide.
  * At most two persistent launches can be resident on a GPU at a time: steps of more than two states issued
  * concurrently on different streams serialise on the barrier waits (and fail with the error word set after 10 s). */
 PHOTON_API int32_t photon_set_persistent(int32_t on);
@@ -451,7 +457,8 @@ PHOTON_API double photon_mfma_probe(int32_t iters, int32_t random_operands, void
  * stream); this allocates events (at most 65536 pairs between two resets, later
  * launches go untimed) and must not be used under stream capture.
  * Kernels are grouped in classes 0 .. photon_profile_num_classes()-1, named by
- * photon_profile_class_name().  photon_profile_get() waits for the recorded
+ * photon_profile_class_name(); a launch that holds a whole level, or the chunker
+ * and the STEP, of a small fp32 model has a class of its own.  photon_profile_get() waits for the recorded
  * events of a class and returns the launch count and the summed elapsed
  * milliseconds; photon_profile_reset() drops all records.  While enabled,
  * photon_decode_step keeps all its work on the caller's stream (no side stream).

@@ -32,7 +32,7 @@ std::vector<ProfRec> g_prof;
 const char* const kClassNames[KC_COUNT] = {
     "coarse_attn_kernel", "coarse_merge_kernel", "local_attn_kernel", "linear_bf16_kernels", "gemm_f32_kernel",
     "chunker_gemm_bf16_kernel", "norm_rows_kernel", "rope_append_kernel",
-    "choose_token_kernel", "misc", "persistent_module_kernel"};
+    "choose_token_kernel", "misc", "persistent_module_kernel", "small_model_kernels"};
 }  // namespace
 
 // At most this many launches are timed between two resets (each holds two events); further launches go untimed.

@@ -677,7 +677,7 @@ int32_t launch_small_level(const SmallLevel& a, hipStream_t st) {
   p.scale_log2e = LOG2E / sqrtf((float)d_h);
   p.freq_ratio = a.theta == 0.f ? 0.0 : pow((double)a.theta, -2.0 / (double)d_h);
   const size_t lds = level_lds(a);
-#define PHOTON_SMALL(KS, MR) PHOTON_LAUNCH(KC_GEMM_F32, st, (small_level_kernel<KS, MR>), dim3((unsigned)a.n_chunks), dim3(SM_THREADS), lds, st, p)
+#define PHOTON_SMALL(KS, MR) PHOTON_LAUNCH(KC_SMALL, st, (small_level_kernel<KS, MR>), dim3((unsigned)a.n_chunks), dim3(SM_THREADS), lds, st, p)
   if (a.D <= 64) { if (a.R == 1) PHOTON_SMALL(1, 1); else PHOTON_SMALL(1, 2); }
   else { if (a.R == 1) PHOTON_SMALL(2, 1); else PHOTON_SMALL(2, 2); }
 #undef PHOTON_SMALL
@@ -697,8 +697,8 @@ int32_t launch_small_step(const SmallStep& a, hipStream_t st) {
   p.kc = a.k_cache; p.vc = a.v_cache; p.seq_len = a.seq_len; p.S_max = a.S_max; p.Bt = a.Bt; p.n_layers = a.n_layers;
   p.D = a.D; p.F = a.F; p.H = a.H; p.CL = a.CL; p.pitch = kv_row_elems(a.D / a.H); p.eps = a.eps; p.theta = a.theta;
   p.scale_log2e = LOG2E / sqrtf((float)(a.D / a.H));
-  if (a.D <= 64) PHOTON_LAUNCH(KC_GEMM_F32, st, small_step_kernel<1>, dim3((unsigned)a.Bt), dim3(SM_THREADS), step_lds(a), st, p);
-  else PHOTON_LAUNCH(KC_GEMM_F32, st, small_step_kernel<2>, dim3((unsigned)a.Bt), dim3(SM_THREADS), step_lds(a), st, p);
+  if (a.D <= 64) PHOTON_LAUNCH(KC_SMALL, st, small_step_kernel<1>, dim3((unsigned)a.Bt), dim3(SM_THREADS), step_lds(a), st, p);
+  else PHOTON_LAUNCH(KC_SMALL, st, small_step_kernel<2>, dim3((unsigned)a.Bt), dim3(SM_THREADS), step_lds(a), st, p);
   return check_launch("small_step_kernel");
 }
 
