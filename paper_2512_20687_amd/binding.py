@@ -223,7 +223,8 @@ def photon_mfma_probe(iters: int, random_operands: bool, sink: torch.Tensor) -> 
 
 
 def photon_set_persistent(on: bool) -> None:
-    """Module passes of at most 16 rows as one persistent launch (default) or as separate launches."""
+    """Module passes of at most 16 rows (bf16), whole levels and the chunker with the STEP (small fp32 models), as one launch
+    each (default) or as separate launches."""
     lib = load_library()
     lib.photon_set_persistent.argtypes = [C.c_int32]
     lib.photon_set_persistent.restype = C.c_int32

@@ -221,7 +221,7 @@ __global__ void step_end_kernel(const unsigned* __restrict__ err, int32_t* __res
   if (threadIdx.x == 0 && blockIdx.x == 0 && err[0] != 0u) atomicOr(status, PHOTON_STATUS_BARRIER_TIMEOUT);
 }
 
-// Test and measurement switch: run every module pass as separate launches (photon_set_option).
+// Test and measurement switch: run every module pass, and every level of a small fp32 model, as separate launches (photon_set_persistent).
 bool g_no_persistent = false;
 
 static inline unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
