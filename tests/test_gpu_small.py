@@ -147,3 +147,83 @@ def test_one_launch_only_where_it_is_faster(kw, Bt, S_max, level, step):
     ph.photon_profile_reset()
     assert ("local_attn_kernel" not in classes) == level and ("coarse_attn_kernel" not in classes) == step, classes
     assert classes.get("small_model_kernels", (0,))[0] == level + step, classes
+
+
+@pytest.mark.parametrize("kw,Bt", [(dict(), 2), (dict(L=3, C=(2, 3, 2), R=(1, 2, 1), D=48, H=4, d_h=12, d_ff=124), 3), (dict(L=1, C=(4,), R=(1,)), 4)])
+def test_small_steps_joined_pipelined_and_captured(kw, Bt):
+    """Steps that leave their lower levels running beside the next one, and steps replayed from a graph, are the joined ones bit for bit
+    (the same kernels in all three), with eager work and a synchronisation between the replays."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    cfg = si.PhotonConfig(**dict(dict(L=2, C=(4, 4), R=(1, 1), D=64, H=2, d_h=32, n_layers=2, d_ff=160, vocab=500, dtype="f32"), **kw))
+    n_steps, S, S_max = 4, 9, 40
+    w, st = si.make_weights(cfg, 31), si.make_decode_state(cfg, Bt, S, S_max, seed=6)
+    model = ph.PhotonModel(cfg, w)
+    names = ("k", "v", "seq_len", "x_top", "carry")
+    res = {}
+    for mode in ("joined", "pipelined", "graph"):
+        state = ph.PhotonState(model, Bt, S_max, k=st["k"], v=st["v"], seq_len=st["seq_len"], x_top=st["x_top"], carry=st["carry"],
+                               pipeline=mode != "joined" and cfg.L > 1)
+        toks = torch.full((n_steps, Bt, cfg.meta_context), -1, dtype=torch.int32, device="cuda")
+        logits = torch.zeros((n_steps, Bt, cfg.meta_context, cfg.vocab), device="cuda")
+        keep = {n: getattr(state, n).clone() for n in names}
+
+        def run():
+            for i in range(n_steps):
+                ph.photon_decode_step(model, state, toks[i], trace={"logits": logits[i]})
+            ph.photon_decode_join(state)
+
+        if mode != "graph":
+            run()
+        else:
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                run()
+            for _ in range(3):
+                toks.fill_(-1)
+                logits.zero_()
+                for n, t in keep.items():
+                    getattr(state, n).copy_(t)
+                g.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(toks, res["joined"][0]) and torch.equal(logits, res["joined"][1])
+        torch.cuda.synchronize()
+        assert int(state.status.item()) == 0 and int(state.c_state.lower_levels_pending) == 0
+        res[mode] = (toks, logits, *(getattr(state, n) for n in names))
+    for mode in ("pipelined", "graph"):
+        for a, b in zip(res["joined"], res[mode]):
+            assert torch.equal(a, b), mode
+
+
+@pytest.mark.parametrize("C,Bt", [((2, 1), 256), ((2, 4), 64), ((1, 2), 128)])
+def test_small_step_at_the_most_chunks(C, Bt):
+    """256 chunks (sequences) are one launch, one sequence more is not: the same results for those that both decode."""
+    require_gpu()
+    cfg = si.PhotonConfig(L=2, C=C, R=(1, 2), D=32, H=2, d_h=16, n_layers=2, d_ff=80, vocab=300, dtype="f32")
+    assert Bt * C[1] == 256
+    w, st = si.make_weights(cfg, 11), si.make_decode_state(cfg, Bt + 1, 5, 12, seed=9)
+    part = lambda n: dict(k=st["k"][:, :n], v=st["v"][:, :n], seq_len=st["seq_len"][:n], x_top=st["x_top"][:n], carry=st["carry"][:, :n])
+    one, toks1, logits1, n1 = _profiled_launches(cfg, w, part(Bt), Bt, 12, True)
+    more, toks2, logits2, n2 = _profiled_launches(cfg, w, part(Bt + 1), Bt + 1, 12, True)
+    sep, toks0, logits0, n0 = _profiled_launches(cfg, w, part(Bt + 1), Bt + 1, 12, False)
+    assert n1 == 5 < n2 <= n0 and (n2 == n0) == (Bt == 256), (n1, n2, n0)
+    for toks, logits, state in ((toks1, logits1, one), (toks2[:Bt], logits2[:Bt], more)):
+        assert torch.equal(toks, toks0[:Bt])
+        assert nerr(logits, logits0[:Bt].double().cpu().numpy()) < 5e-6
+        assert nerr(state.x_top[:Bt], sep.x_top[:Bt].double().cpu().numpy()) < 5e-6
+
+
+def test_small_step_with_a_long_cache():
+    """A cache whose entries a workgroup takes longer for than the launches: the levels stay one launch each, STEP does not."""
+    require_gpu()
+    cfg = si.PhotonConfig(L=2, C=(2, 2), R=(1, 1), D=64, H=4, d_h=16, n_layers=2, d_ff=160, vocab=300, dtype="f32")
+    launches = []
+    for S_max in (512, 8192):
+        w, st = si.make_weights(cfg, 11), si.make_decode_state(cfg, 2, S_max - 3, S_max, seed=9)
+        one, toks1, logits1, n1 = _profiled_launches(cfg, w, st, 2, S_max, True)
+        sep, toks0, logits0, n0 = _profiled_launches(cfg, w, st, 2, S_max, False)
+        launches.append((n1, n0))
+        assert torch.equal(toks1, toks0)
+        for a, b in ((logits1, logits0), (one.x_top, sep.x_top), (one.k, sep.k), (one.v, sep.v)):
+            assert nerr(a, b.double().cpu().numpy()) < 5e-6
+    assert launches[0][0] == 5 and 5 < launches[1][0] < launches[1][1], launches
