@@ -440,3 +440,20 @@ def test_bf16_prefill_with_8bit_cache_then_step():
     assert nerr(logits, otr["logits"]) <= TOL["bf16"]
     assert nerr(state.x_top, otr["x_top"]) <= TOL["bf16"]
 
+
+
+def test_prefill_with_weights_touched_ahead():
+    """Three modules of 121 MB, together more than the memory-side cache holds: the contractions that take a wave that touches the
+    weights ahead (64 x 32, 64 x 64 and 128 x 64 tiles) differ between one, two and three prompts; what a prompt leaves does not."""
+    require_gpu()
+    import paper_2512_20687_amd as ph
+    from paper_2512_20687_amd.binding import PHOTON_CONTRACT_F32
+    D, F, T = 1344, 3200, 600
+    assert {ph.photon_contract_tile(rows, D, K, PHOTON_CONTRACT_F32)[:2] for rows in (150, 300, 600, 450, 900) for K in (D, F)} == {
+        (32, 32), (64, 32), (64, 64), (128, 64)}
+    cfg = si.PhotonConfig(L=2, C=(2, 2), R=(1, 1), D=D, H=21, d_h=64, n_layers=3, d_ff=F, vocab=1008, dtype="bf16")
+    w, toks = si.make_weights(cfg, 14, device="cuda"), si.make_tokens(cfg.vocab, 3, T, 8)
+    states = [gpu_prefill(cfg, w, toks[:Bt], T // 4 + 1)[1] for Bt in (3, 1, 2)]
+    for Bt, state in ((1, states[1]), (2, states[2])):
+        for name, dim in (("x_top", 0), ("carry", 1), ("k", 1), ("v", 1)):
+            assert torch.equal(getattr(state, name), getattr(states[0], name).narrow(dim, 0, Bt)), (Bt, name)
