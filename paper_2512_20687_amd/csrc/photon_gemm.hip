@@ -271,8 +271,8 @@ __device__ __forceinline__ void store_qkv(const GemmArgs& p, const float4_t (&ac
 // 25.4 / 25.8.  (A wave that met no barrier held the others at their first one until it had touched all its lines: from HBM 14.9, 8.3, 24.9 and
 // 27.3 us.)  128 x 96 and 128 x 160 gain less and stay without it (34 and 32 projections: 0.99 / 1.04 and 0.99 / 1.03).
 // The launch bounds name two waves per SIMD also where four make a workgroup: with all 512 registers to deal the compiler keeps
-// accumulators in the accumulation registers and moves them about in every slab, behind the MFMAs (64 x 32, 64 rows, 8192 x 2048:
-// 24.6 us instead of 20.1).
+// accumulators in the accumulation registers and moves them about in every slab, behind the MFMAs (64 x 32 tiles of the chunker: 64 rows,
+// 8192 x 2048 24.7 us instead of 19.5; 512 rows, 2048 x 512 8.2 instead of 6.7; tiles of eight waves are the same).
 // CLASSES: the sum in classes (see ORDERED_ROWS).  A second set of accumulators takes the classes' sums; the slabs are loaded
 // in the classes' order, which costs a few scalar instructions per slab.
 template <int BM, int BN, int WM, int WN, int NB, int OUT, bool CLASSES, bool TOUCH = false>
@@ -895,8 +895,10 @@ static int32_t launch_gemm(GemmArgs p, const GemmPlan& plan, hipStream_t st) {
         static bool attr_set = false;
         return launch_kernel(gemm_tile_kernel<32, 32, 2, 2, 4, OUT, false>, &attr_set, (unsigned)grid, 256, (size_t)4 * 64 * 128, p, st);
       }
-      // W lines touched ahead: tiles that share their columns with others, one round of them (with several workgroups on a unit others
-      // ask for other lines meanwhile), and the wide ones only where W comes from HBM (both sides measured at the kernel)
+      // W lines touched ahead: tiles that share their columns with others, one round of them, and the wide ones only where W comes from
+      // HBM.  354 projections of 192 - 4096 rows, widths 384 - 2048, by the tiles they take: up to 256 tiles 1.02 / 1.13, 0.97 / 1.08 and 1.00 / 1.09 times
+      // as fast with it (memory-side cache / HBM; 64 x 32, 64 x 64 and 128 x 64); the 29 of more tiles, none of them 64 x 32, 0.93 to 1.00 and
+      // 0.99 to 1.06 (0.96 to 1.18 one by one): too few that gain to tell which.
       if (p.tiles_m >= TOUCH_SHARERS && grid <= 256) {
         switch (plan.kind == T_64x32 || p.cold ? plan.kind : T_KINDS) {
           PHOTON_GEMM_TOUCH(T_64x32, (gemm_tile_kernel<64, 32, 4, 1, 4, OUT, false, true>), 256, 4)
