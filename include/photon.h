@@ -338,7 +338,7 @@ PHOTON_API int32_t photon_decode_join(photon_state* st, void* stream);
  * launches are used); on == 0 always uses separate launches.  Results agree to the last bit.
  * In an fp32 configuration of up to 128 columns the switch concerns whole levels, and the chunker with the STEP behind
  * it: on != 0 runs each as one launch, a workgroup per chunk or sequence, where that is faster (up to 256 of them, 8
- * blocks and two converter rows), on == 0 as separate launches.  The sums are the same fp32 sums in another order:
+ * blocks, two converter rows and, for STEP, caches of 2048 entries), on == 0 as separate launches.  The sums are the same fp32 sums in another order:
  * results agree to about 1e-6 of the largest value (5e-7 at most over 221 models).  Process-wide.
  * At most two persistent launches can be resident on a GPU at a time: steps of more than two states issued
  * concurrently on different streams serialise on the barrier waits (and fail with the error word set after 10 s). */

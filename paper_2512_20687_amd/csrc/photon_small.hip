@@ -22,7 +22,7 @@ namespace {
 
 constexpr int SM_THREADS = 512, SM_WAVES = SM_THREADS / 64, SM_GROUPS = SM_THREADS / 16;
 constexpr int CHOOSE_WAVES = CHOOSE_THREADS / 64;
-constexpr int SM_MAX_LAYERS = 8, SM_MAX_D = 128;
+constexpr int SM_MAX_LAYERS = 8, SM_MAX_D = 128, SM_MAX_CACHE = 2048;
 constexpr int SM_AHEAD = 8;                              // float4 per lane requested a phase ahead
 constexpr size_t SM_LDS_LIMIT = 64 * 1024;
 
@@ -685,7 +685,10 @@ int32_t launch_small_level(const SmallLevel& a, hipStream_t st) {
 }
 
 bool small_step_pays(const SmallStep& a) {
-  if (!small_shape(a.n_layers, a.D, a.H, a.Bt) || a.S_max > (1 << 14)) return false;
+  // Longer caches are beyond the times' fit, and a workgroup walks alone what the separate kernel deals over the chip: of 100 models with
+  // full caches of 2049 - 16384 entries that the times had in one launch, 37 were slower so by a twentieth and more (2049 - 4096 entries:
+  // geometric mean 1.05, 14 of 54; 4097 - 8192: 0.96, 17 of 38; above: 0.82, 6 of 8; worst 528 us instead of 361), of 60 up to 2048 one (1.44).
+  if (!small_shape(a.n_layers, a.D, a.H, a.Bt) || a.S_max > SM_MAX_CACHE) return false;
   const SmallTimes t = step_times(a);
   return step_lds(a) <= SM_LDS_LIMIT && 0.9 * t.one < t.separate;
 }

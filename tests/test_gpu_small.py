@@ -127,6 +127,10 @@ def test_token_choice_with_equal_logits_and_nan(vocab, bad):
     (dict(D=72, H=9, d_h=8, C=(1,), d_ff=288, vocab=4000), 1, 512, False, False),
     (dict(D=120, H=6, d_h=20, C=(2,), n_layers=3, d_ff=0, vocab=16000), 2, 512, False, False),   # STEP 139 and 181 us
     (dict(C=(4,)), 1, 128, True, True),
+    # long caches: full, STEP 139 us separate, 210 in one
+    (dict(D=8, H=1, d_h=8, C=(1,), n_layers=4, d_ff=32, vocab=100), 3, 4765, True, False),
+    (dict(D=16, H=1, d_h=16, C=(2,), d_ff=64, vocab=500), 9, 2049, True, False),
+    (dict(D=16, H=1, d_h=16, C=(2,), d_ff=64, vocab=500), 9, 2048, True, True),
 ])
 def test_one_launch_only_where_it_is_faster(kw, Bt, S_max, level, step):
     require_gpu()
