@@ -231,3 +231,18 @@ def test_small_step_with_a_long_cache():
         for a, b in ((logits1, logits0), (one.x_top, sep.x_top), (one.k, sep.k), (one.v, sep.v)):
             assert nerr(a, b.double().cpu().numpy()) < 5e-6
     assert launches[0][0] == 5 and 5 < launches[1][0] < launches[1][1], launches
+
+
+@pytest.mark.parametrize("S_max,one_launch", [(430, True), (431, False)])
+def test_small_step_at_the_most_lds(S_max, one_launch):
+    """Scores of 32 heads over the longest cache that fits the 64 KB of LDS (to 96 bytes), and over one entry more: separate launches."""
+    require_gpu()
+    cfg = si.PhotonConfig(L=1, C=(4,), R=(1,), D=128, H=32, d_h=4, n_layers=1, d_ff=512, vocab=100, dtype="f32")
+    Bt = 96
+    w, st = si.make_weights(cfg, 17), si.make_decode_state(cfg, Bt, S_max - 1, S_max, seed=2)
+    one, toks1, logits1, n1 = _profiled_launches(cfg, w, st, Bt, S_max, True)
+    sep, toks0, logits0, n0 = _profiled_launches(cfg, w, st, Bt, S_max, False)
+    assert (n1 == 3) == one_launch and n1 < n0, (n1, n0)
+    assert torch.equal(toks1, toks0)
+    for a, b in ((logits1, logits0), (one.x_top, sep.x_top), (one.k, sep.k), (one.v, sep.v)):
+        assert nerr(a, b.double().cpu().numpy()) < 5e-6
