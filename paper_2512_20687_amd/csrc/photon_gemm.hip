@@ -771,18 +771,24 @@ enum TileKind { T_64x32 = 0, T_64x64, T_128x64, T_128x128, T_CLASS_KINDS, T_128x
 struct TileShape { int bm, bn, wave_columns; };
 constexpr TileShape TILES[T_KINDS] = {{64, 32, 32}, {64, 64, 32}, {128, 64, 32}, {128, 128, 64}, {128, 256, 64}, {256, 256, 64}, {32, 32, 16}, {128, 96, 48}, {128, 160, 80}};
 // Time model behind the choice, in us: fixed + slabs per split * (slab1 if every compute unit has one workgroup at most,
-// slabn * workgroups per unit otherwise) + what the output bytes cost.  It ranks the choices rather than predicting a time;
-// 256 x 256 with its long first slab and store pays off once the other tiles need several rounds.
-// PASS: fp32 and SwiGLU results summed along K.  Fitted to a sweep of all tiles over 128 - 3000 rows of 16 projections at the widths
-// 448 to 2048, weights half of the time in the memory-side cache and half in HBM (6-8 % rms); its choice is within 0.3 % of the
-// best tile over the sweep (geometric mean), and 11 % faster than the tiles and the kernels before (up to 1.6 times below 300 rows).
+// slabn * workgroups per unit otherwise) + `round` for every workgroup of a unit behind its first + what the output bytes cost.  It
+// ranks the choices rather than predicting a time; 256 x 256 with its long first slab and store pays off once the other tiles need
+// several rounds.
+// PASS: fp32 and SwiGLU results summed along K, workgroups per unit counted as ROUNDED of the whole number that its busiest unit has and
+// the rest of the mean.  Fitted to a sweep of all tiles over 1000 projections of 128 - 4096 rows, widths 64 to 5120, weights half of
+// the time in the memory-side cache and half in HBM (6-8 % rms, 256 x 256 11): its choice is within 1.3 % of the best tile (geometric mean), and
+// 7 % faster than the tiles and kernels before the present ones.  Of 1200 times of 600 other projections 32 are more than 3 % longer than
+// with those, most of them of launches of 3 - 5 us.  (Fitted over the widths 448 to 2048 only, with neither `round` nor means: 59, 576 columns
+// of 2679 rows at K = 192 5.8 us instead of 4.8, 9216 columns of 2025 rows at K = 3072 from HBM 145 instead of 126.)
 // CLASSED: sums in classes, the chunker's own entry point and passes of more than PASS_ROWS rows (where the fit above does not reach:
 // a prefill of 24 x 5696 tokens at the width 384 3482 us with these, 3526 with those), over 128 - 2048 rows at the widths 1024, 1664 and 2048 (5-11 % rms).
-struct TileTime { float fixed, slab1, slabn; };
+struct TileTime { float fixed, slab1, slabn, round = 0.f; };
 constexpr int PASS_ROWS = 4096;
 constexpr TileTime CLASSED[] = {{1.6f, 0.21f, 0.17f}, {2.3f, 0.24f, 0.22f}, {2.8f, 0.34f, 0.34f}, {3.5f, 0.50f, 0.59f}, {6.2f, 0.74f, 0.94f}, {8.6f, 1.00f, 1.36f}};
-constexpr TileTime PASS[T_KINDS] = {{2.8f, 0.165f, 0.150f}, {3.0f, 0.212f, 0.216f}, {3.3f, 0.341f, 0.334f}, {4.8f, 0.472f, 0.538f}, {6.9f, 0.779f, 0.903f},
-                                    {9.4f, 1.10f, 1.28f},   {2.2f, 0.151f, 0.106f}, {4.3f, 0.440f, 0.476f}, {5.6f, 0.583f, 0.648f}};
+constexpr TileTime PASS[T_KINDS] = {{2.9f, 0.150f, 0.143f, 0.3f}, {3.2f, 0.192f, 0.201f, 0.5f},  {3.4f, 0.312f, 0.311f, 0.4f},
+                                    {4.2f, 0.462f, 0.513f, 1.3f}, {6.4f, 0.784f, 0.859f, 2.0f},  {10.1f, 1.033f, 1.272f, 2.5f},
+                                    {2.7f, 0.132f, 0.096f, 0.1f}, {4.2f, 0.407f, 0.438f, 1.7f},  {5.2f, 0.553f, 0.612f, 2.3f}};
+constexpr float ROUNDED = 0.7f;
 constexpr float US_PER_MB_OUT = 0.18f, US_PER_MB_PARTS = 0.17f;      // writing the output; reading partial products back
 
 // parts: partial products (1: none); split_classes: classes of K per split (0: the sum runs along K, unsplit)
@@ -811,7 +817,8 @@ static GemmPlan plan_gemm(int64_t M, int N, int K, PlanOutput output, bool class
   const float out_mb = (float)M * N * (out_f32 ? 4e-6f : 2e-6f);
   for (int k = 0; k < T_KINDS; ++k) {
     if (!tile_takes(k, output, classes, M)) continue;
-    const TileTime& cost = classes || output == PLAN_CHUNKER || M > PASS_ROWS ? CLASSED[k] : PASS[k];
+    const bool pass = !classes && output != PLAN_CHUNKER && M <= PASS_ROWS;
+    const TileTime& cost = pass ? PASS[k] : CLASSED[k];
     const int bn = gate_up ? TILES[k].bn / 2 : TILES[k].bn;
     const int64_t tiles = (M + TILES[k].bm - 1) / TILES[k].bm * ((N + bn - 1) / bn);
     for (int per = K_CLASSES; per >= 1; per /= 2) {               // classes per split: the first split's come in one part, every other class is one
@@ -819,8 +826,9 @@ static GemmPlan plan_gemm(int64_t M, int N, int K, PlanOutput output, bool class
       if (per < K_CLASSES && (splits == 1 || !classes)) continue;
       if (parts > 1 && parts * M * N > part_cap) break;
       const int slabs = splits == 1 ? KT : per * ((chunks + K_CLASSES - 1) / K_CLASSES) * CHUNK_SLABS;
-      const float rounds = (float)((tiles * splits + 255) / 256);
-      const float us = cost.fixed + slabs * (rounds <= 1.f ? cost.slab1 : cost.slabn * rounds) +
+      float rounds = (float)((tiles * splits + 255) / 256);
+      if (pass && rounds > 1.f) rounds = ROUNDED * rounds + (1.f - ROUNDED) / 256.f * (float)tiles;
+      const float us = cost.fixed + cost.round * (rounds - 1.f) + slabs * (rounds <= 1.f ? cost.slab1 : cost.slabn * rounds) +
                        out_mb * parts * US_PER_MB_OUT + (parts > 1 ? out_mb * parts * US_PER_MB_PARTS + join_us : 0.f);
       if (us < best_us) { best_us = us; best = GemmPlan{k, splits, parts, classes ? per : 0}; }
       if (tiles * splits >= 512) break;                           // more splits only add bytes

@@ -75,15 +75,18 @@ def test_greedy_choice_from_wide_stretches(Bt):
     assert torch.equal(out.long(), first) and int(out.max()) < V - V // 2
 
 
-# Contractions of one to three K slabs, fewer than the tiles load ahead, and their last row tiles partly empty.
+# Contractions of one to four K slabs, fewer than the tiles load ahead or no more, and their last row tiles partly empty (128 x 96 and
+# 128 x 160 are not taken below three and four slabs).
 @pytest.mark.parametrize("D,F,V,Bt,tiles", [
     (64, 64, 1008, 333, dict(qkv=(32, 32), down=(32, 32))),
     (128, 128, 1008, 301, dict(qkv=(32, 32), down=(32, 32))),
-    (128, 128, 7008, 3457, dict(logits=(128, 96))),
-    (128, 192, 16016, 3081, dict(logits=(128, 160))),
-    (192, 2688, 7008, 833, dict(logits=(128, 96))),
-    (192, 2688, 1008, 3841, dict(gate_up=(128, 48))),
-    (192, 7616, 1008, 1537, dict(gate_up=(128, 80))),
+    (128, 128, 7008, 3457, dict(logits=(128, 64))),
+    (128, 192, 16016, 3081, dict(logits=(256, 256))),
+    (192, 2688, 7008, 833, dict(logits=(128, 64))),
+    (192, 2688, 1008, 3841, dict(gate_up=(128, 32))),
+    (192, 7616, 1008, 1537, dict(gate_up=(256, 128))),
+    (192, 2432, 4576, 533, dict(logits=(128, 96), gate_up=(128, 48))),
+    (256, 5632, 11296, 333, dict(logits=(128, 160), gate_up=(128, 80))),
 ])
 def test_steps_agree_at_few_slabs(D, F, V, Bt, tiles):
     require_gpu()
