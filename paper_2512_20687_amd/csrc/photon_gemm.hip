@@ -781,9 +781,10 @@ constexpr TileShape TILES[T_KINDS] = {{64, 32, 32}, {64, 64, 32}, {128, 64, 32},
 // with those, most of them of launches of 3 - 5 us.  (Fitted over the widths 448 to 2048 only, with neither `round` nor means: 59, 576 columns
 // of 2679 rows at K = 192 5.8 us instead of 4.8, 9216 columns of 2025 rows at K = 3072 from HBM 145 instead of 126.)
 // CLASSED: sums in classes, the chunker's own entry point and passes of more than PASS_ROWS rows (where the fit above does not reach:
-// a prefill of 24 x 5696 tokens at the width 384 3482 us with these, 3526 with those), over 128 - 2048 rows at the widths 1024, 1664 and 2048 (5-11 % rms).
+// a prefill of 24 x 5696 tokens at the width 384 3482 us with these, 3526 with those) and more than PASS_SLABS slabs of K (up to three, by PASS
+// instead: 47 projections of 4097 - 32768 rows 1.10 times as fast), over 128 - 2048 rows at the widths 1024, 1664 and 2048 (5-11 % rms).
 struct TileTime { float fixed, slab1, slabn, round = 0.f; };
-constexpr int PASS_ROWS = 4096;
+constexpr int PASS_ROWS = 4096, PASS_SLABS = 3;
 constexpr TileTime CLASSED[] = {{1.6f, 0.21f, 0.17f}, {2.3f, 0.24f, 0.22f}, {2.8f, 0.34f, 0.34f}, {3.5f, 0.50f, 0.59f}, {6.2f, 0.74f, 0.94f}, {8.6f, 1.00f, 1.36f}};
 constexpr TileTime PASS[T_KINDS] = {{2.9f, 0.150f, 0.143f, 0.3f}, {3.2f, 0.192f, 0.201f, 0.5f},  {3.4f, 0.312f, 0.311f, 0.4f},
                                     {4.2f, 0.462f, 0.513f, 1.3f}, {6.4f, 0.784f, 0.859f, 2.0f},  {10.1f, 1.033f, 1.272f, 2.5f},
@@ -799,10 +800,10 @@ enum PlanOutput { PLAN_F32, PLAN_SWIGLU, PLAN_LOGITS, PLAN_CHUNKER, PLAN_QKV };
 // (By 32 x 32, 64 - 512 columns: 505 shapes of 128 - 4096 rows, medians 5.2 -> 4.2 us at K = 1024, 11.3 -> 8.7 at K = 4096.)
 // 128 x 96 and 128 x 160 fill the units where the other tiles leave a part of them idle or need a second
 // round: 512 rows, SwiGLU 2 x 5120 x 2048, 160 tiles of 128 x 256 32.8 us, 256 tiles of 128 x 160 25.7 us.
-static bool tile_takes(int kind, PlanOutput output, bool classes, int64_t M) {
+static bool tile_takes(int kind, PlanOutput output, bool classes, bool pass) {
   if (classes) return kind < T_CLASS_KINDS;
   if (output == PLAN_QKV) return kind == T_128x128 || kind == T_128x256 || kind == T_256x256;   // a wave holds a head
-  if (output == PLAN_CHUNKER || M > PASS_ROWS) return kind <= T_256x256;
+  if (!pass) return kind <= T_256x256;
   return kind != T_32x32 || output == PLAN_F32;
 }
 
@@ -812,12 +813,12 @@ static bool tile_takes(int kind, PlanOutput output, bool classes, int64_t M) {
 static GemmPlan plan_gemm(int64_t M, int N, int K, PlanOutput output, bool classes, int64_t part_cap, float join_us, float* model_us = nullptr) {
   const bool gate_up = output == PLAN_SWIGLU, out_f32 = output == PLAN_F32 || output == PLAN_LOGITS;
   const int KT = K / G_BK, chunks = (KT + CHUNK_SLABS - 1) / CHUNK_SLABS, n_classes = chunks < K_CLASSES ? chunks : K_CLASSES;
+  const bool pass = !classes && output != PLAN_CHUNKER && (M <= PASS_ROWS || KT <= PASS_SLABS);
   GemmPlan best{T_64x64, 1, 1, classes ? K_CLASSES : 0};
   float best_us = 1e30f;
   const float out_mb = (float)M * N * (out_f32 ? 4e-6f : 2e-6f);
   for (int k = 0; k < T_KINDS; ++k) {
-    if (!tile_takes(k, output, classes, M)) continue;
-    const bool pass = !classes && output != PLAN_CHUNKER && M <= PASS_ROWS;
+    if (!tile_takes(k, output, classes, pass)) continue;
     const TileTime& cost = pass ? PASS[k] : CLASSED[k];
     const int bn = gate_up ? TILES[k].bn / 2 : TILES[k].bn;
     const int64_t tiles = (M + TILES[k].bm - 1) / TILES[k].bm * ((N + bn - 1) / bn);
